@@ -18,6 +18,9 @@ AMULET_THRES_COL, AMULET_THRES_ROW, AMULET_THRES_CONST, AMULET_THRES_ELEM = 0, 1
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libamulet.so")
 _lib = None
+# set with the library: torch, and its call that returns the raw stream of a device (None: not in this torch)
+_torch = None
+_raw_stream = None
 
 
 class AmuletError(RuntimeError):
@@ -35,7 +38,7 @@ def library_path() -> str:
 
 def load_library():
     """Load libamulet.so (once).  Raises if it has not been built."""
-    global _lib
+    global _lib, _torch, _raw_stream
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -46,7 +49,7 @@ def load_library():
     # torch ships its own HIP runtime (same soname as the system one): import it
     # first so that libamulet.so binds to the runtime torch's allocations and
     # streams live in, instead of bringing a second runtime into the process.
-    import torch  # noqa: F401
+    import torch
     lib = ctypes.CDLL(_LIB_PATH)
     i64, i32, vp = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p
     lib.amulet_mmlike_f32.restype = i32
@@ -146,6 +149,7 @@ def load_library():
     lib.amulet_debug_fail_launches.argtypes = [i32]
     lib.amulet_version.restype = ctypes.c_char_p
     lib.amulet_version.argtypes = []
+    _torch, _raw_stream = torch, getattr(torch._C, "_cuda_getCurrentRawStream", None)
     _lib = lib
     return lib
 
@@ -153,31 +157,42 @@ def load_library():
 _SCORE_FN = ctypes.CFUNCTYPE(ctypes.c_double, ctypes.c_int, ctypes.c_int, ctypes.c_void_p)
 
 
+# What a call costs on the host before its launch is this module's to keep small: calls on matrices of a
+# few hundred rows run in less time on the GPU than the marshalling used to take.  Per call, measured:
+# current_stream() 3.2 us (it builds a Stream object) against 0.3 for the raw handle; checking and
+# reading three tensors 2.0 us with dtypes compared as text, 1.3 as objects; an amulet_mmlike_f32 call
+# of 64^3 9.7 us before, 6.2 now, of which 4.4 are the C call and its launch.
 def _stream_ptr(stream):
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        if _raw_stream is not None:
+            return _raw_stream(_torch.cuda.current_device())
+        stream = _torch.cuda.current_stream()
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
-def _mat(t, dtype_name: str, what: str):
+def _mat(t, dtype, what: str):
     """(data_ptr, rows, cols, leading dimension in elements) of a 2-D device tensor."""
     if not t.is_cuda:
         raise ValueError("%s must live on the GPU" % what)
-    if t.dim() != 2 or str(t.dtype) != dtype_name:
-        raise ValueError("%s must be a 2-D %s tensor" % (what, dtype_name))
+    if t.dim() != 2 or t.dtype is not dtype:
+        raise ValueError("%s must be a 2-D %s tensor" % (what, dtype))
     rows, cols = t.shape
-    if cols > 1 and t.stride(1) != 1:
+    ld, step = t.stride()
+    if cols > 1 and step != 1:
         raise ValueError("%s must have unit column stride" % what)
-    ld = t.stride(0) if rows > 1 else max(cols, 1)
-    return t.data_ptr(), rows, cols, max(ld, 1)
+    if rows <= 1:
+        ld = cols
+    return t.data_ptr(), rows, cols, ld if ld > 0 else 1
+
+
+_N_PARAM_ROWS = {AMULET_DISCOUNT: 2, AMULET_BOOST: 1, AMULET_COUNT_GT: 1}
 
 
 def _params_ptr(task: int, params, N: int):
-    n_rows = {AMULET_IDENTITY: 0, AMULET_DISCOUNT: 2, AMULET_BOOST: 1, AMULET_COUNT_GT: 1}.get(task, 0)
+    n_rows = _N_PARAM_ROWS.get(task, 0)
     if n_rows == 0 or params is None:
         return None
-    if not params.is_cuda or str(params.dtype) != "torch.float32" or not params.is_contiguous() \
+    if not params.is_cuda or params.dtype is not _torch.float32 or not params.is_contiguous() \
             or params.numel() != n_rows * N:
         raise ValueError("params must be a contiguous fp32 device tensor of %d x %d" % (n_rows, N))
     return params.data_ptr()
@@ -192,9 +207,9 @@ def _check(rc: int, where: str):
 def amulet_mmlike_f32(task: int, A, B, params, R, stream=None):
     """R += sum_k g(A[i,k]*B[k,j], params[:, j]) on the GPU, in place; enqueues and returns."""
     lib = load_library()
-    pa, M, K, lda = _mat(A, "torch.float32", "A")
-    pb, K2, N, ldb = _mat(B, "torch.float32", "B")
-    pr, M2, N2, ldr = _mat(R, "torch.float32", "R")
+    pa, M, K, lda = _mat(A, _torch.float32, "A")
+    pb, K2, N, ldb = _mat(B, _torch.float32, "B")
+    pr, M2, N2, ldr = _mat(R, _torch.float32, "R")
     if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch: A %dx%d, B %dx%d, R %dx%d" % (M, K, K2, N, M2, N2))
     _check(lib.amulet_mmlike_f32(task, M, N, K, pa, lda, pb, ldb, _params_ptr(task, params, N), pr, ldr,
@@ -205,9 +220,9 @@ def amulet_mmlike_f32_adaptive(task: int, A, B, params, R, stream=None):
     """R += task(A, B, params) with the paper's in-flight adaptive execution: trial tile shapes
     run on row slabs of this very task.  Returns (chosen shape id, number of trial slabs)."""
     lib = load_library()
-    pa, M, K, lda = _mat(A, "torch.float32", "A")
-    pb, K2, N, ldb = _mat(B, "torch.float32", "B")
-    pr, M2, N2, ldr = _mat(R, "torch.float32", "R")
+    pa, M, K, lda = _mat(A, _torch.float32, "A")
+    pb, K2, N, ldb = _mat(B, _torch.float32, "B")
+    pr, M2, N2, ldr = _mat(R, _torch.float32, "R")
     if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch: A %dx%d, B %dx%d, R %dx%d" % (M, K, K2, N, M2, N2))
     chosen, trials = ctypes.c_int(-1), ctypes.c_int(0)
@@ -219,9 +234,9 @@ def amulet_mmlike_f32_adaptive(task: int, A, B, params, R, stream=None):
 
 def amulet_mmlike_f32_shape(task: int, shape: int, A, B, params, R, stream=None):
     lib = load_library()
-    pa, M, K, lda = _mat(A, "torch.float32", "A")
-    pb, K2, N, ldb = _mat(B, "torch.float32", "B")
-    pr, M2, N2, ldr = _mat(R, "torch.float32", "R")
+    pa, M, K, lda = _mat(A, _torch.float32, "A")
+    pb, K2, N, ldb = _mat(B, _torch.float32, "B")
+    pr, M2, N2, ldr = _mat(R, _torch.float32, "R")
     if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch: A %dx%d, B %dx%d, R %dx%d" % (M, K, K2, N, M2, N2))
     _check(lib.amulet_mmlike_f32_shape(task, shape, M, N, K, pa, lda, pb, ldb,
@@ -229,23 +244,23 @@ def amulet_mmlike_f32_shape(task: int, shape: int, A, B, params, R, stream=None)
            "amulet_mmlike_f32_shape")
 
 
-def _general_args(dtype_name: str, task: int, A, B, thres, dis, R, thres_form: int, trans_a: bool,
+def _general_args(dtype, task: int, A, B, thres, dis, R, thres_form: int, trans_a: bool,
                   trans_b: bool):
     """Pointers, sizes and pitches of a general-form call, in the order the C entry points take
     them from M on: (M, N, K, A, lda, B, ldb, thres, ldt, dis, R, ldr)."""
-    pa, ra, ca, lda = _mat(A, dtype_name, "A")
-    pb, rb, cb, ldb = _mat(B, dtype_name, "B")
-    pr, M, N, ldr = _mat(R, dtype_name, "R")
+    pa, ra, ca, lda = _mat(A, dtype, "A")
+    pb, rb, cb, ldb = _mat(B, dtype, "B")
+    pr, M, N, ldr = _mat(R, dtype, "R")
     Ma, K = (ca, ra) if trans_a else (ra, ca)
     K2, Nb = (cb, rb) if trans_b else (rb, cb)
     if K2 != K or Ma != M or Nb != N:
         raise ValueError("shape mismatch between A, B and R")
     pt, ldt = None, 0
     if task != AMULET_IDENTITY:
-        if thres is None or not thres.is_cuda or str(thres.dtype) != dtype_name:
+        if thres is None or not thres.is_cuda or thres.dtype is not dtype:
             raise ValueError("thres must be a device tensor of the operands' type")
         if thres_form == AMULET_THRES_ELEM:
-            pt, tm, tn, ldt = _mat(thres, dtype_name, "thres")
+            pt, tm, tn, ldt = _mat(thres, dtype, "thres")
             if (tm, tn) != (M, N):
                 raise ValueError("thres[i][j] must be M x N")
         else:
@@ -255,7 +270,7 @@ def _general_args(dtype_name: str, task: int, A, B, thres, dis, R, thres_form: i
             pt = thres.data_ptr()
     pd = None
     if task == AMULET_DISCOUNT:
-        if dis is None or not dis.is_cuda or str(dis.dtype) != dtype_name or not dis.is_contiguous() \
+        if dis is None or not dis.is_cuda or dis.dtype is not dtype or not dis.is_contiguous() \
                 or dis.numel() != N:
             raise ValueError("dis must hold N contiguous values of the operands' type on the device")
         pd = dis.data_ptr()
@@ -267,7 +282,7 @@ def amulet_mmlike_f32_general(task: int, A, B, thres, dis, R, *, thres_form: int
     """General test-query form: A may be stored K x M (trans_a), B N x K (trans_b); `thres` is a
     device tensor of N, M, 1 or M x N values according to `thres_form`; `dis` has N values."""
     lib = load_library()
-    args = _general_args("torch.float32", task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
+    args = _general_args(_torch.float32, task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
     _check(lib.amulet_mmlike_f32_general(task, thres_form, int(trans_a), int(trans_b), shape, *args,
                                          _stream_ptr(stream)), "amulet_mmlike_f32_general")
 
@@ -277,7 +292,7 @@ def amulet_mmlike_f32_adaptive_general(task: int, A, B, thres, dis, R, *, thres_
     """The general test-query form with the paper's in-flight adaptive execution.  Returns
     (chosen shape id, number of trial slabs)."""
     lib = load_library()
-    args = _general_args("torch.float32", task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
+    args = _general_args(_torch.float32, task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
     chosen, trials = ctypes.c_int(-1), ctypes.c_int(0)
     _check(lib.amulet_mmlike_f32_adaptive_general(task, thres_form, int(trans_a), int(trans_b), *args,
                                                   _stream_ptr(stream), ctypes.byref(chosen), ctypes.byref(trials)),
@@ -291,7 +306,7 @@ def amulet_mmlike_f64(task: int, A, B, thres, dis, R, *, thres_form: int = AMULE
     (trans_a), B N x K (trans_b); `thres` holds N, M, 1 or M x N values according to
     `thres_form`; `dis` has N values; `shape` -1 is the selected (else the built-in) fp64 shape."""
     lib = load_library()
-    args = _general_args("torch.float64", task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
+    args = _general_args(_torch.float64, task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
     _check(lib.amulet_mmlike_f64_shape(task, shape, thres_form, int(trans_a), int(trans_b), *args,
                                        _stream_ptr(stream)), "amulet_mmlike_f64_shape")
 
@@ -301,7 +316,7 @@ def amulet_mmlike_f64_adaptive(task: int, A, B, thres, dis, R, *, thres_form: in
     """The fp64 tasks with the paper's in-flight adaptive execution.  Returns (chosen fp64 shape
     id, number of trial slabs)."""
     lib = load_library()
-    args = _general_args("torch.float64", task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
+    args = _general_args(_torch.float64, task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
     chosen, trials = ctypes.c_int(-1), ctypes.c_int(0)
     _check(lib.amulet_mmlike_f64_adaptive(task, thres_form, int(trans_a), int(trans_b), *args, _stream_ptr(stream),
                                           ctypes.byref(chosen), ctypes.byref(trials)), "amulet_mmlike_f64_adaptive")
@@ -354,7 +369,7 @@ def amulet_pack(src, dst, stream=None):
 def _autopack(fn_name: str, dtype_name: str, task, A, B, thres, dis, R, workspace, thres_form, trans_a, trans_b,
               stream):
     lib = load_library()
-    args = _general_args(dtype_name, task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
+    args = _general_args(getattr(_torch, dtype_name), task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
     pw, nw = None, 0
     if workspace is not None:
         if not workspace.is_cuda or not workspace.is_contiguous():
@@ -369,23 +384,23 @@ def amulet_mmlike_f32_autopack(task: int, A, B, thres, dis, R, workspace, *, thr
     """amulet_mmlike_f32_general with packing allowed: `workspace` (any contiguous device tensor
     of at least amulet_autopack_workspace_bytes(4, M, K) bytes, or None) may receive a packed
     copy of A that the task then reads."""
-    _autopack("amulet_mmlike_f32_autopack", "torch.float32", task, A, B, thres, dis, R, workspace, thres_form,
+    _autopack("amulet_mmlike_f32_autopack", "float32", task, A, B, thres, dis, R, workspace, thres_form,
               trans_a, trans_b, stream)
 
 
 def amulet_mmlike_f64_autopack(task: int, A, B, thres, dis, R, workspace, *, thres_form: int = AMULET_THRES_COL,
                                trans_a: bool = False, trans_b: bool = False, stream=None):
     """amulet_mmlike_f64 with packing allowed (see amulet_mmlike_f32_autopack; 8-byte elements)."""
-    _autopack("amulet_mmlike_f64_autopack", "torch.float64", task, A, B, thres, dis, R, workspace, thres_form,
+    _autopack("amulet_mmlike_f64_autopack", "float64", task, A, B, thres, dis, R, workspace, thres_form,
               trans_a, trans_b, stream)
 
 
 def amulet_count_i8(A, B, R, stream=None):
     """R += A @ B for int8 A, B and int32 R on the GPU, exact; enqueues and returns."""
     lib = load_library()
-    pa, M, K, lda = _mat(A, "torch.int8", "A")
-    pb, K2, N, ldb = _mat(B, "torch.int8", "B")
-    pr, M2, N2, ldr = _mat(R, "torch.int32", "R")
+    pa, M, K, lda = _mat(A, _torch.int8, "A")
+    pb, K2, N, ldb = _mat(B, _torch.int8, "B")
+    pr, M2, N2, ldr = _mat(R, _torch.int32, "R")
     if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch: A %dx%d, B %dx%d, R %dx%d" % (M, K, K2, N, M2, N2))
     _check(lib.amulet_count_i8(M, N, K, pa, lda, pb, ldb, pr, ldr, _stream_ptr(stream)),
@@ -397,9 +412,9 @@ def amulet_count_i8_adaptive(A, B, R, stream=None):
     tried on slabs of rows of R, the rest runs with the fastest.  Returns (chosen shape id, number
     of trial slabs)."""
     lib = load_library()
-    pa, M, K, lda = _mat(A, "torch.int8", "A")
-    pb, K2, N, ldb = _mat(B, "torch.int8", "B")
-    pr, M2, N2, ldr = _mat(R, "torch.int32", "R")
+    pa, M, K, lda = _mat(A, _torch.int8, "A")
+    pb, K2, N, ldb = _mat(B, _torch.int8, "B")
+    pr, M2, N2, ldr = _mat(R, _torch.int32, "R")
     if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch: A %dx%d, B %dx%d, R %dx%d" % (M, K, K2, N, M2, N2))
     chosen, trials = ctypes.c_int(-1), ctypes.c_int(0)
@@ -424,9 +439,9 @@ def amulet_count_i8_general(A, B, R, workspace=None, *, trans_a: bool = False, t
     is a contiguous device tensor of at least amulet_count_i8_workspace_bytes(...) bytes, or of
     amulet_count_i8_repack_workspace_bytes(...) to have unaligned operands re-pitched as well."""
     lib = load_library()
-    pa, ra, ca, lda = _mat(A, "torch.int8", "A")
-    pb, rb, cb, ldb = _mat(B, "torch.int8", "B")
-    pr, M, N, ldr = _mat(R, "torch.int32", "R")
+    pa, ra, ca, lda = _mat(A, _torch.int8, "A")
+    pb, rb, cb, ldb = _mat(B, _torch.int8, "B")
+    pr, M, N, ldr = _mat(R, _torch.int32, "R")
     Ma, K = (ca, ra) if trans_a else (ra, ca)
     K2, Nb = (cb, rb) if trans_b else (rb, cb)
     if K2 != K or Ma != M or Nb != N:
@@ -447,9 +462,9 @@ def amulet_count_i8_static(A, B, R, *, trans_a: bool = False, trans_b: bool = Fa
     """amulet_count_i8_general without a workspace argument: the copies go into the library's own
     static device array (AMULET_STATIC_SCRATCH_BYTES); the call allocates nothing."""
     lib = load_library()
-    pa, ra, ca, lda = _mat(A, "torch.int8", "A")
-    pb, rb, cb, ldb = _mat(B, "torch.int8", "B")
-    pr, M, N, ldr = _mat(R, "torch.int32", "R")
+    pa, ra, ca, lda = _mat(A, _torch.int8, "A")
+    pb, rb, cb, ldb = _mat(B, _torch.int8, "B")
+    pr, M, N, ldr = _mat(R, _torch.int32, "R")
     Ma, K = (ca, ra) if trans_a else (ra, ca)
     K2, Nb = (cb, rb) if trans_b else (rb, cb)
     if K2 != K or Ma != M or Nb != N:
@@ -460,9 +475,9 @@ def amulet_count_i8_static(A, B, R, *, trans_a: bool = False, trans_b: bool = Fa
 
 def amulet_count_i8_shape(shape: int, A, B, R, stream=None):
     lib = load_library()
-    pa, M, K, lda = _mat(A, "torch.int8", "A")
-    pb, K2, N, ldb = _mat(B, "torch.int8", "B")
-    pr, M2, N2, ldr = _mat(R, "torch.int32", "R")
+    pa, M, K, lda = _mat(A, _torch.int8, "A")
+    pb, K2, N, ldb = _mat(B, _torch.int8, "B")
+    pr, M2, N2, ldr = _mat(R, _torch.int32, "R")
     if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch: A %dx%d, B %dx%d, R %dx%d" % (M, K, K2, N, M2, N2))
     _check(lib.amulet_count_i8_shape(shape, M, N, K, pa, lda, pb, ldb, pr, ldr, _stream_ptr(stream)),
@@ -473,9 +488,9 @@ def amulet_count_i8_assign(A, B, R, shape: int = -1, stream=None):
     """R = A @ B for int8 A, B and int32 R on the GPU, exact: the counts are written, whatever R
     held before; `shape` -1 is the selected shape.  Enqueues and returns."""
     lib = load_library()
-    pa, M, K, lda = _mat(A, "torch.int8", "A")
-    pb, K2, N, ldb = _mat(B, "torch.int8", "B")
-    pr, M2, N2, ldr = _mat(R, "torch.int32", "R")
+    pa, M, K, lda = _mat(A, _torch.int8, "A")
+    pb, K2, N, ldb = _mat(B, _torch.int8, "B")
+    pr, M2, N2, ldr = _mat(R, _torch.int32, "R")
     if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch: A %dx%d, B %dx%d, R %dx%d" % (M, K, K2, N, M2, N2))
     _check(lib.amulet_count_i8_assign(shape, M, N, K, pa, lda, pb, ldb, pr, ldr, _stream_ptr(stream)),
