@@ -30,7 +30,7 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3
 # in the metric's 2-flop-per-product convention is 2 x 78.6e12 / ops.
 VALU_LANE_OPS_PER_S = 256 * 128 * 2.4e9
 # (count_gt: multiply, subtract, shift, and one three-input add per two products of an accumulator)
-VALU_OPS_PER_PRODUCT = {"discount": 4, "boost": 4, "count_gt": 3.5, "identity": 1}
+VALU_OPS_PER_PRODUCT = {"discount": 4, "boost": 4, "count_gt": 3.03, "identity": 1}
 
 
 class ShaderClock:

@@ -46,8 +46,12 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef f4 f4_any __attribute__((aligned(4)));
 typedef const __attribute__((address_space(4))) float *sptr_f;      // read through the scalar cache
 
-template <int TASK> struct AccT { typedef float type; };
-template <> struct AccT<TASK_COUNT_GT> { typedef int type; };
+// partial and main accumulators: the count task keeps a product's predicate bit, one bit per
+// product of a partial sum, and counts them when they are folded in
+template <int TASK> struct AccT { typedef float type, main_type; };
+template <> struct AccT<TASK_COUNT_GT> { typedef uint32_t type; typedef int main_type; };
+// k of one partial sum: 64, or the 32 bits of the count task's partial
+template <int TASK> constexpr int partial_k() { return TASK == TASK_COUNT_GT ? 32 : FLUSH_K; }
 
 // Four products of one A value with a lane's group of four B values, folded
 // into the (partial) accumulators.  The multiply is a separately rounded fp32
@@ -93,19 +97,18 @@ __device__ __forceinline__ void fold4(float a, f4 b, const float *th, const floa
         // The count needs no lane mask: p > th exactly when th - p is negative (a difference of
         // two floats is zero only when they are equal, subnormal results included, and x - x is
         // +0), so the sign bit of the rounded difference is the predicate bit.  The one
-        // exception, -0 - (+0) = -0, is excluded by the caller: it never passes a threshold of -0.  multiply,
-        // subtract, shift, add: four plain vector instructions, against multiply, compare,
-        // select, add, where the compare and the select pass a lane mask through the scalar
-        // registers (a register-only loop of such a pair takes about as long as four plain
-        // instructions).  Measured: +5 % with A through LDS, +12-14 % with A in scalar registers,
-        // which the masks used to crowd out.
+        // exception, -0 - (+0) = -0, is excluded by the caller: it never passes a threshold of -0.
+        // v_alignbit_b32 shifts that bit into the partial in one instruction -- multiply, subtract,
+        // alignbit, and one bit count per 32 products -- where shifting it down and adding it
+        // took one and a half (register-only loops, 4 waves per SIMD: 8.3 against 6.5 clocks per 64
+        // products; compare and add with carry 9.9).  The kernel at 4096^3: 38.9 -> 42.7 TFLOP/s.
         float p[4], d[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) p[c] = a * b[c];          // one RN multiply (contraction is off)
 #pragma unroll
         for (int c = 0; c < 4; ++c) d[c] = th[c] - p[c];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[c] += (int)(__builtin_bit_cast(unsigned, d[c]) >> 31);
+        for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_alignbit(acc[c], __builtin_bit_cast(uint32_t, d[c]), 31);
     }
 }
 
@@ -259,13 +262,13 @@ mmlike_valu_kernel(const MmlikeArgs args)
     };
 
     acc_t part[TM][NG * 4];
-    float mainacc[TM][NG * 4];
+    typename AccT<TASK>::main_type mainacc[TM][NG * 4];
 #pragma unroll
     for (int r = 0; r < TM; ++r)
 #pragma unroll
         for (int c = 0; c < NG * 4; ++c) {
             part[r][c] = 0;
-            mainacc[r][c] = 0.0f;
+            mainacc[r][c] = 0;
         }
 
     // ---- B tile staging: global -> registers -> LDS -------------------------
@@ -377,21 +380,20 @@ mmlike_valu_kernel(const MmlikeArgs args)
         }
     };
     auto flush = [&]() {
-        if constexpr (TASK != TASK_COUNT_GT) {
 #pragma unroll
-            for (int r = 0; r < TM; ++r)
+        for (int r = 0; r < TM; ++r)
 #pragma unroll
-                for (int c = 0; c < NG * 4; ++c) {
-                    mainacc[r][c] += part[r][c];
-                    part[r][c] = 0;
-                }
-        }
+            for (int c = 0; c < NG * 4; ++c) {
+                if constexpr (TASK == TASK_COUNT_GT) mainacc[r][c] += __builtin_popcount(part[r][c]);
+                else mainacc[r][c] += part[r][c];
+                part[r][c] = 0;
+            }
     };
 
     const int full_tiles = K / BK;
     const int tail = K - full_tiles * BK;
     const int n_tiles = full_tiles + (tail ? 1 : 0);
-    constexpr int FLUSH_TILES = (FLUSH_K / BK) > 0 ? (FLUSH_K / BK) : 1;  // tiles per partial sum
+    constexpr int FLUSH_TILES = partial_k<TASK>() / BK;  // tiles per partial sum
 
     // A values of the chunk of KA k starting at kn, for the wave's TM rows, into SGPRs: TM
     // vectors of 4.  Row-major A: vector r holds row r's KA values.  Transposed A: vector
@@ -592,7 +594,7 @@ mmlike_valu_kernel(const MmlikeArgs args)
             }
         }
 
-        // fold the partial sums into the main accumulators every FLUSH_K products
+        // fold the partial sums into the main accumulators every partial_k products
         if ((t + 1) % FLUSH_TILES == 0)
             flush();
 
@@ -628,7 +630,7 @@ mmlike_valu_kernel(const MmlikeArgs args)
             float v[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                v[c] = (TASK == TASK_COUNT_GT) ? (float)part[r][g * 4 + c] : mainacc[r][g * 4 + c];
+                v[c] = (float)mainacc[r][g * 4 + c];
             if (ksplit) {
                 // several workgroups own this tile: hardware float adds, in whatever order
 #pragma unroll
@@ -709,7 +711,7 @@ static hipError_t launch_one(const MmlikeArgs &a, hipStream_t s)
     // TFLOP/s, count 36.4-37.2 against 36.9-40.4, boost within +-4 % either way).
     const bool a_through_lds = !a.transA && !a.transB && pitch_collides(a.lda, 4);
     constexpr bool DPIPE = TASK == TASK_DISCOUNT && TM == 4 && NG == 1 && BK == 16;
-    constexpr bool BAHEAD = (TASK == TASK_DISCOUNT || TASK == TASK_BOOST) && TM == 4 && NG == 1 && BK == 16;   // B values a chunk ahead
+    constexpr bool BAHEAD = TASK != TASK_IDENTITY && TM == 4 && NG == 1 && BK == 16;   // B values a chunk ahead
     auto launch = [&](int64_t n_blocks, int n_splits) -> hipError_t {
         return launch_row_of_blocks(b, n_blocks, 64 * NW, [&](unsigned n) {
             const dim3 grid(n, (unsigned)n_splits), block(64 * NW);
@@ -722,9 +724,9 @@ static hipError_t launch_one(const MmlikeArgs &a, hipStream_t s)
                         break;
                     }
                 }
-                if constexpr (TASK == TASK_BOOST && TM == 4 && NG == 1 && BK == 16) {
-                    // B values read a chunk ahead (no chunk pipeline: the boost has no lane mask
-                    // to keep at a distance): +0.5-1.5 %
+                if constexpr ((TASK == TASK_BOOST || TASK == TASK_COUNT_GT) && TM == 4 && NG == 1 && BK == 16) {
+                    // B values read a chunk ahead (no chunk pipeline: these tasks have no lane mask
+                    // to keep at a distance): boost +0.5-1.5 %, count +1 % (42.7 -> 43.0 TFLOP/s at 4096^3)
                     if (!a_through_lds) {
                         hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 0, TM, NG, NW, BK, KA, false, false, true>), grid, block, 0, s, b);
                         break;

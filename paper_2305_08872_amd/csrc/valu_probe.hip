@@ -13,15 +13,18 @@ namespace amulet {
 // mix 0: fused multiply-add only (the identity task's inner operation)
 // mix 1: multiply, compare, select, fused multiply-add (the discount task), interleaved as in the kernel
 // mix 2: fma, fma, max, add (the boost task), one product at a time as in the kernel
-// mix 3: multiply, subtract, then the sign bit of the difference added to an integer count (the count task)
+// mix 3: multiply, subtract, then the sign bit of the difference shifted into a register of 32, whose bits
+//        are counted when it is full (the count task)
 template <int MIX>
 __global__ void __launch_bounds__(256) valu_probe_kernel(float *out, float a0, int iters)
 {
     float acc[16], b[16], th[16], q[16];
     int cnt[16];
+    uint32_t bits[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         cnt[i] = 0;
+        bits[i] = 0;
         acc[i] = threadIdx.x * 0.001f + i;
         b[i] = 1.0f + i * 0.01f + threadIdx.x * 1e-6f;
         // per-lane values, as in the kernels: a wave-uniform threshold would be kept in a scalar
@@ -66,7 +69,7 @@ __global__ void __launch_bounds__(256) valu_probe_kernel(float *out, float a0, i
 #pragma unroll
                     for (int c = 0; c < 4; ++c) d[c] = th[g * 4 + c] - p[c];
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) cnt[g * 4 + c] += (int)(__builtin_bit_cast(unsigned, d[c]) >> 31);
+                    for (int c = 0; c < 4; ++c) bits[g * 4 + c] = __builtin_amdgcn_alignbit(bits[g * 4 + c], __builtin_bit_cast(uint32_t, d[c]), 31);
                 } else {
                     // one product at a time, as the kernel runs them
 #pragma unroll
@@ -81,10 +84,14 @@ __global__ void __launch_bounds__(256) valu_probe_kernel(float *out, float a0, i
             }
             a += 1e-7f;
         }
+        if (MIX == 3 && (it & 7) == 7) {   // 8 iterations of 4 products each: the 32 bits are full
+#pragma unroll
+            for (int i = 0; i < 16; ++i) { cnt[i] += __builtin_popcount(bits[i]); bits[i] = 0; }
+        }
     }
     float s = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s += acc[i] + (float)cnt[i];
+    for (int i = 0; i < 16; ++i) s += acc[i] + (float)(cnt[i] + __builtin_popcount(bits[i]));
     out[(size_t)blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
