@@ -29,7 +29,7 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3
 # lane-operations per product (discount: multiply, compare, select, FMA), so its ceiling
 # in the metric's 2-flop-per-product convention is 2 x 78.6e12 / ops.
 VALU_LANE_OPS_PER_S = 256 * 128 * 2.4e9
-# (count_gt: multiply, subtract, shift, and one three-input add per two products of an accumulator)
+# (count_gt: multiply, subtract, shift in the sign bit, and one bit count per 32 products of an accumulator)
 VALU_OPS_PER_PRODUCT = {"discount": 4, "boost": 4, "count_gt": 3.03, "identity": 1}
 
 

@@ -93,7 +93,9 @@ typedef enum {
  *   R       M x N fp32, ldr >= N, accumulated into ("+=", Fig. "12x16 inner kernel")
  *
  * The tile shape is the one amulet_tune() cached for this (task, M, N, K), or
- * a built-in default.  Each dimension must be below 2^31 - 2^16.
+ * a built-in default (where that is the library's own choice, a predicate task on
+ * a small, narrow or odd-sized problem runs a kernel with smaller tiles than
+ * any shape id names, chosen by an estimate of its time; fp64 likewise).  Each dimension must be below 2^31 - 2^16.
  */
 int amulet_mmlike_f32(int task, int64_t M, int64_t N, int64_t K,
                       const float *A, int64_t lda,

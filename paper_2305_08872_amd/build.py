@@ -22,6 +22,10 @@ SOURCES = ["amulet_api.hip", "mmlike_valu_identity_col.hip"] + [
     "mmlike_valu_%s_%s.hip" % (task, form)
     for task in ("discount", "boost", "count_gt")
     for form in ("col", "row", "const", "elem")
+] + [
+    "mmlike_tile_%s_%s.hip" % (elem, task)
+    for elem in ("f64", "f32")
+    for task in ("discount", "boost", "count_gt")
 ] + ["identity_mfma.hip", "identity_mfma_dma.hip", "count_i8.hip", "count_i8_dma.hip", "valu_probe.hip", "mmlike_valu_f64.hip", "identity_mfma_f64.hip", "identity_mfma_f64_dma.hip", "pack.hip"]
 
 HIPCC_FLAGS = [

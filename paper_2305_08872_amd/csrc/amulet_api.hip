@@ -181,8 +181,61 @@ static hipError_t launch_form(int form, int shape, const MmlikeArgs &a, hipStrea
     }
 }
 
-static int run_mmlike(const MmlikeCall &c, int shape, void *stream)
+template <typename T, typename Call>
+static hipError_t launch_tile_call(const Call &c, const TilePlan &plan, hipStream_t s)
 {
+    TileArgs<T> a;
+    a.A = c.A; a.B = c.B; a.thres = c.thres; a.dis = c.dis; a.R = c.R;
+    a.lda = c.lda; a.ldb = c.ldb; a.ldr = c.ldr; a.ldt = c.ldt;
+    a.M = (int)c.M; a.N = (int)c.N; a.K = (int)c.K;
+    const int trans = (c.trans_a ? 1 : 0) | (c.trans_b ? 2 : 0);
+    switch (c.task) {
+    case TASK_DISCOUNT: return launch_mmlike_tile<T, TASK_DISCOUNT>(c.thres_form, trans, plan, a, s);
+    case TASK_BOOST: return launch_mmlike_tile<T, TASK_BOOST>(c.thres_form, trans, plan, a, s);
+    default: return launch_mmlike_tile<T, TASK_COUNT_GT>(c.thres_form, trans, plan, a, s);
+    }
+}
+
+// Predicate tasks: the plan of the tile kernels when they can run the problem -- a stage of K, a
+// 16-byte unit in an operand whose lines run across k, and per-lane byte offsets that fit 31 bits.
+template <typename T, typename Call>
+static bool tile_plan(const Call &c, double us_per_k, TilePlan &plan)
+{
+    constexpr int64_t V = 16 / (int64_t)sizeof(T), BK = 4 * V, MAX = 0x7fffffff / (int64_t)sizeof(T);
+    if (c.K < BK || (c.trans_a && c.M < V) || (!c.trans_b && c.N < V)) return false;
+    if (c.lda > (c.trans_a ? (MAX - 32) / BK : (MAX - BK) / 32) || c.ldb > (c.trans_b ? (MAX - BK) / 64 : (MAX - 64) / BK)) return false;
+    plan = choose_tile_plan<T>(c.M, c.N, c.K, us_per_k);
+    return true;
+}
+
+// fp32: the tile kernels, unless the 32 x 256 kernel's estimate is lower.  That kernel takes twice the
+// columns per LDS read and a scalar-register A, and so 7-9 % less time per product once it has rounds
+// enough; its tiles are 4 times larger (two to a compute unit and round, and a tenth
+// of a tile's time for the launch's two ends, 0.35 when its last round is split), and below one per unit
+// it is never ahead.  Measured, us, 32 x 256 (or
+// 16 x 256) kernel with its own K split / tile kernel: discount 256^3 17.4 / 7.1, 512^3 39.5 / 13.7, 1024^3
+// 98 / 73, 1536^3 265 / 237, 2048^3 527 / 532, 4096^3 4008 / 4230, 3262 x 288 x 5014 699 / 338, 6720 x 64 x 3115 446 /
+// 100, 1251 x 640 x 2527 190 / 153, 5502 x 2560 x 832 boost 781 / 801, 2048 x 4597 x 743 count 388 / 356.
+static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
+{
+    // us per k of one of two resident workgroups (tile kernels), and of a 32 x 256 workgroup
+    static const double tile_us[4] = {0.0, 0.127, 0.140, 0.097}, large_us[4] = {0.0, 0.115, 0.121, 0.0925};
+    if (c.task == TASK_IDENTITY || !tile_plan<float>(c, tile_us[c.task], plan)) return false;
+    const int64_t large = ((c.M + 31) / 32) * ((c.N + 255) / 256);
+    if (large < 256) return true;
+    const double rounds = (double)large / 256.0, part_round = large % 512 == 0 ? 0.1 : 0.35;
+    return plan.us <= (double)c.K * large_us[c.task] * (rounds + part_round) + 7.0 + 4.0 * rounds;
+}
+
+// `built_in`: the shape is nobody's choice but this library's own, so the launch may take the tile
+// kernels, which have no shape id.
+static int run_mmlike(const MmlikeCall &c, int shape, void *stream, bool built_in)
+{
+    TilePlan plan;
+    if (built_in && tile_wanted(c, plan)) {
+        g_last_hip_error = launch_tile_call<float>(c, plan, (hipStream_t)stream);
+        return g_last_hip_error == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
+    }
     MmlikeArgs a;
     a.A = c.A; a.B = c.B; a.thres = c.thres; a.dis = c.dis; a.R = c.R;
     a.lda = c.lda; a.ldb = c.ldb; a.ldr = c.ldr; a.ldt = c.ldt;
@@ -308,7 +361,7 @@ static int trial_launch(TrialCtx *c, int shape)
     MmlikeCall call = {c->task, THRES_COL, 0, 0, c->M, c->N, c->K, (const float *)c->A, c->K,
                        (const float *)c->B, c->N, (const float *)c->params, 0,
                        (const float *)c->params + c->N, (float *)c->R, c->N};
-    return run_mmlike(call, shape, c->stream);
+    return run_mmlike(call, shape, c->stream, shape == default_shape(c->task, c->M, c->N, c->K));
 }
 
 // Milliseconds of `n` back-to-back launches of `shape`, or a negative value on failure.
@@ -457,7 +510,7 @@ static int run_rows(const MmlikeCall &c, int shape, int64_t r0, int64_t rows, hi
     sub.R = c.R + r0 * c.ldr;
     if (c.thres_form == THRES_ROW && c.thres) sub.thres = c.thres + r0;
     if (c.thres_form == THRES_ELEM && c.thres) sub.thres = c.thres + r0 * c.ldt;
-    return run_mmlike(sub, shape, s);
+    return run_mmlike(sub, shape, s, shape == default_shape(c.task, c.M, c.N, c.K));
 }
 
 static double adaptive_trial(AdaptiveCtx *x, int shape)
@@ -509,12 +562,13 @@ int amulet_mmlike_f32_general(int task, int thres_form, int trans_a, int trans_b
                           thres, ldt, dis, R, ldr};
     const int rc = check_mmlike(c);
     if (rc < 0) return rc;
-    if (shape < 0)
+    const bool selected = shape < 0;
+    if (selected)
         shape = lookup_shape(task, M, N, K);
     else if (shape >= n_shapes(task))
         return AMULET_ERR_SHAPE;
     if (rc == 1) return AMULET_OK;
-    return run_mmlike(c, shape, stream);
+    return run_mmlike(c, shape, stream, selected && shape == default_shape(task, M, N, K));
 }
 
 // ---- fp64 ------------------------------------------------------------------------------------
@@ -570,15 +624,31 @@ static int lookup_shape_f64(int task, int64_t M, int64_t N, int64_t K)
 }
 
 // Rows [r0, r0 + rows) of the task with `shape`.
-static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, void *stream)
+static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, void *stream, bool built_in)
 {
+    F64Call sub = c;
+    sub.M = rows;
+    sub.A = c.trans_a ? c.A + r0 : c.A + r0 * c.lda;
+    if (c.thres_form == THRES_ROW && c.thres) sub.thres = c.thres + r0;
+    if (c.thres_form == THRES_ELEM && c.thres) sub.thres = c.thres + r0 * c.ldt;
+    sub.R = c.R + r0 * c.ldr;
+    // (tile kernels: see tile_wanted.  In fp64 they are ahead of the shape grid's kernels nearly
+    // everywhere: TFLOP/s, grid / tile, 4096^3 discount 16.4 / 17.5, boost 15.2 / 17.3, count 22.4 / 24.4; us, 512^3
+    // discount 40 / 24, 256^3 16.3 / 9.5, 1024^3 boost 147 / 134)
+    // but two: thres[i][j] leaves the tile kernel registers for one workgroup per unit, so it is taken where
+    // there are not more than one round of the grid kernel's workgroups (512^3 47 / 36 us, 2048^3 1185 / 1314),
+    // and rows of A a multiple of 256 KiB apart, whose lines a stage of 8 k fetches in halves and the
+    // caches do not keep in between (discount 512^2 x 65536 2158 / 2355 us; the count has room for it).
+    static const double tile_us[4] = {0.0, 0.250, 0.255, 0.172};
+    TilePlan plan;
+    const bool per_output = c.thres_form == THRES_ELEM && ((rows + 15) / 16) * ((c.N + 127) / 128) > 1024;
+    const bool halves = c.task != TASK_COUNT_GT && !c.trans_a && c.lda % 32768 == 0;
+    if (built_in && c.task != TASK_IDENTITY && !per_output && !halves && tile_plan<double>(sub, tile_us[c.task], plan)) {
+        g_last_hip_error = launch_tile_call<double>(sub, plan, (hipStream_t)stream);
+        return g_last_hip_error == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
+    }
     MmlikeArgsF64 a;
-    a.A = c.trans_a ? c.A + r0 : c.A + r0 * c.lda;
-    a.B = c.B; a.dis = c.dis;
-    a.thres = c.thres;
-    if (c.thres_form == THRES_ROW && c.thres) a.thres = c.thres + r0;
-    if (c.thres_form == THRES_ELEM && c.thres) a.thres = c.thres + r0 * c.ldt;
-    a.R = c.R + r0 * c.ldr;
+    a.A = sub.A; a.B = c.B; a.dis = c.dis; a.thres = sub.thres; a.R = sub.R;
     a.lda = c.lda; a.ldb = c.ldb; a.ldr = c.ldr; a.ldt = c.ldt;
     a.M = (int)rows; a.N = (int)c.N; a.K = (int)c.K;
     a.transA = c.trans_a; a.transB = c.trans_b;
@@ -603,9 +673,10 @@ int amulet_mmlike_f64_shape(int task, int shape, int thres_form, int trans_a, in
     const int rc = check_f64(c);
     if (rc < 0) return rc;
     if (shape >= F64_SHAPE_COUNT) return AMULET_ERR_SHAPE;
-    if (shape < 0) shape = lookup_shape_f64(task, M, N, K);
+    const bool selected = shape < 0;
+    if (selected) shape = lookup_shape_f64(task, M, N, K);
     if (rc == 1) return AMULET_OK;
-    return run_f64_rows(c, shape, 0, M, stream);
+    return run_f64_rows(c, shape, 0, M, stream, selected && shape == default_shape_f64(task, M, N));
 }
 
 int amulet_mmlike_f64_general(int task, int thres_form, int trans_a, int trans_b, int64_t M, int64_t N,
@@ -669,7 +740,8 @@ static double adaptive_f64_score(int i0, int i1, void *ctx)
     double sc = 1e300;   // no rows left to test on: infinitely slow, which ends the walk
     if (x->status == AMULET_OK && x->next_row + rows <= x->budget_rows && !x->short_task) {
         (void)hipEventRecord(x->e0, x->stream);
-        const int rc = run_f64_rows(x->call, shape, x->next_row, rows, x->stream);
+        const int rc = run_f64_rows(x->call, shape, x->next_row, rows, x->stream,
+                                    shape == default_shape_f64(x->call.task, x->call.M, x->call.N));
         (void)hipEventRecord(x->e1, x->stream);
         if (rc != AMULET_OK || hipEventSynchronize(x->e1) != hipSuccess) {
             x->status = AMULET_ERR_LAUNCH;
@@ -724,7 +796,7 @@ int amulet_mmlike_f64_adaptive(int task, int thres_form, int trans_a, int trans_
     if (x.e1) (void)hipEventDestroy(x.e1);
     if (x.status != AMULET_OK) return x.status;
     int out = AMULET_OK;
-    if (x.next_row < M) out = run_f64_rows(c, best, x.next_row, M - x.next_row, stream);
+    if (x.next_row < M) out = run_f64_rows(c, best, x.next_row, M - x.next_row, stream, best == default_shape_f64(task, M, N));
     if (out == AMULET_OK && x.trials > 0) {
         std::lock_guard<std::mutex> lock(g_sel_mutex);
         g_selected[sel_key(f64_cache_task(task), M, N, K)] = best;

@@ -309,6 +309,67 @@ struct MmlikeArgs {
     int force_splits; // > 1: every tile's K in this many parts (a k-axis point of the shape grid); 0: the launcher's rule
 };
 
+// Arguments of a mmlike_tile_kernel launch (mmlike_tile_impl.h).
+template <typename T>
+struct TileArgs {
+    const T *A;
+    const T *B;
+    const T *thres;
+    const T *dis;
+    T *R;
+    int64_t lda, ldb, ldr, ldt;
+    int M, N, K;
+    int kpart;       // k range of one of the gridDim.y parts of K
+    int kgroup;      // of which each of a workgroup's groups of waves sums this many k
+    int block_base;  // added to blockIdx.x (launch_row_of_blocks)
+};
+
+// How a tile-kernel launch covers its problem: tiles of 32 x 64 whose K four groups of two waves
+// share, or of 16 x 64 shared by eight waves, and the k ranges that follow.
+struct TilePlan {
+    int wide;           // 1: 32 x 64, 0: 16 x 64
+    int parts;          // workgroups per tile, each over kpart k (more than one: atomic adds into R)
+    int kpart, kgroup;
+    double us;          // the estimate it was chosen by
+};
+
+// The plan with the lowest estimated time.  A compute unit holds two workgroups (16 waves) and is
+// as fast per workgroup with two as with many; with one its SIMDs have two waves each and a
+// workgroup takes 1.12 of the half share.  So W workgroups, counted with the padding of the tile
+// order (an XCD's share is what its units have to take), are W / 512 pairs' time each `us_per_k`
+// per k a group sums -- the time per k of one of two resident workgroups, which is the task's
+// arithmetic -- and a last round of at most 256 is half a round and 12 % more.  Launch, first
+// loads and write-back: 4.75 us and 1.5 for every further round; the atomic adds of a tile in parts: 0.7 us and 0.23 T
+// adds per second.  Checked against the fastest of all plans at 250 drawn sizes (64 ... 8192 each way,
+// both element types): 1 % behind it on average, 11 % at most.
+template <typename T>
+inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_k)
+{
+    constexpr int V = 16 / (int)sizeof(T);
+    auto up = [](int64_t n, int64_t to) { return (n + to - 1) / to * to; };
+    TilePlan best = {0, 0, 0, 0, 0.0};
+    for (int wide = 0; wide < 2; ++wide) {
+        const int rows = wide ? 32 : 16, groups = wide ? 4 : 8;
+        const int64_t grid = xcd_grid((M + rows - 1) / rows, (N + 63) / 64);
+        for (int64_t p = 1; p <= 1024; p = p < 4 ? p + 1 : p % 3 ? p / 2 * 3 : p / 3 * 4) {   // 1 2 3 4 6 8 12 16 24 ...
+            if (p > 1 && (!k_split_allowed() || K < 128 || K / p < 48 || grid * p > 12288)) break;
+            const int64_t kpart = up((K + p - 1) / p, V), parts = (K + kpart - 1) / kpart;
+            const int64_t kgroup = up((kpart + groups - 1) / groups, V);
+            const int64_t W = grid * parts, rem = W % 512;
+            const double rounds = 2.0 * (double)(W / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 1.12 : 2.0);
+            double us = rounds * (double)kgroup * us_per_k + 4.75 + (rounds > 1.0 ? 1.5 * (rounds - 1.0) : 0.0);
+            if (parts > 1) us += 0.7 + (double)M * (double)N * (double)parts / 0.23e6;
+            if (best.parts == 0 || us < best.us) {
+                best.wide = wide; best.parts = (int)parts; best.kpart = (int)kpart; best.kgroup = (int)kgroup; best.us = us;
+            }
+        }
+    }
+    return best;
+}
+
+template <typename T, int TASK>
+hipError_t launch_mmlike_tile(int form, int trans, const TilePlan &plan, const TileArgs<T> &a, hipStream_t s);
+
 // Tile shapes of the VALU kernels, laid out as the two-axis grid the greedy parameter search
 // walks (paper Sec. 4.4-4.6).  Axis 0 is the k axis, the analogue of the paper's k_c (how much
 // of K one unit of work covers): the depth BK of the B tile staged per barrier, and then how

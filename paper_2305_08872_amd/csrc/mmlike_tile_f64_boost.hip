@@ -1,0 +1,6 @@
+// Boost task, f64, tile kernels (see mmlike_tile_impl.h)
+#include "mmlike_tile_impl.h"
+
+namespace amulet {
+template hipError_t launch_mmlike_tile<double, TASK_BOOST>(int, int, const TilePlan &, const TileArgs<double> &, hipStream_t);
+}

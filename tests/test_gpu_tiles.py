@@ -1,0 +1,48 @@
+"""GPU parity of the tile kernels of the predicate tasks (32 x 64 and 16 x 64 tiles whose K a
+workgroup's waves share), which built-in calls take at small, narrow and odd sizes: exact dyadic
+data with ties, so that every form, layout and size must agree bit for bit with the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+# edges of the tiles (16, 32 rows; 64 columns; 16-byte units of 4 and 2), of a stage (16 and 8 k) and
+# of the k ranges: the smallest problem of each layout, one more and one less than whole tiles and
+# stages, ranges of unequal length, K over several workgroups, more than one round of them
+SIZES = [(4, 4, 16), (1, 5, 16), (15, 63, 17), (16, 64, 64), (17, 65, 31), (33, 130, 100), (32, 64, 777), (100, 70, 2047),
+         (509, 515, 130)]
+
+
+@pytest.fixture(scope="module")
+def am():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2305_08872_amd as am
+    am.load_library()
+    return am
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("task", [1, 2, 3])
+@pytest.mark.parametrize("form", [0, 1, 2, 3])
+def test_tile_kernels_at_the_edges_of_tiles_stages_and_k_ranges(am, dtype, task, form):
+    ref = oracle.mmlike_f32_general if dtype == np.float32 else oracle.mmlike_f64_general
+    call = am.amulet_mmlike_f32_general if dtype == np.float32 else am.amulet_mmlike_f64
+    for idx, (M, N, K) in enumerate(SIZES):
+        g = np.random.Generator(np.random.PCG64(7100 + 10 * task + form + 100 * idx))
+        A, B = g.integers(-8, 9, (M, K)).astype(dtype), g.integers(-8, 9, (K, N)).astype(dtype)
+        th = (g.integers(-24, 25, {0: (N,), 1: (M,), 2: (1,), 3: (M, N)}[form]) / 2.0).astype(dtype)
+        dis = (g.integers(0, 9, N) / 8.0).astype(dtype)
+        R_in = g.integers(-5, 6, (M, N)).astype(dtype)
+        R_ref, _, _ = ref(task, A, B, th, dis if task == 1 else None, R_in, thres_form=form)
+        for tA, tB in [(False, False), (True, False), (False, True), (True, True)]:
+            dR = torch.from_numpy(R_in.copy()).cuda()
+            print("tile", dtype.__name__, task, form, tA, tB, M, N, K, flush=True)
+            call(task, torch.from_numpy(np.ascontiguousarray(A.T if tA else A)).cuda(),
+                 torch.from_numpy(np.ascontiguousarray(B.T if tB else B)).cuda(), torch.from_numpy(th).cuda(),
+                 torch.from_numpy(dis).cuda() if task == 1 else None, dR, thres_form=form, trans_a=tA, trans_b=tB)
+            torch.cuda.synchronize()
+            assert np.array_equal(dR.cpu().numpy(), R_ref.astype(dtype)), (M, N, K, tA, tB)
