@@ -348,21 +348,24 @@ int amulet_count_i8_assign(int shape, int64_t M, int64_t N, int64_t K,
 /*
  * The join count with operands stored transposed (the layouts of Sec. 6.3
  * applied to this task): A stored K x M (lda >= M) when trans_a != 0, B stored
- * N x K (ldb >= K) when trans_b != 0.  The matrix-core kernels read row-major
- * operands; a transposed operand is first copied, transposed, into `workspace`
- * (device memory the caller lends for the duration of the call's work on
- * `stream`; amulet_count_i8_workspace_bytes gives the size, 0 when neither
- * flag is set, and then `workspace` may be NULL): one more kernel per such
- * operand on the same stream, 3-4 % of the 8192 x 8192 x 4096 join each.
+ * N x K (ldb >= K) when trans_b != 0.  The built-in kernels read either layout
+ * in place, except where the kernel that wants row-major operands is faster by
+ * more than the copy costs (many whole 256 x 256 tiles and K >= 4096) or they
+ * cannot run the problem (K < 64, an operand's transposed extent < 16); then,
+ * and with a tuned shape, a transposed operand is first copied, transposed, into
+ * `workspace` (device memory the caller lends for the duration of the call's
+ * work on `stream`; amulet_count_i8_workspace_bytes gives the size, 0 when
+ * neither flag is set, and then `workspace` may be NULL): one more kernel per
+ * such operand on the same stream, 3-4 % of the 8192 x 8192 x 4096 join each.
  * The result is that of amulet_count_i8 on the row-major operands, exact.
  * AMULET_ERR_NULL if a workspace is needed and NULL, AMULET_ERR_WORKSPACE if
  * it is too small; other errors as amulet_count_i8.
  *
  * A larger workspace, of amulet_count_i8_repack_workspace_bytes(M, N, K) bytes
- * and 16-byte aligned, is also the operands' aligned home when they need one
- * (this is the packing of Sec. 3.1 for the join count: the fastest kernel
- * streams whole 16-byte units of rows that start on 16-byte boundaries, 64 k
- * at a time, and a workgroup whose whole tile of A rows and B columns exists
+ * and 16-byte aligned, is also the operands' aligned home when the kernels of
+ * explicit shapes run the problem and need one (this is the packing of Sec. 3.1
+ * for the join count: the fastest of them streams whole 16-byte units of rows
+ * that start on 16-byte boundaries, 64 k at a time, and a workgroup whose whole tile of A rows and B columns exists
  * in memory loads without guards).  An operand whose base or row pitch is not
  * a multiple of 16 bytes, or whose M resp. N is not a multiple of 256, is
  * copied to an aligned pitch with room for whole tiles around it, and when K

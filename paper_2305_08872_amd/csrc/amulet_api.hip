@@ -281,11 +281,58 @@ static int check_mmlike(const MmlikeCall &c)
 // phases of the persistent join-count kernels (see count_i8_dma_persistent_kernel)
 static const int kPersPhases[4] = {8, 2, 2, 16};   // groups, stages between groups, XCD modulus, XCD span (sixteenths)
 
+// Join count, built-in choice: runs the tile kernels (count_i8_tile.hip) and returns true, unless they cannot
+// run the problem -- 64 k, a 16-byte unit in an operand whose lines run across k, byte offsets that fit 31
+// bits -- or it is one of many whole tiles that the streamed kernels (count_i8_dma.hip) can take, where those
+// are ahead: their persistent form starts a tile while the last one's R is still on its way, and their
+// write-back of an R that is not read is shorter.  us, theirs / here:
+//   R += : 8192^2 x 4096 218 / 243, 7168 x 8192 x 4096 210 / 229, 8192^2 x 2048 156 / 165; but 8192^2 x 1024
+//     128 / 122, 6144 x 8192 x 4096 171 / 170, and 30 x 30 tiles, which do not divide over the XCDs, 164 / 141;
+//     with an operand to transpose first (at 8192^2 x 4096: A 233 / 244, B 235 / 265, both 250 / 252) from
+//     twice that K on;
+//   R = : 6144^2 x 4096 128 / 140, 3072^2 x 2048 26 / 30, 12288 x 8192 x 512 94 / 112; up to one 128 x 256
+//     tile per unit, where theirs is another kernel, 2048 x 4096 x 4096 42 / 35.
+// Anything ragged or unaligned: 8191^2 x 4095 562 / 357, 8000^2 x 4000 368 / 279, 1000^2 x 1000 38 / 6.5.
+static bool count_tile(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const int8_t *A, int64_t lda, const int8_t *B,
+                       int64_t ldb, int32_t *R, int64_t ldr, bool assign, void *stream, int &rc)
+{
+    const int64_t max_offset = 0x7fff0000;
+    if (K < 64 || (trans_a && M < 16) || (!trans_b && N < 16) || ldr > max_offset / 1024 || lda > max_offset / 256 || ldb > max_offset / 256)
+        return false;
+    const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
+    const bool whole = aligned16(R) && ldr % 4 == 0 && K % 64 == 0 && N % 256 == 0 && M % (tiles256 >= 1024 ? 256 : 128) == 0 &&
+                       (trans_a || (aligned16(A) && lda % 16 == 0)) && (trans_b || (aligned16(B) && ldb % 16 == 0));
+    if (whole && (assign ? M / 128 * (N / 256) > 256
+                         : M % 256 == 0 && tiles256 >= 832 && tiles256 % 8 == 0 && K >= (trans_a || trans_b ? 4096 : 2048)))
+        return false;
+    // (streamed straight to LDS, a piece of a row may start at any 4-byte address)
+    auto dwords = [](const void *p, int64_t ld, int64_t line) { return ((uintptr_t)p & 3u) == 0 && ld % 4 == 0 && line % 4 == 0; };
+    const bool stream_to_lds = dwords(A, lda, trans_a ? M : K) && dwords(B, ldb, trans_b ? K : N);
+    const CountTilePlan plan = choose_count_tile(M, N, K, !stream_to_lds, assign);
+    CountTileArgs a;
+    a.A = A; a.B = B; a.R = R; a.lda = lda; a.ldb = ldb; a.ldr = ldr;
+    a.M = (int)M; a.N = (int)N; a.K = (int)K;
+    a.assign = assign && plan.parts == 1 ? 1 : 0;
+    hipError_t e = hipSuccess;
+    if (assign && plan.parts > 1) {     // several workgroups add into a tile: from zero
+        CountArgs z;
+        z.R = R; z.ldr = ldr; z.M = (int)M; z.N = (int)N;
+        e = launch_zero_r_i32(z, (hipStream_t)stream);
+    }
+    if (e == hipSuccess) e = launch_count_i8_tile((trans_a ? 1 : 0) | (trans_b ? 2 : 0), plan, a, (hipStream_t)stream);
+    g_last_hip_error = e;
+    rc = e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
+    return true;
+}
+
+// built_in: nobody chose `shape`, the tile kernels may run the problem instead
 // m_load / n_load: rows of A / columns of B that exist in memory (0: just M, N)
 static int run_count(int shape, int64_t M, int64_t N, int64_t K, const int8_t *A, int64_t lda,
                      const int8_t *B, int64_t ldb, int32_t *R, int64_t ldr, void *stream,
-                     int64_t m_load = 0, int64_t n_load = 0, bool assign = false)
+                     bool built_in = false, int64_t m_load = 0, int64_t n_load = 0, bool assign = false)
 {
+    int rc;
+    if (built_in && m_load == 0 && count_tile(0, 0, M, N, K, A, lda, B, ldb, R, ldr, assign, stream, rc)) return rc;
     CountArgs a;
     a.assign = assign ? 1 : 0;
     a.A = A; a.B = B; a.R = R;
@@ -357,7 +404,7 @@ static int trial_launch(TrialCtx *c, int shape)
 {
     if (c->task == AMULET_TASK_COUNT_I8)
         return run_count(shape, c->M, c->N, c->K, (const int8_t *)c->A, c->K, (const int8_t *)c->B, c->N,
-                         (int32_t *)c->R, c->N, c->stream);
+                         (int32_t *)c->R, c->N, c->stream, shape == default_shape(AMULET_TASK_COUNT_I8, c->M, c->N, c->K));
     MmlikeCall call = {c->task, THRES_COL, 0, 0, c->M, c->N, c->K, (const float *)c->A, c->K,
                        (const float *)c->B, c->N, (const float *)c->params, 0,
                        (const float *)c->params + c->N, (float *)c->R, c->N};
@@ -925,8 +972,8 @@ int amulet_count_i8(int64_t M, int64_t N, int64_t K, const int8_t *A, int64_t ld
     const int rc = check_common(M, N, K, A, lda, B, ldb, R, ldr);
     if (rc < 0) return rc;
     if (rc == 1) return AMULET_OK;
-    return run_count(lookup_shape(AMULET_TASK_COUNT_I8, M, N, K), M, N, K, A, lda, B, ldb, R, ldr,
-                     stream);
+    const int shape = lookup_shape(AMULET_TASK_COUNT_I8, M, N, K);
+    return run_count(shape, M, N, K, A, lda, B, ldb, R, ldr, stream, shape == default_shape(AMULET_TASK_COUNT_I8, M, N, K));
 }
 
 // In-flight adaptive execution for the join count (paper Sec. 4.4): the candidates here are
@@ -941,6 +988,7 @@ int amulet_count_i8_adaptive(int64_t M, int64_t N, int64_t K, const int8_t *A, i
     const int rc = check_common(M, N, K, A, lda, B, ldb, R, ldr);
     if (rc < 0) return rc;
     int best = lookup_shape(AMULET_TASK_COUNT_I8, M, N, K);
+    const int built_in = default_shape(AMULET_TASK_COUNT_I8, M, N, K);
     if (chosen_shape) *chosen_shape = best;
     if (n_trials) *n_trials = 0;
     if (rc == 1) return AMULET_OK;
@@ -973,8 +1021,8 @@ int amulet_count_i8_adaptive(int64_t M, int64_t N, int64_t K, const int8_t *A, i
                 const int shape = order[i];
                 const int64_t rows = slab_rows(shape);
                 if (next_row + rows > budget) continue;   // no rows left for this one: a narrower tile may still fit
-                if (run_count(shape, rows, N, K, A + next_row * lda, lda, B, ldb, R + next_row * ldr, ldr, stream) !=
-                    AMULET_OK) {
+                if (run_count(shape, rows, N, K, A + next_row * lda, lda, B, ldb, R + next_row * ldr, ldr, stream,
+                              shape == built_in) != AMULET_OK) {
                     status = AMULET_ERR_LAUNCH;
                     break;
                 }
@@ -992,7 +1040,7 @@ int amulet_count_i8_adaptive(int64_t M, int64_t N, int64_t K, const int8_t *A, i
     if (status != AMULET_OK) return status;
     int out = AMULET_OK;
     if (next_row < M)
-        out = run_count(best, M - next_row, N, K, A + next_row * lda, lda, B, ldb, R + next_row * ldr, ldr, stream);
+        out = run_count(best, M - next_row, N, K, A + next_row * lda, lda, B, ldb, R + next_row * ldr, ldr, stream, best == built_in);
     if (out == AMULET_OK && trials > 1) {
         std::lock_guard<std::mutex> lock(g_sel_mutex);
         g_selected[sel_key(AMULET_TASK_COUNT_I8, M, N, K)] = best;
@@ -1040,6 +1088,12 @@ int amulet_count_i8_general(int trans_a, int trans_b, int64_t M, int64_t N, int6
         if (!workspace) return AMULET_ERR_NULL;
         if (workspace_bytes < amulet_count_i8_workspace_bytes(trans_a, trans_b, M, N, K)) return AMULET_ERR_WORKSPACE;
     }
+    // (the tile kernels read any layout and alignment in place: no copy)
+    const int shape = lookup_shape(AMULET_TASK_COUNT_I8, M, N, K);
+    int trc;
+    if (shape == default_shape(AMULET_TASK_COUNT_I8, M, N, K) &&
+        count_tile(trans_a, trans_b, M, N, K, A, lda, B, ldb, R, ldr, false, stream, trc))
+        return trc;
     int8_t *w = (int8_t *)workspace;
     hipStream_t s = (hipStream_t)stream;
     // With room for both operands the workspace also serves as their aligned home: an operand
@@ -1083,8 +1137,8 @@ int amulet_count_i8_general(int trans_a, int trans_b, int64_t M, int64_t N, int6
         n_load = i8_tile_up(N);
     }
     if (e != hipSuccess) { g_last_hip_error = e; return AMULET_ERR_LAUNCH; }
-    return run_count(lookup_shape(AMULET_TASK_COUNT_I8, M, N, K), M, N, Kc, A, lda, B, ldb, R, ldr, stream,
-                     m_load, n_load);
+    return run_count(shape, M, N, Kc, A, lda, B, ldb, R, ldr, stream,
+                     false, m_load, n_load);
 }
 
 // ---- the join count for callers that cannot allocate --------------------------------------
@@ -1164,13 +1218,15 @@ int amulet_count_i8_assign(int shape, int64_t M, int64_t N, int64_t K, const int
         g_last_hip_error = e;
         return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
     }
+    bool built_in = false;
     if (shape < 0) {
         shape = lookup_shape(AMULET_TASK_COUNT_I8, M, N, K);
+        built_in = shape == default_shape(AMULET_TASK_COUNT_I8, M, N, K);
         // (without the read of R the persistent kernel's edge over two 128 x 256 tiles per unit starts
         // later: 768 tiles of 256 x 256 94 against 88 us, 1024 tiles level, 1536 tiles 272 / 277)
         if (shape == 8 && ((M + 255) / 256) * ((N + 255) / 256) < 1024) shape = 6;
     }
-    return run_count(shape, M, N, K, A, lda, B, ldb, R, ldr, stream, 0, 0, true);
+    return run_count(shape, M, N, K, A, lda, B, ldb, R, ldr, stream, built_in, 0, 0, true);
 }
 
 int amulet_greedy_search(int n0, int n1, amulet_score_fn score, void *ctx, int *best0, int *best1)

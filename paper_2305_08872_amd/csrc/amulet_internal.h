@@ -412,6 +412,64 @@ struct CountArgs {
     // alone stores its sums without reading R; a launch that splits K clears R first and adds
     int assign = 0;
 };
+// Arguments of a count_i8_tile_kernel launch (count_i8_tile.hip).
+struct CountTileArgs {
+    const int8_t *A;
+    const int8_t *B;
+    int32_t *R;
+    int64_t lda, ldb, ldr;
+    int M, N, K;
+    int kpart;       // k range of one of the gridDim.y parts of K
+    int kgroup;      // of which each of a workgroup's groups of waves sums this many k
+    int block_base;  // added to blockIdx.x (launch_row_of_blocks)
+    int assign;      // R = the counts instead of R +=
+};
+enum { CT_256 = 0, CT_128x256 = 1, CT_128 = 2, CT_64 = 3 };
+struct CountTilePlan {
+    int tile;               // CT_...
+    int through_registers;  // rows at any byte address, staged through registers; else streamed HBM -> LDS
+    int parts;              // workgroups per tile, each over kpart k (more than one: atomic adds into R)
+    int kpart, kgroup;
+    double us;              // the estimate it was chosen by
+};
+
+// The plan with the lowest estimated time.  Tiles: 256 x 256 (16 waves, one workgroup to a compute unit),
+// 128 x 256 (8 waves, two to a unit; streamed only), 128 x 128 (8 waves, two), 64 x 64 (two groups of 4 waves
+// that share K, two).  A stage of 64 k (64 x 64: 128) takes `alone` us in a workgroup that has its unit for
+// itself and `shared` per pair of workgroups on a unit, half as much again through registers; the rest of a
+// tile -- first loads, sums, write-back -- `rest_...`, a fifth less when R is not read.  W workgroups (with the
+// tile order's padding) are whole rounds and a last one in which at most one workgroup per unit is alone.
+// K over several workgroups: 0.7 us and 0.13 T atomic adds per second, 4 us more to clear an R that is
+// to be written.  Fitted to and checked against every tile and split at 290 drawn sizes (64 ... 8192 each way,
+// all layouts and alignments): 1.2 % behind the fastest on average, 26 % at most.
+inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool through_registers, bool assign)
+{
+    static const struct { int bm, bn, groups, resident; double alone, shared, rest_alone, rest_shared, registers; } tiles[4] = {
+        {256, 256, 1, 1, 0.57, 0.0, 13.7, 0.0, 1.4}, {128, 256, 1, 2, 0.54, 0.55, 8.3, 20.0, 0.0},
+        {128, 128, 1, 2, 0.21, 0.445, 6.0, 9.3, 1.5}, {64, 64, 2, 2, 0.23, 0.46, 3.3, 5.1, 1.6}};
+    auto up64 = [](int64_t n) { return (n + 63) / 64 * 64; };
+    CountTilePlan best = {0, through_registers ? 1 : 0, 0, 0, 0, 0.0};
+    for (int i = 0; i < 4; ++i) {
+        const auto &t = tiles[i];
+        if (through_registers && t.registers == 0.0) continue;
+        const int64_t grid = xcd_grid((M + t.bm - 1) / t.bm, (N + t.bn - 1) / t.bn), round = 256 * t.resident;
+        for (int64_t p = 1; p <= 64; p = p < 4 ? p + 1 : p % 3 ? p / 2 * 3 : p / 3 * 4) {   // 1 2 3 4 6 8 12 16 24 ...
+            if (p > 1 && (K / p < 256 || M * N * p > 4000000)) break;
+            const int64_t kpart = up64((K + p - 1) / p), parts = (K + kpart - 1) / kpart;
+            const int64_t kgroup = up64((kpart + t.groups - 1) / t.groups);
+            const double stages = (double)(kgroup / 64) * (through_registers ? t.registers : 1.0), r = assign ? 0.78 : 1.0;
+            const double alone = stages * t.alone + r * t.rest_alone, shared = t.resident > 1 ? stages * t.shared + r * t.rest_shared : alone;
+            const int64_t W = grid * parts, rem = W % round;
+            double us = 0.4 + (double)(W / round) * shared + (rem == 0 ? 0.0 : rem <= 256 ? alone : shared);
+            if (parts > 1) us += 0.7 + (double)M * (double)N * (double)parts / 0.132e6 + (assign ? 4.0 : 0.0);
+            if (best.parts == 0 || us < best.us) {
+                best.tile = i; best.parts = (int)parts; best.kpart = (int)kpart; best.kgroup = (int)kgroup; best.us = us;
+            }
+        }
+    }
+    return best;
+}
+hipError_t launch_count_i8_tile(int trans, const CountTilePlan &plan, const CountTileArgs &a, hipStream_t s);
 // shape 0: plain per-output loop; MFMA tiles 1: 128 x 128 (4 waves), 2: 256 x 256 (8 waves),
 // 3: 128 x 256 (8 waves)
 enum { COUNT_SHAPE_COUNT = 9 };

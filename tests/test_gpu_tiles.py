@@ -1,6 +1,7 @@
-"""GPU parity of the tile kernels of the predicate tasks (32 x 64 and 16 x 64 tiles whose K a
-workgroup's waves share), which built-in calls take at small, narrow and odd sizes: exact dyadic
-data with ties, so that every form, layout and size must agree bit for bit with the oracle."""
+"""GPU parity of the tile kernels: of the predicate tasks (32 x 64 and 16 x 64 tiles whose K a
+workgroup's waves share), which built-in calls take at small, narrow and odd sizes, on exact dyadic
+data with ties, so that every form, layout and size must agree bit for bit with the oracle; and of
+the join count (64 x 64 to 256 x 256), exact against a float32 product of small integers."""
 import numpy as np
 import pytest
 
@@ -46,3 +47,42 @@ def test_tile_kernels_at_the_edges_of_tiles_stages_and_k_ranges(am, dtype, task,
                  torch.from_numpy(dis).cuda() if task == 1 else None, dR, thres_form=form, trans_a=tA, trans_b=tB)
             torch.cuda.synchronize()
             assert np.array_equal(dR.cpu().numpy(), R_ref.astype(dtype)), (M, N, K, tA, tB)
+
+
+# edges of the join count's tiles (64 ... 256), of its 16-byte units and of its stages (64 k, 128 in two
+# groups): the smallest problem, one more and one less than whole tiles, units and stages, a short last
+# stage in either group, K over several workgroups, each of the four tiles with and without whole tiles
+I8_SIZES = [(16, 16, 64), (17, 31, 65), (63, 65, 127), (64, 64, 128), (65, 80, 193), (130, 100, 1055), (100, 260, 4097),
+            (1000, 1000, 250), (1100, 1500, 300), (2100, 1900, 130), (2048, 4096, 192), (2300, 4112, 208), (3000, 4400, 75)]
+
+
+@pytest.mark.parametrize("layout", [(False, False), (True, False), (False, True), (True, True)])
+def test_count_tile_kernels_at_the_edges_of_tiles_units_and_stages(am, layout):
+    tA, tB = layout
+    for idx, (M, N, K) in enumerate(I8_SIZES):
+        g = torch.Generator().manual_seed(9300 + idx)
+        A = torch.randint(-3, 4, (M, K), dtype=torch.int8, generator=g).cuda()
+        B = torch.randint(-3, 4, (K, N), dtype=torch.int8, generator=g).cuda()
+        want = A.float() @ B.float()          # |sum| < 2^24: exact
+        R_in = torch.randint(-9, 10, (M, N), dtype=torch.int32, generator=g).cuda()
+        ws = torch.empty(am.amulet_count_i8_workspace_bytes(tA, tB, M, N, K) + 16, dtype=torch.int8, device="cuda")
+        # rows as they are, at odd addresses (through registers) and at a pitch of whole 16 bytes (streamed)
+        for pad in (0, 1, 16):
+            def stored(X, trans):
+                X = X.t() if trans else X
+                pitch = X.shape[1] if pad == 0 else (X.shape[1] + 15) // 16 * 16 + pad
+                buf = torch.zeros(X.shape[0] * pitch + pad, dtype=torch.int8, device="cuda")
+                view = buf[pad % 16:][:X.shape[0] * pitch].view(X.shape[0], pitch)[:, :X.shape[1]]
+                view.copy_(X)
+                return view
+            print("count tile", layout, pad, M, N, K, flush=True)
+            sA, sB = stored(A, tA), stored(B, tB)
+            R = R_in.clone()
+            am.amulet_count_i8_general(sA, sB, R, ws, trans_a=tA, trans_b=tB)
+            torch.cuda.synchronize()
+            assert torch.equal(R - R_in, want.to(torch.int32)), (M, N, K, pad)
+            if not tA and not tB:
+                R = R_in.clone()
+                am.amulet_count_i8_assign(sA, sB, R)
+                torch.cuda.synchronize()
+                assert torch.equal(R, want.to(torch.int32)), (M, N, K, pad)
