@@ -1,4 +1,5 @@
-"""ctypes binding over the C ABI of libamulet.so (argument marshalling only).
+"""Binding over the C ABI of libamulet.so (argument marshalling only): ctypes, and a compiled module
+for the calls a program makes most often.
 
 Each function has the name of the C entry point it calls.  Tensor arguments
 are torch tensors already resident on the GPU; the binding takes their data
@@ -21,6 +22,9 @@ _lib = None
 # set with the library: torch, and its call that returns the raw stream of a device (None: not in this torch)
 _torch = None
 _raw_stream = None
+# the compiled marshalling of the calls that a program makes most often (csrc/marshal.cpp); None before the
+# library is loaded and where it was not built for this Python and torch: the functions below do the same
+_marshal = None
 
 
 class AmuletError(RuntimeError):
@@ -38,7 +42,7 @@ def library_path() -> str:
 
 def load_library():
     """Load libamulet.so (once).  Raises if it has not been built."""
-    global _lib, _torch, _raw_stream
+    global _lib, _torch, _raw_stream, _marshal
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -150,6 +154,10 @@ def load_library():
     lib.amulet_version.restype = ctypes.c_char_p
     lib.amulet_version.argtypes = []
     _torch, _raw_stream = torch, getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    try:
+        from . import _marshal
+    except ImportError:
+        _marshal = None
     _lib = lib
     return lib
 
@@ -161,7 +169,9 @@ _SCORE_FN = ctypes.CFUNCTYPE(ctypes.c_double, ctypes.c_int, ctypes.c_int, ctypes
 # few hundred rows run in less time on the GPU than the marshalling used to take.  Per call, measured:
 # current_stream() 3.2 us (it builds a Stream object) against 0.3 for the raw handle; checking and
 # reading three tensors 2.0 us with dtypes compared as text, 1.3 as objects; an amulet_mmlike_f32 call
-# of 64^3 9.7 us before, 6.2 now, of which 4.4 are the C call and its launch.
+# of 64^3 9.7 us before, 6.5 then, of which the launch is 2.7.  So the plain calls hand their arguments to
+# _marshal first; it answers None, having called nothing, for arguments that are not the ordinary ones, and
+# the checks here say what is wrong with them.
 def _stream_ptr(stream):
     if stream is None:
         if _raw_stream is not None:
@@ -206,6 +216,11 @@ def _check(rc: int, where: str):
 
 def amulet_mmlike_f32(task: int, A, B, params, R, stream=None):
     """R += sum_k g(A[i,k]*B[k,j], params[:, j]) on the GPU, in place; enqueues and returns."""
+    if _marshal is not None:
+        rc = _marshal.mmlike_f32(task, A, B, params, R, stream)
+        if rc is not None:
+            _check(rc, "amulet_mmlike_f32")
+            return
     lib = load_library()
     pa, M, K, lda = _mat(A, _torch.float32, "A")
     pb, K2, N, ldb = _mat(B, _torch.float32, "B")
@@ -281,6 +296,11 @@ def amulet_mmlike_f32_general(task: int, A, B, thres, dis, R, *, thres_form: int
                               trans_a: bool = False, trans_b: bool = False, shape: int = -1, stream=None):
     """General test-query form: A may be stored K x M (trans_a), B N x K (trans_b); `thres` is a
     device tensor of N, M, 1 or M x N values according to `thres_form`; `dis` has N values."""
+    if _marshal is not None:
+        rc = _marshal.mmlike_f32_general(task, A, B, thres, dis, R, thres_form, trans_a, trans_b, shape, stream)
+        if rc is not None:
+            _check(rc, "amulet_mmlike_f32_general")
+            return
     lib = load_library()
     args = _general_args(_torch.float32, task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
     _check(lib.amulet_mmlike_f32_general(task, thres_form, int(trans_a), int(trans_b), shape, *args,
@@ -305,6 +325,11 @@ def amulet_mmlike_f64(task: int, A, B, thres, dis, R, *, thres_form: int = AMULE
     """The tasks in the paper's own element type: fp64 device tensors; A may be stored K x M
     (trans_a), B N x K (trans_b); `thres` holds N, M, 1 or M x N values according to
     `thres_form`; `dis` has N values; `shape` -1 is the selected (else the built-in) fp64 shape."""
+    if _marshal is not None:
+        rc = _marshal.mmlike_f64(task, A, B, thres, dis, R, thres_form, trans_a, trans_b, shape, stream)
+        if rc is not None:
+            _check(rc, "amulet_mmlike_f64_shape")
+            return
     lib = load_library()
     args = _general_args(_torch.float64, task, A, B, thres, dis, R, thres_form, trans_a, trans_b)
     _check(lib.amulet_mmlike_f64_shape(task, shape, thres_form, int(trans_a), int(trans_b), *args,
@@ -397,6 +422,11 @@ def amulet_mmlike_f64_autopack(task: int, A, B, thres, dis, R, workspace, *, thr
 
 def amulet_count_i8(A, B, R, stream=None):
     """R += A @ B for int8 A, B and int32 R on the GPU, exact; enqueues and returns."""
+    if _marshal is not None:
+        rc = _marshal.count_i8(A, B, R, stream)
+        if rc is not None:
+            _check(rc, "amulet_count_i8")
+            return
     lib = load_library()
     pa, M, K, lda = _mat(A, _torch.int8, "A")
     pb, K2, N, ldb = _mat(B, _torch.int8, "B")
@@ -438,6 +468,11 @@ def amulet_count_i8_general(A, B, R, workspace=None, *, trans_a: bool = False, t
     """The join count with A stored K x M (trans_a) and / or B stored N x K (trans_b); `workspace`
     is a contiguous device tensor of at least amulet_count_i8_workspace_bytes(...) bytes, or of
     amulet_count_i8_repack_workspace_bytes(...) to have unaligned operands re-pitched as well."""
+    if _marshal is not None:
+        rc = _marshal.count_i8_general(A, B, R, workspace, trans_a, trans_b, stream)
+        if rc is not None:
+            _check(rc, "amulet_count_i8_general")
+            return
     lib = load_library()
     pa, ra, ca, lda = _mat(A, _torch.int8, "A")
     pb, rb, cb, ldb = _mat(B, _torch.int8, "B")
@@ -487,6 +522,11 @@ def amulet_count_i8_shape(shape: int, A, B, R, stream=None):
 def amulet_count_i8_assign(A, B, R, shape: int = -1, stream=None):
     """R = A @ B for int8 A, B and int32 R on the GPU, exact: the counts are written, whatever R
     held before; `shape` -1 is the selected shape.  Enqueues and returns."""
+    if _marshal is not None:
+        rc = _marshal.count_i8_assign(A, B, R, shape, stream)
+        if rc is not None:
+            _check(rc, "amulet_count_i8_assign")
+            return
     lib = load_library()
     pa, M, K, lda = _mat(A, _torch.int8, "A")
     pb, K2, N, ldb = _mat(B, _torch.int8, "B")

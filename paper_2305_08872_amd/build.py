@@ -1,4 +1,5 @@
-"""Builds libamulet.so (HIP, gfx950) in-tree with hipcc.
+"""Builds libamulet.so (HIP, gfx950) in-tree with hipcc, and _marshal.so, the compiled part of the
+Python binding, with the host compiler.
 
 One hipcc invocation per translation unit, run in parallel, then one link.
 Flags: -O3, fp contraction off (the compared product must be a separately
@@ -11,12 +12,14 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libamulet.so")
+MARSHAL_PATH = os.path.join(HERE, "_marshal.so")
 
 SOURCES = ["amulet_api.hip", "mmlike_valu_identity_col.hip"] + [
     "mmlike_valu_%s_%s.hip" % (task, form)
@@ -55,13 +58,39 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_marshal() -> str:
+    """The host-only extension module: this Python's and this torch's headers, no device code."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    obj = os.path.join(OBJ_DIR, "marshal.o")
+    inc = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           sysconfig.get_paths()["include"]]
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden",
+                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", INCLUDE]
+                          + [x for d in inc for x in ("-isystem", d)]
+                          + ["-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj])
+    return obj
+
+
+def _link_marshal(obj: str) -> None:
+    # (torch's libraries are in the process before the module is: no path to them is kept in it)
+    import torch
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-shared", "-o", MARSHAL_PATH, obj, "-L", HERE, "-l:libamulet.so",
+                           "-Wl,-rpath,$ORIGIN", "-Wl,--allow-shlib-undefined",
+                           "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"])
+
+
 def build(jobs: int = 8) -> str:
-    """Compile every HIP source for gfx950 and link libamulet.so; returns its path."""
+    """Compile every HIP source for gfx950 and link libamulet.so, then the binding's module; returns
+    the library's path."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as pool:
+        marshal = pool.submit(_compile_marshal)
         objs = list(pool.map(_compile, SOURCES))
+        marshal_obj = marshal.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH] + objs
     subprocess.check_call(cmd)
+    _link_marshal(marshal_obj)
     return LIB_PATH
 
 
