@@ -204,7 +204,7 @@ static bool tile_plan(const Call &c, double us_per_k, TilePlan &plan)
     constexpr int64_t V = 16 / (int64_t)sizeof(T), BK = 4 * V, MAX = 0x7fffffff / (int64_t)sizeof(T);
     if (c.K < BK || (c.trans_a && c.M < V) || (!c.trans_b && c.N < V)) return false;
     if (c.lda > (c.trans_a ? (MAX - 32) / BK : (MAX - BK) / 32) || c.ldb > (c.trans_b ? (MAX - BK) / 64 : (MAX - 64) / BK)) return false;
-    plan = choose_tile_plan<T>(c.M, c.N, c.K, us_per_k);
+    plan = choose_tile_plan<T>(c.M, c.N, c.K, us_per_k, sizeof(T) == 8 && c.thres_form == THRES_ELEM);
     return true;
 }
 
@@ -219,12 +219,12 @@ static bool tile_plan(const Call &c, double us_per_k, TilePlan &plan)
 static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
 {
     // us per k of one of two resident workgroups (tile kernels), and of a 32 x 256 workgroup
-    static const double tile_us[4] = {0.0, 0.127, 0.140, 0.097}, large_us[4] = {0.0, 0.115, 0.121, 0.0925};
+    static const double tile_us[4] = {0.0, 0.125, 0.130, 0.0955}, large_us[4] = {0.0, 0.115, 0.121, 0.0925};
     if (c.task == TASK_IDENTITY || !tile_plan<float>(c, tile_us[c.task], plan)) return false;
     const int64_t large = ((c.M + 31) / 32) * ((c.N + 255) / 256);
     if (large < 256) return true;
     const double rounds = (double)large / 256.0, part_round = large % 512 == 0 ? 0.1 : 0.35;
-    return plan.us <= (double)c.K * large_us[c.task] * (rounds + part_round) + 7.0 + 4.0 * rounds;
+    return 1.04 * plan.us <= (double)c.K * large_us[c.task] * (rounds + part_round) + 4.4 + 3.8 * rounds;
 }
 
 // `built_in`: the shape is nobody's choice but this library's own, so the launch may take the tile
@@ -686,7 +686,7 @@ static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, v
     // there are not more than one round of the grid kernel's workgroups (512^3 47 / 36 us, 2048^3 1185 / 1314),
     // and rows of A a multiple of 256 KiB apart, whose lines a stage of 8 k fetches in halves and the
     // caches do not keep in between (discount 512^2 x 65536 2158 / 2355 us; the count has room for it).
-    static const double tile_us[4] = {0.0, 0.250, 0.255, 0.172};
+    static const double tile_us[4] = {0.0, 0.251, 0.246, 0.172};
     TilePlan plan;
     const bool per_output = c.thres_form == THRES_ELEM && ((rows + 15) / 16) * ((c.N + 127) / 128) > 1024;
     const bool halves = c.task != TASK_COUNT_GT && !c.trans_a && c.lda % 32768 == 0;

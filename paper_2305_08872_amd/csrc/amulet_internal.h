@@ -299,7 +299,7 @@ struct MmlikeArgs {
     int64_t lda, ldb, ldr, ldt;   // ldt: row pitch of thres[i][j]
     int M, N, K;
     int transA, transB;  // operand stored transposed: a(i,k) = A[k*lda+i], b(k,j) = B[j*ldb+k]
-    int vec;   // 1 when B, R and their row pitches allow 16-byte vector accesses
+    int vec;   // identity: 1 when B, R and their row pitches allow 16-byte vector accesses
     int vecA;  // 1 when A and its row pitch do
     int kchunk;  // k range of one workgroup when a launch splits K (set by the launcher)
     // Tail split: blocks from tail_base on are the launch's last `tail_blocks` places of the tile
@@ -335,15 +335,17 @@ struct TilePlan {
 
 // The plan with the lowest estimated time.  A compute unit holds two workgroups (16 waves) and is
 // as fast per workgroup with two as with many; with one its SIMDs have two waves each and a
-// workgroup takes 1.12 of the half share.  So W workgroups, counted with the padding of the tile
+// workgroup takes 1.15 of the half share.  So W workgroups, counted with the padding of the tile
 // order (an XCD's share is what its units have to take), are W / 512 pairs' time each `us_per_k`
 // per k a group sums -- the time per k of one of two resident workgroups, which is the task's
-// arithmetic -- and a last round of at most 256 is half a round and 12 % more.  Launch, first
-// loads and write-back: 4.75 us and 1.5 for every further round; the atomic adds of a tile in parts: 0.7 us and 0.23 T
-// adds per second.  Checked against the fastest of all plans at 250 drawn sizes (64 ... 8192 each way,
-// both element types): 1 % behind it on average, 11 % at most.
+// arithmetic -- and a last round of at most 256 is half a round and 15 % more.  Launch, first
+// loads and write-back: 2.1 us and 1.3 per round; a tile in parts: 0.3 us and the atomic adds at
+// 1.6 T (fp64 0.8 T) per second beside other workgroups' arithmetic.  Checked against the fastest of all plans at
+// 240 drawn sizes (64 ... 8192 each way, both element types): 1.1 % behind it on average, 12 % at most.
+// (`alone`: the form that holds one workgroup to a unit, fp64 with thres[i][j]; nothing covers the loads of
+// a tile's thresholds there, 3.5 us per round.)
 template <typename T>
-inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_k)
+inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_k, bool alone = false)
 {
     constexpr int V = 16 / (int)sizeof(T);
     auto up = [](int64_t n, int64_t to) { return (n + to - 1) / to * to; };
@@ -352,13 +354,13 @@ inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_
         const int rows = wide ? 32 : 16, groups = wide ? 4 : 8;
         const int64_t grid = xcd_grid((M + rows - 1) / rows, (N + 63) / 64);
         for (int64_t p = 1; p <= 1024; p = p < 4 ? p + 1 : p % 3 ? p / 2 * 3 : p / 3 * 4) {   // 1 2 3 4 6 8 12 16 24 ...
-            if (p > 1 && (!k_split_allowed() || K < 128 || K / p < 48 || grid * p > 12288)) break;
+            if (p > 1 && (!k_split_allowed() || K < 128 || K / p < 32 || grid * p > 12288)) break;
             const int64_t kpart = up((K + p - 1) / p, V), parts = (K + kpart - 1) / kpart;
             const int64_t kgroup = up((kpart + groups - 1) / groups, V);
             const int64_t W = grid * parts, rem = W % 512;
-            const double rounds = 2.0 * (double)(W / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 1.12 : 2.0);
-            double us = rounds * (double)kgroup * us_per_k + 4.75 + (rounds > 1.0 ? 1.5 * (rounds - 1.0) : 0.0);
-            if (parts > 1) us += 0.7 + (double)M * (double)N * (double)parts / 0.23e6;
+            const double rounds = alone ? 1.15 * (double)((W + 255) / 256) : 2.0 * (double)(W / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 1.15 : 2.0);
+            double us = rounds * (double)kgroup * us_per_k + 2.1 + (alone ? 3.5 : 1.3) * rounds;
+            if (parts > 1) us += 0.3 + (double)M * (double)N * (double)parts / (sizeof(T) == 4 ? 1.6e6 : 0.8e6);
             if (best.parts == 0 || us < best.us) {
                 best.wide = wide; best.parts = (int)parts; best.kpart = (int)kpart; best.kgroup = (int)kgroup; best.us = us;
             }
@@ -439,14 +441,14 @@ struct CountTilePlan {
 // itself and `shared` per pair of workgroups on a unit, half as much again through registers; the rest of a
 // tile -- first loads, sums, write-back -- `rest_...`, a fifth less when R is not read.  W workgroups (with the
 // tile order's padding) are whole rounds and a last one in which at most one workgroup per unit is alone.
-// K over several workgroups: 0.7 us and 0.13 T atomic adds per second, 4 us more to clear an R that is
-// to be written.  Fitted to and checked against every tile and split at 290 drawn sizes (64 ... 8192 each way,
-// all layouts and alignments): 1.2 % behind the fastest on average, 26 % at most.
+// K over several workgroups (the two smaller tiles): 0.3 us and 1 T atomic adds per second beside other workgroups' arithmetic, 4 us
+// more to clear an R that is to be written.  Fitted to and checked against every tile and split at 210 drawn
+// sizes (64 ... 8192 each way, all layouts and alignments): 1.4 % behind the fastest on average, 28 % at most.
 inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool through_registers, bool assign)
 {
     static const struct { int bm, bn, groups, resident; double alone, shared, rest_alone, rest_shared, registers; } tiles[4] = {
-        {256, 256, 1, 1, 0.57, 0.0, 13.7, 0.0, 1.4}, {128, 256, 1, 2, 0.54, 0.55, 8.3, 20.0, 0.0},
-        {128, 128, 1, 2, 0.21, 0.445, 6.0, 9.3, 1.5}, {64, 64, 2, 2, 0.23, 0.46, 3.3, 5.1, 1.6}};
+        {256, 256, 1, 1, 0.57, 0.0, 17.0, 0.0, 1.42}, {128, 256, 1, 2, 0.55, 0.60, 8.5, 16.0, 0.0},
+        {128, 128, 1, 2, 0.206, 0.48, 4.8, 9.2, 1.52}, {64, 64, 2, 2, 0.19, 0.46, 2.8, 4.1, 1.67}};
     auto up64 = [](int64_t n) { return (n + 63) / 64 * 64; };
     CountTilePlan best = {0, through_registers ? 1 : 0, 0, 0, 0, 0.0};
     for (int i = 0; i < 4; ++i) {
@@ -454,14 +456,14 @@ inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool thr
         if (through_registers && t.registers == 0.0) continue;
         const int64_t grid = xcd_grid((M + t.bm - 1) / t.bm, (N + t.bn - 1) / t.bn), round = 256 * t.resident;
         for (int64_t p = 1; p <= 64; p = p < 4 ? p + 1 : p % 3 ? p / 2 * 3 : p / 3 * 4) {   // 1 2 3 4 6 8 12 16 24 ...
-            if (p > 1 && (K / p < 256 || M * N * p > 4000000)) break;
+            if (p > 1 && (i < CT_128 || K / p < 192 || M * N * p > 16000000)) break;
             const int64_t kpart = up64((K + p - 1) / p), parts = (K + kpart - 1) / kpart;
             const int64_t kgroup = up64((kpart + t.groups - 1) / t.groups);
-            const double stages = (double)(kgroup / 64) * (through_registers ? t.registers : 1.0), r = assign ? 0.78 : 1.0;
+            const double stages = (double)(kgroup / 64) * (through_registers ? t.registers : 1.0), r = assign ? 0.77 : 1.0;
             const double alone = stages * t.alone + r * t.rest_alone, shared = t.resident > 1 ? stages * t.shared + r * t.rest_shared : alone;
             const int64_t W = grid * parts, rem = W % round;
-            double us = 0.4 + (double)(W / round) * shared + (rem == 0 ? 0.0 : rem <= 256 ? alone : shared);
-            if (parts > 1) us += 0.7 + (double)M * (double)N * (double)parts / 0.132e6 + (assign ? 4.0 : 0.0);
+            double us = 1.2 + (double)(W / round) * shared + (rem == 0 ? 0.0 : rem <= 256 ? alone : shared);
+            if (parts > 1) us += 0.3 + (double)M * (double)N * (double)parts / 1.0e6 + (assign ? 4.0 : 0.0);
             if (best.parts == 0 || us < best.us) {
                 best.tile = i; best.parts = (int)parts; best.kpart = (int)kpart; best.kgroup = (int)kgroup; best.us = us;
             }

@@ -165,29 +165,32 @@ mmlike_tile_kernel(const TileArgs<T> args)
 #pragma unroll
     for (int d = 0; d < NST; ++d) issue(d, d);
 
-    // ---- rows and columns of this lane, and whether it owns them (writes them back) ----
-    auto row_of = [&](int r, bool &own) {
+    // ---- row and column of R at a place of the wave's 16 x 64, and whether it is written from here ----
+    auto row_at = [&](int p, bool &own) {
         if (TA) {
-            const int u = row0 + wm * 16 + lr * 4 + r / V * V;
-            const int row = (u < M - V ? u : M - V) + r % V;
+            const int u = row0 + wm * 16 + p / V * V;
+            const int row = (u < M - V ? u : M - V) + p % V;
             own = row >= u;
             return row;
         }
-        const int row = row0 + wm * 16 + lr * 4 + r;
+        const int row = row0 + wm * 16 + p;
         own = row < M;
         return own ? row : M - 1;
     };
-    auto col_of = [&](int c, bool &own) {
+    auto col_at = [&](int p, bool &own) {
         if (TB) {
-            const int col = col0 + wn * 64 + lc + 16 * c;
+            const int col = col0 + wn * 64 + p;
             own = col < N;
             return own ? col : N - 1;
         }
-        const int u = col0 + wn * 64 + c / V * (16 * V) + lc * V;
-        const int col = (u < N - V ? u : N - V) + c % V;
+        const int u = col0 + wn * 64 + p / V * V;
+        const int col = (u < N - V ? u : N - V) + p % V;
         own = col >= u;
         return col;
     };
+    // (of this lane's products)
+    auto row_of = [&](int r, bool &own) { return row_at(lr * 4 + r, own); };
+    auto col_of = [&](int c, bool &own) { return col_at(TB ? lc + 16 * c : c / V * (16 * V) + lc * V + c % V, own); };
 
     // Thresholds and factors in registers for the whole K loop.  (The count reads its predicate from
     // the sign of th - p, which takes a threshold of -0 for a negative number: held as th + 0.)
@@ -446,24 +449,40 @@ mmlike_tile_kernel(const TileArgs<T> args)
     constexpr int U = VALS < V ? VALS : V; // of which U at a time are neighbours in a row of R (row-major B)
     acc_t out[VALS];
     const int v0 = g * VALS;
-    if constexpr (WK > 1) {
-        __syncthreads();
-        acc_t *const img = (acc_t *)tile_smem;
+    __syncthreads();
+    acc_t *const img = (acc_t *)tile_smem;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) img[(((g * NW + wg) * 4 + r) * 64 + lane) * 4 + c] = result(r, c);
-        __syncthreads();
+        for (int c = 0; c < 4; ++c) img[(((g * NW + wg) * 4 + r) * 64 + lane) * 4 + c] = result(r, c);
+    __syncthreads();
+    if (ksplit) {
+        // Several workgroups own this tile: hardware float adds, in whatever order, 64 neighbours of a row
+        // at a time.  A wave's atomic adds to 256 contiguous bytes go four times as fast as to every fourth
+        // value of 1024: fp32 0.084 -> 0.34 T adds/s, fp64 0.043 -> 0.19.
+        int l = lane;      // (opaque here, or what follows is computed before the K loop and held through it)
+        asm volatile("" : "+v"(l));
+        const int src = TB ? (l % 16) * 4 + l / 16 : l % (16 * V) / V * 4 + l / (16 * V) * V + l % V;
+        bool own_col;
+        const int col = col_at(l, own_col);
 #pragma unroll
-        for (int v = 0; v < VALS; ++v) out[v] = 0;
+        for (int v = 0; v < VALS; ++v) {
+            const int p = v0 + v;
+            acc_t sum = 0;
 #pragma unroll
-        for (int s = 0; s < WK; ++s)
-#pragma unroll
-            for (int v = 0; v < VALS; ++v) out[v] += img[(((s * NW + wg) * 4 + (v0 + v) / 4) * 64 + lane) * 4 + (v0 + v) % 4];
-    } else {
-#pragma unroll
-        for (int v = 0; v < VALS; ++v) out[v] = result(v / 4, v % 4);
+            for (int s = 0; s < WK; ++s) sum += img[((s * NW + wg) * 4 + p % 4) * 256 + p / 4 * 64 + src];
+            bool own_row;
+            const int row = row_at(p, own_row);
+            if (own_row && own_col) unsafeAtomicAdd(args.R + (int64_t)row * args.ldr + col, (T)sum);
+        }
+        return;
     }
+#pragma unroll
+    for (int v = 0; v < VALS; ++v) out[v] = 0;
+#pragma unroll
+    for (int s = 0; s < WK; ++s)
+#pragma unroll
+        for (int v = 0; v < VALS; ++v) out[v] += img[(((s * NW + wg) * 4 + (v0 + v) / 4) * 64 + lane) * 4 + (v0 + v) % 4];
     typedef T uvec_raw __attribute__((ext_vector_type(U)));
     typedef uvec_raw uvec __attribute__((aligned(SZ)));
     bool own_r[VALS / U], own[VALS];
@@ -482,18 +501,17 @@ mmlike_tile_kernel(const TileArgs<T> args)
             dst[j * U + e] = args.R + (int64_t)row * args.ldr + col;
         }
         own_r[j] = all;      // from here on: the U values go out as one access
-        if (!ksplit && all) old[j] = *(const uvec *)dst[j * U];
-        else if (!ksplit) {
-#pragma unroll
-            for (int e = 0; e < U; ++e) if (own[j * U + e]) old[j][e] = *dst[j * U + e];
-        }
+        if (all) old[j] = *(const uvec *)dst[j * U];
     }
+    // (edges after the whole pieces, so that only waves that have one wait between loads of one register)
+#pragma unroll
+    for (int j = 0; j < VALS / U; ++j)
+#pragma unroll
+        for (int e = 0; e < U; ++e)
+            if (!own_r[j] && own[j * U + e]) old[j][e] = *dst[j * U + e];
 #pragma unroll
     for (int j = 0; j < VALS / U; ++j) {
-        if (ksplit) {
-#pragma unroll
-            for (int e = 0; e < U; ++e) if (own[j * U + e]) unsafeAtomicAdd(dst[j * U + e], (T)out[j * U + e]);
-        } else if (own_r[j]) {
+        if (own_r[j]) {
             uvec o = old[j];
 #pragma unroll
             for (int e = 0; e < U; ++e) o[e] += (T)out[j * U + e];
@@ -508,7 +526,7 @@ mmlike_tile_kernel(const TileArgs<T> args)
 template <typename T, int TASK, int TF, int TRANS, int WM, int WN, int WK, int NST>
 static hipError_t launch_tile(int parts, const TileArgs<T> &args, hipStream_t s)
 {
-    constexpr int RING = NST * WK * (1024 * WM + 4096 * WN), SUMS = WK > 1 ? WM * WN * WK * 1024 * (int)sizeof(T) : 0;
+    constexpr int RING = NST * WK * (1024 * WM + 4096 * WN), SUMS = WM * WN * WK * 1024 * (int)sizeof(T);
     constexpr int LDS = RING > SUMS ? RING : SUMS;
     auto *const kernel = &mmlike_tile_kernel<T, TASK, TF, TRANS, WM, WN, WK, NST>;
     static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
