@@ -120,7 +120,7 @@ __device__ __forceinline__ void fold4(float a, f4 b, const float *th, const floa
 // PIPE (discount task, 4 x 4 micro-tile): a chunk runs as one software pipeline instead of k by k
 // (see the chunk loop); the launcher says when.
 template <int TASK, int TF, int TRANS, int TM, int NG, int NW, int BK, int KA, bool ALDS, bool PIPE = false, bool BPRE = false>
-__global__ void __launch_bounds__(64 * NW)
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(TM * NG == 4 ? 4 : 1)))
 mmlike_valu_kernel(const MmlikeArgs args)
 {
     static_assert(!BPRE || (!ALDS && TM == 4 && NG == 1), "B values a chunk ahead: scalar-path A, 4 x 4 micro-tile");
@@ -146,7 +146,6 @@ mmlike_valu_kernel(const MmlikeArgs args)
 
     const int M = args.M, N = args.N;
     int K = args.K;
-    const bool VEC = args.vec != 0;   // B and R rows are 16-byte aligned: float4 global accesses
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // XCD-aware tile order (xcd_tile in amulet_internal.h): each XCD walks its own rectangular
@@ -165,6 +164,23 @@ mmlike_valu_kernel(const MmlikeArgs args)
     if (!xcd_tile(block, tiles_m, tiles_n, tm, tn)) return;   // padding: the whole workgroup leaves
     const int row0 = tm * (NW * TM) + wave * TM;
     const int col0 = tn * BN;
+    // The column at place p of the tile, and whether it is written from there: a group of four that would end
+    // past N is the group of the last four columns instead, of which its place owns those not owned by
+    // the group before (N < 4: one by one).  So B loads without a branch whatever N and the alignment are;
+    // guarded loads into one register wait for each other (the kernel held to 128 registers with this, us:
+    // boost 3001 x 2001 x 1201 with A transposed 554 -> 499, count 3000 x 5001 x 1000 835 -> 789,
+    // thres[i][j] discount 3001 x 2001 x 1201 483 -> 453).
+    const bool groups = args.N >= 4;
+    auto col_at = [&](int p, bool &own) {
+        const int u = col0 + (p & ~3);
+        if (groups) {
+            const int col = (u < args.N - 4 ? u : args.N - 4) + (p & 3);
+            own = col >= u;
+            return col;
+        }
+        own = col0 + p < args.N;
+        return own ? col0 + p : args.N - 1;
+    };
 
     const float *__restrict__ Bg = args.B;
     sptr_f As = (sptr_f)args.A;
@@ -236,18 +252,16 @@ mmlike_valu_kernel(const MmlikeArgs args)
     for (int g = 0; g < NG; ++g)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int col = col0 + g * 256 + lane * 4 + c;
-            q[g * 4 + c] = 1.0f;
-            if constexpr (TF == THRES_COL) th_col[g * 4 + c] = __builtin_inff();
-            if (TASK != TASK_IDENTITY && col < N) {
+            bool own;
+            const int col = col_at(g * 256 + lane * 4 + c, own);
+            q[g * 4 + c] = TASK == TASK_DISCOUNT ? 1.0f - args.dis[col] : 1.0f;
+            if constexpr (TASK != TASK_IDENTITY) {
                 if constexpr (TF == THRES_COL) th_col[g * 4 + c] = held(args.thres[col]);
-                if (TASK == TASK_DISCOUNT) q[g * 4 + c] = 1.0f - args.dis[col];
-            }
-            if constexpr (TF == THRES_ELEM && TASK != TASK_IDENTITY) {
+                if constexpr (TF == THRES_ELEM) {
 #pragma unroll
-                for (int r = 0; r < TM; ++r)
-                    th_el[r][g * 4 + c] = (col < N) ? held(args.thres[(int64_t)rowc(r) * args.ldt + col])
-                                                    : __builtin_inff();
+                    for (int r = 0; r < TM; ++r)
+                        th_el[r][g * 4 + c] = held(args.thres[(int64_t)rowc(r) * args.ldt + col]);
+                }
             }
         }
     // the four thresholds facing row r, column group g
@@ -273,14 +287,13 @@ mmlike_valu_kernel(const MmlikeArgs args)
 
     // ---- B tile staging: global -> registers -> LDS -------------------------
     // Thread t stages float4 slot (row t / F4_PER_ROW + it * ROWS_PER_PASS, column group
-    // t % F4_PER_ROW) of every tile.  Interior tiles (all columns inside N, rows 16-byte
-    // aligned, BK full rows) take the branch-free path.
+    // t % F4_PER_ROW) of every tile.
     constexpr int ROWS_PER_PASS = NT / F4_PER_ROW;
     static_assert(NT % F4_PER_ROW == 0 && LOADS * ROWS_PER_PASS == BK, "slot mapping");
     const int srow = threadIdx.x / F4_PER_ROW;
-    const int scol = col0 + (threadIdx.x % F4_PER_ROW) * 4;
-    const bool fast_cols = VEC && (col0 + BN <= N);
-    const float *bsrc = Bg + (int64_t)srow * args.ldb + scol;   // advanced by BK rows per tile
+    bool own_dummy;
+    const int bcol = col_at((threadIdx.x % F4_PER_ROW) * 4, own_dummy);
+    const float *bsrc = Bg + (int64_t)srow * args.ldb + bcol;   // advanced by BK rows per tile
     const int64_t pass_stride = (int64_t)ROWS_PER_PASS * args.ldb;
     const int64_t tile_stride = (int64_t)BK * args.ldb;
     f4 stage[LOADS];
@@ -292,7 +305,7 @@ mmlike_valu_kernel(const MmlikeArgs args)
     static_assert(NT % BN == 0 && BK % TPC == 0 && KPT == 4 * LOADS, "transposed-B slot mapping");
     const int tcol = threadIdx.x % BN;
     const int tk = (threadIdx.x / BN) * KPT;
-    const float *btsrc = Bg + (int64_t)(col0 + tcol < N ? col0 + tcol : N - 1) * args.ldb + tk;
+    const float *btsrc = Bg + (int64_t)col_at(tcol, own_dummy) * args.ldb + tk;
     // A tile staging (ALDS): thread t < A_F4 stages float4 slot (row t / (BK / 4), k quad t % (BK / 4))
     const int a_sr = threadIdx.x / (BK / 4), a_sq = (threadIdx.x % (BK / 4)) * 4;
     const float *asrc = nullptr;
@@ -318,45 +331,41 @@ mmlike_valu_kernel(const MmlikeArgs args)
             }
         }
         if (transB) {
-            const bool colok = col0 + tcol < N;
+            if (krows == BK) {
 #pragma unroll
-            for (int it = 0; it < LOADS; ++it) {
-                f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-                const int kk = tk + 4 * it;
-                if (colok) {
-                    const float *src = btsrc + 4 * it;
-                    if (kk + 3 < krows) {
-                        v = *(const f4_any *)src;
-                    } else {
-                        if (kk + 0 < krows) v.x = src[0];
-                        if (kk + 1 < krows) v.y = src[1];
-                        if (kk + 2 < krows) v.z = src[2];
-                        if (kk + 3 < krows) v.w = src[3];
+                for (int it = 0; it < LOADS; ++it) stage[it] = *(const f4_any *)(btsrc + 4 * it);
+            } else {
+                // (k past the last one: the last one, never used.  Its number is opaque here, or the addresses are
+                // computed before the K loop and held in registers through it.)
+                int last = krows - 1;
+                asm volatile("" : "+s"(last));
+#pragma unroll
+                for (int it = 0; it < LOADS; ++it)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int kk = tk + 4 * it + e;
+                        stage[it][e] = btsrc[(kk < last ? kk : last) - tk];
                     }
-                }
-                stage[it] = v;
             }
             btsrc += BK;
-        } else if (fast_cols && krows == BK) {
+        } else if (krows == BK && groups) {
 #pragma unroll
             for (int it = 0; it < LOADS; ++it)
-                stage[it] = *(const f4 *)(bsrc + it * pass_stride);
+                stage[it] = *(const f4_any *)(bsrc + it * pass_stride);
             bsrc += tile_stride;
         } else {
+            int last = krows - 1;
+            asm volatile("" : "+s"(last));
 #pragma unroll
             for (int it = 0; it < LOADS; ++it) {
-                f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (srow + it * ROWS_PER_PASS < krows) {
-                    const float *src = bsrc + it * pass_stride;
-                    if (scol + 3 < N) {
-                        v = *(const f4_any *)src;
-                    } else {
-                        if (scol + 0 < N) v.x = src[0];
-                        if (scol + 1 < N) v.y = src[1];
-                        if (scol + 2 < N) v.z = src[2];
-                    }
+                const int kk = srow + it * ROWS_PER_PASS;
+                const float *src = bsrc + (int64_t)((kk < last ? kk : last) - srow) * args.ldb;
+                if (groups) {
+                    stage[it] = *(const f4_any *)src;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) stage[it][e] = src[bcol + e < N ? e : N - 1 - bcol];
                 }
-                stage[it] = v;
             }
             bsrc += tile_stride;
         }
@@ -604,50 +613,69 @@ mmlike_valu_kernel(const MmlikeArgs args)
     }
     flush();
 
+    if (ksplit) {
+        // several workgroups own this tile: hardware float adds, in whatever order; 64 neighbours of a row at
+        // a time, through the wave's kilobyte of the B tile (its own lanes only: no barrier).  A wave's atomic
+        // adds to 256 contiguous bytes go four times as fast as to every fourth value of 1024
+        // (0.34 against 0.084 T adds/s).
+        float *const x = &Bs[0][0][0] + wave * 256;
+#pragma unroll
+        for (int r = 0; r < TM; ++r) {
+            if (row0 + r >= M) break;
+            float *const dst_row = args.R + (int64_t)(row0 + r) * args.ldr;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                *(f4 *)(x + lane * 4) = f4{(float)mainacc[r][g * 4], (float)mainacc[r][g * 4 + 1], (float)mainacc[r][g * 4 + 2], (float)mainacc[r][g * 4 + 3]};
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    bool own;
+                    const int col = col_at(g * 256 + c * 64 + lane, own);
+                    if (own) unsafeAtomicAdd(dst_row + col, x[c * 64 + lane]);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        return;
+    }
+
     // ---- write-back: R += acc, once per tile ---------------------------------
-    // The aligned 16-byte pieces of R are all read before the first sum is stored: as one
+    // The 16-byte pieces of R (at any address) are all read before the first sum is stored: as one
     // read-modify-write after the other the compiler must keep every store behind the load before
     // it (the pointers might alias), a chain of TM x NG round trips to memory.
     f4 old[TM][NG];
-    bool fast[TM][NG];
+    bool whole[NG];
+    int col[NG];
 #pragma unroll
-    for (int r = 0; r < TM; ++r)
+    for (int g = 0; g < NG; ++g) {
+        bool last;
+        col[g] = col_at(g * 256 + lane * 4, whole[g]);
+        (void)col_at(g * 256 + lane * 4 + 3, last);
+        whole[g] = whole[g] && last;
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            const int col = col0 + g * 256 + lane * 4;
-            fast[r][g] = !ksplit && VEC && row0 + r < M && col + 3 < N;
+        for (int r = 0; r < TM; ++r) {
             old[r][g] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (fast[r][g]) old[r][g] = *(const f4 *)(args.R + (int64_t)(row0 + r) * args.ldr + col);
+            if (whole[g] && row0 + r < M) old[r][g] = *(const f4_any *)(args.R + (int64_t)(row0 + r) * args.ldr + col[g]);
         }
+    }
 #pragma unroll
     for (int r = 0; r < TM; ++r) {
-        const int row = row0 + r;
-        if (row >= M) continue;
-        float *dst_row = args.R + (int64_t)row * args.ldr;
+        if (row0 + r >= M) break;
+        float *dst_row = args.R + (int64_t)(row0 + r) * args.ldr;
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-            const int col = col0 + g * 256 + lane * 4;
-            float v[4];
+            f4 o = old[r][g];
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                v[c] = (float)mainacc[r][g * 4 + c];
-            if (ksplit) {
-                // several workgroups own this tile: hardware float adds, in whatever order
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (col + c < N) unsafeAtomicAdd(dst_row + col + c, v[c]);
-            } else if (fast[r][g]) {
-                f4 o = old[r][g];
-                o.x += v[0]; o.y += v[1]; o.z += v[2]; o.w += v[3];
-                *(f4 *)(dst_row + col) = o;
-            } else if (col + 3 < N) {
-                f4 o = *(f4_any *)(dst_row + col);
-                o.x += v[0]; o.y += v[1]; o.z += v[2]; o.w += v[3];
-                *(f4_any *)(dst_row + col) = o;
+            for (int c = 0; c < 4; ++c) o[c] += (float)mainacc[r][g * 4 + c];
+            if (whole[g]) {
+                *(f4_any *)(dst_row + col[g]) = o;
             } else {
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (col + c < N) dst_row[col + c] += v[c];
+                for (int c = 0; c < 4; ++c) {
+                    bool own;
+                    const int at = col_at(g * 256 + lane * 4 + c, own);
+                    if (own) dst_row[at] += o[c];
+                }
             }
         }
     }
