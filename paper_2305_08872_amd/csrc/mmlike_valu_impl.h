@@ -105,8 +105,10 @@ __device__ __forceinline__ void fold4(float a, f4 b, const float *th, const floa
         float p[4], d[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) p[c] = a * b[c];          // one RN multiply (contraction is off)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 4; ++c) d[c] = th[c] - p[c];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_alignbit(acc[c], __builtin_bit_cast(uint32_t, d[c]), 31);
     }
@@ -141,7 +143,7 @@ mmlike_valu_kernel(const MmlikeArgs args)
     __shared__ __attribute__((aligned(16))) float Bs[2][BK][BN];
     constexpr int A_ROWS = NW * TM, A_PITCH = BK + 4;       // rows of the workgroup; padded row of the LDS A tile
     constexpr int A_F4 = A_ROWS * BK / 4;                   // float4 slots of one A tile (<= NT)
-    static_assert(A_F4 <= NT, "one staging slot per thread at most");
+    static_assert(!ALDS || A_F4 <= NT, "one staging slot per thread at most");
     __shared__ __attribute__((aligned(16))) float Asl[ALDS ? 2 : 1][ALDS ? A_ROWS : 1][ALDS ? A_PITCH : 4];
 
     const int M = args.M, N = args.N;
@@ -491,9 +493,10 @@ mmlike_valu_kernel(const MmlikeArgs args)
                     // register pair each) overflow the scalar register file into spills.
                     // (The 8-row micro-tiles spill their A values regardless and lose more
                     // from the fence than they gain: they are left to the scheduler.  The
-                    // count task has no masks but measured 3 % faster with the fence.)
+                    // count task has no masks but measured 3 % faster with the fence, and another
+                    // 2 % with one after every row.)
                     if constexpr ((TASK == TASK_DISCOUNT || TASK == TASK_COUNT_GT) && TM == 4)
-                        if (r == 3) __builtin_amdgcn_sched_barrier(0);
+                        if (r == 3 || TASK == TASK_COUNT_GT) __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
@@ -738,6 +741,10 @@ static hipError_t launch_one(const MmlikeArgs &a, hipStream_t s)
     // A through LDS against A through the scalar cache: discount 30.4-31.0 against 31.3-31.9
     // TFLOP/s, count 36.4-37.2 against 36.9-40.4, boost within +-4 % either way).
     const bool a_through_lds = !a.transA && !a.transB && pitch_collides(a.lda, 4);
+    // The count spends the least arithmetic on a stage of B (three instructions per product) and gains by
+    // fewer barriers: 32 k a stage, two workgroups' 128 KiB of LDS to a unit (with the fences in fold4, 43.0 -> 44.4
+    // TFLOP/s at 4096^3, with A transposed 32.2 -> 38.8; boost is level with it, 32.6 / 32.7).
+    constexpr int DEEP = TASK == TASK_COUNT_GT && TM == 4 && NG == 1 && NW == 8 && BK == 16 ? 32 : BK;
     constexpr bool DPIPE = TASK == TASK_DISCOUNT && TM == 4 && NG == 1 && BK == 16;
     constexpr bool BAHEAD = TASK != TASK_IDENTITY && TM == 4 && NG == 1 && BK == 16;   // B values a chunk ahead
     auto launch = [&](int64_t n_blocks, int n_splits) -> hipError_t {
@@ -756,7 +763,7 @@ static hipError_t launch_one(const MmlikeArgs &a, hipStream_t s)
                     // B values read a chunk ahead (no chunk pipeline: these tasks have no lane mask
                     // to keep at a distance): boost +0.5-1.5 %, count +1 % (42.7 -> 43.0 TFLOP/s at 4096^3)
                     if (!a_through_lds) {
-                        hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 0, TM, NG, NW, BK, KA, false, false, true>), grid, block, 0, s, b);
+                        hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 0, TM, NG, NW, DEEP, KA, false, false, true>), grid, block, 0, s, b);
                         break;
                     }
                 }
@@ -780,9 +787,9 @@ static hipError_t launch_one(const MmlikeArgs &a, hipStream_t s)
             // (transposed layouts: the discount task's pipelined form; with B a chunk ahead where A
             // is row-major -- with a transposed A the unrolled tile keeps the A values of all its
             // chunks in scalar registers at once and spills 80-130 of them)
-            case 1: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 1, TM, NG, NW, BK, KA, false, DPIPE, false>), grid, block, 0, s, b); break;
-            case 2: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 2, TM, NG, NW, BK, KA, false, DPIPE, BAHEAD>), grid, block, 0, s, b); break;
-            default: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 3, TM, NG, NW, BK, KA, false, DPIPE, false>), grid, block, 0, s, b); break;
+            case 1: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 1, TM, NG, NW, DEEP, KA, false, DPIPE, false>), grid, block, 0, s, b); break;
+            case 2: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 2, TM, NG, NW, DEEP, KA, false, DPIPE, BAHEAD>), grid, block, 0, s, b); break;
+            default: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 3, TM, NG, NW, DEEP, KA, false, DPIPE, false>), grid, block, 0, s, b); break;
             }
         });
     };
