@@ -432,11 +432,12 @@ struct CountTilePlan {
     int through_registers;  // rows at any byte address, staged through registers; else streamed HBM -> LDS
     int parts;              // workgroups per tile, each over kpart k (more than one: atomic adds into R)
     int kpart, kgroup;
+    int alone;              // 128 x 256: at most one workgroup to a unit, and K for a ring of all of its LDS
     double us;              // the estimate it was chosen by
 };
 
 // The plan with the lowest estimated time.  Tiles: 256 x 256 (16 waves, one workgroup to a compute unit),
-// 128 x 256 (8 waves, two to a unit; streamed only), 128 x 128 (8 waves, two), 64 x 64 (two groups of 4 waves
+// 128 x 256 (8 waves, two to a unit, a deeper ring with one; streamed only), 128 x 128 (8 waves, two), 64 x 64 (two groups of 4 waves
 // that share K, two).  A stage of 64 k (64 x 64: 128) takes `alone` us in a workgroup that has its unit for
 // itself and `shared` per pair of workgroups on a unit, half as much again through registers; the rest of a
 // tile -- first loads, sums, write-back -- `rest_...`, a fifth less when R is not read.  W workgroups (with the
@@ -447,10 +448,10 @@ struct CountTilePlan {
 inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool through_registers, bool assign)
 {
     static const struct { int bm, bn, groups, resident; double alone, shared, rest_alone, rest_shared, registers; } tiles[4] = {
-        {256, 256, 1, 1, 0.57, 0.0, 17.0, 0.0, 1.42}, {128, 256, 1, 2, 0.55, 0.60, 8.5, 16.0, 0.0},
+        {256, 256, 1, 1, 0.57, 0.0, 17.0, 0.0, 1.42}, {128, 256, 1, 2, 0.42, 0.60, 10.5, 16.0, 0.0},
         {128, 128, 1, 2, 0.206, 0.48, 4.8, 9.2, 1.52}, {64, 64, 2, 2, 0.19, 0.46, 2.8, 4.1, 1.67}};
     auto up64 = [](int64_t n) { return (n + 63) / 64 * 64; };
-    CountTilePlan best = {0, through_registers ? 1 : 0, 0, 0, 0, 0.0};
+    CountTilePlan best = {0, through_registers ? 1 : 0, 0, 0, 0, 0, 0.0};
     for (int i = 0; i < 4; ++i) {
         const auto &t = tiles[i];
         if (through_registers && t.registers == 0.0) continue;
@@ -466,6 +467,7 @@ inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool thr
             if (parts > 1) us += 0.3 + (double)M * (double)N * (double)parts / 1.0e6 + (assign ? 4.0 : 0.0);
             if (best.parts == 0 || us < best.us) {
                 best.tile = i; best.parts = (int)parts; best.kpart = (int)kpart; best.kgroup = (int)kgroup; best.us = us;
+                best.alone = i == CT_128x256 && W <= 256 && kgroup > 4 * 64 ? 1 : 0;
             }
         }
     }
