@@ -292,7 +292,7 @@ static const int kPersPhases[4] = {8, 2, 2, 16};   // groups, stages between gro
 //     twice that K on;
 //   R = : 6144^2 x 4096 128 / 140, 3072^2 x 2048 26 / 30, 12288 x 8192 x 512 94 / 112; up to one 128 x 256
 //     tile per unit, where theirs is another kernel, 2048 x 4096 x 4096 42 / 35.
-// Anything ragged or unaligned: 8191^2 x 4095 562 / 357, 8000^2 x 4000 368 / 279, 1000^2 x 1000 38 / 6.5.
+// Anything ragged or unaligned: 8191^2 x 4095 562 / 314, 8000^2 x 4000 368 / 235, 1000^2 x 1000 38 / 6.5.
 static bool count_tile(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const int8_t *A, int64_t lda, const int8_t *B,
                        int64_t ldb, int32_t *R, int64_t ldr, bool assign, void *stream, int &rc)
 {
@@ -313,6 +313,11 @@ static bool count_tile(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
     a.A = A; a.B = B; a.R = R; a.lda = lda; a.ldb = ldb; a.ldr = ldr;
     a.M = (int)M; a.N = (int)N; a.K = (int)K;
     a.assign = assign && plan.parts == 1 ? 1 : 0;
+    // R around the caches when a call's matrices do not fit the last-level cache (256 MiB) anyway, so that R does
+    // not displace operands: 8000^2 x 4000 280 -> 235 us, 8191^2 x 4095 358 -> 314, 7801^2 x 3001 254 -> 246; where
+    // they do, R is still there at the next call: 7900^2 x 2000 178 / 194, 5000 x 7000 x 3000 144 / 166
+    const double bytes = 4.0 * (double)M * (double)N + (double)K * ((double)M + (double)N);
+    a.bypass = !assign && bytes > 285e6 ? 1 : 0;
     hipError_t e = hipSuccess;
     if (assign && plan.parts > 1) {     // several workgroups add into a tile: from zero
         CountArgs z;

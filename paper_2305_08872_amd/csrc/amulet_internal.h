@@ -425,6 +425,7 @@ struct CountTileArgs {
     int kgroup;      // of which each of a workgroup's groups of waves sums this many k
     int block_base;  // added to blockIdx.x (launch_row_of_blocks)
     int assign;      // R = the counts instead of R +=
+    int bypass;      // R is read and written around the caches (the two largest tiles)
 };
 enum { CT_256 = 0, CT_128x256 = 1, CT_128 = 2, CT_64 = 3 };
 struct CountTilePlan {

@@ -20,7 +20,7 @@
 //
 // Measured, us, the kernels it replaced at these sizes / here: 1000^3 38 / 6.5 (a stage of 128 x 128 guarded
 // loads by one thread each), 2999 x 4001 x 2503 (written) 79 / 33, 5000 x 7000 x 3000 212 / 137, 8191^2 x 4095
-// 562 / 357, 8000^2 x 4000 368 / 279, 2048^2 x 8192 57 / 41; 4096^3 with both operands transposed 85 / 64.
+// 562 / 314, 8000^2 x 4000 368 / 235, 2048^2 x 8192 57 / 41; 4096^3 with both operands transposed 85 / 64.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -49,7 +49,8 @@ template <int N> __device__ __forceinline__ void ct_wait_vmcnt() { asm volatile(
 
 // Waves: WK groups of WR x WC, a group sums its own kgroup of the workgroup's k; a wave MB x NB blocks of 32 x 32.
 // NST: stages of the ring.  TA / TB: A stored K x M / B stored N x K.  REG: through registers.  KS: K over several workgroups.
-template <int MB, int NB, int WR, int WC, int WK, int NST, bool TA, bool TB, bool REG, bool KS>
+// NT: R is read and written around the caches.
+template <int MB, int NB, int WR, int WC, int WK, int NST, bool TA, bool TB, bool REG, bool KS, bool NT>
 __global__ void __launch_bounds__(64 * WR * WC * WK) __attribute__((amdgpu_waves_per_eu(4, 4)))
 count_i8_tile_kernel(const CountTileArgs args)
 {
@@ -402,7 +403,7 @@ count_i8_tile_kernel(const CountTileArgs args)
             off[i] = (uint32_t)row * (uint32_t)args.ldr + (uint32_t)col;
             all[i] = orow && o0 && o3;
             old[i] = v4i{0, 0, 0, 0};
-            if (all[i] && !args.assign) old[i] = *(const v4i_r *)(r_base + off[i]);
+            if (all[i] && !args.assign) old[i] = NT ? __builtin_nontemporal_load((const v4i_r *)(r_base + off[i])) : *(const v4i_r *)(r_base + off[i]);
         }
         // (edges after the whole pieces, so that only waves that have one wait between loads of one register)
         if (!args.assign) {
@@ -429,7 +430,8 @@ count_i8_tile_kernel(const CountTileArgs args)
             if (all[i]) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) sum[e] = (int)((uint32_t)sum[e] + (uint32_t)old[i][e]);
-                *(v4i_r *)(r_base + off[i]) = sum;
+                if (NT) __builtin_nontemporal_store(sum, (v4i_r *)(r_base + off[i]));
+                else *(v4i_r *)(r_base + off[i]) = sum;
                 continue;
             }
             bool orow;
@@ -445,12 +447,12 @@ count_i8_tile_kernel(const CountTileArgs args)
     }
 }
 
-template <int MB, int NB, int WR, int WC, int WK, int NST, bool TA, bool TB, bool REG, bool KS>
+template <int MB, int NB, int WR, int WC, int WK, int NST, bool TA, bool TB, bool REG, bool KS, bool NT = false>
 static hipError_t launch_tile(int parts, const CountTileArgs &args, hipStream_t s)
 {
     constexpr int BM = 32 * MB * WR, BN = 32 * NB * WC, RING = (REG ? 2 : NST) * WK * CT_BK * (BM + BN), IMAGE = 64 * BN * 4;
     constexpr int LDS = RING > IMAGE ? RING : IMAGE;
-    auto *const kernel = &count_i8_tile_kernel<MB, NB, WR, WC, WK, NST, TA, TB, REG, KS>;
+    auto *const kernel = &count_i8_tile_kernel<MB, NB, WR, WC, WK, NST, TA, TB, REG, KS, NT>;
     static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (granted != hipSuccess) return granted;
     const int64_t grid = xcd_grid((args.M + BM - 1) / BM, (args.N + BN - 1) / BN);
@@ -465,10 +467,13 @@ template <bool TA, bool TB, bool REG>
 static hipError_t launch_tile_plan(const CountTilePlan &plan, const CountTileArgs &a, hipStream_t s)
 {
     switch (plan.tile) {
-    case CT_256: return launch_tile<2, 2, 4, 4, 1, 4, TA, TB, REG, false>(1, a, s);
+    case CT_256:
+        if (a.bypass) return launch_tile<2, 2, 4, 4, 1, 4, TA, TB, REG, false, true>(1, a, s);
+        return launch_tile<2, 2, 4, 4, 1, 4, TA, TB, REG, false>(1, a, s);
     case CT_128x256:
         if constexpr (!REG) {
             if (plan.alone) return launch_tile<2, 2, 2, 4, 1, 6, TA, TB, REG, false>(1, a, s);
+            if (a.bypass) return launch_tile<2, 2, 2, 4, 1, 3, TA, TB, REG, false, true>(1, a, s);
             return launch_tile<2, 2, 2, 4, 1, 3, TA, TB, REG, false>(1, a, s);
         }
         return hipErrorInvalidValue;

@@ -51,9 +51,10 @@ def test_tile_kernels_at_the_edges_of_tiles_stages_and_k_ranges(am, dtype, task,
 
 # edges of the join count's tiles (64 ... 256), of its 16-byte units and of its stages (64 k, 128 in two
 # groups): the smallest problem, one more and one less than whole tiles, units and stages, a short last
-# stage in either group, K over several workgroups, each of the four tiles with and without whole tiles
+# stage in either group, K over several workgroups, each of the four tiles with and without whole tiles,
+# an R that is read and written around the caches
 I8_SIZES = [(16, 16, 64), (17, 31, 65), (63, 65, 127), (64, 64, 128), (65, 80, 193), (130, 100, 1055), (100, 260, 4097),
-            (1000, 1000, 250), (1100, 1500, 300), (2100, 1900, 130), (2048, 4096, 192), (1900, 3000, 1000), (2300, 4112, 208), (3000, 4400, 75)]
+            (1000, 1000, 250), (1100, 1500, 300), (2100, 1900, 130), (2048, 4096, 192), (1900, 3000, 1000), (2300, 4112, 208), (3000, 4400, 75), (8500, 8400, 70)]
 
 
 @pytest.mark.parametrize("layout", [(False, False), (True, False), (False, True), (True, True)])
