@@ -64,7 +64,8 @@ template <int N> __device__ __forceinline__ void tile_wait_vmcnt()
 }
 
 // Resident waves per SIMD the registers are held to: two workgroups to a compute unit, but with 32 registers
-// of thresholds (thres[i][j] in fp64) one: held to four waves that form spills inside the K loop.
+// of thresholds (thres[i][j] in fp64) one: held to four waves that form spills inside the K loop (up to 26 scratch
+// accesses per 8 k), every other form fits its 128.
 template <typename T, int TF> constexpr int tile_waves() { return sizeof(T) == 8 && TF == THRES_ELEM ? 2 : 4; }
 
 template <typename T, int TASK, int TF, int TRANS, int WM, int WN, int WK, int NST>
@@ -188,9 +189,9 @@ mmlike_tile_kernel(const TileArgs<T> args)
         own = col >= u;
         return col;
     };
-    // (of this lane's products)
-    auto row_of = [&](int r, bool &own) { return row_at(lr * 4 + r, own); };
-    auto col_of = [&](int c, bool &own) { return col_at(TB ? lc + 16 * c : c / V * (16 * V) + lc * V + c % V, own); };
+    // (of lane l's products)
+    auto row_of = [&](int l, int r, bool &own) { return row_at((l >> 4) * 4 + r, own); };
+    auto col_of = [&](int l, int c, bool &own) { return col_at(TB ? (l & 15) + 16 * c : c / V * (16 * V) + (l & 15) * V + c % V, own); };
 
     // Thresholds and factors in registers for the whole K loop.  (The count reads its predicate from
     // the sign of th - p, which takes a threshold of -0 for a negative number: held as th + 0.)
@@ -200,18 +201,18 @@ mmlike_tile_kernel(const TileArgs<T> args)
     bool own_dummy;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        const int col = col_of(c, own_dummy);
+        const int col = col_of(lane, c, own_dummy);
         q[c] = (T)1;
         if constexpr (TASK == TASK_DISCOUNT) q[c] = (T)1 - args.dis[col];
         if constexpr (TF == THRES_COL) th[0][c] = held(args.thres[col]);
         if constexpr (TF == THRES_ELEM) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) th[r][c] = held(args.thres[(int64_t)row_of(r, own_dummy) * args.ldt + col]);
+            for (int r = 0; r < 4; ++r) th[r][c] = held(args.thres[(int64_t)row_of(lane, r, own_dummy) * args.ldt + col]);
         }
     }
     if constexpr (TF == THRES_ROW) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) th[r][0] = held(args.thres[row_of(r, own_dummy)]);
+        for (int r = 0; r < 4; ++r) th[r][0] = held(args.thres[row_of(lane, r, own_dummy)]);
     }
     if constexpr (TF == THRES_CONST) {
         th[0][0] = held(args.thres[0]);
@@ -450,18 +451,20 @@ mmlike_tile_kernel(const TileArgs<T> args)
     acc_t out[VALS];
     const int v0 = g * VALS;
     __syncthreads();
+    // (opaque from here on, or the rows and columns of the write-back are computed with those of the thresholds, before
+    // the K loop, and held through it: up to 11 registers more than the 128 there are)
+    int l = lane;
+    asm volatile("" : "+v"(l));
     acc_t *const img = (acc_t *)tile_smem;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) img[(((g * NW + wg) * 4 + r) * 64 + lane) * 4 + c] = result(r, c);
+        for (int c = 0; c < 4; ++c) img[(((g * NW + wg) * 4 + r) * 64 + l) * 4 + c] = result(r, c);
     __syncthreads();
     if (ksplit) {
         // Several workgroups own this tile: hardware float adds, in whatever order, 64 neighbours of a row
         // at a time.  A wave's atomic adds to 256 contiguous bytes go four times as fast as to every fourth
         // value of 1024: fp32 0.084 -> 0.34 T adds/s, fp64 0.043 -> 0.19.
-        int l = lane;      // (opaque here, or what follows is computed before the K loop and held through it)
-        asm volatile("" : "+v"(l));
         const int src = TB ? (l % 16) * 4 + l / 16 : l % (16 * V) / V * 4 + l / (16 * V) * V + l % V;
         bool own_col;
         const int col = col_at(l, own_col);
@@ -482,7 +485,7 @@ mmlike_tile_kernel(const TileArgs<T> args)
 #pragma unroll
     for (int s = 0; s < WK; ++s)
 #pragma unroll
-        for (int v = 0; v < VALS; ++v) out[v] += img[(((s * NW + wg) * 4 + (v0 + v) / 4) * 64 + lane) * 4 + (v0 + v) % 4];
+        for (int v = 0; v < VALS; ++v) out[v] += img[(((s * NW + wg) * 4 + (v0 + v) / 4) * 64 + l) * 4 + (v0 + v) % 4];
     typedef T uvec_raw __attribute__((ext_vector_type(U)));
     typedef uvec_raw uvec __attribute__((aligned(SZ)));
     bool own_r[VALS / U], own[VALS];
@@ -490,12 +493,12 @@ mmlike_tile_kernel(const TileArgs<T> args)
     uvec old[VALS / U];
 #pragma unroll
     for (int j = 0; j < VALS / U; ++j) {
-        const int row = row_of((v0 + j * U) / 4, own_r[j]);
+        const int row = row_of(l, (v0 + j * U) / 4, own_r[j]);
         bool all = !TB && own_r[j];
 #pragma unroll
         for (int e = 0; e < U; ++e) {
             bool oc;
-            const int col = col_of((v0 + j * U + e) % 4, oc);
+            const int col = col_of(l, (v0 + j * U + e) % 4, oc);
             own[j * U + e] = own_r[j] && oc;
             all = all && oc;
             dst[j * U + e] = args.R + (int64_t)row * args.ldr + col;

@@ -356,7 +356,7 @@ mmlike_valu_kernel(const MmlikeArgs args)
                 stage[it] = *(const f4_any *)(bsrc + it * pass_stride);
             bsrc += tile_stride;
         } else {
-            int last = krows - 1;
+            int last = krows - 1;      // (opaque, as above; so is the last column below)
             asm volatile("" : "+s"(last));
 #pragma unroll
             for (int it = 0; it < LOADS; ++it) {
@@ -365,8 +365,10 @@ mmlike_valu_kernel(const MmlikeArgs args)
                 if (groups) {
                     stage[it] = *(const f4_any *)src;
                 } else {
+                    int end = N - 1 - bcol;
+                    asm volatile("" : "+v"(end));
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) stage[it][e] = src[bcol + e < N ? e : N - 1 - bcol];
+                    for (int e = 0; e < 4; ++e) stage[it][e] = src[e < end ? e : end];
                 }
             }
             bsrc += tile_stride;
@@ -616,6 +618,10 @@ mmlike_valu_kernel(const MmlikeArgs args)
     }
     flush();
 
+    // (opaque from here on, or the columns of the write-back are computed with those of the thresholds, before the
+    // K loop, and held through it: up to 17 registers more than the 128 there are)
+    int l = lane;
+    asm volatile("" : "+v"(l));
     if (ksplit) {
         // several workgroups own this tile: hardware float adds, in whatever order; 64 neighbours of a row at
         // a time, through the wave's kilobyte of the B tile (its own lanes only: no barrier).  A wave's atomic
@@ -628,13 +634,13 @@ mmlike_valu_kernel(const MmlikeArgs args)
             float *const dst_row = args.R + (int64_t)(row0 + r) * args.ldr;
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
-                *(f4 *)(x + lane * 4) = f4{(float)mainacc[r][g * 4], (float)mainacc[r][g * 4 + 1], (float)mainacc[r][g * 4 + 2], (float)mainacc[r][g * 4 + 3]};
+                *(f4 *)(x + l * 4) = f4{(float)mainacc[r][g * 4], (float)mainacc[r][g * 4 + 1], (float)mainacc[r][g * 4 + 2], (float)mainacc[r][g * 4 + 3]};
                 __builtin_amdgcn_wave_barrier();
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     bool own;
-                    const int col = col_at(g * 256 + c * 64 + lane, own);
-                    if (own) unsafeAtomicAdd(dst_row + col, x[c * 64 + lane]);
+                    const int col = col_at(g * 256 + c * 64 + l, own);
+                    if (own) unsafeAtomicAdd(dst_row + col, x[c * 64 + l]);
                 }
                 __builtin_amdgcn_wave_barrier();
             }
@@ -652,8 +658,8 @@ mmlike_valu_kernel(const MmlikeArgs args)
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
         bool last;
-        col[g] = col_at(g * 256 + lane * 4, whole[g]);
-        (void)col_at(g * 256 + lane * 4 + 3, last);
+        col[g] = col_at(g * 256 + l * 4, whole[g]);
+        (void)col_at(g * 256 + l * 4 + 3, last);
         whole[g] = whole[g] && last;
 #pragma unroll
         for (int r = 0; r < TM; ++r) {
@@ -676,7 +682,7 @@ mmlike_valu_kernel(const MmlikeArgs args)
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     bool own;
-                    const int at = col_at(g * 256 + lane * 4 + c, own);
+                    const int at = col_at(g * 256 + l * 4 + c, own);
                     if (own) dst_row[at] += o[c];
                 }
             }
