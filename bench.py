@@ -90,6 +90,11 @@ class ShaderClock:
         return sorted(self.samples)[len(self.samples) // 2]
 
 
+def kernel_name(am):
+    """Name of the kernel that the last call ran (of a shape id, or a tile kernel, which has none)."""
+    return am.amulet_recent_kernel().split()[0]
+
+
 INT8_MFMA_PEAK_TOPS = 5000.0   # MI355X dense int8 matrix peak, 5.0 POP/s
 FP64_VECTOR_PEAK_TFLOPS = 78.6  # MI355X fp64 vector peak
 
@@ -116,10 +121,11 @@ def bench_count_i8(args, am, torch, np, spec, A, B) -> dict:
             count(dA, dB, dR)
         torch.cuda.synchronize()
         print("traffic probe done: 1 copy of %d bytes, %d launches of %s" %
-              (src.numel() * 4, args.steps, am.amulet_shape_name(T, am.amulet_selected_shape(T, M, N, K))))
+              (src.numel() * 4, args.steps, kernel_name(am)))
         return {}
     t0 = time.perf_counter()
-    shape = am.amulet_selected_shape(T, M, N, K) if args.no_tune else am.amulet_tune(T, M, N, K)
+    if not args.no_tune:
+        am.amulet_tune(T, M, N, K)
     tune_s = time.perf_counter() - t0
     for _ in range(args.warmup):
         count(dA, dB, dR)
@@ -134,6 +140,7 @@ def bench_count_i8(args, am, torch, np, spec, A, B) -> dict:
             stops[i].record()
         torch.cuda.synchronize()
         ms_per_step = (time.perf_counter() - w0) * 1e3 / args.steps
+    kernel = kernel_name(am)
     sclk_mhz = sclk.median_mhz()
     kern_ms = [s.elapsed_time(e) for s, e in zip(starts, stops)]
     kernel_ms_avg = sum(kern_ms) / args.steps
@@ -177,7 +184,7 @@ def bench_count_i8(args, am, torch, np, spec, A, B) -> dict:
         "warmup": args.warmup, "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "int8", "data": "synthetic",
         "config": {"workload": args.workload, "task": "count_i8", "M": M, "N": N, "K": K,
-                   "tile_shape": am.amulet_shape_name(T, shape), "tuned": not args.no_tune,
+                   "tile_shape": kernel, "tuned": not args.no_tune,
                    "tune_seconds": round(tune_s, 3)},
         "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s",
                      "frac": round(achieved / INT8_MFMA_PEAK_TOPS, 4), "traffic": None,
@@ -226,6 +233,7 @@ def bench_f64(args, am, torch, np, wl, spec, A, B, P) -> dict:
             stops[i].record()
         torch.cuda.synchronize()
         ms_per_step = (time.perf_counter() - w0) * 1e3 / args.steps
+    kernel = kernel_name(am)
     sclk_mhz = sclk.median_mhz()
     kern_ms = [s.elapsed_time(e) for s, e in zip(starts, stops)]
     kernel_ms_avg = sum(kern_ms) / args.steps
@@ -261,9 +269,7 @@ def bench_f64(args, am, torch, np, wl, spec, A, B, P) -> dict:
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per_step, 4),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f64", "data": "synthetic",
         "config": {"workload": args.workload, "task": tname, "M": M, "N": N, "K": K,
-                   "tile_shape": ("mfma_f64_64x64_dma4" if am.amulet_selected_shape_f64(task, M, N, K) % 2 == 0
-                                  else "mfma_f64_128x128_dma4") if tname == "identity" else
-                   am.amulet_f64_shape_name(am.amulet_selected_shape_f64(task, M, N, K))},
+                   "tile_shape": kernel},
         "roofline": {"bound": "mfma" if tname == "identity" else "alu", "achieved": round(achieved, 3), "peak": FP64_VECTOR_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(achieved / FP64_VECTOR_PEAK_TFLOPS, 4), "traffic": None,
                      "kernel_ms_avg": round(kernel_ms_avg, 4), "kernel_ms_median": round(kernel_ms_median, 4),
@@ -360,11 +366,12 @@ def bench_workload(args, am, torch, np, wl) -> dict:
             am.amulet_mmlike_f32(task, dA, dB, dP, dR)
         torch.cuda.synchronize()
         print("traffic probe done: 1 copy of %d bytes, %d launches of %s" %
-              (src.numel() * 4, args.steps, am.amulet_shape_name(task, am.amulet_selected_shape(task, M, N, K))))
+              (src.numel() * 4, args.steps, kernel_name(am)))
         return {}
 
     t0 = time.perf_counter()
-    shape = am.amulet_selected_shape(task, M, N, K) if args.no_tune else am.amulet_tune(task, M, N, K)
+    if not args.no_tune:
+        am.amulet_tune(task, M, N, K)
     tune_s = time.perf_counter() - t0
 
     def time_library_sgemm():
@@ -398,6 +405,7 @@ def bench_workload(args, am, torch, np, wl) -> dict:
             stops[i].record()
         torch.cuda.synchronize()
         wall_ms = (time.perf_counter() - w0) * 1e3
+    kernel = kernel_name(am)
     sclk_mhz = sclk.median_mhz()
     kern_ms = [s.elapsed_time(e) for s, e in zip(starts, stops)]
     ms_per_step = wall_ms / args.steps
@@ -439,7 +447,7 @@ def bench_workload(args, am, torch, np, wl) -> dict:
     if os.path.exists(tpath):
         with open(tpath) as f:
             rec = json.load(f).get(args.workload)
-        if rec and rec.get("tile_shape") == am.amulet_shape_name(task, shape):   # measured for this very kernel
+        if rec and rec.get("tile_shape") == kernel:   # measured for this very kernel
             traffic = rec["hbm_bytes_per_launch"]
 
     lib_ratio = None
@@ -450,7 +458,7 @@ def bench_workload(args, am, torch, np, wl) -> dict:
     # register-only issue rate of this task's instruction mix on this chip (measured ceiling)
     probe = None
     mix = {"identity": 0, "discount": 1, "boost": 2, "count_gt": 3}.get(tname)
-    on_valu = am.amulet_shape_name(task, shape).startswith("valu")
+    on_valu = not kernel.startswith("mfma")
     if mix is not None and on_valu and args.probe:
         pps = max(am.amulet_probe_valu(mix, w) for w in (4, 8))
         probe = {"mix": tname, "tflops_equiv": round(2.0 * pps / 1e12, 3),
@@ -482,7 +490,7 @@ def bench_workload(args, am, torch, np, wl) -> dict:
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": args.workload, "task": tname, "M": M, "N": N, "K": K,
-                   "tile_shape": am.amulet_shape_name(task, shape), "tuned": not args.no_tune,
+                   "tile_shape": kernel, "tuned": not args.no_tune,
                    "tune_seconds": round(tune_s, 3)},
         "pct_of_fp32_vector_peak": round(100.0 * value / 1e3 / FP32_VECTOR_PEAK_TFLOPS, 2),
         "roofline": {"bound": "alu" if on_valu else "mfma", "achieved": round(achieved_tflops, 3),

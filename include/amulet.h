@@ -195,9 +195,11 @@ int amulet_mmlike_f64_general(int task, int thres_form, int trans_a, int trans_b
  * 128 x 128 tiles than the chip has compute units).
  *   amulet_f64_shape_count      number of shape ids (6)
  *   amulet_f64_shape_name       static string, "invalid" for a bad id
- *   amulet_selected_shape_f64   shape a plain call uses for (task, M, N, K): the cached
- *                               selection of its size bucket, else the built-in choice;
- *                               AMULET_ERR_TASK for a bad task
+ *   amulet_selected_shape_f64   shape selected for (task, M, N, K): the cached selection
+ *                               of its size bucket, else the built-in choice (where it
+ *                               is the built-in choice, a plain call may run a tile kernel
+ *                               instead, see amulet_recent_kernel); AMULET_ERR_TASK for a
+ *                               bad task
  *   amulet_mmlike_f64_shape     amulet_mmlike_f64_general with an explicit shape
  *                               (-1: as selected); AMULET_ERR_SHAPE for an id >= count
  */
@@ -489,10 +491,28 @@ int amulet_mmlike_f32_adaptive_general(int task, int thres_form, int trans_a, in
 int amulet_tune(int task, int64_t M, int64_t N, int64_t K, void *stream);
 
 /* Shape table introspection: number of tile shapes of a task, a printable name
- * for one, and the shape amulet_mmlike_f32 / amulet_count_i8 would use now. */
+ * for one, and the shape selected for a size (cached, else the built-in choice).
+ * Calls that name no shape run the selected one, except that where it is the
+ * library's own choice they may run a tile kernel, which has no shape id: which
+ * kernel a call ran, amulet_recent_kernel says. */
 int amulet_shape_count(int task);
 const char *amulet_shape_name(int task, int shape);
 int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K);
+/*
+ * The kernel a call ran (the shape its adaptive execution, Sec. 4.4, or the
+ * built-in choice arrived at): text for the calling thread's `back`-th last launch
+ * of a compute kernel -- 0 the last, up to 15; "" where there is none -- whichever
+ * entry point made it.  A shape's name as amulet_shape_name or
+ * amulet_f64_shape_name gives it, or a tile kernel's: f32_tile_16x64,
+ * f32_tile_32x64, f64_tile_... (predicate tasks), i8_tile_64x64 to i8_tile_256x256
+ * (join count; _ring6: the deeper operand ring, _registers: operands staged
+ * through registers, _bypass: R around the caches); then " rows <rows of R>", and
+ * for a tile kernel " parts <workgroups per tile, each over a range of K> kpart
+ * <k of such a range> kgroup <k of it that a group of waves sums>".  The adaptive
+ * calls make one launch per trial and one for the rest.  Static storage of the
+ * calling thread, until its next call of this function.
+ */
+const char *amulet_recent_kernel(int back);
 /* Forget every cached selection. */
 void amulet_clear_selections(void);
 
@@ -580,7 +600,10 @@ const char *amulet_last_launch_error(void);
  * mode on (amulet_set_deterministic(1), or AMULET_DETERMINISTIC=1 in the
  * environment when the library is first used) no fp32 / fp64 launch splits K:
  * every output is summed by one workgroup in a fixed order, and two calls on
- * the same inputs with the same tile shape give the same bits, at the price of
+ * the same inputs give the same bits if they name the same tile shape, or name
+ * none and find the same selection (a call that names a shape sums in that
+ * kernel's order, one that names none perhaps in a tile kernel's: between the
+ * two the bits may differ), at the price of
  * the idle compute units the split was there to fill.  The integer join count
  * is exact either way and is not affected.  Process-wide; takes effect for
  * calls made after it returns.

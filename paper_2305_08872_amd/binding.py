@@ -122,6 +122,8 @@ def load_library():
     lib.amulet_shape_count.argtypes = [i32]
     lib.amulet_shape_name.restype = ctypes.c_char_p
     lib.amulet_shape_name.argtypes = [i32, i32]
+    lib.amulet_recent_kernel.restype = ctypes.c_char_p
+    lib.amulet_recent_kernel.argtypes = [i32]
     lib.amulet_selected_shape.restype = i32
     lib.amulet_selected_shape.argtypes = [i32, i64, i64, i64]
     lib.amulet_clear_selections.restype = None
@@ -552,6 +554,11 @@ def amulet_shape_name(task: int, shape: int) -> str:
 
 def amulet_selected_shape(task: int, M: int, N: int, K: int) -> int:
     return _check(load_library().amulet_selected_shape(task, M, N, K), "amulet_selected_shape")
+
+
+def amulet_recent_kernel(back: int = 0) -> str:
+    """The kernel behind this thread's `back`-th last compute launch, as text ("" if there is none)."""
+    return load_library().amulet_recent_kernel(back).decode()
 
 
 def amulet_clear_selections() -> None:

@@ -141,6 +141,26 @@ static int lookup_shape(int task, int64_t M, int64_t N, int64_t K)
     return default_shape(task, M, N, K);
 }
 
+// What the calling thread's last compute calls sent to the device (amulet_recent_kernel): plain numbers,
+// put into words only when asked for.
+struct KernelNote {
+    int task;                      // AMULET_TASK_COUNT_I8 for the join count
+    int f64;
+    int shape;                     // shape id, or -1: a tile kernel, and then
+    int tile, parts, kpart, kgroup;
+    int ring, registers, bypass;   // (join count)
+    int64_t rows;
+};
+constexpr unsigned KERNEL_NOTES = 16;
+static thread_local KernelNote g_notes[KERNEL_NOTES];
+static thread_local unsigned g_notes_made = 0;
+static KernelNote &new_note(int task, int f64, int shape, int64_t rows)
+{
+    KernelNote &n = g_notes[g_notes_made++ % KERNEL_NOTES];
+    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, rows};
+    return n;
+}
+
 // text of the last HIP error a launch reported (diagnostics for AMULET_ERR_LAUNCH)
 static thread_local hipError_t g_last_hip_error = hipSuccess;
 
@@ -189,6 +209,8 @@ static hipError_t launch_tile_call(const Call &c, const TilePlan &plan, hipStrea
     a.lda = c.lda; a.ldb = c.ldb; a.ldr = c.ldr; a.ldt = c.ldt;
     a.M = (int)c.M; a.N = (int)c.N; a.K = (int)c.K;
     const int trans = (c.trans_a ? 1 : 0) | (c.trans_b ? 2 : 0);
+    KernelNote &n = new_note(c.task, sizeof(T) == 8, -1, c.M);
+    n.tile = plan.wide; n.parts = plan.parts; n.kpart = plan.kpart; n.kgroup = plan.kgroup;
     switch (c.task) {
     case TASK_DISCOUNT: return launch_mmlike_tile<T, TASK_DISCOUNT>(c.thres_form, trans, plan, a, s);
     case TASK_BOOST: return launch_mmlike_tile<T, TASK_BOOST>(c.thres_form, trans, plan, a, s);
@@ -246,6 +268,7 @@ static int run_mmlike(const MmlikeCall &c, int shape, void *stream, bool built_i
     a.kchunk = (int)c.K;
     a.tail_base = 0; a.tail_blocks = 0; a.tail_splits = 1; a.block_base = 0;
     a.force_splits = 0;
+    new_note(c.task, 0, shape, c.M);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     switch (c.task) {
@@ -318,6 +341,9 @@ static bool count_tile(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
     // they do, R is still there at the next call: 7900^2 x 2000 178 / 194, 5000 x 7000 x 3000 144 / 166
     const double bytes = 4.0 * (double)M * (double)N + (double)K * ((double)M + (double)N);
     a.bypass = !assign && bytes > 285e6 ? 1 : 0;
+    KernelNote &n = new_note(AMULET_TASK_COUNT_I8, 0, -1, M);
+    n.tile = plan.tile; n.parts = plan.parts; n.kpart = plan.kpart; n.kgroup = plan.kgroup;
+    n.ring = plan.alone; n.registers = plan.through_registers; n.bypass = a.bypass && plan.tile <= CT_128x256;
     hipError_t e = hipSuccess;
     if (assign && plan.parts > 1) {     // several workgroups add into a tile: from zero
         CountArgs z;
@@ -368,6 +394,7 @@ static int run_count(int shape, int64_t M, int64_t N, int64_t K, const int8_t *A
             a.pers_groups = g; a.pers_group_stages = st; a.pers_xcds = x; a.pers_xcd_span = sp;
         }
     }
+    new_note(AMULET_TASK_COUNT_I8, 0, shape, M);
     hipError_t e = launch_count_i8(shape, a, (hipStream_t)stream);
     g_last_hip_error = e;
     return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
@@ -711,6 +738,7 @@ static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, v
     a.vecA = (aligned16(a.A) && c.lda % 2 == 0) ? 1 : 0;
     a.kchunk = (int)c.K;
     a.tail_base = 0; a.tail_blocks = 0; a.tail_splits = 1; a.block_base = 0;
+    new_note(c.task, 1, shape, rows);
     const hipError_t e = launch_mmlike_f64(c.task, c.thres_form, shape, a, (hipStream_t)stream);
     g_last_hip_error = e;
     return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
@@ -1487,6 +1515,29 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K)
 {
     if (n_shapes(task) == 0) return AMULET_ERR_TASK;
     return lookup_shape(task, M, N, K);
+}
+
+const char *amulet_recent_kernel(int back)
+{
+    static thread_local char text[160];
+    text[0] = 0;
+    if (back < 0 || back >= (int)KERNEL_NOTES || (unsigned)back >= g_notes_made) return text;
+    const KernelNote &n = g_notes[(g_notes_made - 1 - (unsigned)back) % KERNEL_NOTES];
+    const long long rows = (long long)n.rows;
+    if (n.shape >= 0) {
+        const char *name = !n.f64 ? amulet_shape_name(n.task, n.shape)
+                           : n.task != TASK_IDENTITY ? amulet_f64_shape_name(n.shape)
+                           : n.shape % F64_TILES == 0 ? "mfma_f64_64x64_dma4" : "mfma_f64_128x128_dma4";
+        snprintf(text, sizeof(text), "%s rows %lld", name, rows);
+    } else if (n.task == AMULET_TASK_COUNT_I8) {
+        static const char *const tiles[4] = {"256x256", "128x256", "128x128", "64x64"};
+        snprintf(text, sizeof(text), "i8_tile_%s%s%s%s rows %lld parts %d kpart %d kgroup %d", tiles[n.tile], n.ring ? "_ring6" : "",
+                 n.registers ? "_registers" : "", n.bypass ? "_bypass" : "", rows, n.parts, n.kpart, n.kgroup);
+    } else {
+        snprintf(text, sizeof(text), "%s_tile_%s rows %lld parts %d kpart %d kgroup %d", n.f64 ? "f64" : "f32", n.tile ? "32x64" : "16x64",
+                 rows, n.parts, n.kpart, n.kgroup);
+    }
+    return text;
 }
 
 void amulet_clear_selections(void)

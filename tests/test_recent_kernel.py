@@ -1,0 +1,87 @@
+"""Which kernel a call runs, as amulet_recent_kernel tells it.  Every launch here is refused on the host (the
+library's own seam), so this runs without a GPU: pointers are never read, only their alignment is."""
+import ctypes
+import os
+
+import pytest
+
+import paper_2305_08872_amd as am
+
+
+@pytest.fixture(scope="module")
+def lib():
+    if not os.path.exists(am.library_path()):
+        from paper_2305_08872_amd import build
+        build.build()
+    lib = am.load_library()
+    am.amulet_clear_selections()
+    yield lib
+    am.amulet_debug_fail_launches(0)
+
+
+def kernel(lib, call):
+    """amulet_recent_kernel after a call whose launch is refused, as (name, fields)."""
+    am.amulet_debug_fail_launches(1)
+    try:
+        assert call() == -5
+    finally:
+        am.amulet_debug_fail_launches(0)
+    words = am.amulet_recent_kernel().split()
+    return words[0], dict(zip(words[1::2], map(int, words[2::2])))
+
+
+def ptr(address=1 << 20):
+    return ctypes.c_void_p(address)
+
+
+def f32(lib, task, M, N, K, shape=-1):
+    return kernel(lib, lambda: lib.amulet_mmlike_f32_general(task, 0, 0, 0, shape, M, N, K, ptr(), K, ptr(), N, ptr(), 0, ptr(), ptr(), N, None))
+
+
+def f64(lib, task, M, N, K, shape=-1):
+    return kernel(lib, lambda: lib.amulet_mmlike_f64_shape(task, shape, 0, 0, 0, M, N, K, ptr(), K, ptr(), N, ptr(), 0, ptr(), ptr(), N, None))
+
+
+def i8(lib, M, N, K, shape=None, at=1 << 20):
+    if shape is not None:
+        return kernel(lib, lambda: lib.amulet_count_i8_shape(shape, M, N, K, ptr(at), K, ptr(at), N, ptr(), N, None))
+    return kernel(lib, lambda: lib.amulet_count_i8(M, N, K, ptr(at), K, ptr(at), N, ptr(), N, None))
+
+
+def test_a_call_that_names_no_shape_tells_which_kernel_it_ran(lib):
+    """The selected shape is what runs only where no tile kernel does: amulet_selected_shape alone
+    would name a kernel for these sizes that does not run."""
+    for task in (1, 2, 3):
+        name, got = f32(lib, task, 256, 256, 256)
+        assert name in ("f32_tile_16x64", "f32_tile_32x64") and got["rows"] == 256 and got["kpart"] * got["parts"] >= 256
+        name, got = f64(lib, task, 4096, 4096, 4096)
+        assert name in ("f64_tile_16x64", "f64_tile_32x64") and got["rows"] == 4096 and got["parts"] == 1
+    name, got = i8(lib, 1000, 1000, 1000)
+    assert name.startswith("i8_tile_") and got["rows"] == 1000
+    # where no tile kernel runs: the selected shape
+    assert f32(lib, 1, 8192, 8192, 8192)[0] == am.amulet_shape_name(1, am.amulet_selected_shape(1, 8192, 8192, 8192))
+    assert f32(lib, 0, 1024, 1024, 1024)[0] == am.amulet_shape_name(0, am.amulet_selected_shape(0, 1024, 1024, 1024))
+    assert i8(lib, 8192, 8192, 4096)[0] == am.amulet_shape_name(100, am.amulet_selected_shape(100, 8192, 8192, 4096))
+    assert f64(lib, 0, 1024, 1024, 1024)[0] == "mfma_f64_64x64_dma4" and f64(lib, 0, 4096, 4096, 256)[0] == "mfma_f64_128x128_dma4"
+
+
+def test_a_named_shape_is_the_kernel_that_runs(lib):
+    for shape in range(am.amulet_shape_count(1)):
+        assert f32(lib, 1, 256, 256, 256, shape) == (am.amulet_shape_name(1, shape), {"rows": 256})
+    for shape in range(am.amulet_f64_shape_count()):
+        assert f64(lib, 3, 256, 256, 256, shape) == (am.amulet_f64_shape_name(shape), {"rows": 256})
+    for shape in range(1, am.amulet_shape_count(100)):
+        assert i8(lib, 256, 256, 256, shape) == (am.amulet_shape_name(100, shape), {"rows": 256})
+
+
+def test_earlier_launches_stay_readable_and_are_the_threads_own(lib):
+    import threading
+    f32(lib, 1, 300, 256, 256)
+    f32(lib, 1, 301, 256, 256, 3)
+    assert am.amulet_recent_kernel(0) == "valu_32x512_k8 rows 301" and am.amulet_recent_kernel(1).split()[2] == "300"
+    assert am.amulet_recent_kernel(-1) == "" and am.amulet_recent_kernel(16) == ""
+    seen = []
+    t = threading.Thread(target=lambda: seen.append(am.amulet_recent_kernel()))
+    t.start()
+    t.join()
+    assert seen == [""]
