@@ -221,12 +221,12 @@ static hipError_t launch_tile_call(const Call &c, const TilePlan &plan, hipStrea
 // Predicate tasks: the plan of the tile kernels when they can run the problem -- a stage of K, a
 // 16-byte unit in an operand whose lines run across k, and per-lane byte offsets that fit 31 bits.
 template <typename T, typename Call>
-static bool tile_plan(const Call &c, double us_per_k, TilePlan &plan)
+static bool tile_plan(const Call &c, double us_per_k, int64_t max_parts, TilePlan &plan)
 {
     constexpr int64_t V = 16 / (int64_t)sizeof(T), BK = 4 * V, MAX = 0x7fffffff / (int64_t)sizeof(T);
     if (c.K < BK || (c.trans_a && c.M < V) || (!c.trans_b && c.N < V)) return false;
     if (c.lda > (c.trans_a ? (MAX - 32) / BK : (MAX - BK) / 32) || c.ldb > (c.trans_b ? (MAX - BK) / 64 : (MAX - 64) / BK)) return false;
-    plan = choose_tile_plan<T>(c.M, c.N, c.K, us_per_k, sizeof(T) == 8 && c.thres_form == THRES_ELEM);
+    plan = choose_tile_plan<T>(c.M, c.N, c.K, us_per_k, max_parts, sizeof(T) == 8 && c.thres_form == THRES_ELEM);
     return true;
 }
 
@@ -242,7 +242,10 @@ static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
 {
     // us per k of one of two resident workgroups (tile kernels), and of a 32 x 256 workgroup
     static const double tile_us[4] = {0.0, 0.125, 0.130, 0.0955}, large_us[4] = {0.0, 0.115, 0.121, 0.0895};
-    if (c.task == TASK_IDENTITY || !tile_plan<float>(c, tile_us[c.task], plan)) return false;
+    if (c.task == TASK_IDENTITY) return false;
+    const ValuShapeDesc &d = kValuShapes[default_shape(c.task, c.M, c.N, c.K)];
+    const int64_t range = wide_k_range((c.M + d.NW * d.TM - 1) / (d.NW * d.TM) * ((c.N + 255) / 256) * d.NW, c.K);
+    if (!tile_plan<float>(c, tile_us[c.task], (c.K + range - 1) / range, plan)) return false;
     const int64_t large = ((c.M + 31) / 32) * ((c.N + 255) / 256);
     if (large < 256) return true;
     const double rounds = (double)large / 256.0, part_round = large % 512 == 0 ? 0.1 : 0.35;
@@ -722,7 +725,9 @@ static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, v
     TilePlan plan;
     const bool per_output = c.thres_form == THRES_ELEM && ((rows + 15) / 16) * ((c.N + 127) / 128) > 1024;
     const bool halves = c.task != TASK_COUNT_GT && !c.trans_a && c.lda % 32768 == 0;
-    if (built_in && c.task != TASK_IDENTITY && !per_output && !halves && tile_plan<double>(sub, tile_us[c.task], plan)) {
+    const int waves = shape % F64_TILES == 1 ? 8 : 4;
+    const int64_t range = wide_k_range_f64((rows + 4 * waves - 1) / (4 * waves) * ((c.N + 127) / 128) * waves, c.K, 16);
+    if (built_in && c.task != TASK_IDENTITY && !per_output && !halves && tile_plan<double>(sub, tile_us[c.task], (c.K + range - 1) / range, plan)) {
         g_last_hip_error = launch_tile_call<double>(sub, plan, (hipStream_t)stream);
         return g_last_hip_error == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
     }

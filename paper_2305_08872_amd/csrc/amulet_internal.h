@@ -289,6 +289,41 @@ inline int choose_stream_split(int64_t part_tiles, int64_t units, int64_t K, int
     return best_s;
 }
 
+// K split of every tile in the wide vector-ALU kernels (mmlike_valu_impl.h, mmlike_valu_f64.hip): the k range of one
+// workgroup, K where it is not split.  Tiles for at most half of the waves the chip holds at once (small
+// M x N, e.g. an aggregation over a long K): as many workgroups per tile as still fit, at least 64 k each; each
+// adds its part to R with hardware float atomics (the sum order is free, Sec. 4.1).  A SIMD with two waves
+// runs a wave's work 20 % slower than one with four.
+// fp32: as many parts as fill the chip to three waves per SIMD (four when the tiles alone fill one),
+// of at least 64 k each and, from K = 512 on, of about 192: every part pays a first load of
+// B, a pipeline fill and a tile of atomic adds, and parts of one tile that finish together
+// queue on the same lines of R.  Measured over forced counts 1 ... 64, us, this rule / as many
+// parts of 64 k as fit at four waves per SIMD (the earlier rule) / best forced: 512^3 40 / 55 / 40,
+// 640^3 49 / 55 / 46, 768^3 63 / 73 / 61, 512^2 x 1024 58 / 86 / 54, 768^2 x 384 43 / 59 / 43,
+// 128 x 4096 x 512 42 / 64 / 42, 256^2 x 4096 56 / 85 / 55, 512^2 x 2048 80 / 93 / 78,
+// 1024^2 x 512 71 / 76 / 65; 256^3, 384^3, 896^3, 1024^3 unchanged (17, 24, 78, 97).
+inline int64_t wide_k_range(int64_t waves, int64_t K)
+{
+    if (!k_split_allowed() || waves > 2048 || K < 128) return K;
+    int64_t want = (waves >= 1024 ? 4096 : 3072) / waves;
+    const int64_t most = K < 512 ? K / 64 : (K + 96) / 192;
+    if (want > most) want = most;
+    if (want < 1) want = 1;
+    if (want > 1024) want = 1024;
+    const int64_t range = ((K + want - 1) / want + 63) / 64 * 64;   // whole partial-sum periods
+    return range < K ? range : K;
+}
+// fp64: as many parts as fill the chip, in ranges of whole stages
+inline int64_t wide_k_range_f64(int64_t waves, int64_t K, int stage)
+{
+    if (!k_split_allowed() || waves > 2048 || K < 128) return K;
+    int64_t want = 4096 / waves;
+    if (want > K / 64) want = K / 64;
+    if (want > 1024) want = 1024;
+    const int64_t range = ((K + want - 1) / want + stage - 1) / stage * stage;
+    return range < K ? range : K;
+}
+
 // Arguments of an fp32 task launch, already validated on the host.
 struct MmlikeArgs {
     const float *A;
@@ -344,8 +379,12 @@ struct TilePlan {
 // 240 drawn sizes (64 ... 8192 each way, both element types): 1.1 % behind it on average, 12 % at most.
 // (`alone`: the form that holds one workgroup to a unit, fp64 with thres[i][j]; nothing covers the loads of
 // a tile's thresholds there, 3.5 us per round.)
+// `max_parts`: the parts the wide kernel would add for the same call.  Every part is one more rounding of R, so a
+// plan has no more of them: with ranges down to 32 k it had up to eight times as many (64 x 64 x 1024 in 32
+// instead of 4: rms error 8.4e-8 against 4.9e-8 of the sums; now 4.5e-8), and split calls whose bits used to repeat.
+// Unrestricted the estimate is 2.7 % lower on average over drawn sizes (fp64 1.7 %), 40 % at a few tiles.
 template <typename T>
-inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_k, bool alone = false)
+inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_k, int64_t max_parts, bool alone = false)
 {
     constexpr int V = 16 / (int)sizeof(T);
     auto up = [](int64_t n, int64_t to) { return (n + to - 1) / to * to; };
@@ -353,8 +392,9 @@ inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_
     for (int wide = 0; wide < 2; ++wide) {
         const int rows = wide ? 32 : 16, groups = wide ? 4 : 8;
         const int64_t grid = xcd_grid((M + rows - 1) / rows, (N + 63) / 64);
-        for (int64_t p = 1; p <= 1024; p = p < 4 ? p + 1 : p % 3 ? p / 2 * 3 : p / 3 * 4) {   // 1 2 3 4 6 8 12 16 24 ...
-            if (p > 1 && (!k_split_allowed() || K < 128 || K / p < 32 || grid * p > 12288)) break;
+        auto next = [](int64_t p) { return p < 4 ? p + 1 : p % 3 ? p / 2 * 3 : p / 3 * 4; };   // 1 2 3 4 6 8 12 16 24 ...
+        for (int64_t p = 1; p <= max_parts; p = p < max_parts && next(p) > max_parts ? max_parts : next(p)) {
+            if (p > 1 && (K / p < 32 || grid * p > 12288)) break;
             const int64_t kpart = up((K + p - 1) / p, V), parts = (K + kpart - 1) / kpart;
             const int64_t kgroup = up((kpart + groups - 1) / groups, V);
             const int64_t W = grid * parts, rem = W % 512;

@@ -582,22 +582,19 @@ static hipError_t launch_mmlike_f64_waves(int task, int form, int force_splits, 
     const int64_t tiles_n = (a.N + D_BN - 1) / D_BN;
     const int64_t wgs = xcd_grid(tiles_m, tiles_n);
     if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
-    // tiles for at most half of the waves the chip holds at once (4 per SIMD): split K over
-    // as many workgroups per tile as still fit (at least 64 k each), which add their parts
-    // to R with hardware fp64 atomics
+    // few tiles: K over several workgroups (wide_k_range_f64 in amulet_internal.h)
     MmlikeArgsF64 b = a;
     int splits = 1;
     b.kchunk = a.K;
     const int64_t waves = tiles_m * tiles_n * D_NW;
     const bool forced = force_splits > 1 && k_split_allowed() && a.K >= 128;
-    if (forced || (k_split_allowed() && waves <= 2048 && a.K >= 128)) {
-        int64_t want = forced ? force_splits : 4096 / waves;
-        if (want > a.K / 64) want = a.K / 64;
-        if (want > 1024) want = 1024;
-        const int64_t chunk = ((a.K + want - 1) / want + D_BK - 1) / D_BK * D_BK;
-        b.kchunk = (int)chunk;
-        splits = (int)((a.K + chunk - 1) / chunk);
+    int64_t chunk = wide_k_range_f64(waves, a.K, D_BK);
+    if (forced) {
+        const int64_t want = force_splits < a.K / 64 ? force_splits : a.K / 64;
+        chunk = ((a.K + want - 1) / want + D_BK - 1) / D_BK * D_BK;
     }
+    b.kchunk = (int)chunk;
+    splits = (int)((a.K + chunk - 1) / chunk);
     b.tail_base = 0; b.tail_blocks = 0; b.tail_splits = 1;
     dim3 grid((unsigned)wgs, (unsigned)splits);
     // a last round of workgroups that would leave most of the chip idle: its tiles are launched

@@ -85,3 +85,51 @@ def test_earlier_launches_stay_readable_and_are_the_threads_own(lib):
     t.start()
     t.join()
     assert seen == [""]
+
+
+def _wide_parts(f64_, task, M, N, K):
+    """K parts of the wide kernels' own rule: none above 2048 waves or below 128 k; fp32 fills the chip to three
+    waves per SIMD (four from 1024 waves on) with parts of at least 64 k, about 192 from K = 512; fp64 to four,
+    with at least 64 k each, in whole stages."""
+    if f64_:
+        nw = 8 if task == 2 and 1024 ** 2 <= M * N <= 2048 ** 2 else 4
+        rows, cols, unit = 4 * nw, 128, 16
+    else:
+        tiles = -(-M // 32) * -(-N // 256)
+        nw = 8 if tiles >= 512 or (tiles >= 128 and K >= 8192) else 4
+        rows, cols, unit = 4 * nw, 256, 64
+    waves = -(-M // rows) * -(-N // cols) * nw
+    if waves > 2048 or K < 128:
+        return 1
+    if f64_:
+        want = min(4096 // waves, K // 64, 1024)
+    else:
+        want = max(1, min((4096 if waves >= 1024 else 3072) // waves, K // 64 if K < 512 else (K + 96) // 192, 1024))
+    return -(-K // (-(-(-(-K // want)) // unit) * unit))
+
+
+def test_tile_kernels_split_k_no_finer_than_the_wide_ones(lib):
+    """Every part of a split K is one more rounding of each result, in an order that varies: the tile
+    kernels' plans may not have more parts than the wide kernels they stand in for (64 x 64 x 1024 had
+    32 for 4, 5018 x 590 x 6504 3 for none), and none in the deterministic mode."""
+    import random
+    rng = random.Random(3)
+    sizes = [(64, 64, 1024), (64, 64, 2048), (5018, 590, 6504), (64, 64, 256), (16, 64, 8192), (73, 64, 832), (2880, 568, 6178)]
+    sizes += [tuple(int(round(64 * 128 ** rng.random())) for _ in range(3)) for _ in range(150)]
+    tiles = 0
+    for call, is64 in ((f32, False), (f64, True)):
+        for M, N, K in sizes:
+            for task in (1, 2, 3):
+                name, got = call(lib, task, M, N, K)
+                if "tile" not in name:
+                    continue
+                tiles += 1
+                assert got["parts"] <= _wide_parts(is64, task, M, N, K), (name, task, M, N, K, got)
+                assert got["parts"] * got["kpart"] >= K > (got["parts"] - 1) * got["kpart"]
+    assert tiles > 600
+    was = am.amulet_get_deterministic()
+    try:
+        am.amulet_set_deterministic(True)
+        assert f32(lib, 1, 64, 64, 1024)[1]["parts"] == 1 and f64(lib, 1, 64, 64, 1024)[1]["parts"] == 1
+    finally:
+        am.amulet_set_deterministic(was)
