@@ -235,8 +235,8 @@ mmlike_tile_kernel(const TileArgs<T> args)
             const T p = a * b;
             part[r][c] = __builtin_elementwise_fma(p, p > t ? q[c] : (T)1, part[r][c]);
         } else if constexpr (TASK == TASK_BOOST) {
-            const T p = a * b;
-            part[r][c] += __builtin_elementwise_max(p, __builtin_elementwise_fma((T)2, p, -t));
+            part[r][c] = __builtin_elementwise_fma(a, b, part[r][c]);
+            part[r][c] += __builtin_elementwise_max(__builtin_elementwise_fma(a, b, -t), (T)0);
         } else {
             const T p = a * b;
             part[r][c] += (int)(p > t);
@@ -246,9 +246,10 @@ mmlike_tile_kernel(const TileArgs<T> args)
     // One chunk of V k, four units of each operand; side(kk) after the products of k kk, where the units
     // whose last use that was may be refilled.  Per product: discount fp32 multiply, compare, select,
     // fma as one software pipeline (compare i, multiply i + 1, fma i - 1, select i: see mmlike_valu_impl.h);
-    // discount fp64 under the execution mask; boost p + max(p - th, 0) = max(p, 2p - th), four plain
-    // instructions of which one has a constant operand (8.75 clocks per 64 products against 9.1 for fma,
-    // fma, max, add); count multiply, subtract, and the sign bit shifted into a register of 32 (in fp64 the
+    // discount fp64 under the execution mask; boost p + max(p - th, 0) with the unrounded product inside its two fused
+    // operations, one product at a time (multiply, fma, max, add on the rounded one, max(p, 2p - th), is no
+    // faster: us, that / this, 1024^3 70.3 / 70.8, 1003 x 1501 x 777 81.9 / 82.2, fp64 2048^3 978 / 968; in groups of
+    // four 71.6, 82.5, 962); count multiply, subtract, and the sign bit shifted into a register of 32 (in fp64 the
     // sign bit of the high half: 20.7 -> 23.7 TFLOP/s at 2048^3 against compare, select, add).
     auto a_of = [](const vec (&v)[4], int r, int kk) -> T { return TA ? v[kk * H + r / V][r % V] : v[r][kk]; };
     auto b_of = [](const vec (&v)[4], int kk, int c) -> T { return TB ? v[c][kk] : v[kk * H + c / V][c % V]; };
@@ -305,17 +306,16 @@ mmlike_tile_kernel(const TileArgs<T> args)
             for (int kk = 0; kk < V; ++kk) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    T p[4], d[4];
                     if constexpr (TASK == TASK_BOOST) {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) p[c] = a_of(a, r, kk) * b_of(b, kk, c);
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) d[c] = __builtin_elementwise_fma((T)2, p[c], -thr(r, c));
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) d[c] = __builtin_elementwise_max(p[c], d[c]);
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) part[r][c] += d[c];
+                        for (int c = 0; c < 4; ++c) {
+                            const T d = __builtin_elementwise_fma(a_of(a, r, kk), b_of(b, kk, c), -thr(r, c));
+                            part[r][c] = __builtin_elementwise_fma(a_of(a, r, kk), b_of(b, kk, c), part[r][c]);
+                            part[r][c] += __builtin_elementwise_max(d, (T)0);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
                     } else {
+                        T p[4], d[4];
 #pragma unroll
                         for (int c = 0; c < 4; ++c) p[c] = a_of(a, r, kk) * b_of(b, kk, c);
 #pragma unroll

@@ -87,3 +87,28 @@ def test_count_tile_kernels_at_the_edges_of_tiles_units_and_stages(am, layout):
                 am.amulet_count_i8_assign(sA, sB, R)
                 torch.cuda.synchronize()
                 assert torch.equal(R, want.to(torch.int32)), (M, N, K, pad)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("form", [0, 3])
+def test_boost_terms_enter_the_sum_with_the_unrounded_product(am, dtype, form):
+    """Row i holds -fl(x * x) * 1 at an even k and x * x at the next one, x = 1 + 2^-13 (fp64: 2^-28), below any
+    threshold: in whichever k range the two stand, the sum is the product's own rounding error, 2^-26
+    (2^-56), if the product goes into the fused add as it is, and 0 if it was rounded first."""
+    e = 13 if dtype == np.float32 else 28
+    x, want = dtype(1 + 2.0 ** -e), dtype(2.0 ** (-2 * e))
+    call = am.amulet_mmlike_f32_general if dtype == np.float32 else am.amulet_mmlike_f64
+    for M, N, K in [(40, 70, 16), (40, 70, 18), (300, 70, 577), (40, 260, 1024)]:
+        A, B = np.zeros((M, K), dtype), np.ones((K, N), dtype)
+        k = 2 * (np.arange(M) % (K // 2))
+        A[np.arange(M), k], A[np.arange(M), k + 1] = -(1 + 2.0 ** (1 - e)), x
+        B[1::2] = x
+        th = np.full({0: (N,), 3: (M, N)}[form], 1e30, dtype)
+        for tA, tB in [(False, False), (True, False), (False, True), (True, True)]:
+            dR = torch.zeros((M, N), dtype=torch.from_numpy(A).dtype, device="cuda")
+            call(2, torch.from_numpy(np.ascontiguousarray(A.T if tA else A)).cuda(),
+                 torch.from_numpy(np.ascontiguousarray(B.T if tB else B)).cuda(), torch.from_numpy(th).cuda(), None, dR,
+                 thres_form=form, trans_a=tA, trans_b=tB)
+            torch.cuda.synchronize()
+            assert "tile" in am.amulet_recent_kernel()
+            assert np.all(dR.cpu().numpy() == want), (M, N, K, tA, tB)
