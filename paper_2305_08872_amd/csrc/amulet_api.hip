@@ -218,16 +218,14 @@ static hipError_t launch_tile_call(const Call &c, const TilePlan &plan, hipStrea
     }
 }
 
-// Predicate tasks: the plan of the tile kernels when they can run the problem -- a stage of K, a
-// 16-byte unit in an operand whose lines run across k, and per-lane byte offsets that fit 31 bits.
+// Can the tile kernels of the predicate tasks run the problem: a stage of K, a 16-byte unit in an operand
+// whose lines run across k, and per-lane byte offsets that fit 31 bits.
 template <typename T, typename Call>
-static bool tile_plan(const Call &c, double us_per_k, int64_t max_parts, TilePlan &plan)
+static bool tile_runs(const Call &c)
 {
     constexpr int64_t V = 16 / (int64_t)sizeof(T), BK = 4 * V, MAX = 0x7fffffff / (int64_t)sizeof(T);
     if (c.K < BK || (c.trans_a && c.M < V) || (!c.trans_b && c.N < V)) return false;
-    if (c.lda > (c.trans_a ? (MAX - 32) / BK : (MAX - BK) / 32) || c.ldb > (c.trans_b ? (MAX - BK) / 64 : (MAX - 64) / BK)) return false;
-    plan = choose_tile_plan<T>(c.M, c.N, c.K, us_per_k, max_parts, sizeof(T) == 8 && c.thres_form == THRES_ELEM);
-    return true;
+    return c.lda <= (c.trans_a ? (MAX - 32) / BK : (MAX - BK) / 32) && c.ldb <= (c.trans_b ? (MAX - BK) / 64 : (MAX - 64) / BK);
 }
 
 // fp32: the tile kernels, unless the 32 x 256 kernel's estimate is lower.  That kernel takes twice the
@@ -242,23 +240,24 @@ static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
 {
     // us per k of one of two resident workgroups (tile kernels), and of a 32 x 256 workgroup
     static const double tile_us[4] = {0.0, 0.125, 0.130, 0.0955}, large_us[4] = {0.0, 0.115, 0.121, 0.0895};
-    if (c.task == TASK_IDENTITY) return false;
+    if (c.task == TASK_IDENTITY || !tile_runs<float>(c)) return false;
     const ValuShapeDesc &d = kValuShapes[default_shape(c.task, c.M, c.N, c.K)];
     const int64_t range = wide_k_range((c.M + d.NW * d.TM - 1) / (d.NW * d.TM) * ((c.N + 255) / 256) * d.NW, c.K);
-    if (!tile_plan<float>(c, tile_us[c.task], (c.K + range - 1) / range, plan)) return false;
+    plan = choose_tile_plan<float>(c.M, c.N, c.K, tile_us[c.task], (c.K + range - 1) / range);
     const int64_t large = ((c.M + 31) / 32) * ((c.N + 255) / 256);
     if (large < 256) return true;
     const double rounds = (double)large / 256.0, part_round = large % 512 == 0 ? 0.1 : 0.35;
     return 1.04 * plan.us <= (double)c.K * large_us[c.task] * (rounds + part_round) + 4.4 + 3.8 * rounds;
 }
 
-// `built_in`: the shape is nobody's choice but this library's own, so the launch may take the tile
-// kernels, which have no shape id.
-static int run_mmlike(const MmlikeCall &c, int shape, void *stream, bool built_in)
+// `tile`: the tile kernels run the call, with this plan; null: the shape's kernel does.  The tile kernels have no
+// shape id: they may stand in for a shape that is nobody's choice but this library's own.  An adaptive
+// call decides that once, for its whole task, and hands every slab the same answer, so that what was timed as
+// the built-in shape is what runs as it afterwards.
+static int run_mmlike(const MmlikeCall &c, int shape, void *stream, const TilePlan *tile)
 {
-    TilePlan plan;
-    if (built_in && tile_wanted(c, plan)) {
-        g_last_hip_error = launch_tile_call<float>(c, plan, (hipStream_t)stream);
+    if (tile && tile_runs<float>(c)) {
+        g_last_hip_error = launch_tile_call<float>(c, *tile, (hipStream_t)stream);
         return g_last_hip_error == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
     }
     MmlikeArgs a;
@@ -307,7 +306,12 @@ static int check_mmlike(const MmlikeCall &c)
 // phases of the persistent join-count kernels (see count_i8_dma_persistent_kernel)
 static const int kPersPhases[4] = {8, 2, 2, 16};   // groups, stages between groups, XCD modulus, XCD span (sixteenths)
 
-// Join count, built-in choice: runs the tile kernels (count_i8_tile.hip) and returns true, unless they cannot
+// How the tile kernels of the join count (count_i8_tile.hip) run a call.
+struct CountRoute {
+    CountTilePlan plan;
+    int bypass;
+};
+// Join count, built-in choice: true, and how, if the tile kernels are to run the call.  They are, unless they cannot
 // run the problem -- 64 k, a 16-byte unit in an operand whose lines run across k, byte offsets that fit 31
 // bits -- or it is one of many whole tiles that the streamed kernels (count_i8_dma.hip) can take, where those
 // are ahead: their persistent form starts a tile while the last one's R is still on its way, and their
@@ -319,8 +323,8 @@ static const int kPersPhases[4] = {8, 2, 2, 16};   // groups, stages between gro
 //   R = : 6144^2 x 4096 128 / 140, 3072^2 x 2048 26 / 30, 12288 x 8192 x 512 94 / 112; up to one 128 x 256
 //     tile per unit, where theirs is another kernel, 2048 x 4096 x 4096 42 / 35.
 // Anything ragged or unaligned: 8191^2 x 4095 562 / 314, 8000^2 x 4000 368 / 235, 1000^2 x 1000 38 / 6.5.
-static bool count_tile(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const int8_t *A, int64_t lda, const int8_t *B,
-                       int64_t ldb, int32_t *R, int64_t ldr, bool assign, void *stream, int &rc)
+static bool count_tile_wanted(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const int8_t *A, int64_t lda, const int8_t *B,
+                              int64_t ldb, const int32_t *R, int64_t ldr, bool assign, CountRoute &route)
 {
     const int64_t max_offset = 0x7fff0000;
     if (K < 64 || (trans_a && M < 16) || (!trans_b && N < 16) || ldr > max_offset / 1024 || lda > max_offset / 256 || ldb > max_offset / 256)
@@ -334,16 +338,24 @@ static bool count_tile(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
     // (streamed straight to LDS, a piece of a row may start at any 4-byte address)
     auto dwords = [](const void *p, int64_t ld, int64_t line) { return ((uintptr_t)p & 3u) == 0 && ld % 4 == 0 && line % 4 == 0; };
     const bool stream_to_lds = dwords(A, lda, trans_a ? M : K) && dwords(B, ldb, trans_b ? K : N);
-    const CountTilePlan plan = choose_count_tile(M, N, K, !stream_to_lds, assign);
-    CountTileArgs a;
-    a.A = A; a.B = B; a.R = R; a.lda = lda; a.ldb = ldb; a.ldr = ldr;
-    a.M = (int)M; a.N = (int)N; a.K = (int)K;
-    a.assign = assign && plan.parts == 1 ? 1 : 0;
+    route.plan = choose_count_tile(M, N, K, !stream_to_lds, assign);
     // R around the caches when a call's matrices do not fit the last-level cache (256 MiB) anyway, so that R does
     // not displace operands: 8000^2 x 4000 280 -> 235 us, 8191^2 x 4095 358 -> 314, 7801^2 x 3001 254 -> 246; where
     // they do, R is still there at the next call: 7900^2 x 2000 178 / 194, 5000 x 7000 x 3000 144 / 166
     const double bytes = 4.0 * (double)M * (double)N + (double)K * ((double)M + (double)N);
-    a.bypass = !assign && bytes > 285e6 ? 1 : 0;
+    route.bypass = !assign && bytes > 285e6 ? 1 : 0;
+    return true;
+}
+
+static int run_count_tile(const CountRoute &route, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const int8_t *A, int64_t lda,
+                          const int8_t *B, int64_t ldb, int32_t *R, int64_t ldr, bool assign, void *stream)
+{
+    const CountTilePlan &plan = route.plan;
+    CountTileArgs a;
+    a.A = A; a.B = B; a.R = R; a.lda = lda; a.ldb = ldb; a.ldr = ldr;
+    a.M = (int)M; a.N = (int)N; a.K = (int)K;
+    a.assign = assign && plan.parts == 1 ? 1 : 0;
+    a.bypass = route.bypass;
     KernelNote &n = new_note(AMULET_TASK_COUNT_I8, 0, -1, M);
     n.tile = plan.tile; n.parts = plan.parts; n.kpart = plan.kpart; n.kgroup = plan.kgroup;
     n.ring = plan.alone; n.registers = plan.through_registers; n.bypass = a.bypass && plan.tile <= CT_128x256;
@@ -355,18 +367,14 @@ static bool count_tile(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
     }
     if (e == hipSuccess) e = launch_count_i8_tile((trans_a ? 1 : 0) | (trans_b ? 2 : 0), plan, a, (hipStream_t)stream);
     g_last_hip_error = e;
-    rc = e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
-    return true;
+    return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
 }
 
-// built_in: nobody chose `shape`, the tile kernels may run the problem instead
 // m_load / n_load: rows of A / columns of B that exist in memory (0: just M, N)
 static int run_count(int shape, int64_t M, int64_t N, int64_t K, const int8_t *A, int64_t lda,
                      const int8_t *B, int64_t ldb, int32_t *R, int64_t ldr, void *stream,
-                     bool built_in = false, int64_t m_load = 0, int64_t n_load = 0, bool assign = false)
+                     int64_t m_load = 0, int64_t n_load = 0, bool assign = false)
 {
-    int rc;
-    if (built_in && m_load == 0 && count_tile(0, 0, M, N, K, A, lda, B, ldb, R, ldr, assign, stream, rc)) return rc;
     CountArgs a;
     a.assign = assign ? 1 : 0;
     a.A = A; a.B = B; a.R = R;
@@ -427,7 +435,11 @@ __global__ void fill_i8_kernel(int8_t *p, size_t n, uint32_t salt)
 
 struct TrialCtx {
     int task;
-    int64_t M, N, K;
+    int64_t M, N, K;   // of a trial: as many of the task's rows as the time allows
+    int built_in;      // the whole task's built-in shape,
+    bool tile;         // whether tile kernels stand in for it,
+    TilePlan plan;     // and how
+    CountRoute route;
     void *A, *B, *params, *R;
     hipStream_t stream;
     hipEvent_t e0, e1;
@@ -437,13 +449,15 @@ struct TrialCtx {
 // One launch of `shape` on the trial operands.
 static int trial_launch(TrialCtx *c, int shape)
 {
+    const bool tile = c->tile && shape == c->built_in;
     if (c->task == AMULET_TASK_COUNT_I8)
-        return run_count(shape, c->M, c->N, c->K, (const int8_t *)c->A, c->K, (const int8_t *)c->B, c->N,
-                         (int32_t *)c->R, c->N, c->stream, shape == default_shape(AMULET_TASK_COUNT_I8, c->M, c->N, c->K));
+        return tile ? run_count_tile(c->route, 0, 0, c->M, c->N, c->K, (const int8_t *)c->A, c->K, (const int8_t *)c->B, c->N,
+                                     (int32_t *)c->R, c->N, false, c->stream)
+                    : run_count(shape, c->M, c->N, c->K, (const int8_t *)c->A, c->K, (const int8_t *)c->B, c->N, (int32_t *)c->R, c->N, c->stream);
     MmlikeCall call = {c->task, THRES_COL, 0, 0, c->M, c->N, c->K, (const float *)c->A, c->K,
                        (const float *)c->B, c->N, (const float *)c->params, 0,
                        (const float *)c->params + c->N, (float *)c->R, c->N};
-    return run_mmlike(call, shape, c->stream, shape == default_shape(c->task, c->M, c->N, c->K));
+    return run_mmlike(call, shape, c->stream, tile ? &c->plan : nullptr);
 }
 
 // Milliseconds of `n` back-to-back launches of `shape`, or a negative value on failure.
@@ -538,6 +552,9 @@ struct BatchedTrials {
 struct AdaptiveCtx {
     bool short_task;      // the first trial showed a task too short to be worth more trials
     MmlikeCall call;      // the whole task
+    int built_in;         // its built-in shape,
+    bool tile;            // whether tile kernels stand in for it,
+    TilePlan plan;        // and how
     int64_t next_row;     // first row no trial has computed yet
     int64_t budget_rows;  // trials may use rows below this
     hipStream_t stream;
@@ -584,15 +601,16 @@ static int64_t trial_rows(const MmlikeCall &c, int shape)
 }
 
 // Runs rows [r0, r0 + rows) of the task with `shape`.
-static int run_rows(const MmlikeCall &c, int shape, int64_t r0, int64_t rows, hipStream_t s)
+static int run_rows(const AdaptiveCtx &x, int shape, int64_t r0, int64_t rows, hipStream_t s)
 {
+    const MmlikeCall &c = x.call;
     MmlikeCall sub = c;
     sub.M = rows;
     sub.A = c.trans_a ? c.A + r0 : c.A + r0 * c.lda;
     sub.R = c.R + r0 * c.ldr;
     if (c.thres_form == THRES_ROW && c.thres) sub.thres = c.thres + r0;
     if (c.thres_form == THRES_ELEM && c.thres) sub.thres = c.thres + r0 * c.ldt;
-    return run_mmlike(sub, shape, s, shape == default_shape(c.task, c.M, c.N, c.K));
+    return run_mmlike(sub, shape, s, x.tile && shape == x.built_in ? &x.plan : nullptr);
 }
 
 static double adaptive_trial(AdaptiveCtx *x, int shape)
@@ -601,7 +619,7 @@ static double adaptive_trial(AdaptiveCtx *x, int shape)
     if (x->status != AMULET_OK || x->next_row + rows > x->budget_rows) return 1e300;  // no data left to test on
     if (x->short_task) return 1e300;   // (see below)
     (void)hipEventRecord(x->e0, x->stream);
-    const int rc = run_rows(x->call, shape, x->next_row, rows, x->stream);
+    const int rc = run_rows(*x, shape, x->next_row, rows, x->stream);
     (void)hipEventRecord(x->e1, x->stream);
     if (rc != AMULET_OK || hipEventSynchronize(x->e1) != hipSuccess) {
         x->status = AMULET_ERR_LAUNCH;
@@ -650,7 +668,9 @@ int amulet_mmlike_f32_general(int task, int thres_form, int trans_a, int trans_b
     else if (shape >= n_shapes(task))
         return AMULET_ERR_SHAPE;
     if (rc == 1) return AMULET_OK;
-    return run_mmlike(c, shape, stream, selected && shape == default_shape(task, M, N, K));
+    TilePlan plan;
+    const bool tile = selected && shape == default_shape(task, M, N, K) && tile_wanted(c, plan);
+    return run_mmlike(c, shape, stream, tile ? &plan : nullptr);
 }
 
 // ---- fp64 ------------------------------------------------------------------------------------
@@ -705,8 +725,27 @@ static int lookup_shape_f64(int task, int64_t M, int64_t N, int64_t K)
     return default_shape_f64(task, M, N);
 }
 
-// Rows [r0, r0 + rows) of the task with `shape`.
-static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, void *stream, bool built_in)
+// fp64: the tile kernels in place of the built-in `shape` (see tile_wanted).  They are ahead of the shape grid's
+// kernels nearly everywhere: TFLOP/s, grid / tile, 4096^3 discount 16.4 / 17.5, boost 15.2 / 17.3, count 22.4 / 24.4; us, 512^3
+// discount 40 / 24, 256^3 16.3 / 9.5, 1024^3 boost 147 / 134; but not in two cases: thres[i][j] leaves the tile kernel
+// registers for one workgroup per unit, so it is taken where there are not more than one round of the grid
+// kernel's workgroups (512^3 47 / 36 us, 2048^3 1185 / 1314), and rows of A a multiple of 256 KiB apart, whose
+// lines a stage of 8 k fetches in halves and the caches do not keep in between (discount 512^2 x 65536 2158 /
+// 2355 us; the count has room for it).
+static bool tile_wanted_f64(const F64Call &c, int shape, TilePlan &plan)
+{
+    static const double tile_us[4] = {0.0, 0.251, 0.246, 0.172};
+    const bool per_output = c.thres_form == THRES_ELEM && ((c.M + 15) / 16) * ((c.N + 127) / 128) > 1024;
+    const bool halves = c.task != TASK_COUNT_GT && !c.trans_a && c.lda % 32768 == 0;
+    if (c.task == TASK_IDENTITY || per_output || halves || !tile_runs<double>(c)) return false;
+    const int waves = shape % F64_TILES == 1 ? 8 : 4;
+    const int64_t range = wide_k_range_f64((c.M + 4 * waves - 1) / (4 * waves) * ((c.N + 127) / 128) * waves, c.K, 16);
+    plan = choose_tile_plan<double>(c.M, c.N, c.K, tile_us[c.task], (c.K + range - 1) / range, c.thres_form == THRES_ELEM);
+    return true;
+}
+
+// Rows [r0, r0 + rows) of the task with `shape`, or with the tile kernels (see run_mmlike).
+static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, void *stream, const TilePlan *tile)
 {
     F64Call sub = c;
     sub.M = rows;
@@ -714,21 +753,8 @@ static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, v
     if (c.thres_form == THRES_ROW && c.thres) sub.thres = c.thres + r0;
     if (c.thres_form == THRES_ELEM && c.thres) sub.thres = c.thres + r0 * c.ldt;
     sub.R = c.R + r0 * c.ldr;
-    // (tile kernels: see tile_wanted.  In fp64 they are ahead of the shape grid's kernels nearly
-    // everywhere: TFLOP/s, grid / tile, 4096^3 discount 16.4 / 17.5, boost 15.2 / 17.3, count 22.4 / 24.4; us, 512^3
-    // discount 40 / 24, 256^3 16.3 / 9.5, 1024^3 boost 147 / 134)
-    // but two: thres[i][j] leaves the tile kernel registers for one workgroup per unit, so it is taken where
-    // there are not more than one round of the grid kernel's workgroups (512^3 47 / 36 us, 2048^3 1185 / 1314),
-    // and rows of A a multiple of 256 KiB apart, whose lines a stage of 8 k fetches in halves and the
-    // caches do not keep in between (discount 512^2 x 65536 2158 / 2355 us; the count has room for it).
-    static const double tile_us[4] = {0.0, 0.251, 0.246, 0.172};
-    TilePlan plan;
-    const bool per_output = c.thres_form == THRES_ELEM && ((rows + 15) / 16) * ((c.N + 127) / 128) > 1024;
-    const bool halves = c.task != TASK_COUNT_GT && !c.trans_a && c.lda % 32768 == 0;
-    const int waves = shape % F64_TILES == 1 ? 8 : 4;
-    const int64_t range = wide_k_range_f64((rows + 4 * waves - 1) / (4 * waves) * ((c.N + 127) / 128) * waves, c.K, 16);
-    if (built_in && c.task != TASK_IDENTITY && !per_output && !halves && tile_plan<double>(sub, tile_us[c.task], (c.K + range - 1) / range, plan)) {
-        g_last_hip_error = launch_tile_call<double>(sub, plan, (hipStream_t)stream);
+    if (tile && tile_runs<double>(sub)) {
+        g_last_hip_error = launch_tile_call<double>(sub, *tile, (hipStream_t)stream);
         return g_last_hip_error == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
     }
     MmlikeArgsF64 a;
@@ -761,7 +787,9 @@ int amulet_mmlike_f64_shape(int task, int shape, int thres_form, int trans_a, in
     const bool selected = shape < 0;
     if (selected) shape = lookup_shape_f64(task, M, N, K);
     if (rc == 1) return AMULET_OK;
-    return run_f64_rows(c, shape, 0, M, stream, selected && shape == default_shape_f64(task, M, N));
+    TilePlan plan;
+    const bool tile = selected && shape == default_shape_f64(task, M, N) && tile_wanted_f64(c, shape, plan);
+    return run_f64_rows(c, shape, 0, M, stream, tile ? &plan : nullptr);
 }
 
 int amulet_mmlike_f64_general(int task, int thres_form, int trans_a, int trans_b, int64_t M, int64_t N,
@@ -794,6 +822,9 @@ int amulet_selected_shape_f64(int task, int64_t M, int64_t N, int64_t K)
 struct AdaptiveF64 {
     bool short_task;
     F64Call call;
+    int built_in;       // the whole task's built-in shape,
+    bool tile;          // whether tile kernels stand in for it,
+    TilePlan plan;      // and how
     int64_t next_row, budget_rows;
     hipStream_t stream;
     hipEvent_t e0, e1;
@@ -826,7 +857,7 @@ static double adaptive_f64_score(int i0, int i1, void *ctx)
     if (x->status == AMULET_OK && x->next_row + rows <= x->budget_rows && !x->short_task) {
         (void)hipEventRecord(x->e0, x->stream);
         const int rc = run_f64_rows(x->call, shape, x->next_row, rows, x->stream,
-                                    shape == default_shape_f64(x->call.task, x->call.M, x->call.N));
+                                    x->tile && shape == x->built_in ? &x->plan : nullptr);
         (void)hipEventRecord(x->e1, x->stream);
         if (rc != AMULET_OK || hipEventSynchronize(x->e1) != hipSuccess) {
             x->status = AMULET_ERR_LAUNCH;
@@ -860,6 +891,8 @@ int amulet_mmlike_f64_adaptive(int task, int thres_form, int trans_a, int trans_
     AdaptiveF64 x;
     memset(&x, 0, sizeof(x));
     x.call = c;
+    x.built_in = default_shape_f64(task, M, N);
+    x.tile = tile_wanted_f64(c, x.built_in, x.plan);
     x.stream = (hipStream_t)stream;
     x.budget_rows = M / 2;   // at least half of the task runs with the winner
     x.best_score = 1e300;
@@ -881,7 +914,7 @@ int amulet_mmlike_f64_adaptive(int task, int thres_form, int trans_a, int trans_
     if (x.e1) (void)hipEventDestroy(x.e1);
     if (x.status != AMULET_OK) return x.status;
     int out = AMULET_OK;
-    if (x.next_row < M) out = run_f64_rows(c, best, x.next_row, M - x.next_row, stream, best == default_shape_f64(task, M, N));
+    if (x.next_row < M) out = run_f64_rows(c, best, x.next_row, M - x.next_row, stream, x.tile && best == x.built_in ? &x.plan : nullptr);
     if (out == AMULET_OK && x.trials > 0) {
         std::lock_guard<std::mutex> lock(g_sel_mutex);
         g_selected[sel_key(f64_cache_task(task), M, N, K)] = best;
@@ -1011,7 +1044,10 @@ int amulet_count_i8(int64_t M, int64_t N, int64_t K, const int8_t *A, int64_t ld
     if (rc < 0) return rc;
     if (rc == 1) return AMULET_OK;
     const int shape = lookup_shape(AMULET_TASK_COUNT_I8, M, N, K);
-    return run_count(shape, M, N, K, A, lda, B, ldb, R, ldr, stream, shape == default_shape(AMULET_TASK_COUNT_I8, M, N, K));
+    CountRoute route;
+    if (shape == default_shape(AMULET_TASK_COUNT_I8, M, N, K) && count_tile_wanted(0, 0, M, N, K, A, lda, B, ldb, R, ldr, false, route))
+        return run_count_tile(route, 0, 0, M, N, K, A, lda, B, ldb, R, ldr, false, stream);
+    return run_count(shape, M, N, K, A, lda, B, ldb, R, ldr, stream);
 }
 
 // In-flight adaptive execution for the join count (paper Sec. 4.4): the candidates here are
@@ -1043,6 +1079,14 @@ int amulet_count_i8_adaptive(int64_t M, int64_t N, int64_t K, const int8_t *A, i
     order[n_order++] = best;
     for (int sidx = COUNT_SHAPE_COUNT - 1; sidx >= 1; --sidx)
         if (sidx != best) order[n_order++] = sidx;
+    // (what stands in for the built-in shape is decided for the whole count: see run_mmlike)
+    CountRoute route;
+    const bool tile = count_tile_wanted(0, 0, M, N, K, A, lda, B, ldb, R, ldr, false, route);
+    auto run_slab = [&](int shape, int64_t r0, int64_t rows) {
+        if (tile && shape == built_in)
+            return run_count_tile(route, 0, 0, rows, N, K, A + r0 * lda, lda, B, ldb, R + r0 * ldr, ldr, false, stream);
+        return run_count(shape, rows, N, K, A + r0 * lda, lda, B, ldb, R + r0 * ldr, ldr, stream);
+    };
     const int64_t budget = M / 2;
     int64_t next_row = 0;
     int trials = 0, status = AMULET_OK;
@@ -1059,8 +1103,7 @@ int amulet_count_i8_adaptive(int64_t M, int64_t N, int64_t K, const int8_t *A, i
                 const int shape = order[i];
                 const int64_t rows = slab_rows(shape);
                 if (next_row + rows > budget) continue;   // no rows left for this one: a narrower tile may still fit
-                if (run_count(shape, rows, N, K, A + next_row * lda, lda, B, ldb, R + next_row * ldr, ldr, stream,
-                              shape == built_in) != AMULET_OK) {
+                if (run_slab(shape, next_row, rows) != AMULET_OK) {
                     status = AMULET_ERR_LAUNCH;
                     break;
                 }
@@ -1077,8 +1120,7 @@ int amulet_count_i8_adaptive(int64_t M, int64_t N, int64_t K, const int8_t *A, i
     }
     if (status != AMULET_OK) return status;
     int out = AMULET_OK;
-    if (next_row < M)
-        out = run_count(best, M - next_row, N, K, A + next_row * lda, lda, B, ldb, R + next_row * ldr, ldr, stream, best == built_in);
+    if (next_row < M) out = run_slab(best, next_row, M - next_row);
     if (out == AMULET_OK && trials > 1) {
         std::lock_guard<std::mutex> lock(g_sel_mutex);
         g_selected[sel_key(AMULET_TASK_COUNT_I8, M, N, K)] = best;
@@ -1128,10 +1170,9 @@ int amulet_count_i8_general(int trans_a, int trans_b, int64_t M, int64_t N, int6
     }
     // (the tile kernels read any layout and alignment in place: no copy)
     const int shape = lookup_shape(AMULET_TASK_COUNT_I8, M, N, K);
-    int trc;
-    if (shape == default_shape(AMULET_TASK_COUNT_I8, M, N, K) &&
-        count_tile(trans_a, trans_b, M, N, K, A, lda, B, ldb, R, ldr, false, stream, trc))
-        return trc;
+    CountRoute route;
+    if (shape == default_shape(AMULET_TASK_COUNT_I8, M, N, K) && count_tile_wanted(trans_a, trans_b, M, N, K, A, lda, B, ldb, R, ldr, false, route))
+        return run_count_tile(route, trans_a, trans_b, M, N, K, A, lda, B, ldb, R, ldr, false, stream);
     int8_t *w = (int8_t *)workspace;
     hipStream_t s = (hipStream_t)stream;
     // With room for both operands the workspace also serves as their aligned home: an operand
@@ -1175,8 +1216,7 @@ int amulet_count_i8_general(int trans_a, int trans_b, int64_t M, int64_t N, int6
         n_load = i8_tile_up(N);
     }
     if (e != hipSuccess) { g_last_hip_error = e; return AMULET_ERR_LAUNCH; }
-    return run_count(shape, M, N, Kc, A, lda, B, ldb, R, ldr, stream,
-                     false, m_load, n_load);
+    return run_count(shape, M, N, Kc, A, lda, B, ldb, R, ldr, stream, m_load, n_load);
 }
 
 // ---- the join count for callers that cannot allocate --------------------------------------
@@ -1256,15 +1296,16 @@ int amulet_count_i8_assign(int shape, int64_t M, int64_t N, int64_t K, const int
         g_last_hip_error = e;
         return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
     }
-    bool built_in = false;
     if (shape < 0) {
         shape = lookup_shape(AMULET_TASK_COUNT_I8, M, N, K);
-        built_in = shape == default_shape(AMULET_TASK_COUNT_I8, M, N, K);
+        CountRoute route;
+        if (shape == default_shape(AMULET_TASK_COUNT_I8, M, N, K) && count_tile_wanted(0, 0, M, N, K, A, lda, B, ldb, R, ldr, true, route))
+            return run_count_tile(route, 0, 0, M, N, K, A, lda, B, ldb, R, ldr, true, stream);
         // (without the read of R the persistent kernel's edge over two 128 x 256 tiles per unit starts
         // later: 768 tiles of 256 x 256 94 against 88 us, 1024 tiles level, 1536 tiles 272 / 277)
         if (shape == 8 && ((M + 255) / 256) * ((N + 255) / 256) < 1024) shape = 6;
     }
-    return run_count(shape, M, N, K, A, lda, B, ldb, R, ldr, stream, built_in, 0, 0, true);
+    return run_count(shape, M, N, K, A, lda, B, ldb, R, ldr, stream, 0, 0, true);
 }
 
 int amulet_greedy_search(int n0, int n1, amulet_score_fn score, void *ctx, int *best0, int *best1)
@@ -1311,6 +1352,8 @@ int amulet_mmlike_f32_adaptive_general(int task, int thres_form, int trans_a, in
     AdaptiveCtx x;
     memset(&x, 0, sizeof(x));
     x.call = c;
+    x.built_in = default_shape(task, M, N, K);
+    x.tile = tile_wanted(c, x.plan);
     x.stream = (hipStream_t)stream;
     x.budget_rows = M / 2;   // at least half of the task runs with the winner
     x.best_score = 1e300;
@@ -1337,7 +1380,7 @@ int amulet_mmlike_f32_adaptive_general(int task, int thres_form, int trans_a, in
                 for (int i = 0; i < 3 && x.status == AMULET_OK; ++i) {
                     const int64_t rows = trial_rows(c, cand[i]);
                     if (x.next_row + rows > x.budget_rows) continue;
-                    if (run_rows(c, cand[i], x.next_row, rows, x.stream) != AMULET_OK) { x.status = AMULET_ERR_LAUNCH; break; }
+                    if (run_rows(x, cand[i], x.next_row, rows, x.stream) != AMULET_OK) { x.status = AMULET_ERR_LAUNCH; break; }
                     bt.mark(cand[i], rows, x.stream);
                     x.next_row += rows;
                     x.trials += 1;
@@ -1364,7 +1407,7 @@ int amulet_mmlike_f32_adaptive_general(int task, int thres_form, int trans_a, in
     if (x.e1) (void)hipEventDestroy(x.e1);
     if (x.status != AMULET_OK) return x.status;
     int out = AMULET_OK;
-    if (x.next_row < M) out = run_rows(c, best, x.next_row, M - x.next_row, x.stream);
+    if (x.next_row < M) out = run_rows(x, best, x.next_row, M - x.next_row, x.stream);
     if (out == AMULET_OK && x.trials > 0) {
         std::lock_guard<std::mutex> lock(g_sel_mutex);
         g_selected[sel_key(task, M, N, K)] = best;
@@ -1411,6 +1454,15 @@ int amulet_tune(int task, int64_t M, int64_t N, int64_t K, void *stream)
               hipMalloc(&c.params, (size_t)2 * N * 4) == hipSuccess &&
               hipEventCreate(&c.e0) == hipSuccess && hipEventCreate(&c.e1) == hipSuccess;
     if (ok) {
+        // (what stands in for the built-in shape is decided for the whole task: see run_mmlike)
+        c.built_in = default_shape(task, M, N, K);
+        if (i8) {
+            c.tile = count_tile_wanted(0, 0, M, N, K, (const int8_t *)c.A, K, (const int8_t *)c.B, N, (const int32_t *)c.R, N, false, c.route);
+        } else {
+            const MmlikeCall whole = {task, THRES_COL, 0, 0, M, N, K, (const float *)c.A, K, (const float *)c.B, N, (const float *)c.params, 0,
+                                      (const float *)c.params + N, (float *)c.R, N};
+            c.tile = tile_wanted(whole, c.plan);
+        }
         if (i8) {
             hipLaunchKernelGGL(fill_i8_kernel, dim3(1024), dim3(256), 0, c.stream, (int8_t *)c.A,
                                (size_t)Mt * K, 17u);
@@ -1434,7 +1486,7 @@ int amulet_tune(int task, int64_t M, int64_t N, int64_t K, void *stream)
         // (30 ms of the default shape; 150 ms for the matrix-core tasks, whose clocks keep
         // settling for longer: the persistent join-count kernel measures 0.245 ms cold and 0.223
         // warm, which decided a tune against it)
-        const int dflt = default_shape(task, M, N, K);
+        const int dflt = c.built_in;
         const float warm_ms = (i8 || task == TASK_IDENTITY) ? 150.0f : 30.0f;
         float spent = 0.0f;
         for (int i = 0; i < 4096 && spent < warm_ms; ++i) {

@@ -112,3 +112,52 @@ def test_boost_terms_enter_the_sum_with_the_unrounded_product(am, dtype, form):
             torch.cuda.synchronize()
             assert "tile" in am.amulet_recent_kernel()
             assert np.all(dR.cpu().numpy() == want), (M, N, K, tA, tB)
+
+
+def _kernel(am, back=0):
+    """amulet_recent_kernel without the rows."""
+    words = am.amulet_recent_kernel(back).split()
+    return [words[0]] + words[3:]
+
+
+@pytest.mark.parametrize("M,N,K", [(16384, 8192, 2048), (12001, 16003, 130)])
+def test_adaptive_count_times_as_the_built_in_kernel_what_a_plain_call_runs(am, monkeypatch, M, N, K):
+    """The first trial of an adaptive call is what a plain call would run, and if it wins the rest runs with
+    it: decided for the slab alone, one of 4096 rows of 16384 x 8192 x 2048 went to the tile kernels, which the
+    whole count does not take."""
+    monkeypatch.setenv("AMULET_ADAPTIVE_MIN_TASK_MS", "0")   # (lift the no-trials limit)
+    g = torch.Generator(device="cuda").manual_seed(77)
+    A = torch.randint(-3, 4, (M, K), dtype=torch.int8, device="cuda", generator=g)
+    B = torch.randint(-3, 4, (K, N), dtype=torch.int8, device="cuda", generator=g)
+    am.amulet_clear_selections()
+    R = torch.zeros(M, N, dtype=torch.int32, device="cuda")
+    am.amulet_count_i8(A, B, R)
+    plain, built_in = _kernel(am), am.amulet_selected_shape(am.AMULET_TASK_COUNT_I8, M, N, K)
+    R.fill_(5)
+    chosen, trials = am.amulet_count_i8_adaptive(A, B, R)
+    torch.cuda.synchronize()
+    am.amulet_clear_selections()
+    assert trials >= 2
+    assert _kernel(am, trials) == plain
+    assert _kernel(am, 0) == (plain if chosen == built_in else [am.amulet_shape_name(am.AMULET_TASK_COUNT_I8, chosen)])
+    assert torch.equal(R, (A.float() @ B.float()).to(torch.int32) + 5)      # |sum| < 2^24: exact
+
+
+@pytest.mark.parametrize("task", [1, 2, 3])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_adaptive_calls_time_as_the_built_in_kernel_what_a_plain_call_runs(am, monkeypatch, task, dtype):
+    monkeypatch.setenv("AMULET_ADAPTIVE_MIN_TASK_MS", "0")
+    M, N, K = 24576, 2048, 72
+    g = torch.Generator(device="cuda").manual_seed(78)
+    A, B, th, dis = (torch.randint(-9, 10, s, device="cuda", generator=g).to(dtype) for s in ((M, K), (K, N), (N,), (N,)))
+    R, call = torch.zeros(M, N, dtype=dtype, device="cuda"), am.amulet_mmlike_f32_general if dtype == torch.float32 else am.amulet_mmlike_f64
+    adaptive = am.amulet_mmlike_f32_adaptive_general if dtype == torch.float32 else am.amulet_mmlike_f64_adaptive
+    am.amulet_clear_selections()
+    call(task, A, B, th, dis / 8, R)
+    plain, whole = _kernel(am), R.clone()
+    R.zero_()
+    _, trials = adaptive(task, A, B, th, dis / 8, R)
+    torch.cuda.synchronize()
+    am.amulet_clear_selections()
+    assert trials >= 2 and _kernel(am, trials) == plain
+    assert torch.equal(R, whole)        # multiples of 1/8 well below 2^24 of them: exact in any order
