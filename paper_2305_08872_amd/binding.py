@@ -10,6 +10,7 @@ raises.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 
 AMULET_IDENTITY, AMULET_DISCOUNT, AMULET_BOOST, AMULET_COUNT_GT = 0, 1, 2, 3
@@ -156,12 +157,20 @@ def load_library():
     lib.amulet_version.restype = ctypes.c_char_p
     lib.amulet_version.argtypes = []
     _torch, _raw_stream = torch, getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    try:
-        from . import _marshal
-    except ImportError:
-        _marshal = None
+    _marshal = _compiled_marshalling()
     _lib = lib
     return lib
+
+
+def _compiled_marshalling():
+    """The compiled module, if it was built, and for the torch that is loaded: it reads tensors by the layout
+    of that torch's headers."""
+    try:
+        from .build import torch_build
+        module = importlib.import_module("._marshal", __package__)
+        return module if getattr(module, "built_for_torch", None) == torch_build() else None
+    except (ImportError, AttributeError):
+        return None
 
 
 _SCORE_FN = ctypes.CFUNCTYPE(ctypes.c_double, ctypes.c_int, ctypes.c_int, ctypes.c_void_p)

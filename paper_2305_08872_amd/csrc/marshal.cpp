@@ -248,5 +248,10 @@ PyMODINIT_FUNC PyInit__marshal()
         PyErr_SetString(PyExc_ImportError, "torch has no raw stream handles");
         return nullptr;
     }
-    return PyModule_Create(&module);
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for_torch", BUILT_FOR_TORCH) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }
