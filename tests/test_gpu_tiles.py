@@ -51,8 +51,8 @@ def test_tile_kernels_at_the_edges_of_tiles_stages_and_k_ranges(am, dtype, task,
 
 # edges of the join count's tiles (64 ... 256), of its 16-byte units and of its stages (64 k, 128 in two
 # groups): the smallest problem, one more and one less than whole tiles, units and stages, a short last
-# stage in either group, K over several workgroups, each of the four tiles with and without whole tiles,
-# an R that is read and written around the caches
+# stage in either group, K over several workgroups, an R that is read and written around the caches (which
+# kernel a size gets follows from a model of its time; every kernel at a size of its own: I8_KERNELS below)
 I8_SIZES = [(16, 16, 64), (17, 31, 65), (63, 65, 127), (64, 64, 128), (65, 80, 193), (130, 100, 1055), (100, 260, 4097),
             (1000, 1000, 250), (1100, 1500, 300), (2100, 1900, 130), (2048, 4096, 192), (1900, 3000, 1000), (2300, 4112, 208), (3000, 4400, 75), (8500, 8400, 70)]
 
@@ -161,3 +161,85 @@ def test_adaptive_calls_time_as_the_built_in_kernel_what_a_plain_call_runs(am, m
     am.amulet_clear_selections()
     assert trials >= 2 and _kernel(am, trials) == plain
     assert torch.equal(R, whole)        # multiples of 1/8 well below 2^24 of them: exact in any order
+
+
+# Every kernel of the join count's tile family at a size whose plan it is: (kernel, K over several workgroups,
+# R = instead of R +=, M, N, K).  Streamed ones on tight rows, the ones through registers on rows at odd
+# addresses; ragged in all three.  A model of the kernels' times makes the plans: where a constant of it changes,
+# the size here has to follow, or that kernel goes untested.
+I8_KERNELS = [
+    ("i8_tile_64x64", False, False, 100, 68, 76), ("i8_tile_64x64", True, False, 72, 68, 460), ("i8_tile_64x64", True, True, 64, 68, 3780),
+    ("i8_tile_64x64_registers", False, False, 65, 67, 103), ("i8_tile_64x64_registers", True, False, 77, 65, 385),
+    ("i8_tile_64x64_registers", True, True, 71, 89, 2109),
+    ("i8_tile_128x128", False, False, 6660, 268, 72), ("i8_tile_128x128", False, True, 8820, 208, 68),
+    ("i8_tile_128x128", True, False, 72, 8684, 1148), ("i8_tile_128x128", True, True, 8336, 68, 3144),
+    ("i8_tile_128x128_registers", False, False, 8321, 77, 277), ("i8_tile_128x128_registers", True, False, 8961, 67, 617),
+    ("i8_tile_128x128_registers", True, True, 67, 8769, 1917),
+    ("i8_tile_128x256", False, False, 4648, 2564, 68), ("i8_tile_128x256", False, True, 7620, 1576, 76),
+    ("i8_tile_128x256_bypass", False, False, 8852, 8096, 96),
+    ("i8_tile_128x256_ring6", False, False, 2400, 1724, 1352), ("i8_tile_128x256_ring6", False, True, 5980, 704, 1088),
+    ("i8_tile_256x256", False, False, 2724, 2948, 2204), ("i8_tile_256x256", False, True, 1388, 5964, 1672),
+    ("i8_tile_256x256_bypass", False, False, 7644, 8236, 2388),
+    ("i8_tile_256x256_registers", False, False, 6949, 1785, 65), ("i8_tile_256x256_registers", False, True, 1625, 7825, 69),
+    ("i8_tile_256x256_registers_bypass", False, False, 8741, 8897, 69),
+    # whole aligned tiles: the streamed kernels that have shape ids
+    ("mfma_i8_256x256_w16_dma4_persistent", False, False, 8192, 8192, 2048), ("mfma_i8_256x256_w16_dma4_persistent", False, True, 8192, 8192, 320),
+    ("mfma_i8_128x256_dma3", False, True, 4096, 4352, 256),
+]
+
+
+@pytest.mark.parametrize("kernel,split,assign,M,N,K", I8_KERNELS)
+def test_every_count_kernel_at_a_size_of_its_own(am, kernel, split, assign, M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K)
+    A = torch.randint(-3, 4, (M, K), dtype=torch.int8, device="cuda", generator=g)
+    B = torch.randint(-3, 4, (K, N), dtype=torch.int8, device="cuda", generator=g)
+    want = (A.float() @ B.float()).to(torch.int32)      # |sum| < 2^24: exact
+    odd = 1 if "registers" in kernel else 0
+    am.amulet_clear_selections()
+    for tA, tB in [(False, False)] if assign or kernel.startswith("mfma") else [(False, False), (True, False), (False, True), (True, True)]:
+        def stored(X, trans):
+            X = X.t() if trans else X
+            buf = torch.zeros(X.numel() + odd, dtype=torch.int8, device="cuda")
+            view = buf[odd:].view(X.shape)
+            view.copy_(X)
+            return view
+        print(kernel, split, assign, tA, tB, M, N, K, flush=True)
+        sA, sB = stored(A, tA), stored(B, tB)
+        R = torch.full((M, N), 11, dtype=torch.int32, device="cuda")
+        if assign:
+            am.amulet_count_i8_assign(sA, sB, R)
+        else:
+            am.amulet_count_i8_general(sA, sB, R, torch.empty(am.amulet_count_i8_workspace_bytes(tA, tB, M, N, K) + 16, dtype=torch.int8,
+                                                              device="cuda"), trans_a=tA, trans_b=tB)
+        torch.cuda.synchronize()
+        ran = _kernel(am)
+        assert ran[0] == kernel and ("parts" in ran and int(ran[2]) > 1) == split, ran
+        assert torch.equal(R, want if assign else want + 11), (tA, tB)
+
+
+@pytest.mark.parametrize("dtype,kernel,split,M,N,K", [
+    (np.float32, "f32_tile_32x64", True, 815, 141, 265), (np.float32, "f32_tile_32x64", False, 600, 1301, 333),
+    (np.float32, "f32_tile_16x64", False, 903, 145, 243), (np.float32, "f32_tile_16x64", True, 71, 67, 1003),
+    (np.float64, "f64_tile_32x64", True, 815, 141, 265), (np.float64, "f64_tile_32x64", False, 600, 1301, 333),
+    (np.float64, "f64_tile_16x64", False, 903, 145, 243), (np.float64, "f64_tile_16x64", True, 71, 67, 1003)])
+@pytest.mark.parametrize("task", [1, 2, 3])
+def test_every_predicate_tile_at_a_size_of_its_own(am, dtype, kernel, split, M, N, K, task):
+    """Both tiles, K whole and over several workgroups, with K loops of many stages, a short last one and
+    ragged edges: as above, on data whose sums are exact in any order."""
+    ref = oracle.mmlike_f32_general if dtype == np.float32 else oracle.mmlike_f64_general
+    call = am.amulet_mmlike_f32_general if dtype == np.float32 else am.amulet_mmlike_f64
+    g = np.random.Generator(np.random.PCG64(7900 + task + M))
+    A, B = g.integers(-8, 9, (M, K)).astype(dtype), g.integers(-8, 9, (K, N)).astype(dtype)
+    th, dis = (g.integers(-24, 25, N) / 2.0).astype(dtype), (g.integers(0, 9, N) / 8.0).astype(dtype)
+    R_in = g.integers(-5, 6, (M, N)).astype(dtype)
+    R_ref, _, _ = ref(task, A, B, th, dis if task == 1 else None, R_in, thres_form=0)
+    am.amulet_clear_selections()
+    for tA, tB in [(False, False), (True, False), (False, True), (True, True)]:
+        dR = torch.from_numpy(R_in.copy()).cuda()
+        print(kernel, split, task, tA, tB, M, N, K, flush=True)
+        call(task, torch.from_numpy(np.ascontiguousarray(A.T if tA else A)).cuda(), torch.from_numpy(np.ascontiguousarray(B.T if tB else B)).cuda(),
+             torch.from_numpy(th).cuda(), torch.from_numpy(dis).cuda() if task == 1 else None, dR, trans_a=tA, trans_b=tB)
+        torch.cuda.synchronize()
+        ran = _kernel(am)
+        assert ran[0] == kernel and (int(ran[2]) > 1) == split, ran
+        assert np.array_equal(dR.cpu().numpy(), R_ref.astype(dtype)), (tA, tB)
