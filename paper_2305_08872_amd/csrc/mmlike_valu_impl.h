@@ -128,6 +128,9 @@ mmlike_valu_kernel(const MmlikeArgs args)
     static_assert(!BPRE || (!ALDS && TM == 4 && NG == 1), "B values a chunk ahead: scalar-path A, 4 x 4 micro-tile");
     static_assert(!PIPE || (TASK == TASK_DISCOUNT && TM == 4 && NG == 1), "chunk pipeline: discount task, 4 x 4 micro-tile");
     static_assert(!ALDS || (TRANS == 0 && TM == 4 && NG == 1), "A through LDS: row-major operands, 4 x 4 micro-tile");
+    // Forms that hold more than their loop needs: A's tile, or a threshold per output.  (The others fit 128 registers as
+    // they are, and a transposed A's scalar loads are sensitive to any change of schedule: 6 % either way.)
+    constexpr bool TIGHT = ALDS || (TF == THRES_ELEM && (TRANS == 0 || (TRANS == 2 && TASK == TASK_COUNT_GT)));
     typedef typename AccT<TASK>::type acc_t;
     static_assert(KA == 4 && TM % 4 == 0, "a transposed A is fetched as 4 rows x 4 k blocks");
     constexpr int BN = 256 * NG;           // tile columns
@@ -356,7 +359,7 @@ mmlike_valu_kernel(const MmlikeArgs args)
                 stage[it] = *(const f4_any *)(bsrc + it * pass_stride);
             bsrc += tile_stride;
         } else {
-            int last = krows - 1;      // (opaque, as above; so is the last column below)
+            int last = krows - 1;      // (opaque, as above; so is the column below where registers are short)
             asm volatile("" : "+s"(last));
 #pragma unroll
             for (int it = 0; it < LOADS; ++it) {
@@ -365,10 +368,15 @@ mmlike_valu_kernel(const MmlikeArgs args)
                 if (groups) {
                     stage[it] = *(const f4_any *)src;
                 } else {
-                    int end = N - 1 - bcol;
-                    asm volatile("" : "+v"(end));
+                    if constexpr (TIGHT) {
+                        int end = N - 1 - bcol;
+                        asm volatile("" : "+v"(end));
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) stage[it][e] = src[e < end ? e : end];
+                        for (int e = 0; e < 4; ++e) stage[it][e] = src[e < end ? e : end];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) stage[it][e] = src[bcol + e < N ? e : N - 1 - bcol];
+                    }
                 }
             }
             bsrc += tile_stride;
@@ -618,10 +626,10 @@ mmlike_valu_kernel(const MmlikeArgs args)
     }
     flush();
 
-    // (opaque from here on, or the columns of the write-back are computed with those of the thresholds, before the
-    // K loop, and held through it: up to 17 registers more than the 128 there are)
+    // (where registers are short opaque from here on, or the columns of the write-back are computed with those of the
+    // thresholds, before the K loop, and held through it: up to 17 registers more than the 128 there are)
     int l = lane;
-    asm volatile("" : "+v"(l));
+    if constexpr (TIGHT) asm volatile("" : "+v"(l));
     if (ksplit) {
         // several workgroups own this tile: hardware float adds, in whatever order; 64 neighbours of a row at
         // a time, through the wave's kilobyte of the B tile (its own lanes only: no barrier).  A wave's atomic
