@@ -376,7 +376,8 @@ struct TilePlan {
 // arithmetic -- and a last round of at most 256 is half a round and 15 % more.  Launch, first
 // loads and write-back: 2.1 us and 1.3 per round; a tile in parts: 0.3 us and the atomic adds at
 // 1.6 T (fp64 0.8 T) per second beside other workgroups' arithmetic.  Checked against the fastest of all plans at
-// 240 drawn sizes (64 ... 8192 each way, both element types): 1.1 % behind it on average, 12 % at most.
+// 240 drawn sizes (64 ... 8192 each way, both element types): 1.1 % behind it on average, 12 % at most (with any
+// number of parts).
 // (`alone`: the form that holds one workgroup to a unit, fp64 with thres[i][j]; nothing covers the loads of
 // a tile's thresholds there, 3.5 us per round.)
 // `max_parts`: the parts the wide kernel would add for the same call.  Every part is one more rounding of R, so a
@@ -392,8 +393,7 @@ inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_
     for (int wide = 0; wide < 2; ++wide) {
         const int rows = wide ? 32 : 16, groups = wide ? 4 : 8;
         const int64_t grid = xcd_grid((M + rows - 1) / rows, (N + 63) / 64);
-        auto next = [](int64_t p) { return p < 4 ? p + 1 : p % 3 ? p / 2 * 3 : p / 3 * 4; };   // 1 2 3 4 6 8 12 16 24 ...
-        for (int64_t p = 1; p <= max_parts; p = p < max_parts && next(p) > max_parts ? max_parts : next(p)) {
+        for (int64_t p = 1; p <= max_parts; p = p < 4 ? p + 1 : p % 3 ? p / 2 * 3 : p / 3 * 4) {   // 1 2 3 4 6 8 12 16 24 ...
             if (p > 1 && (K / p < 32 || grid * p > 12288)) break;
             const int64_t kpart = up((K + p - 1) / p, V), parts = (K + kpart - 1) / kpart;
             const int64_t kgroup = up((kpart + groups - 1) / groups, V);
@@ -480,7 +480,7 @@ struct CountTilePlan {
 // The plan with the lowest estimated time.  Tiles: 256 x 256 (16 waves, one workgroup to a compute unit),
 // 128 x 256 (8 waves, two to a unit, a deeper ring with one; streamed only), 128 x 128 (8 waves, two), 64 x 64 (two groups of 4 waves
 // that share K, two).  A stage of 64 k (64 x 64: 128) takes `alone` us in a workgroup that has its unit for
-// itself and `shared` per pair of workgroups on a unit, half as much again through registers; the rest of a
+// itself and `shared` per pair of workgroups on a unit, 1.4 to 1.7 times that through registers; the rest of a
 // tile -- first loads, sums, write-back -- `rest_...`, a fifth less when R is not read.  W workgroups (with the
 // tile order's padding) are whole rounds and a last one in which at most one workgroup per unit is alone.
 // K over several workgroups (the two smaller tiles): 0.3 us and 1 T atomic adds per second beside other workgroups' arithmetic, 4 us
