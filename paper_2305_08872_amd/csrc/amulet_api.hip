@@ -233,9 +233,10 @@ static bool tile_runs(const Call &c)
 // enough; its tiles are 4 times larger (two to a compute unit and round, and a tenth
 // of a tile's time for the launch's two ends, 0.35 when its last round is split), and below one per unit
 // it is never ahead.  Measured, us, 32 x 256 (or
-// 16 x 256) kernel with its own K split / tile kernel: discount 256^3 17.4 / 7.1, 512^3 39.5 / 13.7, 1024^3
-// 98 / 73, 1536^3 265 / 237, 2048^3 527 / 532, 4096^3 4008 / 4230, 3262 x 288 x 5014 699 / 338, 6720 x 64 x 3115 446 /
-// 100, 1251 x 640 x 2527 190 / 153, 5502 x 2560 x 832 boost 781 / 801, 2048 x 4597 x 743 count 388 / 356.
+// 16 x 256) kernel with its own K split / tile kernel: discount 256^3 13.5 / 5.4, 512^3 31.8 / 13.2, 1024^3
+// 80 / 72, 1536^3 245 / 228, 3262 x 288 x 5014 670 / 334, 6720 x 64 x 3115 424 / 111, 1251 x 640 x 2527 171 / 141; and
+// where the wide kernel runs, before its B loads lost their guards: 2048^3 527 / 532, 4096^3 4008 / 4230,
+// 5502 x 2560 x 832 boost 781 / 801 (now 712 / -).
 static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
 {
     // us per k of one of two resident workgroups (tile kernels), and of a 32 x 256 workgroup
@@ -726,10 +727,10 @@ static int lookup_shape_f64(int task, int64_t M, int64_t N, int64_t K)
 }
 
 // fp64: the tile kernels in place of the built-in `shape` (see tile_wanted).  They are ahead of the shape grid's
-// kernels nearly everywhere: TFLOP/s, grid / tile, 4096^3 discount 16.4 / 17.5, boost 15.2 / 17.3, count 22.4 / 24.4; us, 512^3
-// discount 40 / 24, 256^3 16.3 / 9.5, 1024^3 boost 147 / 134; but not in two cases: thres[i][j] leaves the tile kernel
+// kernels nearly everywhere: TFLOP/s, grid / tile, 4096^3 discount 16.9 / 17.6, boost 16.4 / 18.0, count 22.4 / 24.3; us, 512^3
+// discount 40.5 / 22.8, 256^3 16.3 / 7.5, 1024^3 boost 139 / 128; but not in two cases: thres[i][j] leaves the tile kernel
 // registers for one workgroup per unit, so it is taken where there are not more than one round of the grid
-// kernel's workgroups (512^3 47 / 36 us, 2048^3 1185 / 1314), and rows of A a multiple of 256 KiB apart, whose
+// kernel's workgroups (512^3 47 / 25 us, 2048^3 1185 / 1314), and rows of A a multiple of 256 KiB apart, whose
 // lines a stage of 8 k fetches in halves and the caches do not keep in between (discount 512^2 x 65536 2158 /
 // 2355 us; the count has room for it).
 static bool tile_wanted_f64(const F64Call &c, int shape, TilePlan &plan)

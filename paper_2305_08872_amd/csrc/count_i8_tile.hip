@@ -16,11 +16,13 @@
 // Two ways in.  Streamed (global_load_lds, a ring of 3 or 4 stages; the 128 x 256 tile, alone on its unit, of 6:
 // 2048 x 4096 x 4096 49 -> 36 us, while the smaller tiles gain nothing from 8) where pieces of rows start at 4-byte
 // addresses: 64 KiB in flight per unit and no register or LDS-write cycles.  Through registers (two sets, two
-// LDS slots) for rows at any byte address, 40-60 % more per stage.
+// LDS slots) for rows at any byte address, 42-67 % more per stage by tile; a whole call, us, streamed / the same
+// call one byte off: 3000 x 4004 x 2504 (written) 38 / 49, 5000 x 7000 x 3000 145 / 175, 8000^2 x 4000 235 / 314,
+// 2048^2 x 8192 40 / 67.
 //
 // Measured, us, the kernels it replaced at these sizes / here: 1000^3 38 / 6.5 (a stage of 128 x 128 guarded
-// loads by one thread each), 2999 x 4001 x 2503 (written) 79 / 33, 5000 x 7000 x 3000 212 / 137, 8191^2 x 4095
-// 562 / 314, 8000^2 x 4000 368 / 235, 2048^2 x 8192 57 / 41; 4096^3 with both operands transposed 85 / 64.
+// loads by one thread each), 2999 x 4001 x 2503 (written) 79 / 45, 5000 x 7000 x 3000 212 / 145, 8191^2 x 4095
+// 562 / 314, 8000^2 x 4000 368 / 235, 2048^2 x 8192 57 / 40; 4096^3 with both operands transposed 85 / 64.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

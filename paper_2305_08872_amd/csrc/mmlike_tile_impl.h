@@ -27,8 +27,8 @@
 // Bound: vector-ALU issue (fp32 9.1-9.2 clocks per 64 products of discount and boost in a register-only
 // loop, 6.6 count; fp64 16 of an ideal 16), and below about 1024^3 the launch, the first loads and the
 // write-back, 5 us in all.  LDS reads are 40-60 % of what a compute unit can do.  Measured, wide / tile, us:
-// fp32 discount 64^3 14.4 / 5.9, 256^3 17.4 / 7.0, 512^3 39.5 / 13.2, 1024^3 97 / 72, 1536^3 263 / 232; fp64
-// discount 256^3 16.3 / 9.2, 512^3 40.6 / 24.6, 4096^3 8313 / 7829 (17.6 TFLOP/s), count 6121 / 5639.  From 2048^3 on
+// fp32 discount 64^3 12.9 / 5.0, 256^3 13.5 / 5.4, 512^3 31.8 / 13.2, 1024^3 80 / 72, 1536^3 245 / 228; fp64
+// discount 256^3 16.3 / 7.5, 512^3 40.5 / 22.8, 4096^3 8155 / 7823 (17.6 TFLOP/s), count 6146 / 5650.  From 2048^3 on
 // the wide fp32 kernel is as fast or faster (33.8 against 32.5 TFLOP/s at 4096^2): half the LDS reads.
 //
 // LDS layout of a group's stage: A, then B.  An operand whose lines run along k (row-major A, transposed B)
