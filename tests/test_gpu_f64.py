@@ -459,3 +459,29 @@ def test_f64_deterministic_mode_gives_the_same_bits_twice(am, task, M, N, K):
     check(R1, R_ref, ab, R_in, task, "f64 deterministic mode, task %d" % task)
     R3 = run(am, task, 0, dev(A), dev(B), th, dis, dev(R_in))
     check(R3, R_ref, ab, R_in, task, "f64 default mode, task %d" % task)
+
+
+@pytest.mark.parametrize("shape", [0, 1])
+@pytest.mark.parametrize("task", [1, 2, 3])
+def test_grid_kernels_own_splits_and_A_through_lds_by_shape(am, task, shape):
+    """What the vector-ALU kernels of the shape grid do by their launcher's own rules, which built-in calls of such
+    sizes leave to the tile kernels: K over several workgroups with few tiles, a last round of
+    workgroups split over K (1176 tiles of 16 x 128, 600 of 32 x 128), and with A's row pitch a multiple
+    of 64 KiB the variant that stages A through LDS, whole and in both splits; a threshold form each."""
+    cases = [(64, 64, 5000, 0), (770, 3050, 1100, 0), (129, 1030, 77, 8192), (64, 256, 1100, 8192), (770, 3050, 600, 8192)]
+    for idx, (M, N, K, pitch) in enumerate(cases):
+        form = (idx + task) % 4
+        A, B, th, dis, R_in = make_case(form, M, N, K, seed=8700 + 10 * task + idx, exact=(task == 3))
+        R_ref, ab, _ = oracle.mmlike_f64_general(task, A, B, th, dis if task == 1 else None, R_in, thres_form=form)
+        dA = dev(A)
+        if pitch:
+            wide = torch.zeros((M, pitch), dtype=torch.float64, device="cuda")
+            wide[:, :K].copy_(dA)
+            dA = wide[:, :K]
+            assert am.amulet_pitch_collides(pitch, 8)
+        print("f64 grid kernel", task, shape, form, M, N, K, pitch, flush=True)
+        dR = dev(R_in)
+        am.amulet_mmlike_f64(task, dA, dev(B), dev(th), dev(dis) if task == 1 else None, dR, thres_form=form, shape=shape)
+        torch.cuda.synchronize()
+        assert am.amulet_recent_kernel().split()[0] == am.amulet_f64_shape_name(shape)
+        check(dR.cpu().numpy(), R_ref, ab, R_in, task, "f64 grid kernel task %d shape %d %dx%dx%d" % (task, shape, M, N, K))
