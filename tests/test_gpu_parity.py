@@ -409,8 +409,8 @@ def test_count_i8_adaptive_execution_trials_contribute_to_the_result(am, monkeyp
 
 @pytest.mark.parametrize("tA,tB", [(True, False), (False, True), (True, True), (False, False)])
 def test_count_i8_transposed_operands(am, tA, tB):
-    """A stored K x M and / or B stored N x K: transposed into the lent workspace, then the
-    row-major kernels.  Ragged and whole-tile sizes, padded pitches, non-zero R_in; bit-exact."""
+    """A stored K x M and / or B stored N x K: read in place by the tile kernels, or with K < 64
+    transposed into the lent workspace, then the row-major kernels.  Ragged and whole-tile sizes, padded pitches, non-zero R_in; bit-exact."""
     for idx, (M, N, K, pad) in enumerate([(70, 300, 37, 0), (129, 1030, 77, 5), (256, 512, 128, 0),
                                            (1, 1, 1, 0), (300, 70, 1000, 16), (512, 1024, 640, 0)]):
         g = np.random.Generator(np.random.PCG64(420 + idx))
@@ -444,8 +444,9 @@ def test_count_i8_transposed_operands(am, tA, tB):
 
 @pytest.mark.parametrize("tA,tB", [(False, False), (True, False), (False, True), (True, True)])
 def test_count_i8_repacked_operands(am, tA, tB):
-    """With the larger workspace the general entry point re-pitches operands whose rows are not
-    16-byte aligned and pads a K that is not a multiple of 64 with zeros: same counts, bit for bit.
+    """With the larger workspace the general entry point, where the tile kernels do not run (here K < 64;
+    with a tuned shape see test_a_tuned_shape_runs_on_copies_of_operands_it_cannot_take), re-pitches operands whose rows are
+    not 16-byte aligned and pads a K that is not a multiple of 64 with zeros: same counts, bit for bit.
     The workspace starts out poisoned, the operands sit at odd byte offsets inside larger buffers,
     and sizes span whole streamed tiles plus ragged edges."""
     for idx, (M, N, K, pad, off) in enumerate([(300, 777, 1000, 3, 1), (512, 1024, 640, 0, 0), (257, 513, 63, 5, 7),

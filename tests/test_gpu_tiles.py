@@ -182,7 +182,8 @@ I8_KERNELS = [
     ("i8_tile_256x256_bypass", False, False, 7644, 8236, 2388),
     ("i8_tile_256x256_registers", False, False, 6949, 1785, 65), ("i8_tile_256x256_registers", False, True, 1625, 7825, 69),
     ("i8_tile_256x256_registers_bypass", False, False, 8741, 8897, 69),
-    # whole aligned tiles: the streamed kernels that have shape ids
+    # whole aligned tiles: the streamed kernels that have shape ids (transposed operands copied first, from K = 4096 on)
+    ("mfma_i8_256x256_w16_dma4_persistent", False, False, 8192, 8192, 4096),
     ("mfma_i8_256x256_w16_dma4_persistent", False, False, 8192, 8192, 2048), ("mfma_i8_256x256_w16_dma4_persistent", False, True, 8192, 8192, 320),
     ("mfma_i8_128x256_dma3", False, True, 4096, 4352, 256),
 ]
@@ -196,7 +197,7 @@ def test_every_count_kernel_at_a_size_of_its_own(am, kernel, split, assign, M, N
     want = (A.float() @ B.float()).to(torch.int32)      # |sum| < 2^24: exact
     odd = 1 if "registers" in kernel else 0
     am.amulet_clear_selections()
-    for tA, tB in [(False, False)] if assign or kernel.startswith("mfma") else [(False, False), (True, False), (False, True), (True, True)]:
+    for tA, tB in [(False, False)] if assign or (kernel.startswith("mfma") and K < 4096) else [(False, False), (True, False), (False, True), (True, True)]:
         def stored(X, trans):
             X = X.t() if trans else X
             buf = torch.zeros(X.numel() + odd, dtype=torch.int8, device="cuda")
@@ -243,3 +244,36 @@ def test_every_predicate_tile_at_a_size_of_its_own(am, dtype, kernel, split, M, 
         ran = _kernel(am)
         assert ran[0] == kernel and (int(ran[2]) > 1) == split, ran
         assert np.array_equal(dR.cpu().numpy(), R_ref.astype(dtype)), (tA, tB)
+
+
+def test_a_tuned_shape_runs_on_copies_of_operands_it_cannot_take(am):
+    """With a shape selected that is not the built-in one, the general join count copies operands that are
+    transposed, unaligned or ragged into the workspace.  100 and 250 rows share a selection and have different
+    built-in shapes (at most 256 tiles of 128 x 256, and more), so whatever the tuner picks, one of the two
+    does not run the built-in choice."""
+    N, K, on_copies = 33000, 1000, 0
+    am.amulet_clear_selections()
+    try:
+        assert am.amulet_selected_shape(100, 100, N, K) != am.amulet_selected_shape(100, 250, N, K)
+        chosen = am.amulet_tune(am.AMULET_TASK_COUNT_I8, 250, N, K)
+        for M in (100, 250):
+            g = torch.Generator(device="cuda").manual_seed(M)
+            A = torch.randint(-3, 4, (M, K), dtype=torch.int8, device="cuda", generator=g)
+            B = torch.randint(-3, 4, (K, N), dtype=torch.int8, device="cuda", generator=g)
+            want = (A.float() @ B.float()).to(torch.int32) + 5
+            for tA, tB, off in [(False, False, 1), (True, False, 3), (False, True, 0), (True, True, 1)]:
+                def stored(X, trans):
+                    X = X.t() if trans else X
+                    view = torch.zeros(X.numel() + off, dtype=torch.int8, device="cuda")[off:].view(X.shape)
+                    view.copy_(X)
+                    return view
+                ws = torch.full((am.amulet_count_i8_repack_workspace_bytes(M, N, K),), 77, dtype=torch.int8, device="cuda")
+                R = torch.full((M, N), 5, dtype=torch.int32, device="cuda")
+                print("tuned join", chosen, M, tA, tB, off, flush=True)
+                am.amulet_count_i8_general(stored(A, tA), stored(B, tB), R, ws, trans_a=tA, trans_b=tB)
+                torch.cuda.synchronize()
+                on_copies += _kernel(am) == [am.amulet_shape_name(am.AMULET_TASK_COUNT_I8, chosen)]
+                assert torch.equal(R, want), (chosen, M, tA, tB)
+        assert on_copies >= 4
+    finally:
+        am.amulet_clear_selections()
