@@ -150,6 +150,7 @@ struct KernelNote {
     int tile, parts, kpart, kgroup;
     int ring, registers, bypass;   // (join count)
     int64_t rows;
+    int split;                     // (identity: rows of a tile of the bf16-piece kernel that stood in for the shape)
 };
 constexpr unsigned KERNEL_NOTES = 16;
 static thread_local KernelNote g_notes[KERNEL_NOTES];
@@ -157,7 +158,7 @@ static thread_local unsigned g_notes_made = 0;
 static KernelNote &new_note(int task, int f64, int shape, int64_t rows)
 {
     KernelNote &n = g_notes[g_notes_made++ % KERNEL_NOTES];
-    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, rows};
+    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, rows, 0};
     return n;
 }
 
@@ -228,6 +229,34 @@ static bool tile_runs(const Call &c)
     return c.lda <= (c.trans_a ? (MAX - 32) / BK : (MAX - BK) / 32) && c.ldb <= (c.trans_b ? (MAX - BK) / 64 : (MAX - 64) / BK);
 }
 
+// Identity: the bf16-piece kernel (identity_split.hip), with tiles of 128 or 256 rows, unless the fp32 kernels' estimate is
+// lower.  Estimates in ns per k, two workgroups to a compute unit: a round of 128 x 128 tiles 85 (51.5 with
+// at most one to a unit, a fifth less after whole rounds; from 65 on with more), of 256 x 128 tiles 155 (78.5, 120); the fp32 kernels 0.232 per 128 x 128 outputs (in their finest tiles, 64 x 64),
+// a quarter more where they neither fill the chip nor have a K long enough to split.  us, fp32 kernels / 128 / 256:
+// 1536^3 74 / 75 / 122, 1792^3 111 / 87 / 141, 2048^3 128 / 106 / 161, 2048^2 x 128 15.5 / 14.8 / 19, 2304^3 204 / 168 / 180, 3072^3 419 / 379 / 391,
+// 1700^2 x 8000 357 / 370 / 600, 4096^3 942 / 697 / 637, 4096^2 x 128 46.7 / 40.6 / 39.6, 6000 x 3000 x 2000 530 / 414 / 442, 8192^2 x 1024 967 / 743 / 674.
+// The 256-row tile's one set of accumulators is as precise as the fp32 kernels' where those do not split K, the
+// 128-row tile's two sets three times as precise (512 x 8192^2, split: 1.1e-6 / 5.5e-7 / 1.5e-6): the 256-row
+// tile only where they do not.
+static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
+{
+    if (c.K < 96 || !identity_split_runs(c.trans_a, c.trans_b, c.K, c.lda, c.ldb)) return false;
+    const int64_t n128 = (c.N + 127) / 128, small = ((c.M + 127) / 128) * n128, tall = ((c.M + 255) / 256) * n128;
+    const int64_t units = compute_units();
+    auto rounds = [&](int64_t tiles, double full, double half, double more) {
+        const int64_t rest = tiles % (2 * units), whole = tiles / (2 * units);
+        const double part = rest == 0 ? 0.0 : rest <= units ? (whole > 0 ? 0.8 : 1.0) * half : more + (full - more) * (double)(rest - units) / (double)units;
+        return full * (double)whole + part;
+    };
+    const double fp32 = 0.232 / 4.0 * (double)((c.M + 63) / 64) * (double)((c.N + 63) / 64) * (small < units && c.K < 3000 ? 1.25 : 1.0);
+    const double t128 = rounds(small, 85.0, 51.5, 65.0), t256 = rounds(tall, 155.0, 78.5, 120.0);
+    static const double rate3[3] = {0.92, 0.985, 1.0};
+    const bool fp32_splits = small <= 6 * units &&
+        choose_stream_split(xcd_grid((c.M + 127) / 128, n128) / 8, units / 8, c.K, 3, rate3) > 1;
+    plan.split = t256 < t128 && !fp32_splits ? 256 : 128;
+    return (plan.split == 256 ? t256 : t128) < fp32;
+}
+
 // fp32: the tile kernels, unless the 32 x 256 kernel's estimate is lower.  That kernel takes twice the
 // columns per LDS read and a scalar-register A, and so 7-9 % less time per product once it has rounds
 // enough; its tiles are 4 times larger (two to a compute unit and round, and a tenth
@@ -241,7 +270,9 @@ static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
 {
     // us per k of one of two resident workgroups (tile kernels), and of a 32 x 256 workgroup
     static const double tile_us[4] = {0.0, 0.125, 0.130, 0.0955}, large_us[4] = {0.0, 0.115, 0.121, 0.0895};
-    if (c.task == TASK_IDENTITY || !tile_runs<float>(c)) return false;
+    plan.split = 0;
+    if (c.task == TASK_IDENTITY) return identity_split_wanted(c, plan);
+    if (!tile_runs<float>(c)) return false;
     const ValuShapeDesc &d = kValuShapes[default_shape(c.task, c.M, c.N, c.K)];
     const int64_t range = wide_k_range((c.M + d.NW * d.TM - 1) / (d.NW * d.TM) * ((c.N + 255) / 256) * d.NW, c.K);
     plan = choose_tile_plan<float>(c.M, c.N, c.K, tile_us[c.task], (c.K + range - 1) / range);
@@ -257,7 +288,7 @@ static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
 // the built-in shape is what runs as it afterwards.
 static int run_mmlike(const MmlikeCall &c, int shape, void *stream, const TilePlan *tile)
 {
-    if (tile && tile_runs<float>(c)) {
+    if (tile && !tile->split && tile_runs<float>(c)) {
         g_last_hip_error = launch_tile_call<float>(c, *tile, (hipStream_t)stream);
         return g_last_hip_error == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
     }
@@ -271,9 +302,14 @@ static int run_mmlike(const MmlikeCall &c, int shape, void *stream, const TilePl
     a.kchunk = (int)c.K;
     a.tail_base = 0; a.tail_blocks = 0; a.tail_splits = 1; a.block_base = 0;
     a.force_splits = 0;
-    new_note(c.task, 0, shape, c.M);
+    KernelNote &note = new_note(c.task, 0, shape, c.M);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
+    if (tile && tile->split && identity_split_runs(c.trans_a, c.trans_b, c.K, c.lda, c.ldb)) {
+        note.split = tile->split;
+        g_last_hip_error = launch_identity_split(a, tile->split, s);
+        return g_last_hip_error == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
+    }
     switch (c.task) {
     case TASK_IDENTITY:
         e = shape >= IDENTITY_MFMA_SHAPE ? launch_identity_mfma(a, shape - IDENTITY_MFMA_SHAPE, s)
@@ -1586,7 +1622,8 @@ const char *amulet_recent_kernel(int back)
         const char *name = !n.f64 ? amulet_shape_name(n.task, n.shape)
                            : n.task != TASK_IDENTITY ? amulet_f64_shape_name(n.shape)
                            : n.shape % F64_TILES == 0 ? "mfma_f64_64x64_dma4" : "mfma_f64_128x128_dma4";
-        snprintf(text, sizeof(text), "%s rows %lld", name, rows);
+        if (n.split) snprintf(text, sizeof(text), "%s rows %lld bf16_pieces 3 tile_rows %d", name, rows, n.split);
+        else snprintf(text, sizeof(text), "%s rows %lld", name, rows);
     } else if (n.task == AMULET_TASK_COUNT_I8) {
         static const char *const tiles[4] = {"256x256", "128x256", "128x128", "64x64"};
         snprintf(text, sizeof(text), "i8_tile_%s%s%s%s rows %lld parts %d kpart %d kgroup %d", tiles[n.tile], n.ring ? "_ring6" : "",

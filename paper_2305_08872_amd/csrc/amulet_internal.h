@@ -366,6 +366,7 @@ struct TilePlan {
     int parts;          // workgroups per tile, each over kpart k (more than one: atomic adds into R)
     int kpart, kgroup;
     double us;          // the estimate it was chosen by
+    int split;          // identity task instead: rows of a tile of the bf16-piece kernel (identity_split.hip)
 };
 
 // The plan with the lowest estimated time.  A compute unit holds two workgroups (16 waves) and is
@@ -536,6 +537,9 @@ enum { IDENTITY_MFMA_SHAPE = VALU_DEPTHS * VALU_TILES, IDENTITY_MFMA_BIG_SHAPE =
 hipError_t launch_identity_mfma(const MmlikeArgs &a, int variant, hipStream_t s);
 // the streamed kernel (identity_mfma_dma.hip)
 bool identity_dma_eligible(const MmlikeArgs &a);
+// the identity task from bf16 pieces (identity_split.hip): tiles of tile_rows (128 or 256) x 128
+hipError_t launch_identity_split(const MmlikeArgs &a, int tile_rows, hipStream_t s);
+bool identity_split_runs(bool trans_a, bool trans_b, int64_t K, int64_t lda, int64_t ldb);
 constexpr int ID_SMALL_STAGES = 4;   // ring depth of the streamed 64 x 64 tiles (fp32 and fp64)
 hipError_t enqueue_identity_dma(const MmlikeArgs &a, int tile, int nstage, unsigned grid_x, unsigned grid_y, hipStream_t s);
 
