@@ -509,9 +509,10 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K);
  * through registers, _bypass: R around the caches); then " rows <rows of R>", and
  * for a tile kernel " parts <workgroups per tile, each over a range of K> kpart
  * <k of such a range> kgroup <k of it that a group of waves sums>"; and for the
- * identity task " bf16_pieces 3 tile_rows <128 or 256>" where the bf16-piece
- * kernel stood in for the shape (large problems; three bf16 pieces per value,
- * fp32 sums, no less precise than the fp32 matrix instruction).  The adaptive
+ * identity and boost tasks " bf16_pieces 3 tile_rows <32, 128 or 256>" where a
+ * kernel that forms plain sums on the bf16 matrix cores stood in for the shape
+ * (larger problems; three bf16 pieces per value, fp32 sums, no less precise than
+ * the fp32 kernels).  The adaptive
  * calls make one launch per trial and one for the rest.  Static storage of the
  * calling thread, until its next call of this function.
  */

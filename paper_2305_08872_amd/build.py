@@ -29,7 +29,7 @@ SOURCES = ["amulet_api.hip", "mmlike_valu_identity_col.hip"] + [
     "mmlike_valu_%s_%s.hip" % (task, form)
     for task in ("discount", "boost", "count_gt")
     for form in ("col", "row", "const", "elem")
-] + [
+] + ["mmlike_boost_%s.hip" % form for form in ("col", "row", "const", "elem")] + [
     "mmlike_tile_%s_%s.hip" % (elem, task)
     for elem in ("f64", "f32")
     for task in ("discount", "boost", "count_gt")

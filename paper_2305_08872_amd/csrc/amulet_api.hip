@@ -150,7 +150,7 @@ struct KernelNote {
     int tile, parts, kpart, kgroup;
     int ring, registers, bypass;   // (join count)
     int64_t rows;
-    int split;                     // (identity: rows of a tile of the bf16-piece kernel that stood in for the shape)
+    int pieces;                    // (rows of a tile of the kernel on the matrix cores that stood in for the shape)
 };
 constexpr unsigned KERNEL_NOTES = 16;
 static thread_local KernelNote g_notes[KERNEL_NOTES];
@@ -238,9 +238,27 @@ static bool tile_runs(const Call &c)
 // The 256-row tile's one set of accumulators is as precise as the fp32 kernels' where those do not split K, the
 // 128-row tile's two sets three times as precise (512 x 8192^2, split: 1.1e-6 / 5.5e-7 / 1.5e-6): the 256-row
 // tile only where they do not.
+static bool pieces_run(const MmlikeCall &c)
+{
+    if (c.task == TASK_IDENTITY) return identity_split_runs(c.trans_a, c.trans_b, c.K, c.lda, c.ldb);
+    return c.task == TASK_BOOST && (c.trans_a || !pitch_collides(c.lda, 4));
+}
+// us of BOOST with its plain sum on the matrix cores: a pair of workgroups on a compute unit takes 0.185 us per k, one alone
+// 0.104 (a little more here for launch and write-back).  It is ahead of the wide kernel at every size and layout that both run (1.1 to 1.4 times), and of the tile
+// kernels from some 768^3 on, us, tile kernel / here: 512^3 15.1 / 28.0, 768^3 42.1 / 42.9, 1024^3 82 / 62, 1003 x 1501 x 777 96 /
+// 78, 256 x 4096^2 313 / 221, 1536^3 270 / 199, 4096 x 512 x 8192 1232 / 863.
+static double boost_pieces_us(const MmlikeCall &c)
+{
+    const int64_t tiles = ((c.M + 31) / 32) * ((c.N + 255) / 256), range = wide_k_range(tiles * 8, c.K), parts = (c.K + range - 1) / range;
+    const int64_t W = tiles * parts, rest = W % 512;
+    double us = 6.0 + 1.5 * (double)W / 256.0;
+    if (parts > 1) us += (double)range * (0.19 * (double)(W / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.11 : 0.175)) + (double)c.M * (double)c.N * (double)parts / 1.6e6;
+    else us += (double)c.K * (W <= 256 ? 0.11 : 0.0925 * ((double)W / 256.0 + (rest == 0 ? 0.1 : 0.35)));
+    return us;
+}
 static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
 {
-    if (c.K < 96 || !identity_split_runs(c.trans_a, c.trans_b, c.K, c.lda, c.ldb)) return false;
+    if (c.K < 96 || !pieces_run(c)) return false;
     const int64_t n128 = (c.N + 127) / 128, small = ((c.M + 127) / 128) * n128, tall = ((c.M + 255) / 256) * n128;
     const int64_t units = compute_units();
     auto rounds = [&](int64_t tiles, double full, double half, double more) {
@@ -253,8 +271,8 @@ static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
     static const double rate3[3] = {0.92, 0.985, 1.0};
     const bool fp32_splits = small <= 6 * units &&
         choose_stream_split(xcd_grid((c.M + 127) / 128, n128) / 8, units / 8, c.K, 3, rate3) > 1;
-    plan.split = t256 < t128 && !fp32_splits ? 256 : 128;
-    return (plan.split == 256 ? t256 : t128) < fp32;
+    plan.pieces = t256 < t128 && !fp32_splits ? 256 : 128;
+    return (plan.pieces == 256 ? t256 : t128) < fp32;
 }
 
 // fp32: the tile kernels, unless the 32 x 256 kernel's estimate is lower.  That kernel takes twice the
@@ -270,12 +288,21 @@ static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
 {
     // us per k of one of two resident workgroups (tile kernels), and of a 32 x 256 workgroup
     static const double tile_us[4] = {0.0, 0.125, 0.130, 0.0955}, large_us[4] = {0.0, 0.115, 0.121, 0.0895};
-    plan.split = 0;
+    plan.pieces = 0;
     if (c.task == TASK_IDENTITY) return identity_split_wanted(c, plan);
-    if (!tile_runs<float>(c)) return false;
+    double pieces_us = -1.0;
+    if (c.task == TASK_BOOST && pieces_run(c)) {
+        pieces_us = boost_pieces_us(c);
+        plan.pieces = 32;
+    }
+    if (!tile_runs<float>(c)) return plan.pieces != 0;
     const ValuShapeDesc &d = kValuShapes[default_shape(c.task, c.M, c.N, c.K)];
     const int64_t range = wide_k_range((c.M + d.NW * d.TM - 1) / (d.NW * d.TM) * ((c.N + 255) / 256) * d.NW, c.K);
     plan = choose_tile_plan<float>(c.M, c.N, c.K, tile_us[c.task], (c.K + range - 1) / range);
+    if (pieces_us >= 0.0) {
+        plan.pieces = pieces_us < 1.04 * plan.us ? 32 : 0;
+        return true;
+    }
     const int64_t large = ((c.M + 31) / 32) * ((c.N + 255) / 256);
     if (large < 256) return true;
     const double rounds = (double)large / 256.0, part_round = large % 512 == 0 ? 0.1 : 0.35;
@@ -288,7 +315,7 @@ static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
 // the built-in shape is what runs as it afterwards.
 static int run_mmlike(const MmlikeCall &c, int shape, void *stream, const TilePlan *tile)
 {
-    if (tile && !tile->split && tile_runs<float>(c)) {
+    if (tile && !tile->pieces && tile_runs<float>(c)) {
         g_last_hip_error = launch_tile_call<float>(c, *tile, (hipStream_t)stream);
         return g_last_hip_error == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
     }
@@ -305,10 +332,15 @@ static int run_mmlike(const MmlikeCall &c, int shape, void *stream, const TilePl
     KernelNote &note = new_note(c.task, 0, shape, c.M);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
-    if (tile && tile->split && identity_split_runs(c.trans_a, c.trans_b, c.K, c.lda, c.ldb)) {
-        note.split = tile->split;
-        g_last_hip_error = launch_identity_split(a, tile->split, s);
-        return g_last_hip_error == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
+    if (tile && tile->pieces && pieces_run(c)) {
+        note.pieces = tile->pieces;
+        if (c.task == TASK_IDENTITY) e = launch_identity_split(a, tile->pieces, s);
+        else if (c.thres_form == THRES_COL) e = launch_mmlike_boost<THRES_COL>(a, s);
+        else if (c.thres_form == THRES_ROW) e = launch_mmlike_boost<THRES_ROW>(a, s);
+        else if (c.thres_form == THRES_CONST) e = launch_mmlike_boost<THRES_CONST>(a, s);
+        else e = launch_mmlike_boost<THRES_ELEM>(a, s);
+        g_last_hip_error = e;
+        return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
     }
     switch (c.task) {
     case TASK_IDENTITY:
@@ -1622,7 +1654,7 @@ const char *amulet_recent_kernel(int back)
         const char *name = !n.f64 ? amulet_shape_name(n.task, n.shape)
                            : n.task != TASK_IDENTITY ? amulet_f64_shape_name(n.shape)
                            : n.shape % F64_TILES == 0 ? "mfma_f64_64x64_dma4" : "mfma_f64_128x128_dma4";
-        if (n.split) snprintf(text, sizeof(text), "%s rows %lld bf16_pieces 3 tile_rows %d", name, rows, n.split);
+        if (n.pieces) snprintf(text, sizeof(text), "%s rows %lld bf16_pieces 3 tile_rows %d", name, rows, n.pieces);
         else snprintf(text, sizeof(text), "%s rows %lld", name, rows);
     } else if (n.task == AMULET_TASK_COUNT_I8) {
         static const char *const tiles[4] = {"256x256", "128x256", "128x128", "64x64"};

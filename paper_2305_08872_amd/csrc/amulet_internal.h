@@ -366,7 +366,9 @@ struct TilePlan {
     int parts;          // workgroups per tile, each over kpart k (more than one: atomic adds into R)
     int kpart, kgroup;
     double us;          // the estimate it was chosen by
-    int split;          // identity task instead: rows of a tile of the bf16-piece kernel (identity_split.hip)
+    // instead of a tile kernel, a kernel that shares its sums with the bf16 matrix cores: the identity task's
+    // (identity_split.hip), rows of its tile; BOOST's (mmlike_boost_impl.h), 32; 0: neither
+    int pieces;
 };
 
 // The plan with the lowest estimated time.  A compute unit holds two workgroups (16 waves) and is
@@ -390,7 +392,7 @@ inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_
 {
     constexpr int V = 16 / (int)sizeof(T);
     auto up = [](int64_t n, int64_t to) { return (n + to - 1) / to * to; };
-    TilePlan best = {0, 0, 0, 0, 0.0};
+    TilePlan best = {0, 0, 0, 0, 0.0, 0};
     for (int wide = 0; wide < 2; ++wide) {
         const int rows = wide ? 32 : 16, groups = wide ? 4 : 8;
         const int64_t grid = xcd_grid((M + rows - 1) / rows, (N + 63) / 64);
@@ -542,6 +544,10 @@ hipError_t launch_identity_split(const MmlikeArgs &a, int tile_rows, hipStream_t
 bool identity_split_runs(bool trans_a, bool trans_b, int64_t K, int64_t lda, int64_t ldb);
 constexpr int ID_SMALL_STAGES = 4;   // ring depth of the streamed 64 x 64 tiles (fp32 and fp64)
 hipError_t enqueue_identity_dma(const MmlikeArgs &a, int tile, int nstage, unsigned grid_x, unsigned grid_y, hipStream_t s);
+
+// BOOST with its plain sum on the matrix cores (mmlike_boost_impl.h)
+template <int TF>
+hipError_t launch_mmlike_boost(const MmlikeArgs &a, hipStream_t s);
 
 template <int TASK, int TF>
 hipError_t launch_mmlike_valu_task(int shape, const MmlikeArgs &a, hipStream_t s);

@@ -1,0 +1,118 @@
+"""GPU parity of BOOST with its plain sum on the matrix cores: remainders of tiles and of K, K in parts, every threshold
+form and layout, and the values that send a workgroup to its second way of forming a tile."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+FORMS = ("col", "row", "const", "elem")
+
+
+@pytest.fixture(scope="module")
+def am():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2305_08872_amd as am
+    am.load_library()
+    am.amulet_clear_selections()
+    return am
+
+
+def run(am, A, B, th, R, form, tA, tB):
+    am.amulet_mmlike_f32_general(am.AMULET_BOOST, A, B, th, None, R, thres_form=FORMS.index(form), trans_a=tA, trans_b=tB)
+    kernel = am.amulet_recent_kernel()
+    torch.cuda.synchronize()
+    assert "bf16_pieces" in kernel, kernel
+
+
+def check(R, R0, A, B, th, form, tA, tB, bound):
+    """Sampled rows (the first and last tile's, some between) against 64 bits: |error| within `bound` of the sum of magnitudes."""
+    a, b = (A.T if tA else A), (B.T if tB else B).double()
+    M = a.shape[0]
+    rows = sorted(set(list(range(0, M, max(1, M // 23))) + [M - 1, M - 2, 31, 32]) & set(range(M)))
+    for i in rows:
+        t = {"col": lambda: th, "row": lambda: th[i], "const": lambda: th[0], "elem": lambda: th[i]}[form]().double()
+        p = a[i].double()[:, None] * b
+        term = p + (p - t).clamp_min(0)
+        want, mag = term.sum(0) + R0, term.abs().sum(0)
+        err = (R[i].double() - want).abs() - 2.0 ** -23 * want.abs() - 2.0 ** -149
+        assert bool((err <= bound * mag).all()), (i, float((err / mag.clamp_min(1e-300)).max()))
+
+
+def make(g, M, N, K, form, tA, tB, pad=0):
+    def normal(r, c):
+        return torch.empty(r, c + pad, device="cuda").normal_(generator=g)[:, :c]
+    A, B = normal(*((K, M) if tA else (M, K))), normal(*((N, K) if tB else (K, N)))
+    shape = {"col": (N,), "row": (M,), "const": (1,), "elem": (M, N)}[form]
+    return A, B, torch.empty(*shape, device="cuda").normal_(generator=g)
+
+
+# whole tiles; a part of K per workgroup and its remainders 1 .. 15; rows and columns one past and one short of a tile; an unaligned pitch
+SIZES = [(2048, 2048, 64, 0), (2048, 2048, 79, 0), (2049, 2047, 65, 1), (1024, 1024, 1031, 3), (1000, 1300, 1024, 0), (2079, 1793, 527, 2)]
+
+
+@pytest.mark.parametrize("tA,tB", [(False, False), (True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("form", FORMS)
+def test_remainders_forms_and_layouts(am, form, tA, tB):
+    for M, N, K, pad in SIZES:
+        g = torch.Generator(device="cuda").manual_seed(M + N + K)
+        A, B, th = make(g, M, N, K, form, tA, tB, pad)
+        R = torch.full((M, N + pad), 0.25, device="cuda")[:, :N]
+        print("boost pieces", form, tA, tB, M, N, K, pad, flush=True)
+        run(am, A, B, th, R, form, tA, tB)
+        # partial sums over 64 k: 64 + 24 roundings of at most half an ulp each, then one per part
+        check(R, 0.25, A, B, th, form, tA, tB, 100 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("tA,tB", [(False, False), (True, True)])
+@pytest.mark.parametrize("what", ["tiny a", "tiny b", "large sums", "thresholds", "subnormal"])
+def test_values_of_the_second_way(am, what, tA, tB):
+    M, N, K = 1024, 1100, 1029
+    for form in FORMS:
+        g = torch.Generator(device="cuda").manual_seed(3)
+        A, B, th = make(g, M, N, K, form, tA, tB)
+        a, b = (A.T if tA else A), (B.T if tB else B)
+        if what == "tiny a":
+            a[5] *= 2.0 ** -60
+            a[31, 3] = 2.0 ** -120
+            a[31, 4:] = 0
+        elif what == "tiny b":
+            b[7, 40] = 2.0 ** -100
+            b[:7, 40] = 0
+            b[8:, 40] = 0
+            a[9] *= 2.0 ** 90
+        elif what == "large sums":
+            a[33] *= 2.0 ** 40
+            b[:, 300] *= 2.0 ** 30
+            a[64] *= 2.0 ** 100
+        elif what == "thresholds":
+            special = torch.tensor([0.0, -0.0, 1e-30, -1e-30, float("inf"), -1e30, 2.0 ** 60, 1e-45], device="cuda")
+            th.view(-1)[:8] = special[: min(8, th.numel())] if th.numel() >= 8 else special[2:3]
+        else:
+            A *= 2.0 ** -63
+            B *= 2.0 ** -64
+            th *= 2.0 ** -127
+        R = torch.zeros(M, N, device="cuda")
+        print("boost pieces special", what, form, tA, tB, flush=True)
+        run(am, A, B, th, R, form, tA, tB)
+        # (subnormal: a product of some 2^-128 is rounded to 2^-149, in each of the three places it is used)
+        check(R, 0.0, A, B, th, form, tA, tB, 3 * 2.0 ** -20 if what == "subnormal" else 1e-5)
+
+
+def test_infinities_and_nan_stay_with_their_rows(am):
+    M, N, K = 1024, 1024, 1024
+    g = torch.Generator(device="cuda").manual_seed(4)
+    A, B, th = make(g, M, N, K, "col", False, False)
+    B[0] = 1.0
+    A[3, 0], A[70, 0], A[100, 0] = float("inf"), float("-inf"), float("nan")
+    R = torch.zeros(M, N, device="cuda")
+    run(am, A, B, th, R, "col", False, False)
+    assert bool((R[3] == float("inf")).all()) and bool((R[70] == float("-inf")).all()) and bool(R[100].isnan().all())
+    rest = torch.ones(M, dtype=torch.bool, device="cuda")
+    rest[[3, 70, 100]] = False
+    assert bool(R[rest].isfinite().all())
+    th[7] = float("-inf")         # always triggers
+    A[3, 0] = A[70, 0] = A[100, 0] = 1.0
+    R.zero_()
+    run(am, A, B, th, R, "col", False, False)
+    assert bool((R[:, 7] == float("inf")).all()) and bool(R[:, :7].isfinite().all()) and bool(R[:, 8:].isfinite().all())
