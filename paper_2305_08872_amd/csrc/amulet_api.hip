@@ -125,8 +125,10 @@ static int default_shape(int task, int64_t M, int64_t N, int64_t K)
     // ... or, with fewer tiles, when K is long (from 8192 on) and the launcher's K split makes up
     // the number (4096 x 512 x 8192: 31.0 against 29.2 TFLOP/s, 4096 x 512 x 32768: 31.3 against
     // 26.6; at K <= 4096 the 4-wave tile stays ahead, 1536^2 x 4096: 28.5 against 27.2)
+    // (the count, whose stage of B is 32 k deep in the 8-wave tile only: from 128 tiles on; us, 4 waves / 8, 1536^3 154 / 145,
+    // 1280^3 104 / 95, 256 x 4096^2 172 / 151, 1500 x 2500 x 700 119 / 107, thresholds per output 158 / 142; 896^3 41 / 46)
     const int64_t tiles32 = ((M + 31) / 32) * ((N + 255) / 256);
-    if (tiles32 >= 512) return VALU_TILES + 1;
+    if (tiles32 >= (task == TASK_COUNT_GT ? 128 : 512)) return VALU_TILES + 1;
     if (tiles32 >= 128 && K >= 8192) return VALU_TILES + 1;
     return VALU_TILES + 0;
 }
@@ -256,6 +258,23 @@ static double boost_pieces_us(const MmlikeCall &c)
     else us += (double)c.K * (W <= 256 ? 0.11 : 0.0925 * ((double)W / 256.0 + (rest == 0 ? 0.1 : 0.35)));
     return us;
 }
+// us of the count by rounding (count_rounding.h) in the wide kernel, with the K split it chooses: a pair of workgroups on a
+// compute unit takes 0.135 us per k, one alone 0.08; with A transposed 1.2 to 1.3 times that, with thresholds that face rows
+// 1.15.  From 128 tiles on, us, tile kernel / here: 1003 x 1501 x 777 65 / 61, 1024^3 56.7 / 49.4 (transposed A 56 / 56), 1536^3 182 / 145
+// (179 / 177), 256 x 4096^2 208 / 151, 4096 x 512 x 1024 107 / 82, 3262 x 288 x 5014 259 / 346; thresholds that the rounding leaves to
+// the comparison 1024^3 56 / 60, 1536^3 180 / 188, 256 x 4096^2 208 / 200.  Below, those are up to 17 % slower here
+// (768^3 31.9 / 37.5; by rounding 29.5), and nobody but the device knows which thresholds they are.
+static double count_wide_us(const MmlikeCall &c)
+{
+    const int64_t tiles = ((c.M + 31) / 32) * ((c.N + 255) / 256), range = wide_k_range(tiles * 8, c.K), parts = (c.K + range - 1) / range;
+    if (tiles < 128) return 1e30;
+    const int64_t W = tiles * parts, rest = W % 512;
+    const double more = (c.trans_a ? 1.3 : 1.0) * (c.thres_form == THRES_ROW ? 1.15 : 1.0);
+    double us = 6.0 + 1.5 * (double)W / 256.0;
+    if (parts > 1) us += more * (double)range * (0.135 * (double)(W / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.08 : 0.125)) + (double)c.M * (double)c.N * (double)parts / 1.6e6;
+    else us += more * (double)c.K * (W <= 256 ? 0.08 : 0.0675 * ((double)W / 256.0 + (rest == 0 ? 0.1 : 0.35)));
+    return us;
+}
 static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
 {
     if (c.K < 96 || !pieces_run(c)) return false;
@@ -303,6 +322,7 @@ static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
         plan.pieces = pieces_us < 1.04 * plan.us ? 32 : 0;
         return true;
     }
+    if (c.task == TASK_COUNT_GT && c.thres_form != THRES_ELEM) return plan.us <= 1.03 * count_wide_us(c);
     const int64_t large = ((c.M + 31) / 32) * ((c.N + 255) / 256);
     if (large < 256) return true;
     const double rounds = (double)large / 256.0, part_round = large % 512 == 0 ? 0.1 : 0.35;

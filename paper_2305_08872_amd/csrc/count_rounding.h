@@ -1,0 +1,65 @@
+// The fp32 count's predicate in two operations that need neither the rounded product nor its comparison:
+//
+//     t   = clamp(fma(a, b g, -th g), 0, 1)       g = 1 / (distance from th to the next float above)
+//     sum = fma(t, s, sum)                        sum in [2^23, 2^24), where it has no fraction
+//
+// and sum - 2^23 is the number of products with RN(a b) > th.  Why this is exact:
+//   * g is a power of two, so b g is b with another exponent and th g is a whole number of at most 24 bits;
+//     the first fma's t is (a b - th) in units of that distance.
+//   * RN(a b) > th exactly when a b lies more than half the distance above th, or half of it and th is odd (its
+//     last bit is set: the tie goes to the even neighbour above).  So the predicate is t against 1/2.
+//   * a b is a product of two numbers of 24 bits, and for 0 < t < 1 it lies between th and its neighbour: it is a multiple
+//     of 2^-47 of its power of two, t of 2^-24, which fp32 holds exactly from 1/4 on.
+//   * the second fma rounds sum + t s to a whole number, once.  With s = 1 - 2^-24 (th even) t = 1/2 rounds down and
+//     1/2 + 2^-24, the next one, up; with s = 1 + 2^-23 (th odd) t = 1/2 rounds up and 1/2 - 2^-24 down; 0 and 1
+//     add 0 and 1.
+// Below a negative power of two the next float is half as far as below its neighbours: g is taken from there.
+// (NaN products: the clamp makes them 0, as not above.  An infinite threshold has g = 1.)
+//
+// It holds for thresholds of magnitudes 2^-40 to 2^24 (g >= 1: no b g loses bits) as long as no b g overflows, which the
+// kernel watches (a b would have to be 2^105 thresholds away).  Tiles with other thresholds -- zero, smaller, larger, NaN
+// -- take the comparison.  (Zero with g = 2^64 needs every positive product to be at least 2^-64: with the smallest operands
+// looked for beside the staging 4096^3 took 2770 us, by comparison 2970, and the loop without that 2520 for 2340.)
+//
+// Bound: vector-ALU issue, 4.7 clocks per 64 products in a register-only loop (a in a scalar register) where multiply, subtract and the
+// sign bit shifted in take 6.5.  The wide kernel, us before / after: 4096^3 2970 / 2350, thresholds that face rows 2945 / 2600, one 2950 / 2270,
+// A transposed 3820 / 2960, B transposed 3020 / 2330; 2048^3 405 / 335.  Not for thresholds per output (a factor each), and not in the
+// tile kernels: those read both operands from LDS and are bound there (768^3 31.6 / 28.8 us), and looking at
+// the thresholds costs their short calls 0.4 us (256^3 5.0 / 5.4).
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#ifndef AMULET_COUNT_ROUNDING_H
+#define AMULET_COUNT_ROUNDING_H
+
+namespace amulet {
+
+constexpr float COUNT_ROUNDING_ZERO = 0x1p23f;
+constexpr int COUNT_ROUNDING_K = (1 << 23) - 1;      // products a sum holds
+
+// g, s and -th g of a threshold; whether it has them
+__device__ __forceinline__ bool count_rounding(float th, float &g, float &s, float &neg)
+{
+    const uint32_t bits = __builtin_bit_cast(uint32_t, th);
+    const int exponent = (int)((bits >> 23) & 255) - 127;
+    const int e = exponent - ((bits & 0x807fffffu) == 0x80000000u ? 1 : 0);
+    const bool inf = (bits & 0x7fffffffu) == 0x7f800000u, in_range = exponent >= -40 && exponent < 24;
+    g = in_range ? __builtin_bit_cast(float, (uint32_t)(150 - e) << 23) : 1.0f;
+    s = (bits & 1u) ? 0x1.000002p0f : 0x1.fffffep-1f;
+    neg = -th * g;
+    return inf || in_range;
+}
+
+// four products of a with b, one of which carries g
+__device__ __forceinline__ void count_by_rounding4(float a, const float *b, const float *neg, const float *s, float *sum)
+{
+    float t[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) t[c] = __builtin_amdgcn_fmed3f(__builtin_fmaf(a, b[c], neg[c]), 0.0f, 1.0f);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sum[c] = __builtin_fmaf(t[c], s[c], sum[c]);
+}
+
+}  // namespace amulet
+#endif

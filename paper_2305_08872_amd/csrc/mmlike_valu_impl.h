@@ -29,8 +29,10 @@
 // sequence "mul, gtcmp, mul, masksub, add" (Sec. 4.3.1) minus one.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "amulet_internal.h"
+#include "count_rounding.h"
 
 #ifndef AMULET_MMLIKE_VALU_IMPL_H
 #define AMULET_MMLIKE_VALU_IMPL_H
@@ -102,6 +104,7 @@ __device__ __forceinline__ void fold4(float a, f4 b, const float *th, const floa
         // alignbit, and one bit count per 32 products -- where shifting it down and adding it
         // took one and a half (register-only loops, 4 waves per SIMD: 8.3 against 6.5 clocks per 64
         // products; compare and add with carry 9.9).  The kernel at 4096^3: 38.9 -> 42.7 TFLOP/s.
+        // (Thresholds per output, and those that counting by rounding leaves to it.)
         float p[4], d[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) p[c] = a * b[c];          // one RN multiply (contraction is off)
@@ -131,6 +134,9 @@ mmlike_valu_kernel(const MmlikeArgs args)
     // Forms that hold more than their loop needs: A's tile, or a threshold per output.  (The others fit 128 registers as
     // they are, and a transposed A's scalar loads are sensitive to any change of schedule: 6 % either way.)
     constexpr bool TIGHT = ALDS || (TF == THRES_ELEM && (TRANS == 0 || (TRANS == 2 && TASK == TASK_COUNT_GT)));
+    // the count by rounding (count_rounding.h), where a threshold faces a row or a column; the factor goes on B as it is
+    // staged, or on A where thresholds face rows
+    constexpr bool ROUNDED = TASK == TASK_COUNT_GT && TF != THRES_ELEM && TM == 4 && NG == 1;
     typedef typename AccT<TASK>::type acc_t;
     static_assert(KA == 4 && TM % 4 == 0, "a transposed A is fetched as 4 rows x 4 k blocks");
     constexpr int BN = 256 * NG;           // tile columns
@@ -280,6 +286,25 @@ mmlike_valu_kernel(const MmlikeArgs args)
         }
     };
 
+    float sum[ROUNDED ? TM : 1][4], gain[4], sway[4], most = 0.0f, bt_gain = 1.0f;
+    bool rounded = false;
+    if constexpr (ROUNDED) {
+        bool every = K <= COUNT_ROUNDING_K;
+        float neg[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) every = count_rounding(TF == THRES_COL ? th_col[i] : TF == THRES_ROW ? th_row[i] : th_const, gain[i], sway[i], neg[i]) && every;
+        // (the workgroup's waves agree: by themselves where they face the same thresholds)
+        rounded = __builtin_amdgcn_ballot_w64(!every) == 0;
+        if constexpr (TF == THRES_ROW) rounded = __syncthreads_or(!rounded) == 0;
+        if (rounded) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) (TF == THRES_COL ? th_col[i] : TF == THRES_ROW ? th_row[i] : th_const) = neg[i];
+        }
+#pragma unroll
+        for (int r = 0; r < TM; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum[r][c] = COUNT_ROUNDING_ZERO;
+    }
     acc_t part[TM][NG * 4];
     typename AccT<TASK>::main_type mainacc[TM][NG * 4];
 #pragma unroll
@@ -311,6 +336,12 @@ mmlike_valu_kernel(const MmlikeArgs args)
     const int tcol = threadIdx.x % BN;
     const int tk = (threadIdx.x / BN) * KPT;
     const float *btsrc = Bg + (int64_t)col_at(tcol, own_dummy) * args.ldb + tk;
+    if constexpr (ROUNDED && TF == THRES_COL && transB) {     // (row-major B: a thread stages the columns it computes)
+        float sw, ng;
+        count_rounding(args.thres[col_at(tcol, own_dummy)], bt_gain, sw, ng);
+    } else if constexpr (ROUNDED) {
+        bt_gain = gain[0];
+    }
     // A tile staging (ALDS): thread t < A_F4 stages float4 slot (row t / (BK / 4), k quad t % (BK / 4))
     const int a_sr = threadIdx.x / (BK / 4), a_sq = (threadIdx.x % (BK / 4)) * 4;
     const float *asrc = nullptr;
@@ -384,7 +415,16 @@ mmlike_valu_kernel(const MmlikeArgs args)
     };
     float *const bdst = &Bs[0][srow][(threadIdx.x % F4_PER_ROW) * 4];
     float *const btdst = &Bs[0][tk][tcol];
-    auto store_tile = [&](int buf) {
+    auto store_tile = [&](int buf, auto by_rounding) {
+        if constexpr (decltype(by_rounding)::value && TF != THRES_ROW) {
+#pragma unroll
+            for (int it = 0; it < LOADS; ++it) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) stage[it][e] *= transB ? bt_gain : gain[e];
+                most = __builtin_fmaxf(most, __builtin_fmaxf(__builtin_fabsf(stage[it][0]), __builtin_fabsf(stage[it][1])));
+                most = __builtin_fmaxf(most, __builtin_fmaxf(__builtin_fabsf(stage[it][2]), __builtin_fabsf(stage[it][3])));
+            }
+        }
         if constexpr (ALDS) {
             if (threadIdx.x < A_F4) *(f4 *)&Asl[buf][a_sr][a_sq] = a_stage;
         }
@@ -454,14 +494,37 @@ mmlike_valu_kernel(const MmlikeArgs args)
                     a_next[kk * (TM / 4) + r / 4][r % 4] = As[(int64_t)(kn + kk) * args.lda + trow(r)];
         }
     };
-    load_tile(full_tiles > 0 ? BK : tail);
-    store_tile(0);
-    if (!ALDS && full_tiles > 0) fetch_a(0, 0);
-    __syncthreads();
-
+    // one k of the wave's rows by rounding
+    auto round_k = [&](const float (&a)[TM], const f4 &b) {
+        float as[TM];
+        const float bs[4] = {b[0], b[1], b[2], b[3]};
+#pragma unroll
+        for (int r = 0; r < TM; ++r) as[r] = TF == THRES_ROW ? a[r] * gain[r] : a[r];
+        if constexpr (TF == THRES_ROW) {
+#pragma unroll
+            for (int r = 0; r < TM; r += 2) most = __builtin_fmaxf(most, __builtin_fmaxf(__builtin_fabsf(as[r]), __builtin_fabsf(as[r + 1])));
+        }
+#pragma unroll
+        for (int r = 0; r < TM; ++r) {
+            float t4[4], s4[4];
+            thres4(r, 0, t4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) s4[c] = sway[TF == THRES_ROW ? r : TF == THRES_COL ? c : 0];
+            count_by_rounding4(as[r], bs, t4, s4, sum[r]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
     // The arithmetic of one chunk: KA k of the wave's TM rows against a lane's 4 NG columns.
-    auto compute_chunk = [&](const av_t (&a)[TM], const f4 (&b)[KA][NG]) {
-        if constexpr (PIPE) {
+    auto compute_chunk = [&](const av_t (&a)[TM], const f4 (&b)[KA][NG], auto by_rounding) {
+        if constexpr (decltype(by_rounding)::value) {
+#pragma unroll
+            for (int kk = 0; kk < KA; ++kk) {
+                float ak[TM];
+#pragma unroll
+                for (int r = 0; r < TM; ++r) ak[r] = a_of(a, r, kk);
+                round_k(ak, b[kk][0]);
+            }
+        } else if constexpr (PIPE) {
             // The whole chunk as one software pipeline: compare i, multiply i + 1, FMA
             // i - 1, select i.  Every compare writes the same lane-mask register (vcc,
             // the 32-bit encodings) and its select reads it two instructions later, with
@@ -520,111 +583,46 @@ mmlike_valu_kernel(const MmlikeArgs args)
     // with too few waves to fill both slots (measured: +5 % when a launch is one or two rounds
     // of workgroups, +0-2 % at sixteen).
     const int prio_phase = block >> 8;
-    for (int t = 0; t < n_tiles; ++t) {
-        const int buf = t & 1;
-        const int k0 = t * BK;
-        switch ((t + prio_phase) & 3) {
-        case 0: __builtin_amdgcn_s_setprio(0); break;
-        case 1: __builtin_amdgcn_s_setprio(1); break;
-        case 2: __builtin_amdgcn_s_setprio(2); break;
-        default: __builtin_amdgcn_s_setprio(3); break;
-        }
-        if (t + 1 < n_tiles)
-            load_tile((t + 1 < full_tiles) ? BK : tail);
-        const float *bs = bs_lane + buf * (BK * BN);
-
-        if constexpr (BPRE) {
-          if (t < full_tiles) {
-            // The B values of a chunk are read from LDS while the chunk before it computes: the
-            // wave waits for LDS once per tile (its first chunk) instead of once per chunk.
-            f4 bq[2][KA][NG];
+    if constexpr (ROUNDED) {
+        auto k_loop = [&](auto by_rounding) {
+#include "mmlike_valu_k_loop.inc"
+        };
+        if (rounded) {
+            k_loop(std::true_type());
 #pragma unroll
-            for (int kk = 0; kk < KA; ++kk)
+            for (int r = 0; r < TM; ++r)
 #pragma unroll
-                for (int g = 0; g < NG; ++g) bq[0][kk][g] = *(const f4 *)(bs + kk * BN + g * 256);
+                for (int c = 0; c < 4; ++c) mainacc[r][c] = (int)(sum[r][c] - COUNT_ROUNDING_ZERO);
+            // an operand left fp32 with its factor, in some wave of the workgroup: all of the tile again, by comparison
+            int *const out = (int *)&Bs[1][0][0];
+            if (lane == 0) out[wave] = __builtin_amdgcn_ballot_w64(most == __builtin_inff()) != 0;
+            __syncthreads();
+            int any = 0;
 #pragma unroll
-            for (int c = 0; c < BK / KA; ++c) {
-                const int kc = c * KA;
-                av_t a[TM];
+            for (int w = 0; w < NW; ++w) any |= out[w];
+            rounded = __builtin_amdgcn_readfirstlane(any) == 0;
+            if (!rounded) {
+                __syncthreads();
 #pragma unroll
-                for (int r = 0; r < TM; ++r) a[r] = a_next[r];
-                __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): this chunk's B and A values have landed
-                __builtin_amdgcn_sched_barrier(0);
-                if (c + 1 < BK / KA) {
-#pragma unroll
-                    for (int kk = 0; kk < KA; ++kk)
-#pragma unroll
-                        for (int g = 0; g < NG; ++g) bq[(c + 1) & 1][kk][g] = *(const f4 *)(bs + (kc + KA + kk) * BN + g * 256);
+                for (int i = 0; i < 4; ++i) {
+                    if constexpr (TF == THRES_COL) th_col[i] = held(args.thres[col_at(lane * 4 + i, own_dummy)]);
+                    else if constexpr (TF == THRES_ROW) th_row[i] = held(args.thres[rowc(i)]);
+                    else th_const = held(args.thres[0]);
                 }
-                // the next chunk's A values: inside this (full) tile, or the next tile's first chunk
-                // (past the last full chunk: this one again)
-                if (c + 1 < BK / KA) fetch_a(k0, kc + KA);
-                else fetch_a(k0, k0 + BK + KA <= K ? BK : BK - KA);
-                __builtin_amdgcn_sched_barrier(0);
-                compute_chunk(a, bq[c & 1]);
-            }
-          }
-        }
-        if (!BPRE && t < full_tiles) {
-#pragma unroll 1
-            for (int kc = 0; kc < BK; kc += KA) {
-                // B values of the whole chunk first, so that one wait covers them ...
-                f4 b[KA][NG];
-#pragma unroll
-                for (int kk = 0; kk < KA; ++kk)
-#pragma unroll
-                    for (int g = 0; g < NG; ++g)
-                        b[kk][g] = *(const f4 *)(bs + (kc + kk) * BN + g * 256);
-                av_t a[TM];
-                if constexpr (ALDS) {
-                    // the wave's four rows of this chunk: one broadcast 16-byte LDS read each
-#pragma unroll
-                    for (int r = 0; r < TM; ++r) a[r] = *(const f4 *)&Asl[buf][wave * TM + r][kc];
-                } else {
-#pragma unroll
-                    for (int r = 0; r < TM; ++r) a[r] = a_next[r];
-                    // ... and the scalar fetch of the next chunk's A values is issued only after
-                    // that wait: scalar loads return out of order, so any later LDS wait would
-                    // have to drain them too.  Here they have the whole chunk's arithmetic to land.
-                    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0), vmcnt and expcnt untouched
-                    __builtin_amdgcn_sched_barrier(0);
-                    fetch_a(k0, k0 + kc + 2 * KA <= K ? kc + KA : kc);   // past the last full chunk: re-read this one
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                compute_chunk(a, b);
-            }
-        } else if (t >= full_tiles) {
-            // K remainder: k by k, so no padded product is ever evaluated.
-            for (int kk = 0; kk < tail; ++kk) {
-                float a1[TM];
-#pragma unroll
-                for (int r = 0; r < TM; ++r)
-                    a1[r] = ALDS ? Asl[ALDS ? buf : 0][ALDS ? wave * TM + r : 0][ALDS ? kk : 0]
-                                 : transA ? As[(int64_t)(k0 + kk) * args.lda + trow(r)] : As[arow[transA ? 0 : r] + k0 + kk];
-                f4 b[NG];
-#pragma unroll
-                for (int g = 0; g < NG; ++g)
-                    b[g] = *(const f4 *)(bs + kk * BN + g * 256);
+                bsrc -= n_tiles * tile_stride;
+                btsrc -= n_tiles * BK;
+                asrc -= n_tiles * BK;
 #pragma unroll
                 for (int r = 0; r < TM; ++r)
 #pragma unroll
-                    for (int g = 0; g < NG; ++g) {
-                        float t4[4];
-                        thres4(r, g, t4);
-                        fold4<TASK>(a1[r], b[g], t4, &q[g * 4], &part[r][g * 4]);
-                    }
+                    for (int c = 0; c < 4; ++c) mainacc[r][c] = 0;
             }
         }
-
-        // fold the partial sums into the main accumulators every partial_k products
-        if ((t + 1) % FLUSH_TILES == 0)
-            flush();
-
-        if (t + 1 < n_tiles)
-            store_tile(buf ^ 1);
-        __syncthreads();
+        if (!rounded) k_loop(std::false_type());
+    } else {
+        constexpr std::false_type by_rounding;
+#include "mmlike_valu_k_loop.inc"
     }
-    flush();
 
     // (where registers are short opaque from here on, or the columns of the write-back are computed with those of the
     // thresholds, before the K loop, and held through it: up to 17 registers more than the 128 there are)
