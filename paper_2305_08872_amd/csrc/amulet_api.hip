@@ -427,12 +427,12 @@ static bool count_tile_wanted(int trans_a, int trans_b, int64_t M, int64_t N, in
     // (streamed straight to LDS, a piece of a row may start at any 4-byte address)
     auto dwords = [](const void *p, int64_t ld, int64_t line) { return ((uintptr_t)p & 3u) == 0 && ld % 4 == 0 && line % 4 == 0; };
     const bool stream_to_lds = dwords(A, lda, trans_a ? M : K) && dwords(B, ldb, trans_b ? K : N);
-    route.plan = choose_count_tile(M, N, K, !stream_to_lds, assign);
     // R around the caches when a call's matrices do not fit the last-level cache (256 MiB) anyway, so that R does
     // not displace operands: 8000^2 x 4000 280 -> 235 us, 8191^2 x 4095 358 -> 314, 7801^2 x 3001 254 -> 246; where
     // they do, R is still there at the next call: 7900^2 x 2000 178 / 194, 5000 x 7000 x 3000 144 / 166
     const double bytes = 4.0 * (double)M * (double)N + (double)K * ((double)M + (double)N);
     route.bypass = !assign && bytes > 285e6 ? 1 : 0;
+    route.plan = choose_count_tile(M, N, K, !stream_to_lds, assign, !stream_to_lds && !trans_a && !route.bypass);
     return true;
 }
 
@@ -1677,7 +1677,7 @@ const char *amulet_recent_kernel(int back)
         if (n.pieces) snprintf(text, sizeof(text), "%s rows %lld bf16_pieces 3 tile_rows %d", name, rows, n.pieces);
         else snprintf(text, sizeof(text), "%s rows %lld", name, rows);
     } else if (n.task == AMULET_TASK_COUNT_I8) {
-        static const char *const tiles[4] = {"256x256", "128x256", "128x128", "64x64"};
+        static const char *const tiles[5] = {"256x256", "128x256", "128x128", "64x64", "192x256"};
         snprintf(text, sizeof(text), "i8_tile_%s%s%s%s rows %lld parts %d kpart %d kgroup %d", tiles[n.tile], n.ring ? "_ring6" : "",
                  n.registers ? "_registers" : "", n.bypass ? "_bypass" : "", rows, n.parts, n.kpart, n.kgroup);
     } else {

@@ -470,7 +470,7 @@ struct CountTileArgs {
     int assign;      // R = the counts instead of R +=
     int bypass;      // R is read and written around the caches (the two largest tiles)
 };
-enum { CT_256 = 0, CT_128x256 = 1, CT_128 = 2, CT_64 = 3 };
+enum { CT_256 = 0, CT_128x256 = 1, CT_128 = 2, CT_64 = 3, CT_192x256 = 4 };
 struct CountTilePlan {
     int tile;               // CT_...
     int through_registers;  // rows at any byte address, staged through registers; else streamed HBM -> LDS
@@ -489,19 +489,21 @@ struct CountTilePlan {
 // K over several workgroups (the two smaller tiles): 0.3 us and 1 T atomic adds per second beside other workgroups' arithmetic, 4 us
 // more to clear an R that is to be written.  Fitted to and checked against every tile and split at 210 drawn
 // sizes (64 ... 8192 each way, all layouts and alignments): 1.4 % behind the fastest on average, 28 % at most.
-inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool through_registers, bool assign)
+// (`rows192`: the 192 x 256 tile, 12 waves, may be taken: rows at any byte address, A not transposed, R through the caches.)
+inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool through_registers, bool assign, bool rows192)
 {
-    static const struct { int bm, bn, groups, resident; double alone, shared, rest_alone, rest_shared, registers; } tiles[4] = {
+    static const struct { int bm, bn, groups, resident; double alone, shared, rest_alone, rest_shared, registers; } tiles[5] = {
         {256, 256, 1, 1, 0.57, 0.0, 17.0, 0.0, 1.42}, {128, 256, 1, 2, 0.42, 0.60, 10.5, 16.0, 0.0},
-        {128, 128, 1, 2, 0.206, 0.48, 4.8, 9.2, 1.52}, {64, 64, 2, 2, 0.19, 0.46, 2.8, 4.1, 1.67}};
+        {128, 128, 1, 2, 0.206, 0.48, 4.8, 9.2, 1.52}, {64, 64, 2, 2, 0.19, 0.46, 2.8, 4.1, 1.67},
+        {192, 256, 1, 1, 0.56, 0.0, 12.8, 0.0, 1.42}};
     auto up64 = [](int64_t n) { return (n + 63) / 64 * 64; };
     CountTilePlan best = {0, through_registers ? 1 : 0, 0, 0, 0, 0, 0.0};
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 5; ++i) {
         const auto &t = tiles[i];
-        if (through_registers && t.registers == 0.0) continue;
+        if ((through_registers && t.registers == 0.0) || (i == CT_192x256 && !rows192)) continue;
         const int64_t grid = xcd_grid((M + t.bm - 1) / t.bm, (N + t.bn - 1) / t.bn), round = 256 * t.resident;
         for (int64_t p = 1; p <= 64; p = p < 4 ? p + 1 : p % 3 ? p / 2 * 3 : p / 3 * 4) {   // 1 2 3 4 6 8 12 16 24 ...
-            if (p > 1 && (i < CT_128 || K / p < 192 || M * N * p > 16000000)) break;
+            if (p > 1 && (i < CT_128 || i == CT_192x256 || K / p < 192 || M * N * p > 16000000)) break;
             const int64_t kpart = up64((K + p - 1) / p), parts = (K + kpart - 1) / kpart;
             const int64_t kgroup = up64((kpart + t.groups - 1) / t.groups);
             const double stages = (double)(kgroup / 64) * (through_registers ? t.registers : 1.0), r = assign ? 0.77 : 1.0;

@@ -1,6 +1,6 @@
 // Join count on the int8 matrix cores for operands of any size, alignment and layout, in place.
 //
-// A workgroup owns a tile of 256 x 256, 128 x 256, 128 x 128 or 64 x 64 counts (the last with two groups of
+// A workgroup owns a tile of 256 x 256, 192 x 256, 128 x 256, 128 x 128 or 64 x 64 counts (the last with two groups of
 // waves that share K) and walks K in stages of 64: v_mfma_i32_32x32x32_i8 on fragments that an operand stored
 // along k gives by ds_read_b128 and one stored across k by ds_read_b64_tr_b8, which transposes on the way.  So
 // the four layouts are four kernels of one body, and none is copied first.  What bounds it: at large sizes the
@@ -19,6 +19,11 @@
 // LDS slots) for rows at any byte address, 42-67 % more per stage by tile; a whole call, us, streamed / the same
 // call one byte off: 3000 x 4004 x 2504 (written) 38 / 49, 5000 x 7000 x 3000 145 / 175, 8000^2 x 4000 235 / 314,
 // 2048^2 x 8192 40 / 67.
+//
+// Through registers a stage takes 0.8 us in a tile of 256 rows and in one of 192 (not its loads' round trip: with 4 stages on their
+// way in registers instead of 2 the same), and what a unit does not overlap is the write-back of its tile, 24 us and 19: so rows at any
+// address have a tile of 192 x 256, us, 256 / 192: 2999 x 4001 x 2503 57.7 / 53.3 (written 52 / 47), 6000 x 6001 x 1501 113 / 100,
+// 5999 x 4001 x 2503 104 / 94, with B transposed 110 / 101, 3071 x 4095 x 8191 127 / 121.
 //
 // Measured, us, the kernels it replaced at these sizes / here: 1000^3 38 / 6.5 (a stage of 128 x 128 guarded
 // loads by one thread each), 2999 x 4001 x 2503 (written) 79 / 45, 5000 x 7000 x 3000 212 / 145, 8191^2 x 4095
@@ -49,19 +54,24 @@ constexpr int CT_BK = 64;
 
 template <int N> __device__ __forceinline__ void ct_wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
+// resident waves per SIMD the registers are held to (the workgroup of 12 waves has its unit for itself)
+constexpr int ct_waves(int waves) { return waves == 12 ? 3 : 4; }
+
 // Waves: WK groups of WR x WC, a group sums its own kgroup of the workgroup's k; a wave MB x NB blocks of 32 x 32.
 // NST: stages of the ring.  TA / TB: A stored K x M / B stored N x K.  REG: through registers.  KS: K over several workgroups.
 // NT: R is read and written around the caches.
 template <int MB, int NB, int WR, int WC, int WK, int NST, bool TA, bool TB, bool REG, bool KS, bool NT>
-__global__ void __launch_bounds__(64 * WR * WC * WK) __attribute__((amdgpu_waves_per_eu(4, 4)))
+__global__ void __launch_bounds__(64 * WR * WC * WK) __attribute__((amdgpu_waves_per_eu(ct_waves(WR * WC * WK), ct_waves(WR * WC * WK))))
 count_i8_tile_kernel(const CountTileArgs args)
 {
     constexpr int BM = 32 * MB * WR, BN = 32 * NB * WC;
     constexpr int A_BYTES = BM * CT_BK, B_BYTES = BN * CT_BK, G_BYTES = A_BYTES + B_BYTES, STAGE_BYTES = WK * G_BYTES;
     constexpr int NW = WR * WC;                          // waves of a group
-    constexpr int LINES = G_BYTES / 1024, A_LINES = A_BYTES / 1024, LOADS = LINES / NW;
+    constexpr int LINES = G_BYTES / 1024, A_LINES = A_BYTES / 1024, LOADS = (LINES + NW - 1) / NW;
     constexpr int A_LOADS = A_LINES / NW;                // of a wave's loads the first ones are A's
-    static_assert(LINES % NW == 0 && A_LINES % NW == 0, "the stage's kilobytes divide over the group's waves");
+    constexpr bool RAGGED = LINES % NW != 0;             // the last load is the first waves' only
+    static_assert((REG || !RAGGED) && A_LINES % NW == 0, "the stage's kilobytes divide over the group's waves");
+    static_assert(!(TA && (BM & (BM - 1)) != 0), "the units of a k-row are exchanged within powers of two");
     constexpr int UA = BM / 16, UB = BN / 16;            // 16-byte units in a k-row of an operand kept k-major
 
     const int M = args.M, N = args.N, K = args.K;
@@ -89,7 +99,7 @@ count_i8_tile_kernel(const CountTileArgs args)
     const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void_ptr)ct_smem;
 #pragma unroll
     for (int q = 0; q < LOADS; ++q) {
-        const int line = wg + NW * q;
+        const int line = !RAGGED || q < LOADS - 1 || wg + NW * q < LINES ? wg + NW * q : wg + NW * (q - 1);
         const bool is_a = q < A_LOADS;
         const int s = (is_a ? line : line - A_LINES) * 64 + lane;
         const int edge = is_a ? M : N, org = is_a ? row0 : col0, base = is_a ? rbase : cbase;
@@ -148,7 +158,8 @@ count_i8_tile_kernel(const CountTileArgs args)
     // REG: the same pieces through registers (rows at any byte address)
     auto fetch = [&](v4i (&st)[LOADS]) {
 #pragma unroll
-        for (int q = 0; q < LOADS; ++q) st[q] = *(const v4i_any *)((q < A_LOADS ? pa : pb) + voff[q]);
+        for (int q = 0; q < LOADS; ++q)
+            if (!RAGGED || q < LOADS - 1 || wg + NW * q < LINES) st[q] = *(const v4i_any *)((q < A_LOADS ? pa : pb) + voff[q]);
         advance();
     };
     // (A's bytes outside the k of the range are zeroed on the way -- a zero adds nothing -- in the last,
@@ -168,6 +179,7 @@ count_i8_tile_kernel(const CountTileArgs args)
 #pragma unroll
         for (int q = 0; q < LOADS; ++q) {
             const int line = wg + NW * q;
+            if (RAGGED && q == LOADS - 1 && line >= LINES) continue;
             v4i x = st[q];
             if (q >= A_LOADS) {
             } else if constexpr (TA) {
@@ -347,8 +359,8 @@ count_i8_tile_kernel(const CountTileArgs args)
     // in 16-byte pieces of rows.  Every other group of four image rows has its 128-byte halves exchanged, so
     // that the two half-waves of a scatter, four rows apart, use different banks.
     constexpr int NWT = WR * WC * WK, PR = BN / (4 * NWT) > 4 ? 32 : 64;   // (four pieces of R in a lane's registers: more spill)
-    constexpr int NA = PR * BN / (256 * NWT), ROW_U = BN / 4;
-    static_assert(PR * BN % (256 * NWT) == 0, "the image's pieces divide over the waves");
+    constexpr int NA = (PR * BN + 256 * NWT - 1) / (256 * NWT), ROW_U = BN / 4;
+    static_assert(!KS || PR * BN % (256 * NWT) == 0, "the image's pieces divide over the waves");
     int32_t *const img = (int32_t *)ct_smem;
     auto img_at = [](int r, int c) { return r * BN + (BN > 32 ? c ^ (((r >> 2) & 1) << 5) : c); };
     auto scatter = [&](int part, auto add) {
@@ -401,6 +413,7 @@ count_i8_tile_kernel(const CountTileArgs args)
             const int idx = i * (64 * NWT) + tid, r = idx / ROW_U, c = idx % ROW_U * 4;
             bool orow, o0, o3;
             const int row = row_of(part * PR + r, orow), col = col_of(c, o0);
+            if (PR * BN % (256 * NWT) != 0) orow = orow && r < PR;
             (void)col_of(c + 3, o3);
             off[i] = (uint32_t)row * (uint32_t)args.ldr + (uint32_t)col;
             all[i] = orow && o0 && o3;
@@ -414,6 +427,7 @@ count_i8_tile_kernel(const CountTileArgs args)
                 const int idx = i * (64 * NWT) + tid, r = idx / ROW_U, c = idx % ROW_U * 4;
                 bool orow;
                 (void)row_of(part * PR + r, orow);
+                if (PR * BN % (256 * NWT) != 0) orow = orow && r < PR;
                 if (orow && !all[i]) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
@@ -438,6 +452,7 @@ count_i8_tile_kernel(const CountTileArgs args)
             }
             bool orow;
             (void)row_of(part * PR + r, orow);
+            if (PR * BN % (256 * NWT) != 0) orow = orow && r < PR;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 bool o;
@@ -478,6 +493,9 @@ static hipError_t launch_tile_plan(const CountTilePlan &plan, const CountTileArg
             if (a.bypass) return launch_tile<2, 2, 2, 4, 1, 3, TA, TB, REG, false, true>(1, a, s);
             return launch_tile<2, 2, 2, 4, 1, 3, TA, TB, REG, false>(1, a, s);
         }
+        return hipErrorInvalidValue;
+    case CT_192x256:      // (a transposed A's k-rows have 12 units there, which the exchange of units does not fit)
+        if constexpr (REG && !TA) return launch_tile<2, 2, 3, 4, 1, 4, TA, TB, REG, false>(1, a, s);
         return hipErrorInvalidValue;
     case CT_128:
         if (plan.parts > 1) return launch_tile<2, 1, 2, 4, 1, 4, TA, TB, REG, true>(plan.parts, a, s);
