@@ -245,35 +245,29 @@ static bool pieces_run(const MmlikeCall &c)
     if (c.task == TASK_IDENTITY) return identity_split_runs(c.trans_a, c.trans_b, c.K, c.lda, c.ldb);
     return c.task == TASK_BOOST && (c.trans_a || !pitch_collides(c.lda, 4));
 }
-// us of BOOST with its plain sum on the matrix cores: a pair of workgroups on a compute unit takes 0.185 us per k, one alone
-// 0.104 (a little more here for launch and write-back).  It is ahead of the wide kernel at every size and layout that both run (1.1 to 1.4 times), and of the tile
-// kernels from some 768^3 on, us, tile kernel / here: 512^3 15.1 / 28.0, 768^3 42.1 / 42.9, 1024^3 82 / 62, 1003 x 1501 x 777 96 /
-// 78, 256 x 4096^2 313 / 221, 1536^3 270 / 199, 4096 x 512 x 8192 1232 / 863.
+// us of BOOST with its plain sum on the matrix cores: a pair of workgroups on a compute unit takes 0.188 us per k, one alone
+// 0.11; with A transposed a quarter more, with a threshold per output a tenth.  It is ahead of the wide kernel at every size and
+// layout that both run (1.1 to 1.4 times), and of the tile kernels from some 768^3 on, us, tile kernel / here: 512^3 15.1 / 28.0,
+// 1024^3 82 / 62, 1003 x 1501 x 777 96 / 78, 256 x 4096^2 313 / 221, 1536^3 270 / 199, 4096 x 512 x 8192 1232 / 863, but not where tiles
+// just miss a round of a short K or columns one of 256: 900 x 2100 x 500 72 / 99, 2699 x 261 x 2999 191 / 320.  The estimate
+// is within a tenth for three calls in four of 260 drawn ones; a plan of the tile kernels has to be 6 % slower than it,
+// which loses 3.7 % at most there and gains 1.9 % on average where 2.2 % was there to gain.
 static double boost_pieces_us(const MmlikeCall &c)
 {
-    const int64_t tiles = ((c.M + 31) / 32) * ((c.N + 255) / 256), range = wide_k_range(tiles * 8, c.K), parts = (c.K + range - 1) / range;
-    const int64_t W = tiles * parts, rest = W % 512;
-    double us = 6.0 + 1.5 * (double)W / 256.0;
-    if (parts > 1) us += (double)range * (0.19 * (double)(W / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.11 : 0.175)) + (double)c.M * (double)c.N * (double)parts / 1.6e6;
-    else us += (double)c.K * (W <= 256 ? 0.11 : 0.0925 * ((double)W / 256.0 + (rest == 0 ? 0.1 : 0.35)));
-    return us;
+    const double more = (c.trans_a ? 1.25 : 1.0) * (c.thres_form == THRES_ELEM ? 1.1 : 1.0);
+    return wide_launch_us(c.M, c.N, c.K, more * 0.188, more * 0.11, more * 0.175) / 0.94;
 }
-// us of the count by rounding (count_rounding.h) in the wide kernel, with the K split it chooses: a pair of workgroups on a
-// compute unit takes 0.135 us per k, one alone 0.08; with A transposed 1.2 to 1.3 times that, with thresholds that face rows
-// 1.15.  From 128 tiles on, us, tile kernel / here: 1003 x 1501 x 777 65 / 61, 1024^3 56.7 / 49.4 (transposed A 56 / 56), 1536^3 182 / 145
-// (179 / 177), 256 x 4096^2 208 / 151, 4096 x 512 x 1024 107 / 82, 3262 x 288 x 5014 259 / 346; thresholds that the rounding leaves to
-// the comparison 1024^3 56 / 60, 1536^3 180 / 188, 256 x 4096^2 208 / 200.  Below, those are up to 17 % slower here
-// (768^3 31.9 / 37.5; by rounding 29.5), and nobody but the device knows which thresholds they are.
+// us of the count by rounding (count_rounding.h) in the wide kernel: a pair of workgroups on a compute unit takes 0.136 us per k, one
+// alone 0.08; with A transposed a third more, with thresholds that face rows 1.15 times that.  From 128 tiles on, us, tile
+// kernel / here: 1024^3 56.7 / 49.4 (transposed A 56 / 56), 1536^3 182 / 145 (179 / 177), 256 x 4096^2 208 / 151, 4096 x 512 x 1024 107 / 82,
+// 3262 x 288 x 5014 259 / 346; thresholds that the rounding leaves to the comparison 1024^3 56 / 60, 1536^3 180 / 188, 256 x
+// 4096^2 208 / 200.  Below, those are up to 17 % slower here (768^3 31.9 / 37.5; by rounding 29.5), and nobody but
+// the device knows which thresholds they are.  (A tenth for the estimate, as above: no drawn call lost by it.)
 static double count_wide_us(const MmlikeCall &c)
 {
-    const int64_t tiles = ((c.M + 31) / 32) * ((c.N + 255) / 256), range = wide_k_range(tiles * 8, c.K), parts = (c.K + range - 1) / range;
-    if (tiles < 128) return 1e30;
-    const int64_t W = tiles * parts, rest = W % 512;
-    const double more = (c.trans_a ? 1.3 : 1.0) * (c.thres_form == THRES_ROW ? 1.15 : 1.0);
-    double us = 6.0 + 1.5 * (double)W / 256.0;
-    if (parts > 1) us += more * (double)range * (0.135 * (double)(W / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.08 : 0.125)) + (double)c.M * (double)c.N * (double)parts / 1.6e6;
-    else us += more * (double)c.K * (W <= 256 ? 0.08 : 0.0675 * ((double)W / 256.0 + (rest == 0 ? 0.1 : 0.35)));
-    return us;
+    if (((c.M + 31) / 32) * ((c.N + 255) / 256) < 128) return 1e30;
+    const double more = (c.trans_a ? 1.32 : 1.03) * (c.thres_form == THRES_ROW ? 1.15 : 1.0);
+    return wide_launch_us(c.M, c.N, c.K, more * 0.136, more * 0.08, more * 0.125) / 0.9;
 }
 static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
 {
@@ -291,7 +285,9 @@ static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
     const bool fp32_splits = small <= 6 * units &&
         choose_stream_split(xcd_grid((c.M + 127) / 128, n128) / 8, units / 8, c.K, 3, rate3) > 1;
     plan.pieces = t256 < t128 && !fp32_splits ? 256 : 128;
-    return (plan.pieces == 256 ? t256 : t128) < fp32;
+    // (420 drawn calls, all layouts: ahead by 7.8 % on average; without a margin calls with A alone transposed, short K or a
+    // ragged last round lost up to 7 %)
+    return (plan.pieces == 256 ? t256 : t128) < (c.trans_a && !c.trans_b ? 0.91 : 0.97) * fp32;
 }
 
 // fp32: the tile kernels, unless the 32 x 256 kernel's estimate is lower.  That kernel takes twice the
@@ -319,10 +315,10 @@ static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
     const int64_t range = wide_k_range((c.M + d.NW * d.TM - 1) / (d.NW * d.TM) * ((c.N + 255) / 256) * d.NW, c.K);
     plan = choose_tile_plan<float>(c.M, c.N, c.K, tile_us[c.task], (c.K + range - 1) / range);
     if (pieces_us >= 0.0) {
-        plan.pieces = pieces_us < 1.04 * plan.us ? 32 : 0;
+        plan.pieces = pieces_us < plan.us ? 32 : 0;
         return true;
     }
-    if (c.task == TASK_COUNT_GT && c.thres_form != THRES_ELEM) return plan.us <= 1.03 * count_wide_us(c);
+    if (c.task == TASK_COUNT_GT && c.thres_form != THRES_ELEM) return plan.us <= count_wide_us(c);
     const int64_t large = ((c.M + 31) / 32) * ((c.N + 255) / 256);
     if (large < 256) return true;
     const double rounds = (double)large / 256.0, part_round = large % 512 == 0 ? 0.1 : 0.35;

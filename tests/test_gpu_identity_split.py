@@ -37,7 +37,7 @@ def exact(A, B, tA, tB):
 
 
 # the least K the kernel is chosen for, one stage's remainders, an odd K; both tile heights; edges by one line and by less than a block
-SIZES = [(2048, 2048, 96, 0, 128), (2047, 1921, 111, 3, 128), (1985, 1985, 257, 1, 128), (2304, 2241, 112, 2, 128),
+SIZES = [(2048, 2048, 96, 0, 128), (2047, 1921, 111, 3, 128), (1985, 1985, 257, 1, 128), (1985, 2047, 112, 2, 128),
          (4096, 4096, 96, 0, 256), (3841, 4095, 97, 1, 256), (4095, 4001, 113, 5, 256)]
 
 
