@@ -741,6 +741,11 @@ static hipError_t launch_one(const MmlikeArgs &a, hipStream_t s)
     // fewer barriers: 32 k a stage, two workgroups' 128 KiB of LDS to a unit (with the fences in fold4, 43.0 -> 44.4
     // TFLOP/s at 4096^3, with A transposed 32.2 -> 38.8; boost is level with it, 32.6 / 32.7).
     constexpr int DEEP = TASK == TASK_COUNT_GT && TM == 4 && NG == 1 && NW == 8 && BK == 16 ? 32 : BK;
+    // Discount with A transposed, whose scalar loads of four rows at a time are a longer chain per stage: as deep (us, 16 k /
+    // 32: 8192^3 34 900 / 33 930, 4096^3 4382 / 4190, 2048^3 556 / 531, 5501 x 2560 x 833 801 / 768, 2048^2 x 128 44.2 / 40.4, both operands transposed
+    // 4427 / 4268 at 4096^3); level with A row-major (4164 / 4159), where 3 registers too many spill in some forms, as with both
+    // transposed and a threshold per output.
+    constexpr int DEEP_AT = TASK == TASK_DISCOUNT && TM == 4 && NG == 1 && NW == 8 && BK == 16 ? 32 : DEEP;
     constexpr bool DPIPE = TASK == TASK_DISCOUNT && TM == 4 && NG == 1 && BK == 16;
     constexpr bool BAHEAD = TASK != TASK_IDENTITY && TM == 4 && NG == 1 && BK == 16;   // B values a chunk ahead
     auto launch = [&](int64_t n_blocks, int n_splits) -> hipError_t {
@@ -783,9 +788,9 @@ static hipError_t launch_one(const MmlikeArgs &a, hipStream_t s)
             // (transposed layouts: the discount task's pipelined form; with B a chunk ahead where A
             // is row-major -- with a transposed A the unrolled tile keeps the A values of all its
             // chunks in scalar registers at once and spills 80-130 of them)
-            case 1: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 1, TM, NG, NW, DEEP, KA, false, DPIPE, false>), grid, block, 0, s, b); break;
+            case 1: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 1, TM, NG, NW, DEEP_AT, KA, false, DPIPE, false>), grid, block, 0, s, b); break;
             case 2: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 2, TM, NG, NW, DEEP, KA, false, DPIPE, BAHEAD>), grid, block, 0, s, b); break;
-            default: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 3, TM, NG, NW, DEEP, KA, false, DPIPE, false>), grid, block, 0, s, b); break;
+            default: hipLaunchKernelGGL((mmlike_valu_kernel<TASK, TF, 3, TM, NG, NW, TF == THRES_ELEM ? DEEP : DEEP_AT, KA, false, DPIPE, false>), grid, block, 0, s, b); break;
             }
         });
     };
