@@ -29,8 +29,13 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3
 # lane-operations per product (discount: multiply, compare, select, FMA), so its ceiling
 # in the metric's 2-flop-per-product convention is 2 x 78.6e12 / ops.
 VALU_LANE_OPS_PER_S = 256 * 128 * 2.4e9
-# (count_gt: multiply, subtract, shift in the sign bit, and one bit count per 32 products of an accumulator)
+# (count_gt by comparison: multiply, subtract, shift in the sign bit, and one bit count per 32 products of an accumulator)
 VALU_OPS_PER_PRODUCT = {"discount": 4, "boost": 4, "count_gt": 3.03, "identity": 1}
+# ... of the kernels that do with fewer: BOOST with its plain sum on the matrix cores (clamped FMA, add) and the count by
+# rounding (clamped FMA, FMA; the wide kernels)
+FEWER_OPS_PER_PRODUCT = {"boost": 2, "count_gt": 2}
+# dense bf16 matrix peak; fp32 products as six bf16 piece products have a sixth of it
+BF16_MFMA_PEAK_TFLOPS = 2500.0
 
 
 class ShaderClock:
@@ -406,6 +411,7 @@ def bench_workload(args, am, torch, np, wl) -> dict:
         torch.cuda.synchronize()
         wall_ms = (time.perf_counter() - w0) * 1e3
     kernel = kernel_name(am)
+    pieces = "bf16_pieces" in am.amulet_recent_kernel()     # (a kernel on the matrix cores that stands in for the named shape)
     sclk_mhz = sclk.median_mhz()
     kern_ms = [s.elapsed_time(e) for s, e in zip(starts, stops)]
     ms_per_step = wall_ms / args.steps
@@ -415,8 +421,10 @@ def bench_workload(args, am, torch, np, wl) -> dict:
     flops = 2.0 * M * N * K
     value = flops / (ms_per_step * 1e-3) / 1e9                 # GFLOP/s, whole job
     achieved_tflops = flops / (kernel_ms_avg * 1e-3) / 1e12    # dominant (only) kernel
-    ops = VALU_OPS_PER_PRODUCT[tname]
-    ceiling_tflops = 2.0 * VALU_LANE_OPS_PER_S / ops / 1e12
+    fewer = pieces or (tname == "count_gt" and kernel.startswith("valu_"))
+    ops = FEWER_OPS_PER_PRODUCT.get(tname, VALU_OPS_PER_PRODUCT[tname]) if fewer else VALU_OPS_PER_PRODUCT[tname]
+    peak = BF16_MFMA_PEAK_TFLOPS / 6 if tname == "identity" and pieces else FP32_VECTOR_PEAK_TFLOPS
+    ceiling_tflops = peak if tname == "identity" and pieces else 2.0 * VALU_LANE_OPS_PER_S / ops / 1e12
 
     # parity spot check + CPU baseline: the oracle on a bounded sample of whole rows
     cpu = None
@@ -459,7 +467,7 @@ def bench_workload(args, am, torch, np, wl) -> dict:
     probe = None
     mix = {"identity": 0, "discount": 1, "boost": 2, "count_gt": 3}.get(tname)
     on_valu = not kernel.startswith("mfma")
-    if mix is not None and on_valu and args.probe:
+    if mix is not None and on_valu and not fewer and args.probe:      # (the probe issues the longer mixes)
         pps = max(am.amulet_probe_valu(mix, w) for w in (4, 8))
         probe = {"mix": tname, "tflops_equiv": round(2.0 * pps / 1e12, 3),
                  "kernel_over_probe": round(achieved_tflops / (2.0 * pps / 1e12), 4)}
@@ -490,12 +498,12 @@ def bench_workload(args, am, torch, np, wl) -> dict:
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": args.workload, "task": tname, "M": M, "N": N, "K": K,
-                   "tile_shape": kernel, "tuned": not args.no_tune,
+                   "tile_shape": kernel + ("_bf16_pieces" if pieces else ""), "tuned": not args.no_tune,
                    "tune_seconds": round(tune_s, 3)},
         "pct_of_fp32_vector_peak": round(100.0 * value / 1e3 / FP32_VECTOR_PEAK_TFLOPS, 2),
         "roofline": {"bound": "alu" if on_valu else "mfma", "achieved": round(achieved_tflops, 3),
-                     "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(achieved_tflops / FP32_VECTOR_PEAK_TFLOPS, 4), "traffic": traffic,
+                     "peak": round(peak, 1), "unit": "TFLOP/s",
+                     "frac": round(achieved_tflops / peak, 4), "traffic": traffic,
                      "kernel_ms_avg": round(kernel_ms_avg, 4), "kernel_ms_median": round(kernel_ms_median, 4),
                      "valu_ops_per_product": ops,
                      "op_mix_ceiling_tflops": round(ceiling_tflops, 3),
