@@ -258,16 +258,16 @@ static double boost_pieces_us(const MmlikeCall &c)
     return wide_launch_us(c.M, c.N, c.K, more * 0.188, more * 0.11, more * 0.175) / 0.94;
 }
 // us of the count by rounding (count_rounding.h) in the wide kernel: a pair of workgroups on a compute unit takes 0.136 us per k, one
-// alone 0.08; with A transposed a third more, with thresholds that face rows 1.15 times that.  From 128 tiles on, us, tile
-// kernel / here: 1024^3 56.7 / 49.4 (transposed A 56 / 56), 1536^3 182 / 145 (179 / 177), 256 x 4096^2 208 / 151, 4096 x 512 x 1024 107 / 82,
-// 3262 x 288 x 5014 259 / 346; thresholds that the rounding leaves to the comparison 1024^3 56 / 60, 1536^3 180 / 188, 256 x
-// 4096^2 208 / 200.  Below, those are up to 17 % slower here (768^3 31.9 / 37.5; by rounding 29.5), and nobody but
-// the device knows which thresholds they are.  (A tenth for the estimate, as above: no drawn call lost by it.)
+// alone 0.08; with A transposed a third more, with thresholds that face rows 1.15 times that.  From 128 tiles on, us, tile kernel (by
+// rounding as well) / here: 1024^3 49 / 49.4, 1536^3 158 / 145, 256 x 4096^2 182 / 151, 4096 x 512 x 1024 94 / 82, 3262 x 288 x 5014 225 / 346;
+// thresholds that the rounding leaves to the comparison 1536^3 180 / 188, 256 x 4096^2 208 / 200; below, those are up to
+// 17 % slower here (768^3 31.9 / 37.5), and nobody but the device knows which thresholds they are.  The estimate has
+// to be 5 % lower: 160 drawn calls of 2e8 products on, 1.115 times faster than by comparison, the better of the two each time 1.123, none slower.
 static double count_wide_us(const MmlikeCall &c)
 {
     if (((c.M + 31) / 32) * ((c.N + 255) / 256) < 128) return 1e30;
     const double more = (c.trans_a ? 1.32 : 1.03) * (c.thres_form == THRES_ROW ? 1.15 : 1.0);
-    return wide_launch_us(c.M, c.N, c.K, more * 0.136, more * 0.08, more * 0.125) / 0.9;
+    return wide_launch_us(c.M, c.N, c.K, more * 0.136, more * 0.08, more * 0.125) / 0.95;
 }
 static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
 {
@@ -318,7 +318,7 @@ static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
         plan.pieces = pieces_us < plan.us ? 32 : 0;
         return true;
     }
-    if (c.task == TASK_COUNT_GT && c.thres_form != THRES_ELEM) return plan.us <= count_wide_us(c);
+    if (c.task == TASK_COUNT_GT && c.thres_form != THRES_ELEM) return plan.us * (plan.us > COUNT_ROUNDING_TILE_US ? 0.88 : 1.0) <= count_wide_us(c);
     const int64_t large = ((c.M + 31) / 32) * ((c.N + 255) / 256);
     if (large < 256) return true;
     const double rounds = (double)large / 256.0, part_round = large % 512 == 0 ? 0.1 : 0.35;

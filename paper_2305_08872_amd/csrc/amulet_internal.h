@@ -426,6 +426,8 @@ inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_
     return best;
 }
 
+// From this estimate on the tile kernels count by rounding, in 0.88 of it (mmlike_tile_impl.h)
+constexpr double COUNT_ROUNDING_TILE_US = 15.0;
 template <typename T, int TASK>
 hipError_t launch_mmlike_tile(int form, int trans, const TilePlan &plan, const TileArgs<T> &a, hipStream_t s);
 

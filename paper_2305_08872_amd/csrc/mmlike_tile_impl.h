@@ -31,14 +31,21 @@
 // discount 256^3 16.3 / 7.5, 512^3 40.5 / 22.8, 4096^3 8155 / 7823 (17.6 TFLOP/s), count 6146 / 5650.  From 2048^3 on
 // the wide fp32 kernel is as fast or faster (33.8 against 32.5 TFLOP/s at 4096^2): half the LDS reads.
 //
+// FAST: the count by rounding (count_rounding.h), thresholds that face rows, columns or all: the factor is multiplied to four operands
+// of each k after they are read.  us, by comparison / so: 768^3 31.7 / 28.2, 1003 x 1501 x 777 66.3 / 58.2, 3262 x 288 x 5014 262 / 225, 640^3 20.7 /
+// 19.8, 128 x 4096 x 512 17.5 / 16.8, but 2048 x 300 x 200 14.6 / 14.8, 256^3 5.0 / 5.4: looking at the thresholds and the waves' words at the end take
+// 0.4 us, so from 15 us of plan on.
+//
 // LDS layout of a group's stage: A, then B.  An operand whose lines run along k (row-major A, transposed B)
 // is kept as lines of 4 units, the other kind as k-rows of units.  16 lanes are served per clock: of A they
 // read one unit (broadcast), of row-major B 16 neighbouring units; transposed B takes columns lc, lc + 16, ...
 // to a lane and keeps unit u of column c at u ^ ((c >> 2) & 3), so that 16 lanes read 16 distinct bank groups.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "amulet_internal.h"
+#include "count_rounding.h"
 
 #ifndef AMULET_MMLIKE_TILE_IMPL_H
 #define AMULET_MMLIKE_TILE_IMPL_H
@@ -68,7 +75,11 @@ template <int N> __device__ __forceinline__ void tile_wait_vmcnt()
 // accesses per 8 k), every other form fits its 128.
 template <typename T, int TF> constexpr int tile_waves() { return sizeof(T) == 8 && TF == THRES_ELEM ? 2 : 4; }
 
-template <typename T, int TASK, int TF, int TRANS, int WM, int WN, int WK, int NST>
+// LDS of a workgroup: the ring, and behind the image its sums meet in a word of each wave's
+constexpr int tile_ring(int wm, int wn, int wk, int nst) { return nst * wk * (1024 * wm + 4096 * wn); }
+constexpr int tile_sums(int sz, int wm, int wn, int wk) { return wm * wn * wk * 1024 * sz; }
+
+template <typename T, int TASK, int TF, int TRANS, int WM, int WN, int WK, int NST, bool FAST>
 __global__ void __launch_bounds__(64 * WM * WN * WK) __attribute__((amdgpu_waves_per_eu(tile_waves<T, TF>(), tile_waves<T, TF>())))
 mmlike_tile_kernel(const TileArgs<T> args)
 {
@@ -193,6 +204,8 @@ mmlike_tile_kernel(const TileArgs<T> args)
     auto row_of = [&](int l, int r, bool &own) { return row_at((l >> 4) * 4 + r, own); };
     auto col_of = [&](int l, int c, bool &own) { return col_at(TB ? (l & 15) + 16 * c : c / V * (16 * V) + (l & 15) * V + c % V, own); };
 
+    static_assert(!FAST || (SZ == 4 && TASK == TASK_COUNT_GT && TF != THRES_ELEM), "the count by rounding");
+    static_assert(!FAST || tile_sums(SZ, WM, WN, WK) + 64 <= tile_ring(WM, WN, WK, NST), "the waves' words");
     // Thresholds and factors in registers for the whole K loop.  (The count reads its predicate from
     // the sign of th - p, which takes a threshold of -0 for a negative number: held as th + 0.)
     auto held = [](T t) { return TASK == TASK_COUNT_GT ? t + (T)0 : t; };
@@ -228,6 +241,46 @@ mmlike_tile_kernel(const TileArgs<T> args)
     for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int c = 0; c < 4; ++c) { part[r][c] = 0; mainacc[r][c] = 0; bits[r][c] = 0; }
+    // FAST, the count by rounding (count_rounding.h): sums, factors and rounding constants of the thresholds, the largest operand
+    // with its factor
+    constexpr int NS = TF == THRES_ROW || TF == THRES_COL ? 4 : 1;
+    T sum[4][4], gain[NS], sway[NS], most = 0;
+    bool quick = false;
+    if constexpr (FAST) {
+        bool every = args.kgroup <= COUNT_ROUNDING_K;
+        T neg[NS];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) every = count_rounding(thr(TF == THRES_ROW ? i : 0, i), gain[i], sway[i], neg[i]) && every;
+        quick = __builtin_amdgcn_ballot_w64(!every) == 0;
+        if (quick)
+#pragma unroll
+            for (int i = 0; i < NS; ++i) th[TF == THRES_ROW ? i : 0][TF == THRES_COL ? i : 0] = neg[i];
+        if constexpr (TF == THRES_CONST) asm volatile("" : "+v"(gain[0]), "+v"(sway[0]), "+v"(th[0][0]));
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum[r][c] = COUNT_ROUNDING_ZERO;
+    }
+    // one k of the lane's 4 x 4: the factors go on the operand that faces the thresholds
+    auto fast_k = [&](const T (&a)[4], const T (&b)[4]) {
+        if constexpr (FAST) {
+            constexpr bool ROW = TF == THRES_ROW;
+            T x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = (ROW ? a[i] : b[i]) * gain[i % NS];
+            most = __builtin_fmaxf(most, __builtin_fmaxf(__builtin_fabsf(x[0]), __builtin_fabsf(x[1])));
+            most = __builtin_fmaxf(most, __builtin_fmaxf(__builtin_fabsf(x[2]), __builtin_fabsf(x[3])));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                T neg[4], s[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) { neg[c] = thr(r, c); s[c] = sway[ROW ? r : c % NS]; }
+                count_by_rounding4(ROW ? x[r] : a[r], ROW ? b : x, neg, s, sum[r]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
 
     auto product = [&](T a, T b, int r, int c) {     // one product on its own (the K remainder)
         const T t = thr(r, c);
@@ -253,8 +306,18 @@ mmlike_tile_kernel(const TileArgs<T> args)
     // sign bit of the high half: 20.7 -> 23.7 TFLOP/s at 2048^3 against compare, select, add).
     auto a_of = [](const vec (&v)[4], int r, int kk) -> T { return TA ? v[kk * H + r / V][r % V] : v[r][kk]; };
     auto b_of = [](const vec (&v)[4], int kk, int c) -> T { return TB ? v[c][kk] : v[kk * H + c / V][c % V]; };
-    auto chunk = [&](const vec (&a)[4], const vec (&b)[4], auto side) {
-        if constexpr (TASK == TASK_DISCOUNT && sizeof(T) == 8) {
+    auto chunk = [&](const vec (&a)[4], const vec (&b)[4], auto side, auto fast) {
+        if constexpr (decltype(fast)::value) {
+#pragma unroll
+            for (int kk = 0; kk < V; ++kk) {
+                T ak[4], bk[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { ak[i] = a_of(a, i, kk); bk[i] = b_of(b, kk, i); }
+                fast_k(ak, bk);
+                side(kk);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else if constexpr (TASK == TASK_DISCOUNT && sizeof(T) == 8) {
             const uint64_t active = __builtin_amdgcn_read_exec();
 #pragma unroll
             for (int kk = 0; kk < V; ++kk) {
@@ -334,7 +397,8 @@ mmlike_tile_kernel(const TileArgs<T> args)
         }
     };
     constexpr int FLUSH_STAGES = (TASK == TASK_COUNT_GT ? 32 : 64) / BK;
-    auto flush = [&]() {
+    auto flush = [&](auto fast) {
+        if (decltype(fast)::value) return;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -363,7 +427,6 @@ mmlike_tile_kernel(const TileArgs<T> args)
     // in use to the chunk's end and have a second set
     constexpr int AS = TA ? 1 : 2, BS = TB ? 2 : 1;     // register sets
 
-    int slot = 0;
     // until stage t has landed: the loads of stages t + 1 ... t + NST - 2 may still be on their way
     auto wait_for = [&](int t, int later) {
         if (later == 0) { tile_wait_vmcnt<0>(); return; }
@@ -373,10 +436,6 @@ mmlike_tile_kernel(const TileArgs<T> args)
                      "1:\n\t"
                      "s_waitcnt vmcnt(%2)" :: "s"(t + later), "s"(n_st), "n"(LOADS * (NST - 2)) : "memory", "scc");
     };
-    if (NST - 1 < n_st) tile_wait_vmcnt<(NST - 1) * LOADS>();
-    else tile_wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
     // the end of stage t: every wave holds its last fragments, stage t + 1 has landed, the slot of
     // stage t takes the request for stage t + NST
     auto next_stage = [&](int t, int sl) {
@@ -386,63 +445,43 @@ mmlike_tile_kernel(const TileArgs<T> args)
         asm volatile("" ::: "memory");
         issue(t + NST, sl);
     };
-    int t = 0;
-    if (n_full > 0) {
-        vec av[AS][4], bv[BS][4];
+    if constexpr (FAST) {
+        auto k_loop = [&](auto fast) {
+#include "mmlike_tile_k_loop.inc"
+        };
+        if (quick) {
+            k_loop(std::true_type());
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { av[0][i] = read_a(tile_smem, 0, i); bv[0][i] = read_b(tile_smem, 0, i); }
-        for (; t < n_full; ++t) {
-            const char *st = tile_smem + slot * STAGE_BYTES;
-            const int nslot = slot == NST - 1 ? 0 : slot + 1;
-            const char *nst = tile_smem + nslot * STAGE_BYTES;
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                chunk(av[c % AS], bv[c % BS], [&](int kk) {
-                    if (c == 3 && kk == 0) next_stage(t, slot);
-                    // the next chunk's units (past the last stage: read, never used)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (i / H == kk) {
-                            av[(c + 1) % AS][i] = read_a(c == 3 ? nst : st, (c + 1) & 3, i);
-                            bv[(c + 1) % BS][i] = read_b(c == 3 ? nst : st, (c + 1) & 3, i);
-                        }
-                });
-            if ((t + 1) % FLUSH_STAGES == 0) flush();
-            slot = nslot;
+                for (int c = 0; c < 4; ++c) part[r][c] = (int)(sum[r][c] - COUNT_ROUNDING_ZERO);
+        } else {
+            k_loop(std::false_type());
         }
-    }
-    for (; t < n_st; ++t) {      // the remainder of the k range, and other groups' further stages
-        if (t == n_full && tail > 0) {
-            const char *st = tile_smem + slot * STAGE_BYTES;
-            const int off = kb + n_full * BK - window(t), end = off + tail;
-#pragma unroll 1
-            for (int kk = off; kk < end;) {
-                if (kk % V == 0 && kk + V <= end) {
-                    vec av[4], bv[4];
+        // an operand left fp32 with its factor, in some wave: all of the tile again, by comparison.  (The ring is free but for what
+        // waves still read ahead and never use.)
+        int *const redo = (int *)(tile_smem + tile_ring(WM, WN, WK, NST) - 64);
+        const bool out = quick && __builtin_amdgcn_ballot_w64(most == __builtin_inff()) != 0;
+        if (lane == 0) redo[wave] = out ? 1 : 0;
+        __syncthreads();
+        if (__builtin_amdgcn_ballot_w64(redo[lane & 7] != 0) != 0) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) { av[i] = read_a(st, kk / V, i); bv[i] = read_b(st, kk / V, i); }
-                    chunk(av, bv, [](int) {});
-                    kk += V;
-                } else {
-                    T a1[4], b1[4];
+            for (int i = 0; i < NS; ++i)
+                th[TF == THRES_ROW ? i : 0][TF == THRES_COL ? i : 0] =
+                    held(args.thres[TF == THRES_ROW ? row_of(lane, i, own_dummy) : TF == THRES_COL ? col_of(lane, i, own_dummy) : 0]);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        a1[i] = *(const T *)(st + a_lds + (TA ? kk * (TR * SZ) + i * SZ : i * 64 + kk * SZ));
-                        b1[i] = *(const T *)(st + b_lds + (TB ? i * 1024 + ((kk / V) ^ b_swz) * 16 + kk % V * SZ
-                                                              : kk * (TC * SZ) + (i / V) * 256 + i % V * SZ));
-                    }
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
+                for (int c = 0; c < 4; ++c) part[r][c] = 0;
+            __syncthreads();
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) product(a1[r], b1[c], r, c);
-                    ++kk;
-                }
-            }
+            for (int d = 0; d < NST; ++d) issue(d, d);
+            k_loop(std::false_type());
         }
-        next_stage(t, slot);
-        slot = slot == NST - 1 ? 0 : slot + 1;
+    } else {
+        constexpr std::false_type fast;
+#include "mmlike_tile_k_loop.inc"
     }
-    flush();
     auto result = [&](int r, int c) -> acc_t { return TASK == TASK_COUNT_GT || sizeof(T) == 8 ? part[r][c] : mainacc[r][c]; };
 
     // ---- sum over the k groups through LDS, write-back ----
@@ -526,12 +565,12 @@ mmlike_tile_kernel(const TileArgs<T> args)
     }
 }
 
-template <typename T, int TASK, int TF, int TRANS, int WM, int WN, int WK, int NST>
+template <typename T, int TASK, int TF, int TRANS, int WM, int WN, int WK, int NST, bool FAST>
 static hipError_t launch_tile(int parts, const TileArgs<T> &args, hipStream_t s)
 {
-    constexpr int RING = NST * WK * (1024 * WM + 4096 * WN), SUMS = WM * WN * WK * 1024 * (int)sizeof(T);
+    constexpr int RING = tile_ring(WM, WN, WK, NST), SUMS = tile_sums(sizeof(T), WM, WN, WK);
     constexpr int LDS = RING > SUMS ? RING : SUMS;
-    auto *const kernel = &mmlike_tile_kernel<T, TASK, TF, TRANS, WM, WN, WK, NST>;
+    auto *const kernel = &mmlike_tile_kernel<T, TASK, TF, TRANS, WM, WN, WK, NST, FAST>;
     static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (granted != hipSuccess) return granted;
     const int64_t grid = xcd_grid((args.M + 16 * WM - 1) / (16 * WM), (args.N + 64 * WN - 1) / (64 * WN));
@@ -545,8 +584,15 @@ static hipError_t launch_tile(int parts, const TileArgs<T> &args, hipStream_t s)
 template <typename T, int TASK, int TF, int TRANS>
 static hipError_t launch_tile_plan(const TilePlan &plan, const TileArgs<T> &a, hipStream_t s)
 {
-    if (plan.wide) return launch_tile<T, TASK, TF, TRANS, 2, 1, 4, 3>(plan.parts, a, s);
-    return launch_tile<T, TASK, TF, TRANS, 1, 1, 8, 2>(plan.parts, a, s);
+    constexpr bool FASTER = sizeof(T) == 4 && TASK == TASK_COUNT_GT && TF != THRES_ELEM;
+    if constexpr (FASTER) {
+        if (plan.us > COUNT_ROUNDING_TILE_US) {
+            if (plan.wide) return launch_tile<T, TASK, TF, TRANS, 2, 1, 4, 3, true>(plan.parts, a, s);
+            return launch_tile<T, TASK, TF, TRANS, 1, 1, 8, 2, true>(plan.parts, a, s);
+        }
+    }
+    if (plan.wide) return launch_tile<T, TASK, TF, TRANS, 2, 1, 4, 3, false>(plan.parts, a, s);
+    return launch_tile<T, TASK, TF, TRANS, 1, 1, 8, 2, false>(plan.parts, a, s);
 }
 
 template <typename T, int TASK, int TF>

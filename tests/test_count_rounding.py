@@ -95,7 +95,7 @@ def check(am, A, B, th, form, tA, tB, shape, want=None, pad=0):
     R = torch.full((M, N), 2.0, device="cuda")
     am.amulet_mmlike_f32_general(am.AMULET_COUNT_GT, stored(A, tA), stored(B, tB), th, None, R, thres_form=FORMS.index(form),
                                  trans_a=tA, trans_b=tB, shape=shape)
-    assert "valu_" in am.amulet_recent_kernel()
+    assert ("valu_" if shape >= 0 else "f32_tile_") in am.amulet_recent_kernel(), am.amulet_recent_kernel()
     assert torch.equal(R, want + 2.0), (form, tA, tB, shape, int((R != want + 2.0).sum()))
     return want
 
@@ -134,6 +134,28 @@ def test_ties_and_neighbours(am, form, tA, tB):
         want = None
         for shape in shapes:
             want = check(am, A, B, T, form, tA, tB, shape, want, pad)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tA,tB", [(False, False), (True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("form", ("col", "row", "const"))
+def test_tile_kernels(am, form, tA, tB):
+    """The same in the tile kernels, at sizes from which they round: both tiles, K shared by their waves and in parts, remainders of
+    its stages, ragged edges; and what sends a tile to its second way."""
+    for M, N, K, pad in [(801, 701, 799, 0), (129, 4003, 515, 1), (65, 2001, 2047, 3), (640, 512, 720, 0)]:
+        g = torch.Generator(device="cuda").manual_seed(M + N + K)
+        a = torch.randint(-4096, 4096, (6,), device="cuda", generator=g).float() * 2 + 1
+        b = (torch.randint(-8192, 8192, (6,), device="cuda", generator=g).float() * 2 + 1) * 2.0 ** -20
+        th = (a[:, None] * b[None, :]).flatten()
+        th = torch.cat([th, torch.nextafter(th, torch.full_like(th, 1e38)), torch.nextafter(th, torch.full_like(th, -1e38))])
+        A, B, T = some(g, a, (M, K)), some(g, b, (K, N)), some(g, th, thresholds(form, M, N))
+        check(am, A, B, T, form, tA, tB, -1, pad=pad)
+        B[K // 2, N // 3] = 3e38      # (in the rows' form A carries the factor)
+        A[M // 2, K // 3] = -3e38
+        A[:, K // 2] = 0.0
+        check(am, A, B, T, form, tA, tB, -1, pad=pad)
+        T.view(-1)[::3] = 0.0
+        check(am, A, B, T, form, tA, tB, -1, pad=pad)
 
 
 @pytest.mark.gpu
