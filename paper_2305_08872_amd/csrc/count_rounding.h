@@ -17,7 +17,7 @@
 // (NaN products: the clamp makes them 0, as not above.  An infinite threshold has g = 1.)
 //
 // It holds for thresholds of magnitudes 2^-40 to 2^24 (g >= 1: no b g loses bits) as long as no b g overflows, which the
-// kernel watches (a b would have to be 2^105 thresholds away).  Tiles with other thresholds -- zero, smaller, larger, NaN
+// kernels watch (b would have to be 2^105 times the threshold).  Tiles with other thresholds -- zero, smaller, larger, NaN
 // -- take the comparison.  (Zero with g = 2^64 needs every positive product to be at least 2^-64: with the smallest operands
 // looked for beside the staging 4096^3 took 2770 us, by comparison 2970, and the loop without that 2520 for 2340.)
 //
