@@ -258,16 +258,16 @@ static double boost_pieces_us(const MmlikeCall &c)
     return wide_launch_us(c.M, c.N, c.K, more * 0.188, more * 0.11, more * 0.175) / 0.94;
 }
 // us of the count by rounding (count_rounding.h) in the wide kernel: a pair of workgroups on a compute unit takes 0.136 us per k, one
-// alone 0.08; with A transposed a third more, with thresholds that face rows 1.15 times that.  From 128 tiles on, us, tile kernel (by
+// alone 0.08; with A transposed a third more, with thresholds that face rows 1.12 times that.  From 128 tiles on, us, tile kernel (by
 // rounding as well) / here: 1024^3 49 / 49.4, 1536^3 158 / 145, 256 x 4096^2 182 / 151, 4096 x 512 x 1024 94 / 82, 3262 x 288 x 5014 225 / 346;
 // thresholds that the rounding leaves to the comparison 1536^3 180 / 188, 256 x 4096^2 208 / 200; below, those are up to
 // 17 % slower here (768^3 31.9 / 37.5), and nobody but the device knows which thresholds they are.  The estimate has
-// to be 5 % lower: 160 drawn calls of 2e8 products on, 1.115 times faster than by comparison, the better of the two each time 1.123, none slower.
+// to be 4 % lower: 160 drawn calls of 2e8 products on, 1.115 times faster than by comparison, the better of the two each time 1.123, none slower.
 static double count_wide_us(const MmlikeCall &c)
 {
     if (((c.M + 31) / 32) * ((c.N + 255) / 256) < 128) return 1e30;
-    const double more = (c.trans_a ? 1.32 : 1.03) * (c.thres_form == THRES_ROW ? 1.15 : 1.0);
-    return wide_launch_us(c.M, c.N, c.K, more * 0.136, more * 0.08, more * 0.125) / 0.95;
+    const double more = (c.trans_a ? 1.32 : 1.03) * (c.thres_form == THRES_ROW ? 1.12 : 1.0);
+    return wide_launch_us(c.M, c.N, c.K, more * 0.136, more * 0.08, more * 0.125) / 0.96;
 }
 static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
 {
