@@ -106,3 +106,25 @@ def test_values_the_pieces_do_not_carry(am, M, N):
     rest = torch.ones(M, dtype=torch.bool, device="cuda")
     rest[40:43] = False
     assert bool(R[rest].isfinite().all())
+
+
+@pytest.mark.parametrize("M,N", [(2048, 2048), (4096, 4096)])
+@pytest.mark.parametrize("what", ["subnormal products", "subnormal pieces"])
+def test_subnormals_on_the_bf16_matrix_cores(am, what, M, N):
+    """Pieces and piece products below the smallest normal number count like any other."""
+    K = 112
+    g = torch.Generator(device="cuda").manual_seed(11)
+    A, B = operand(g, M, K, 0), operand(g, K, N, 0)
+    if what == "subnormal products":     # the products straddle 2^-126, no piece is subnormal
+        A, B = A * 2.0 ** -63, B * 2.0 ** -63
+    else:                                # 16 bits from 2^-133 up: the pieces carry all of them, most in subnormal bf16 numbers
+        A = (A * 65535).round() * 2.0 ** -126 * 2.0 ** -7
+        B = B * 2.0 ** 100
+    ref, ab = exact(A, B, False, False)
+    R = torch.zeros(M, N, device="cuda")
+    print("identity pieces", what, M, N, flush=True)
+    run(am, A, B, R, False, False)
+    # fp32 accumulators, and of each product six pieces that round to a multiple of 2^-149
+    worst = float((((R.double() - ref).abs() - 6 * K * 2.0 ** -150) / ab).max())
+    print("worst", worst, flush=True)
+    assert worst <= 1e-5
