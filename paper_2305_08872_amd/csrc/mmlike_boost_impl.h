@@ -25,8 +25,11 @@
 // <= th, the predicate a clamp too -- has three vector instructions for its four and was slower, 4297 / 4050 us at 4096^3.
 //
 // Values it does not take: nonzero |a| or |b| below 2^-36 (products in the subnormal range once scaled, pieces below
-// bf16's), a triggered part of 2^52 or more (the clamp at 1), thresholds of 0 < |th| < 2^-70, results that are not finite.  A
-// workgroup that finds any of these, at its end, forms its tile again with the wide kernel's arithmetic.
+// bf16's), triggered parts of 2^51 or more over 64 k (a term at the clamp is one), sums of 2^72 or more, thresholds of
+// 0 < |th| < 2^-70, results that are not finite.  A workgroup that finds any of these, at its end, forms its tile again with the wide
+// kernel's arithmetic.  The bound on the sums is for the clamp's sake: a partial sum starts at what the fold before it rounded away, less
+// than 0.1 for scaled sums below 2^20 (half an ulp of the sum, and of the difference it is found by), and a term at the clamp takes
+// it to 0.9 and so beyond the 0.5 it is known by.  (Without it a partial sum could start far below zero, and hide the term.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -149,7 +152,7 @@ mmlike_boost_kernel(const MmlikeArgs args)
 #pragma unroll
     for (int v = 0; v < 16; ++v) sum[v] = 0.0f;
     // the least nonzero magnitude staged by this thread (twice its bits, less 1: zeros are the largest), and the largest
-    // partial sum of clamped terms
+    // partial sum of clamped terms, or 2^-21 of a main accumulator
     uint32_t least = 0xffffffffu;
     float most = 0.0f;
     auto see = [&](float x, float y) {
@@ -306,14 +309,17 @@ mmlike_boost_kernel(const MmlikeArgs args)
 #pragma unroll
         for (int r = 0; r < TM; ++r) {
             const f4 s4 = *(const f4 *)&L.s[wave * TM + r][lane * 4];
+            float sums = 0.0f;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                most = __builtin_fmaxf(most, part[r][c]);
                 // (what the addition rounds away starts the next partial sum)
                 const float v = part[r][c] + s4[c], m = mainacc[r][c] + v;
+                most = __builtin_fmaxf(most, part[r][c]);
+                sums = __builtin_fmaxf(sums, __builtin_fabsf(m));
                 part[r][c] = v - (m - mainacc[r][c]);
                 mainacc[r][c] = m;
             }
+            most = __builtin_fmaxf(most, sums * 0x1p-21f);
         }
     };
     auto term = [&](float a, float b, int r, int c) { return __builtin_amdgcn_fmed3f(__builtin_fmaf(a, b, thres(r, c)), 0.0f, 1.0f); };
@@ -403,7 +409,7 @@ mmlike_boost_kernel(const MmlikeArgs args)
     // (opaque from here on, or what follows has its columns computed before the K loop and held through it)
     int l = lane;
     asm volatile("" : "+v"(l));
-    bool again = odd || least < (0x2dc00000u << 1) - 1u || !(most < 1.0f);   // (2^-36)
+    bool again = odd || least < (0x2dc00000u << 1) - 1u || !(most < 0.5f);   // (2^-36)
 #pragma unroll
     for (int r = 0; r < TM; ++r)
 #pragma unroll

@@ -103,6 +103,25 @@ def test_values_of_the_second_way(am, what, tA, tB):
         check(R, 0.0, A, B, th, form, tA, tB, 3 * 2.0 ** -20 if what == "subnormal" else 1e-5)
 
 
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("size", [46, 52, 60])
+def test_a_term_beyond_the_clamp_is_found_beside_large_sums(am, size, form):
+    """Negative products of 2^size and, after two folds, one large positive one in a row of each tile: its term counts as
+    2^52 where the clamp goes unnoticed, as it does where the partial sum began below zero with what a fold had rounded away."""
+    M, N, K = 2048, 2048, 256
+    g = torch.Generator(device="cuda").manual_seed(size)
+    A = -(torch.rand(M, K, device="cuda", generator=g) + 0.5) * 2.0 ** size
+    rows = torch.arange(0, M, 32, device="cuda") + torch.randint(0, 32, (M // 32,), device="cuda", generator=g)
+    A[rows, torch.randint(128, K, (M // 32,), device="cuda", generator=g)] = 2.0 ** (max(size, 52) + 8)
+    B, th = torch.ones(K, N, device="cuda"), torch.ones({"col": (N,), "row": (M,), "const": (1,), "elem": (M, N)}[form], device="cuda")
+    R = torch.zeros(M, N, device="cuda")
+    print("boost pieces clamp", size, form, flush=True)
+    run(am, A, B, th, R, form, False, False)
+    term = A.double() + (A.double() - 1).clamp_min(0)
+    worst = ((R.double() - term.sum(1)[:, None]).abs() / term.abs().sum(1)[:, None]).max()
+    assert float(worst) <= 1e-5, float(worst)
+
+
 def test_infinities_and_nan_stay_with_their_rows(am):
     M, N, K = 1024, 1024, 1024
     g = torch.Generator(device="cuda").manual_seed(4)
