@@ -103,6 +103,33 @@ def test_values_of_the_second_way(am, what, tA, tB):
         check(R, 0.0, A, B, th, form, tA, tB, 3 * 2.0 ** -20 if what == "subnormal" else 1e-5)
 
 
+@pytest.mark.parametrize("tA,tB", [(False, False), (True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("form", FORMS)
+def test_where_the_second_way_begins(am, form, tA, tB):
+    """One value that the pieces do not take, found after the first partial sum, the second, some later one or at the end
+    only; in tiles of their own, beside tiles without one, and where K is in parts and their remainders."""
+    for M, N, K, pad in [(2048, 2048, 300, 0), (2049, 2047, 143, 1), (1024, 2048, 2033, 3)]:
+        g = torch.Generator(device="cuda").manual_seed(K)
+        A, B, th = make(g, M, N, K, form, tA, tB, pad)
+        a, b = (A.T if tA else A), (B.T if tB else B)
+        for i, k in enumerate([0, 63, 64, 100, 128, K // 2, K - 1]):
+            a[40 * i + 1, k] = 1e-12 if i % 2 else 1e-40
+        b[K - 2, 700] = -1e-30
+        R = torch.full((M, N + pad), 0.25, device="cuda")[:, :N]
+        print("boost pieces second way", form, tA, tB, M, N, K, pad, flush=True)
+        run(am, A, B, th, R, form, tA, tB, must=K == 300 and not (tA and form == "elem"))
+        check(R, 0.25, A, B, th, form, tA, tB, 100 * 2.0 ** -24)
+        rows = [40 * i + 1 for i in range(7)]      # (check samples rows: these, and one beside them in the tile)
+        rows += [r + 1 for r in rows]
+        t = {"col": lambda: th[None], "row": lambda: th[rows][:, None], "const": lambda: th[0], "elem": lambda: th[rows]}[form]().double()
+        want, mag = torch.full((len(rows), N), 0.25, dtype=torch.float64, device="cuda"), torch.zeros(len(rows), N, dtype=torch.float64, device="cuda")
+        for k in range(K):
+            p = a[rows, k].double()[:, None] * b[k].double()[None]
+            term = p + (p - t).clamp_min(0)
+            want, mag = want + term, mag + term.abs()
+        assert bool(((R[rows].double() - want).abs() - 2.0 ** -23 * want.abs() <= 100 * 2.0 ** -24 * mag).all())
+
+
 @pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("size", [46, 52, 60])
 def test_a_term_beyond_the_clamp_is_found_beside_large_sums(am, size, form):
