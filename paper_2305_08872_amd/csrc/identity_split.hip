@@ -25,8 +25,11 @@
 //
 // Values that the pieces do not carry: one with bits below 2^-133, the least a bf16 has (any below 2^-109 may), leaves a
 // remainder, whose low half is not zero; a NaN or infinity (also a finite value that rounds to an infinite
-// bf16) leaves a NaN in the accumulators.  A workgroup that finds either at its end forms its tile again with the fp32
-// matrix instruction, from global memory.
+// bf16) leaves a NaN in the accumulators.  A workgroup that finds a NaN at its end, or a remainder there or in its
+// first stage, forms its tile again with the fp32 matrix instruction (fp32_sums).  us, none of these / all values / one, or an
+// infinity / one in every tile / the fp32 kernels: 2048^3 106 / 169 / 256 / 260 / 128, 4096^3 705 / 1098 / 931 / 1800 / 943, 3000 x 5000 x 1000
+// 165 / 274 / 285 / 424 / 247.  (From global memory, a matrix instruction for every 2 k, as this once was: 2048^3 one 593, all 549,
+// 4096^3 1496, 2710, B transposed 4103.  Looks during the loop, after 8, 16, 32 ... stages, cost 4096^3 0.5 to 1 % wherever they stood.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -45,6 +48,7 @@ struct SplitTile {
     static constexpr int BM = 64 * WM, BN = 64 * WN, BK = 16;
     static constexpr int A_PIECE = BM * 32, B_PIECE = BN * 32;                 // bytes of a piece in a stage
     static constexpr int A_BYTES = 3 * A_PIECE, STAGE_BYTES = A_BYTES + 3 * B_PIECE;
+    static constexpr int LDS_BYTES = 2 * STAGE_BYTES + 16;                     // (and a word per wave: what it has found)
     static constexpr int UA = BM / 128, UB = BN / 128;                         // units (8 k of a line) per thread
     static constexpr int NACC = WM * WN >= 8 ? 1 : 2;                          // accumulator sets
     static constexpr int DEPTH = WM * WN >= 8 ? 1 : 2;                         // stages in flight in registers (a fuller wave has fewer left)
@@ -101,6 +105,13 @@ struct Operand {
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[d][j][i] = k0 + i < left ? x[d][j][i] : 0.0f;
     }
+    // unit j of ring slot 0 into LDS as it is: [k / 4][line][4 k]
+    __device__ __forceinline__ void put(int j, int tid, char *lds)
+    {
+        const int line = (tid + 256 * j) >> 1, quad = (tid & 1) * 2;
+        *(f4 *)(lds + (quad * U * 128 + line) * 16) = f4{x[0][j][0], x[0][j][1], x[0][j][2], x[0][j][3]};
+        *(f4 *)(lds + ((quad + 1) * U * 128 + line) * 16) = f4{x[0][j][4], x[0][j][5], x[0][j][6], x[0][j][7]};
+    }
     __device__ __forceinline__ void advance(int k) { base += KMINOR ? (int64_t)k : (int64_t)k * ld; }
     // pair i of unit j into pieces; after the fourth, the unit into LDS
     __device__ __forceinline__ void take(int d, int j, int i, int tid, char *lds)
@@ -114,6 +125,72 @@ struct Operand {
         }
     }
 };
+
+// The tile's sums on the fp32 matrix cores, whatever the values: a stage of 16 k in registers, one in LDS, one being multiplied.
+// A lane's fragment is 8 k in a row of its line, those of the lanes 32 on the other 8: a matrix instruction's two k are 8 apart.
+template <int WM, int WN, bool TA, bool TB, typename Args>
+__device__ __forceinline__ void fp32_sums(const Args &args, const int tid, const int row0, const int col0, f16v (&acc)[WM][WN])
+{
+    typedef SplitTile<WM, WN> TL;
+    constexpr int BK = TL::BK, UA = TL::UA, UB = TL::UB, A_BYTES = TL::BM * BK * 4, BYTES = A_BYTES + TL::BN * BK * 4;
+    static_assert(2 * BYTES <= TL::LDS_BYTES, "two stages in the pieces' LDS");
+    const int K = args.K, n_stages = (K + BK - 1) / BK, first_k = K - (n_stages - 1) * BK;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave >> 1, wc = wave & 1, li = lane & 31, lh = lane >> 5;
+    Operand<UA, 1, !TA> a;
+    Operand<UB, 1, TB> b;
+    a.start(TA ? args.A + row0 : args.A + (int64_t)row0 * args.lda, args.lda, args.M - row0, K, tid);
+    b.start(TB ? args.B + (int64_t)col0 * args.ldb : args.B + col0, args.ldb, args.N - col0, K, tid);
+    auto load = [&]() {
+#pragma unroll
+        for (int u = 0; u < UA; ++u) a.load(0, u);
+#pragma unroll
+        for (int u = 0; u < UB; ++u) b.load(0, u);
+    };
+    auto put = [&](char *lds) {
+#pragma unroll
+        for (int u = 0; u < UA; ++u) a.put(u, tid, lds);
+#pragma unroll
+        for (int u = 0; u < UB; ++u) b.put(u, tid, lds + A_BYTES);
+    };
+    load();
+#pragma unroll
+    for (int u = 0; u < UA; ++u) a.cut(0, u, tid, first_k);
+#pragma unroll
+    for (int u = 0; u < UB; ++u) b.cut(0, u, tid, first_k);
+    put(split_smem);
+    if (n_stages > 1) { a.advance(first_k); b.advance(first_k); }
+    load();
+#pragma unroll
+    for (int mi = 0; mi < WM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < WN; ++ni)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
+    __syncthreads();
+#pragma unroll 1
+    for (int s = 0; s < n_stages; ++s) {
+        const char *lds = split_smem + (s & 1) * BYTES;
+        f4 af[WM][2], bf[WN][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int mi = 0; mi < WM; ++mi) af[mi][h] = *(const f4 *)(lds + ((2 * lh + h) * TL::BM + (wr * WM + mi) * 32 + li) * 16);
+#pragma unroll
+            for (int ni = 0; ni < WN; ++ni) bf[ni][h] = *(const f4 *)(lds + A_BYTES + ((2 * lh + h) * TL::BN + (wc * WN + ni) * 32 + li) * 16);
+        }
+        // (past the last stage: the last one again, which nothing reads)
+        put(split_smem + ((s + 1) & 1) * BYTES);
+        if (s + 2 < n_stages) { a.advance(BK); b.advance(BK); }
+        load();
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int mi = 0; mi < WM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < WN; ++ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi][k / 4][k % 4], bf[ni][k / 4][k % 4], acc[mi][ni], 0, 0, 0);
+        __syncthreads();
+    }
+}
 
 template <int WM, int WN, bool TA, bool TB>
 __global__ void __launch_bounds__(256, 2) identity_split_kernel(const MmlikeArgs args)
@@ -187,7 +264,13 @@ __global__ void __launch_bounds__(256, 2) identity_split_kernel(const MmlikeArgs
     for (int d = 0; d < DEPTH; ++d)
 #pragma unroll
         for (int u = 0; u < UA + UB; ++u) load(d, u);
+    // (where stage 0 already has values that the pieces do not carry, as operands full of them have, no further one is begun)
+    uint32_t *const found = (uint32_t *)(split_smem + 2 * TL::STAGE_BYTES);
+    const bool any = __builtin_amdgcn_ballot_w64(((a.left_over | b.left_over) & 0xffffu) != 0) != 0;
+    if (lane == 0) found[wave] = any;
     __syncthreads();
+    const u4 told = *(const u4 *)found;
+    const int stages = __builtin_amdgcn_readfirstlane(told[0] | told[1] | told[2] | told[3]) != 0 ? 0 : n_stages;
     read_a(split_smem, 2);
     read_b(split_smem, 0);
 
@@ -232,11 +315,11 @@ __global__ void __launch_bounds__(256, 2) identity_split_kernel(const MmlikeArgs
         }
     };
     if constexpr (DEPTH == 1) {
-        for (int s = 0; s < n_stages; ++s) stage(s, 0);
+        for (int s = 0; s < stages; ++s) stage(s, 0);
     } else {
         int s = 0;
-        for (; s + 1 < n_stages; s += 2) { stage(s, 0); stage(s + 1, 1); }
-        if (s < n_stages) stage(s, 0);
+        for (; s + 1 < stages; s += 2) { stage(s, 0); stage(s + 1, 1); }
+        if (s < stages) stage(s, 0);
     }
 
     f16v (&acc)[WM][WN] = sums[0];
@@ -255,36 +338,11 @@ __global__ void __launch_bounds__(256, 2) identity_split_kernel(const MmlikeArgs
 #pragma unroll
             for (int v = 0; v < 16; ++v) again |= !(__builtin_fabsf(acc[mi][ni][v]) <= 3.402823466e+38f);
     if (__syncthreads_or(again)) {
-#pragma unroll
-        for (int mi = 0; mi < WM; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < WN; ++ni)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
-#pragma unroll 1
-        for (int k = 0; k < K; k += 2) {
-            const bool in = k + lh < K;
-            const int64_t kk = in ? k + lh : K - 1;
-            float av[WM], bv[WN];
-#pragma unroll
-            for (int mi = 0; mi < WM; ++mi) {
-                const int r = (wr * WM + mi) * 32 + li;
-                const int64_t row = row0 + (r < rows_in ? r : rows_in - 1);
-                av[mi] = TA ? args.A[kk * args.lda + row] : args.A[row * args.lda + kk];
-                av[mi] = in ? av[mi] : 0.0f;
-            }
-#pragma unroll
-            for (int ni = 0; ni < WN; ++ni) {
-                const int c = (wc * WN + ni) * 32 + li;
-                const int64_t col = col0 + (c < cols_in ? c : cols_in - 1);
-                bv[ni] = TB ? args.B[col * args.ldb + kk] : args.B[kk * args.ldb + col];
-                bv[ni] = in ? bv[ni] : 0.0f;
-            }
-#pragma unroll
-            for (int mi = 0; mi < WM; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < WN; ++ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[mi], bv[ni], acc[mi][ni], 0, 0, 0);
-        }
+        // (from arguments and a thread's number that are opaque: nothing of it is held through the loop above)
+        auto at = (const __attribute__((address_space(4))) MmlikeArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        int t = tid;
+        asm volatile("" : "+s"(at), "+v"(t));
+        fp32_sums<WM, WN, TA, TB>(*at, t, row0, col0, acc);
     }
 
     // accumulator element v of lane l is R[8*(v/4) + 4*(l/32) + v%4][l%32] of its 32 x 32 block; a row of
@@ -319,7 +377,7 @@ __global__ void __launch_bounds__(256, 2) identity_split_kernel(const MmlikeArgs
 template <int WM, int WN, bool TA, bool TB>
 static hipError_t launch_layout(MmlikeArgs &a, int64_t grid, hipStream_t s)
 {
-    constexpr int LDS = 2 * SplitTile<WM, WN>::STAGE_BYTES;
+    constexpr int LDS = SplitTile<WM, WN>::LDS_BYTES;
     static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(&identity_split_kernel<WM, WN, TA, TB>),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (granted != hipSuccess) return granted;

@@ -108,6 +108,32 @@ def test_values_the_pieces_do_not_carry(am, M, N):
     assert bool(R[rest].isfinite().all())
 
 
+@pytest.mark.parametrize("tA,tB", [(False, False), (True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("M,N,pad,tile_rows", [(2047, 1921, 3, 128), (4095, 4001, 5, 256)])
+def test_where_the_second_way_begins(am, M, N, pad, tile_rows, tA, tB):
+    """One value that the pieces do not carry in some tiles, found in the first stage or at the end only, beside tiles
+    without one; remainders of K and of the tiles; every value of a block of rows."""
+    K = 300
+    g = torch.Generator(device="cuda").manual_seed(13)
+    A = operand(g, *((K, M) if tA else (M, K)), pad)
+    B = operand(g, *((N, K) if tB else (K, N)), pad)
+    a = A.T if tA else A
+    for i, k in enumerate([0, 11, 100, 128, 143, 200, 256, K - 1]):
+        a[256 * (i % 7) + 3 + i, k] = 1.2345e-40 * (i + 1)
+    a[M - 5:] *= 1e-36
+    a[M - 1, 7] = float("inf")
+    R = torch.full((M, N + pad), 0.5, device="cuda")[:, :N]
+    print("identity pieces second way", M, N, tA, tB, flush=True)
+    assert run(am, A, B, R, tA, tB) == tile_rows
+    ref, ab = exact(A, B, tA, tB)
+    rest = slice(0, M - 1)
+    # fp32 accumulators over K <= 300, one rounding per product where the tile is formed in fp32, and what R += rounds
+    err = (R[rest].double() - (ref[rest] + 0.5)).abs() - 2.0 ** -23 * (ref[rest] + 0.5).abs() - 2.0 ** -149
+    assert float((err / ab[rest]).max()) <= K * 2.0 ** -24
+    assert torch.equal(R[M - 1].double(), ref[M - 1])          # infinities and the NaN of 0 inf, where the products have them
+    assert bool(R[rest].isfinite().all())
+
+
 @pytest.mark.parametrize("M,N", [(2048, 2048), (4096, 4096)])
 @pytest.mark.parametrize("what", ["subnormal products", "subnormal pieces"])
 def test_subnormals_on_the_bf16_matrix_cores(am, what, M, N):
