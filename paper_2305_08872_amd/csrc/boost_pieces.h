@@ -148,7 +148,7 @@ struct BoostPieces {
             take_pieces(raw[2 * i], raw[2 * i + 1], p0, p1, p2);
             bp[0][i] = p0; bp[1][i] = p1; bp[2][i] = p2;
         }
-        constexpr int PA[6] = {2, 1, 1, 0, 0, 0}, PB[6] = {0, 0, 1, 1, 0, 2};
+        constexpr int PA[6] = {2, 1, 1, 0, 0, 0}, PB[6] = {0, 0, 1, 1, 2, 0};     // (the largest last)
 #pragma unroll
         for (int i = 0; i < 6; ++i)
             sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, ap[PA[i]]), __builtin_bit_cast(bf8, bp[PB[i]]), sum, 0, 0, 0);

@@ -1,14 +1,16 @@
 // Identity task (g = p, plain matmul; paper Sec. 6.1) in fp32 on the bf16 matrix cores, for problems that fill the chip.
 //
 // An fp32 value is the sum of three bf16 pieces exactly: the value rounded to 8 significant bits, what that leaves
-// (at most 16 bits) cut to 8, and the rest.  A product of two values is then the sum of nine piece products, each exact in
+// (at most 16 bits) rounded to 8, and the rest.  A product of two values is then the sum of nine piece products, each exact in
 // fp32, of which the six largest are formed here:
 //     a b  =  a0 b0 + (a0 b1 + a1 b0) + (a0 b2 + a1 b1 + a2 b0)  +  [a1 b2 + a2 b1 + a2 b2, left out]
-// With |a1| <= 2^-8 |a| and |a2| <= 2^-15 |a| what is left out is random in sign and 1.4e-8 |a b| on average, less than
-// the one rounding an fp32 product has.  v_mfma_f32_32x32x16_bf16 runs at sixteen times the rate of
-// v_mfma_f32_32x32x2_f32 and rounds the accumulators once where that one does 8 times: six of them are faster and no less
-// precise.  Relative error against 64 bits, fp32 matrix instructions / here, uniform values: K = 16 7.5e-8 / 3.2e-8, 256
-// 2.7e-7 / 2.3e-7, 4096 1.12e-6 / 0.99e-6; 3.7e-7 with two sets of accumulators (below).
+// With |a1| <= 2^-8 |a| and |a2| <= 2^-17 |a| what is left out is random in sign, 3e-9 |a b| on average and 2^-24 |a b| at most
+// (with a second piece that is cut, 9e-9 and 1.1e-7), beside the 2^-24 of an fp32 product's one rounding.
+// v_mfma_f32_32x32x16_bf16 runs at sixteen times the rate of v_mfma_f32_32x32x2_f32 and rounds the accumulators once where that
+// one does 8 times: six of them are faster, and over sums no less precise.  Relative error against 64 bits, fp32 matrix
+// instructions / here with one set of accumulators / with two (below), uniform values: K = 96 1.8e-7 / 1.4e-7 / 5.3e-8, 256 2.9e-7 / 2.3e-7 /
+// 8.1e-8, 1000 5.7e-7 / 4.8e-7 / 1.7e-7, 4096 1.15e-6 / - / 3.8e-7.  A product that stands alone in its sum -- A diagonal -- is rounded
+// once by the fp32 instruction, 2.1e-8 of it on average and 6.0e-8 at most; here 2.7e-8 and 1.5e-7, with two sets 2.2e-8 and 9.6e-8.
 //
 // What bounds it is power: at 4096^3 the matrix cores are busy 65 % of the time at a clock that has fallen to some
 // 1.75 GHz (the library's own bf16 product of that many operations runs at 1409 T/s, this kernel's six at 1290).
@@ -271,8 +273,8 @@ __global__ void __launch_bounds__(256, 2) identity_split_kernel(const MmlikeArgs
     __syncthreads();
     const u4 told = *(const u4 *)found;
     const int stages = __builtin_amdgcn_readfirstlane(told[0] | told[1] | told[2] | told[3]) != 0 ? 0 : n_stages;
-    read_a(split_smem, 2);
-    read_b(split_smem, 0);
+    read_a(split_smem, 1);
+    read_b(split_smem, 1);
 
     // One stage.  The six piece products in an order in which few pieces are live at a time, the fragments read a
     // product ahead; between the matrix instructions (some six vector instructions to each run in its shade) the next
@@ -282,20 +284,20 @@ __global__ void __launch_bounds__(256, 2) identity_split_kernel(const MmlikeArgs
     // instructions enough to cover the first reads of the next.
     auto stage = [&](int s, int d) {
         char *lds = split_smem + (s & 1) * TL::STAGE_BYTES, *other = split_smem + ((s + 1) & 1) * TL::STAGE_BYTES;
-        constexpr int PA[6] = {2, 1, 1, 0, 0, 0}, PB[6] = {0, 0, 1, 1, 0, 2};
+        constexpr int PA[6] = {1, 1, 2, 0, 0, 0}, PB[6] = {1, 0, 0, 1, 2, 0};     // (the largest last: a product that stands alone is rounded once)
         constexpr int BLOCKS = WM * WN, NM = 5 * BLOCKS, PAIRS = 4 * (UA + UB);   // (nothing to take apart during the last product)
 #pragma unroll
         for (int pq = 0; pq < 6; ++pq) {
-            if (pq == 0) read_a(lds, 1);
-            else if (pq == 1) read_b(lds, 1);
+            if (pq == 0) read_b(lds, 0);
+            else if (pq == 1) read_a(lds, 2);
             else if (pq == 2) read_a(lds, 0);
-            else if (pq == 4) read_b(lds, 2);
+            else if (pq == 3) read_b(lds, 2);
             else if (pq == 5) {
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();   // bare: the fence of __syncthreads() would drain the loads in flight
                 asm volatile("" ::: "memory");
-                read_a(other, 2);
-                read_b(other, 0);
+                read_a(other, 1);
+                read_b(other, 1);
             }
 #pragma unroll
             for (int m = 0; m < BLOCKS; ++m) {

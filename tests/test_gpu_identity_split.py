@@ -76,6 +76,22 @@ def test_no_less_precise_than_the_fp32_matrix_instruction(am, M, N, K):
         assert (R.double() - ref).norm() <= (F.double() - ref).norm()
 
 
+@pytest.mark.parametrize("size,most", [(2048, 1.02 * 2.0 ** -23), (4096, 1.5 * 2.0 ** -23)])
+def test_a_product_alone_in_its_sum(am, size, most):
+    """A row of A with one value: every result is one product, of which the pieces leave out at most 2^-24; the sum of the
+    rest is rounded once with two sets of accumulators (2048), and to an ulp by the matrix instruction with one (4096)."""
+    K = 128
+    g = torch.Generator(device="cuda").manual_seed(17)
+    A = torch.zeros(size, K, device="cuda")
+    A[torch.arange(size, device="cuda"), torch.randint(0, K, (size,), device="cuda", generator=g)] = torch.empty(size, device="cuda").uniform_(1, 2, generator=g)
+    B = torch.empty(K, size, device="cuda").normal_(generator=g)
+    R = torch.zeros(size, size, device="cuda")
+    run(am, A, B, R, False, False)
+    ref, ab = exact(A, B, False, False)
+    err = (R.double() - ref).abs() / ab
+    assert float(err.max()) <= most and float(err.mean()) <= 2.0 ** -25
+
+
 @pytest.mark.parametrize("M,N", [(2048, 2048), (4096, 4096)])
 def test_values_the_pieces_do_not_carry(am, M, N):
     """Small, subnormal and near-overflow values are as exact as any other; infinities and NaN reach the results that
