@@ -316,16 +316,17 @@ inline int64_t wide_k_range(int64_t waves, int64_t K)
 // us of a launch over tiles of 32 x 256 by workgroups of 8 waves, two to a compute unit, with the K split and the tail split
 // they choose: a pair on a unit takes `pair` us per k, one alone `alone`, a last round of parts in between `between`.  Where
 // neither split applies (one round and a bit, of a short K) the bit takes as long as the round.
-inline double wide_launch_us(int64_t M, int64_t N, int64_t K, double pair, double alone, double between)
+// (`units`: the device's, as the launchers ask for it too)
+inline double wide_launch_us(int64_t M, int64_t N, int64_t K, double pair, double alone, double between, int64_t units = compute_units())
 {
     const int64_t tiles = ((M + 31) / 32) * ((N + 255) / 256), range = wide_k_range(tiles * 8, K), parts = (K + range - 1) / range;
-    const int64_t W = (tiles + 7) / 8 * 8 * parts, rest = W % 512;     // (an XCD's share is what its units have to take)
-    const double us = 6.0 + 1.5 * (double)W / 256.0;
-    if (parts > 1) return us + (double)range * (pair * (double)(W / 512) + (rest == 0 ? 0.0 : rest <= 256 ? alone : between)) + (double)M * (double)N * (double)parts / 1.6e6;
+    const int64_t round = 2 * units, W = (tiles + 7) / 8 * 8 * parts, rest = W % round;     // (an XCD's share is what its units have to take)
+    const double us = 6.0 + 1.5 * (double)W / (double)units;
+    if (parts > 1) return us + (double)range * (pair * (double)(W / round) + (rest == 0 ? 0.0 : rest <= units ? alone : between)) + (double)M * (double)N * (double)parts / 1.6e6;
     TailSplit t;
-    if (!choose_tail_split(tiles, tiles, 512, K, 64, t)) return us + (double)K * (pair * (double)(W / 512) + (rest == 0 ? 0.0 : rest <= 256 ? alone : pair));
+    if (!choose_tail_split(tiles, tiles, round, K, 64, t)) return us + (double)K * (pair * (double)(W / round) + (rest == 0 ? 0.0 : rest <= units ? alone : pair));
     const int64_t region = (tiles - t.base) * t.splits;
-    return us + (double)K * pair * ((double)(t.base / 512) + (double)((region + 511) / 512) / t.splits * (1.0 + 0.01 * t.splits));
+    return us + (double)K * pair * ((double)(t.base / round) + (double)((region + round - 1) / round) / t.splits * (1.0 + 0.01 * t.splits));
 }
 // fp64: as many parts as fill the chip, in ranges of whole stages
 inline int64_t wide_k_range_f64(int64_t waves, int64_t K, int stage)

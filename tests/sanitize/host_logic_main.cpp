@@ -53,6 +53,14 @@ int main()
     CHECK(amulet_greedy_search(0, 3, grid_score, nullptr, &b0, &b1) == AMULET_ERR_DIM);
     CHECK(amulet_greedy_search(2, 2, nullptr, nullptr, &b0, &b1) == AMULET_ERR_NULL);
 
+    // ---- the wide kernels' estimate counts in the device's own units: as many rounds of them take as long
+    for (int64_t units : {32, 64, 128, 256})
+        for (int64_t tiles_per_unit : {16, 17, 35, 40}) {
+            const double here = amulet::wide_launch_us(32 * tiles_per_unit * units, 256, 1500, 0.19, 0.11, 0.17, units);
+            const double whole = amulet::wide_launch_us(32 * tiles_per_unit * 256, 256, 1500, 0.19, 0.11, 0.17, 256);
+            CHECK(here > whole * (1 - 1e-12) && here < whole * (1 + 1e-12));
+        }
+
     // ---- the register rule over a range of kernels
     for (int h = 1; h <= 16; ++h)
         for (int w = 1; w <= 64; w += 5)
