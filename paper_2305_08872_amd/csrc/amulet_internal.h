@@ -374,6 +374,17 @@ struct TileArgs {
     int block_base;  // added to blockIdx.x (launch_row_of_blocks)
 };
 
+// A kernel's arguments (its first parameter) and its thread's number, opaque: for a second way of forming a tile after a first one
+// that failed.  What both ways compute alike would else be held in registers through the first one's loop (BOOST's, 42 registers
+// more than there are).
+template <typename Args>
+__device__ __forceinline__ const __attribute__((address_space(4))) Args &opaque_args(unsigned &tid)
+{
+    auto at = (const __attribute__((address_space(4))) Args *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at), "+v"(tid));
+    return *at;
+}
+
 // How a tile-kernel launch covers its problem: tiles of 32 x 64 whose K four groups of two waves
 // share, or of 16 x 64 shared by eight waves, and the k ranges that follow.
 struct TilePlan {

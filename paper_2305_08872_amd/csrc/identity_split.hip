@@ -340,11 +340,9 @@ __global__ void __launch_bounds__(256, 2) identity_split_kernel(const MmlikeArgs
 #pragma unroll
             for (int v = 0; v < 16; ++v) again |= !(__builtin_fabsf(acc[mi][ni][v]) <= 3.402823466e+38f);
     if (__syncthreads_or(again)) {
-        // (from arguments and a thread's number that are opaque: nothing of it is held through the loop above)
-        auto at = (const __attribute__((address_space(4))) MmlikeArgs *)__builtin_amdgcn_kernarg_segment_ptr();
-        int t = tid;
-        asm volatile("" : "+s"(at), "+v"(t));
-        fp32_sums<WM, WN, TA, TB>(*at, t, row0, col0, acc);
+        unsigned t = tid;
+        const auto &same = opaque_args<MmlikeArgs>(t);
+        fp32_sums<WM, WN, TA, TB>(same, (int)t, row0, col0, acc);
     }
 
     // accumulator element v of lane l is R[8*(v/4) + 4*(l/32) + v%4][l%32] of its 32 x 32 block; a row of

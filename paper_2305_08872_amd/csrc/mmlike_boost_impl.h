@@ -6,32 +6,19 @@
 
 namespace amulet {
 
-// A workgroup's work on its tile, by pieces or by the wide kernel's own arithmetic.  False: the tile holds values that the
-// pieces do not take, and R is as it was.
-template <int TF, int TRANS, bool PIECES, typename Args>
-__device__ __forceinline__ bool boost_tile(const Args &args, const unsigned tid, BoostLds &L)
-{
-    constexpr int TASK = TASK_BOOST, TM = 4, NG = 1, NW = 8, BK = BOOST_BK, KA = 4;
-    constexpr bool ALDS = false, PIPE = false, BPRE = (TRANS & 1) == 0;
-    auto &Bs = L.b;
-    auto &Asl = *(float (*)[1][1][4])L.s;
-    auto done = [](bool whole) { return whole; };
-#include "mmlike_valu_tile.inc"
-}
-
-// A tile that has to be formed again is, from the start, with nothing of the first way in registers: the kernel's arguments and
-// the thread's number are opaque there, or what both ways compute alike is held through the first's loop (42 registers too many).
+// A tile by pieces, or, if it holds what they do not take, by the wide kernel's own arithmetic.
 template <int TF, int TRANS>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 mmlike_boost_kernel(const MmlikeArgs args)
 {
+    constexpr bool BPRE = (TRANS & 1) == 0;
     extern __shared__ __attribute__((aligned(16))) char boost_smem[];
     BoostLds &L = *(BoostLds *)boost_smem;
-    if (__builtin_expect(boost_tile<TF, TRANS, true>(args, threadIdx.x, L), true)) return;
-    auto at = (const __attribute__((address_space(4))) MmlikeArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    auto &no_a = *(float (*)[1][1][4])L.s;
+    if (valu_tile<TASK_BOOST, TF, TRANS, 4, 1, 8, BOOST_BK, 4, false, false, BPRE, true, false>(args, threadIdx.x, L.b, no_a)) return;
     unsigned tid = threadIdx.x;
-    asm volatile("" : "+s"(at), "+v"(tid));
-    boost_tile<TF, TRANS, false>(*at, tid, L);
+    const auto &again = opaque_args<MmlikeArgs>(tid);
+    valu_tile<TASK_BOOST, TF, TRANS, 4, 1, 8, BOOST_BK, 4, false, false, BPRE, false, false>(again, tid, L.b, no_a);
 }
 
 template <int TF, int TRANS>

@@ -125,16 +125,33 @@ __device__ __forceinline__ void fold4(float a, f4 b, const float *th, const floa
 // workgroup's 32 rows all fall into the same L2 sets they are evicted between the pieces.
 // PIPE (discount task, 4 x 4 micro-tile): a chunk runs as one software pipeline instead of k by k
 // (see the chunk loop); the launcher says when.
+template <int TASK, int TF, int TRANS, int TM, int NG, int NW, int BK, int KA, bool ALDS, bool PIPE, bool BPRE, bool PIECES, bool ROUNDED, typename Args>
+__device__ __forceinline__ bool valu_tile(const Args &args, const unsigned tid, float (&Bs)[2][BK][256 * NG],
+                                          float (&Asl)[ALDS ? 2 : 1][ALDS ? NW * TM : 1][ALDS ? BK + 4 : 4])
+{
+    constexpr bool SECOND = !PIECES && !ROUNDED;
+    auto done = [](bool whole) { return whole; };
+#include "mmlike_valu_tile.inc"
+}
+
 template <int TASK, int TF, int TRANS, int TM, int NG, int NW, int BK, int KA, bool ALDS, bool PIPE = false, bool BPRE = false>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(TM * NG == 4 ? 4 : 1)))
 mmlike_valu_kernel(const MmlikeArgs args)
 {
-    constexpr bool PIECES = false;       // (BOOST's plain sum on the matrix cores: mmlike_boost_impl.h)
-    const unsigned tid = threadIdx.x;
-    auto done = [](bool) {};
     __shared__ __attribute__((aligned(16))) float Bs[2][BK][256 * NG];
     __shared__ __attribute__((aligned(16))) float Asl[ALDS ? 2 : 1][ALDS ? NW * TM : 1][ALDS ? BK + 4 : 4];
+    if constexpr (TASK == TASK_COUNT_GT && TF != THRES_ELEM && TM == 4 && NG == 1) {
+        // by rounding, or all of the tile again by comparison
+        if (valu_tile<TASK, TF, TRANS, TM, NG, NW, BK, KA, ALDS, PIPE, BPRE, false, true>(args, threadIdx.x, Bs, Asl)) return;
+        unsigned tid = threadIdx.x;
+        const auto &again = opaque_args<MmlikeArgs>(tid);
+        valu_tile<TASK, TF, TRANS, TM, NG, NW, BK, KA, ALDS, PIPE, BPRE, false, false>(again, tid, Bs, Asl);
+    } else {
+        constexpr bool PIECES = false, ROUNDED = false, SECOND = false;
+        const unsigned tid = threadIdx.x;
+        auto done = [](bool) {};
 #include "mmlike_valu_tile.inc"
+    }
 }
 
 template <int TASK, int TF, int TM, int NG, int NW, int BK, int KA>
