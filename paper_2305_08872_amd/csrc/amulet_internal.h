@@ -376,12 +376,14 @@ struct TileArgs {
 
 // A kernel's arguments (its first parameter) and its thread's number, opaque: for a second way of forming a tile after a first one
 // that failed.  What both ways compute alike would else be held in registers through the first one's loop (BOOST's, 42 registers
-// more than there are).
+// more than there are); so would the thread's number itself, but for its wave's, in a scalar register.
+__device__ __forceinline__ unsigned own_wave() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 template <typename Args>
-__device__ __forceinline__ const __attribute__((address_space(4))) Args &opaque_args(unsigned &tid)
+__device__ __forceinline__ const __attribute__((address_space(4))) Args &opaque_args(unsigned wave, unsigned &tid)
 {
     auto at = (const __attribute__((address_space(4))) Args *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(at), "+v"(tid));
+    asm volatile("" : "+s"(at), "+s"(wave));
+    tid = wave * 64 + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     return *at;
 }
 

@@ -17,14 +17,21 @@
 // (NaN products: the clamp makes them 0, as not above.  An infinite threshold has g = 1.)
 //
 // It holds for thresholds of magnitudes 2^-40 to 2^24 (g >= 1: no b g loses bits) as long as no b g overflows, which the
-// kernels watch (b would have to be 2^105 times the threshold).  Tiles with other thresholds -- zero, smaller, larger, NaN
-// -- take the comparison.  (Zero with g = 2^64 needs every positive product to be at least 2^-64: with the smallest operands
-// looked for beside the staging 4096^3 took 2770 us, by comparison 2970, and the loop without that 2520 for 2340.)
+// kernels watch (b would have to be 2^105 times the threshold).  Tiles with other thresholds -- smaller, larger, NaN, zeros beside
+// others -- take the comparison.
+//
+// Where all thresholds of a tile are zero the wide kernel counts RN(a b) > 0, a b > 2^-150 (2^-150 itself ties to zero), in the same loop:
+//     t = clamp(fma(a', b', -2^47)),  a' b' = 2^197 a b,  s = 1
+// a b 2^150 is a multiple of 2^-47 around 1, so t is 1 above it, and 0 at it and below.  All of the factor, 2^99 and 2^98 one
+// after the other, goes on B as it is staged, whatever the thresholds face.  b' overflows from 2^-69 on, which is as good: times a nonzero
+// a it is infinite, t 1 or 0, and times zero NaN, t 0.  Except that a nonzero |a| below 2^-80 could make a product that rounds to zero:
+// the rows of A are read once ahead of the loop, and such a value sends the tile to the comparison.
 //
 // Bound: vector-ALU issue, 4.7 clocks per 64 products in a register-only loop (a in a scalar register) where multiply, subtract and the
-// sign bit shifted in take 6.5.  The wide kernel, us before / after: 4096^3 2970 / 2350, thresholds that face rows 2945 / 2600, one 2950 / 2270,
-// A transposed 3820 / 2960, B transposed 3020 / 2330; 2048^3 405 / 335.  Not for thresholds per output (a factor each).
-// The tile kernels, which read both operands from LDS and are bound there too, gain 4 to 18 % from 15 us on (mmlike_tile_impl.h).
+// sign bit shifted in take 6.5.  The wide kernel, us, by comparison / so / thresholds of zero: 4096^3 3110 / 2420 / 2380, thresholds that face
+// rows 3030 / 2750 / 2255, one 3030 / 2340 / 2240, A transposed 3820 / 2960, B transposed 3150 / 2420 / 2250; 2048^3 398 / 308 / 316, 1536^3 191 (in
+// the tile kernels) / 150 / 162.  Not for thresholds per output (a factor each).  The tile kernels, which read both operands from LDS and
+// are bound there too, gain 4 to 18 % from 15 us on (mmlike_tile_impl.h); they compare with zeros.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -34,6 +41,8 @@
 namespace amulet {
 
 constexpr float COUNT_ROUNDING_ZERO = 0x1p23f;
+constexpr float COUNT_ZERO_A = 0x1p98f, COUNT_ZERO_B = 0x1p99f, COUNT_ZERO_NEG = -0x1p47f;
+constexpr uint32_t COUNT_ZERO_LEAST = ((127u - 80u) << 24) - 1u;     // twice the bits of 2^-80, less 1 (a zero's are the largest)
 constexpr int COUNT_ROUNDING_K = (1 << 23) - 1;      // products a sum holds
 
 // g, s and -th g of a threshold; whether it has them

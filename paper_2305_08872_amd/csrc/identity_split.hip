@@ -340,8 +340,8 @@ __global__ void __launch_bounds__(256, 2) identity_split_kernel(const MmlikeArgs
 #pragma unroll
             for (int v = 0; v < 16; ++v) again |= !(__builtin_fabsf(acc[mi][ni][v]) <= 3.402823466e+38f);
     if (__syncthreads_or(again)) {
-        unsigned t = tid;
-        const auto &same = opaque_args<MmlikeArgs>(t);
+        unsigned t;
+        const auto &same = opaque_args<MmlikeArgs>(wave, t);
         fp32_sums<WM, WN, TA, TB>(same, (int)t, row0, col0, acc);
     }
 

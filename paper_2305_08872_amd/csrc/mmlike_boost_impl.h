@@ -15,10 +15,11 @@ mmlike_boost_kernel(const MmlikeArgs args)
     extern __shared__ __attribute__((aligned(16))) char boost_smem[];
     BoostLds &L = *(BoostLds *)boost_smem;
     auto &no_a = *(float (*)[1][1][4])L.s;
-    if (valu_tile<TASK_BOOST, TF, TRANS, 4, 1, 8, BOOST_BK, 4, false, false, BPRE, true, false>(args, threadIdx.x, L.b, no_a)) return;
-    unsigned tid = threadIdx.x;
-    const auto &again = opaque_args<MmlikeArgs>(tid);
-    valu_tile<TASK_BOOST, TF, TRANS, 4, 1, 8, BOOST_BK, 4, false, false, BPRE, false, false>(again, tid, L.b, no_a);
+    const unsigned wave = own_wave();
+    if (valu_tile<TASK_BOOST, TF, TRANS, 4, 1, 8, BOOST_BK, 4, false, false, BPRE, true, false, false>(args, threadIdx.x, L.b, no_a)) return;
+    unsigned tid;
+    const auto &again = opaque_args<MmlikeArgs>(wave, tid);
+    valu_tile<TASK_BOOST, TF, TRANS, 4, 1, 8, BOOST_BK, 4, false, false, BPRE, false, false, false>(again, tid, L.b, no_a);
 }
 
 template <int TF, int TRANS>

@@ -125,7 +125,7 @@ __device__ __forceinline__ void fold4(float a, f4 b, const float *th, const floa
 // workgroup's 32 rows all fall into the same L2 sets they are evicted between the pieces.
 // PIPE (discount task, 4 x 4 micro-tile): a chunk runs as one software pipeline instead of k by k
 // (see the chunk loop); the launcher says when.
-template <int TASK, int TF, int TRANS, int TM, int NG, int NW, int BK, int KA, bool ALDS, bool PIPE, bool BPRE, bool PIECES, bool ROUNDED, typename Args>
+template <int TASK, int TF, int TRANS, int TM, int NG, int NW, int BK, int KA, bool ALDS, bool PIPE, bool BPRE, bool PIECES, bool ROUNDED, bool ZERO, typename Args>
 __device__ __forceinline__ bool valu_tile(const Args &args, const unsigned tid, float (&Bs)[2][BK][256 * NG],
                                           float (&Asl)[ALDS ? 2 : 1][ALDS ? NW * TM : 1][ALDS ? BK + 4 : 4])
 {
@@ -141,13 +141,16 @@ mmlike_valu_kernel(const MmlikeArgs args)
     __shared__ __attribute__((aligned(16))) float Bs[2][BK][256 * NG];
     __shared__ __attribute__((aligned(16))) float Asl[ALDS ? 2 : 1][ALDS ? NW * TM : 1][ALDS ? BK + 4 : 4];
     if constexpr (TASK == TASK_COUNT_GT && TF != THRES_ELEM && TM == 4 && NG == 1) {
-        // by rounding, or all of the tile again by comparison
-        if (valu_tile<TASK, TF, TRANS, TM, NG, NW, BK, KA, ALDS, PIPE, BPRE, false, true>(args, threadIdx.x, Bs, Asl)) return;
-        unsigned tid = threadIdx.x;
-        const auto &again = opaque_args<MmlikeArgs>(tid);
-        valu_tile<TASK, TF, TRANS, TM, NG, NW, BK, KA, ALDS, PIPE, BPRE, false, false>(again, tid, Bs, Asl);
+        // by rounding; where every threshold of the tile is 0, by rounding too; or all of the tile again by comparison
+        const unsigned wave = own_wave();
+        if (valu_tile<TASK, TF, TRANS, TM, NG, NW, BK, KA, ALDS, PIPE, BPRE, false, true, false>(args, threadIdx.x, Bs, Asl)) return;
+        unsigned tid;
+        const auto &again = opaque_args<MmlikeArgs>(wave, tid);
+        if (valu_tile<TASK, TF, TRANS, TM, NG, NW, BK, KA, ALDS, PIPE, BPRE, false, true, true>(again, tid, Bs, Asl)) return;
+        const auto &last = opaque_args<MmlikeArgs>(wave, tid);
+        valu_tile<TASK, TF, TRANS, TM, NG, NW, BK, KA, ALDS, PIPE, BPRE, false, false, false>(last, tid, Bs, Asl);
     } else {
-        constexpr bool PIECES = false, ROUNDED = false, SECOND = false;
+        constexpr bool PIECES = false, ROUNDED = false, ZERO = false, SECOND = false;
         const unsigned tid = threadIdx.x;
         auto done = [](bool) {};
 #include "mmlike_valu_tile.inc"

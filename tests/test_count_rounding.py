@@ -68,6 +68,42 @@ def test_rounding_is_the_comparison():
     assert ties > 20 and 1000 < above < 5000
 
 
+def test_zero_by_rounding_is_the_comparison():
+    """The factors of a threshold of zero, in exact arithmetic rounded where the hardware rounds and infinite where fp32
+    overflows, against RN(a b) > 0: products around 2^-150, subnormal operands, and factors that overflow."""
+    rng = random.Random(6)
+    top = Fraction(2) ** 128
+
+    def up(x, e):       # x 2^e as fp32 has it: exact, or infinite
+        y = x * Fraction(2) ** e
+        return y if abs(y) < top else (None if y > 0 else -1)
+    near = seen = 0
+    for _ in range(6000):
+        ea = rng.randrange(-126, 127)
+        a = Fraction(rng.getrandbits(23) | 1 << 23) * Fraction(2) ** (ea - 23)
+        eb = rng.choice((-150 - ea + rng.randrange(-2, 3), rng.randrange(-149, 127)))
+        b = Fraction(rng.getrandbits(23) | 1 << 23) * Fraction(2) ** (eb - 23)
+        if rng.random() < 0.5:      # the partner that makes 2^-150, or its neighbours
+            b = round32(Fraction(2) ** -150 / a) * (1 + Fraction(rng.randrange(-1, 2), 2 ** 23))
+        b = Fraction(int(b * 2 ** 149), 2 ** 149)           # (fp32 below its normal numbers)
+        if not 0 < b < top:
+            continue
+        above = a * b > Fraction(2) ** -150
+        for first, then in ((99, 98), (98, None)):          # on B alone; on A, with 99 on B
+            if then is not None:
+                if a < Fraction(2) ** -80:
+                    continue
+                x, y = a, up(b, first)
+                y = None if y is None else up(y, then)
+            else:
+                x, y = up(a, 98), up(b, 99)
+            t = 1 if x is None or y is None else min(max(round32(x * y - Fraction(2) ** 47), Fraction(0)), Fraction(1))
+            assert t == (1 if above else 0), (float(a), float(b), first)
+            seen += 1
+        near += abs(a * b * Fraction(2) ** 150 - 1) < Fraction(1, 2 ** 20)
+    assert near > 500 and seen > 6000
+
+
 @pytest.fixture(scope="module")
 def am():
     if not torch.cuda.is_available():
@@ -156,6 +192,31 @@ def test_tile_kernels(am, form, tA, tB):
         check(am, A, B, T, form, tA, tB, -1, pad=pad)
         T.view(-1)[::3] = 0.0
         check(am, A, B, T, form, tA, tB, -1, pad=pad)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tA,tB", [(False, False), (True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("form", ("col", "row", "const"))
+def test_threshold_zero(am, form, tA, tB):
+    """Products at 2^-150 and next to it, subnormal operands, and factors whose scaled value overflows, against a threshold of
+    zero (of either sign) alone; then with values that leave it to the comparison, and with other thresholds beside it."""
+    f32 = lambda *v: torch.tensor(v, device="cuda")  # noqa: E731
+    odd = torch.tensor([1 + 2.0 ** -12, 1 + 2.0 ** -23, 1.7], dtype=torch.float32)
+    part = (1 / odd.double()).float()
+    part = torch.cat([part, torch.nextafter(part, torch.full_like(part, 9.0)), torch.nextafter(part, torch.zeros_like(part))])
+    a = torch.cat([odd.cuda() * 2.0 ** -75, f32(0.0, -0.0, -1.0, 2.0 ** -80, 2.0 ** -75, 1.5, -3e38, 1e30, 2.0 ** -79)])
+    b = torch.cat([part.cuda() * 2.0 ** -75, f32(0.0, 2.0 ** -149, -1e-45, 2.0 ** -70, 2.0 ** -71, 2.0 ** -75, 3e38, -1e30, 2.0 ** -126, 1.0)])
+    small = f32(1e-45, -2.0 ** -149, 2.0 ** -81, 1e-40)
+    for M, N, K, pad in SIZES + [(40, 260, 3, 1), (70, 300, 2100, 3)]:
+        g = torch.Generator(device="cuda").manual_seed(M + N + K)
+        T = some(g, f32(0.0, -0.0), thresholds(form, M, N))
+        for pool in (a, torch.cat([a, f32(float("inf"), -float("inf"), float("nan"))]), torch.cat([a, small])):
+            A, B = some(g, pool, (M, K)), some(g, b, (K, N))
+            want = None
+            for shape in (4, 5, 0):
+                want = check(am, A, B, T, form, tA, tB, shape, want, pad)
+        T.view(-1)[::3] = 0.5
+        check(am, A, B, T, form, tA, tB, 5, pad=pad)
 
 
 @pytest.mark.gpu
