@@ -260,8 +260,8 @@ static double boost_pieces_us(const MmlikeCall &c)
 // us of the count by rounding (count_rounding.h) in the wide kernel: a pair of workgroups on a compute unit takes 0.136 us per k, one
 // alone 0.08; with A transposed a third more, with thresholds that face rows 1.12 times that.  From 128 tiles on, us, tile kernel (by
 // rounding as well) / here: 1024^3 49 / 49.4, 1536^3 158 / 145, 256 x 4096^2 182 / 151, 4096 x 512 x 1024 94 / 82, 3262 x 288 x 5014 225 / 346;
-// thresholds of zero 1280^3 121 / 97, 1536^3 191 / 162, 256 x 4096^2 220 / 161; those that the rounding leaves to the comparison
-// 1536^3 191 / 195, 256 x 4096^2 220 / 207, 1280^3 121 / 128; below, the comparison is up to 17 % slower here (768^3 31.9 / 37.5), and
+// thresholds of zero 1536^3 170 / 162; those that the rounding leaves to the comparison, in
+// the tile kernels too, 1536^3 191 / 195, 256 x 4096^2 220 / 207, 1280^3 121 / 128; below, the comparison is up to 17 % slower here (768^3 31.9 / 37.5), and
 // nobody but the device knows which thresholds they are.  The estimate has
 // to be 4 % lower: 160 drawn calls of 2e8 products on, 1.115 times faster than by comparison, the better of the two each time 1.123, none slower.
 static double count_wide_us(const MmlikeCall &c)

@@ -20,18 +20,19 @@
 // kernels watch (b would have to be 2^105 times the threshold).  Tiles with other thresholds -- smaller, larger, NaN, zeros beside
 // others -- take the comparison.
 //
-// Where all thresholds of a tile are zero the wide kernel counts RN(a b) > 0, a b > 2^-150 (2^-150 itself ties to zero), in the same loop:
+// Where all thresholds of a tile are zero, RN(a b) > 0 is counted, a b > 2^-150 (2^-150 itself ties to zero), by the same two operations:
 //     t = clamp(fma(a', b', -2^47)),  a' b' = 2^197 a b,  s = 1
-// a b 2^150 is a multiple of 2^-47 around 1, so t is 1 above it, and 0 at it and below.  All of the factor, 2^99 and 2^98 one
-// after the other, goes on B as it is staged, whatever the thresholds face.  b' overflows from 2^-69 on, which is as good: times a nonzero
-// a it is infinite, t 1 or 0, and times zero NaN, t 0.  Except that a nonzero |a| below 2^-80 could make a product that rounds to zero:
-// the rows of A are read once ahead of the loop, and such a value sends the tile to the comparison.
+// a b 2^150 is a multiple of 2^-47 around 1, so t is 1 above it, and 0 at it and below.  The tile kernels put 2^98 on A and 2^99 on B
+// as they are read from LDS; what overflows there is as good infinite: times a nonzero factor t is 1 or 0, and times zero NaN, t 0.
+// In the wide kernel, whose A stays in scalar registers, both factors go on B as it is staged, one after the other.  b' then
+// overflows from 2^-69 on, and a nonzero |a| below 2^-80 could make a product that rounds to zero: the rows of A are read once
+// ahead of the loop, and such a value sends the tile to the comparison.
 //
 // Bound: vector-ALU issue, 4.7 clocks per 64 products in a register-only loop (a in a scalar register) where multiply, subtract and the
 // sign bit shifted in take 6.5.  The wide kernel, us, by comparison / so / thresholds of zero: 4096^3 3110 / 2420 / 2380, thresholds that face
 // rows 3030 / 2750 / 2255, one 3030 / 2340 / 2240, A transposed 3820 / 2960, B transposed 3150 / 2420 / 2250; 2048^3 398 / 308 / 316, 1536^3 191 (in
 // the tile kernels) / 150 / 162.  Not for thresholds per output (a factor each).  The tile kernels, which read both operands from LDS and
-// are bound there too, gain 4 to 18 % from 15 us on (mmlike_tile_impl.h); they compare with zeros.
+// are bound there too, gain 4 to 18 % from 15 us on, with thresholds of zero too (mmlike_tile_impl.h).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -34,7 +34,8 @@
 // FAST: the count by rounding (count_rounding.h), thresholds that face rows, columns or all: the factor is multiplied to four operands
 // of each k after they are read.  us, by comparison / so: 768^3 31.7 / 28.2, 1003 x 1501 x 777 66.3 / 58.2, 3262 x 288 x 5014 262 / 225, 640^3 20.7 /
 // 19.8, 128 x 4096 x 512 17.5 / 16.8, but 2048 x 300 x 200 14.6 / 14.8, 256^3 5.0 / 5.4: looking at the thresholds and the waves' words at the end take
-// 0.4 us, so from 15 us of plan on.
+// 0.4 us, so from 15 us of plan on.  Thresholds of zero have a loop of their own (a factor on both operands, none to look at): 768^3
+// 32.8 / 29.1, 1003 x 1501 x 777 68.0 / 60.9, 1536^3 facing rows 197 / 170.
 //
 // LDS layout of a group's stage: A, then B.  An operand whose lines run along k (row-major A, transposed B)
 // is kept as lines of 4 units, the other kind as k-rows of units.  16 lanes are served per clock: of A they
@@ -57,6 +58,8 @@ namespace amulet {
 
 typedef __attribute__((address_space(3))) void *tile_lds_ptr;
 extern __shared__ __attribute__((aligned(16))) char tile_smem[];
+
+enum { BY_COMPARISON = 0, BY_ROUNDING = 1, BY_ROUNDING_ZERO = 2 };     // how the count decides its predicate
 
 template <typename T> struct TileVec;
 template <> struct TileVec<float> { typedef float type __attribute__((ext_vector_type(4))); };
@@ -245,13 +248,18 @@ mmlike_tile_kernel(const TileArgs<T> args)
     // with its factor
     constexpr int NS = TF == THRES_ROW || TF == THRES_COL ? 4 : 1;
     T sum[4][4], gain[NS], sway[NS], most = 0;
-    bool quick = false;
+    bool quick = false, zero = false;
     if constexpr (FAST) {
-        bool every = args.kgroup <= COUNT_ROUNDING_K;
+        bool every = args.kgroup <= COUNT_ROUNDING_K, none = every;
         T neg[NS];
 #pragma unroll
-        for (int i = 0; i < NS; ++i) every = count_rounding(thr(TF == THRES_ROW ? i : 0, i), gain[i], sway[i], neg[i]) && every;
+        for (int i = 0; i < NS; ++i) {
+            const T t = thr(TF == THRES_ROW ? i : 0, i);
+            every = count_rounding(t, gain[i], sway[i], neg[i]) && every;
+            none = t == 0 && none;
+        }
         quick = __builtin_amdgcn_ballot_w64(!every) == 0;
+        zero = __builtin_amdgcn_ballot_w64(!none) == 0;
         if (quick)
 #pragma unroll
             for (int i = 0; i < NS; ++i) th[TF == THRES_ROW ? i : 0][TF == THRES_COL ? i : 0] = neg[i];
@@ -261,9 +269,20 @@ mmlike_tile_kernel(const TileArgs<T> args)
 #pragma unroll
             for (int c = 0; c < 4; ++c) sum[r][c] = COUNT_ROUNDING_ZERO;
     }
-    // one k of the lane's 4 x 4: the factors go on the operand that faces the thresholds
-    auto fast_k = [&](const T (&a)[4], const T (&b)[4]) {
-        if constexpr (FAST) {
+    // one k of the lane's 4 x 4: the factors go on the operand that faces the thresholds; a threshold of zero's on both, where
+    // an overflow is always as good as the value (count_rounding.h)
+    auto fast_k = [&](const T (&a)[4], const T (&b)[4], auto fast) {
+        if constexpr (FAST && decltype(fast)::value == BY_ROUNDING_ZERO) {
+            T x[4], y[4], neg[4], s[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { x[i] = a[i] * COUNT_ZERO_A; y[i] = b[i] * COUNT_ZERO_B; neg[i] = COUNT_ZERO_NEG; s[i] = 1; }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                count_by_rounding4(x[r], y, neg, s, sum[r]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else if constexpr (FAST) {
             constexpr bool ROW = TF == THRES_ROW;
             T x[4];
 #pragma unroll
@@ -313,7 +332,7 @@ mmlike_tile_kernel(const TileArgs<T> args)
                 T ak[4], bk[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { ak[i] = a_of(a, i, kk); bk[i] = b_of(b, kk, i); }
-                fast_k(ak, bk);
+                fast_k(ak, bk, fast);
                 side(kk);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -449,14 +468,20 @@ mmlike_tile_kernel(const TileArgs<T> args)
         auto k_loop = [&](auto fast) {
 #include "mmlike_tile_k_loop.inc"
         };
-        if (quick) {
-            k_loop(std::true_type());
+        auto counted = [&]() {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int c = 0; c < 4; ++c) part[r][c] = (int)(sum[r][c] - COUNT_ROUNDING_ZERO);
+        };
+        if (quick) {
+            k_loop(std::integral_constant<int, BY_ROUNDING>());
+            counted();
+        } else if (zero) {
+            k_loop(std::integral_constant<int, BY_ROUNDING_ZERO>());
+            counted();
         } else {
-            k_loop(std::false_type());
+            k_loop(std::integral_constant<int, BY_COMPARISON>());
         }
         // an operand left fp32 with its factor, in some wave: all of the tile again, by comparison.  (The ring is free but for what
         // waves still read ahead and never use.)
@@ -476,10 +501,10 @@ mmlike_tile_kernel(const TileArgs<T> args)
             __syncthreads();
 #pragma unroll
             for (int d = 0; d < NST; ++d) issue(d, d);
-            k_loop(std::false_type());
+            k_loop(std::integral_constant<int, BY_COMPARISON>());
         }
     } else {
-        constexpr std::false_type fast;
+        constexpr std::integral_constant<int, BY_COMPARISON> fast;
 #include "mmlike_tile_k_loop.inc"
     }
     auto result = [&](int r, int c) -> acc_t { return TASK == TASK_COUNT_GT || sizeof(T) == 8 ? part[r][c] : mainacc[r][c]; };
