@@ -235,8 +235,9 @@ static bool tile_runs(const Call &c)
 // lower.  Estimates in ns per k, two workgroups to a compute unit: a round of 128 x 128 tiles 85 (51.5 with
 // at most one to a unit, a fifth less after whole rounds; from 65 on with more), of 256 x 128 tiles 155 (78.5, 120); the fp32 kernels 0.232 per 128 x 128 outputs (in their finest tiles, 64 x 64),
 // a quarter more where they neither fill the chip nor have a K long enough to split.  us, fp32 kernels / 128 / 256:
-// 1536^3 74 / 75 / 122, 1792^3 111 / 87 / 141, 2048^3 128 / 106 / 161, 2048^2 x 128 15.5 / 14.8 / 19, 2304^3 204 / 168 / 180, 3072^3 419 / 379 / 391,
-// 1700^2 x 8000 357 / 370 / 600, 4096^3 942 / 697 / 637, 4096^2 x 128 46.7 / 40.6 / 39.6, 6000 x 3000 x 2000 530 / 414 / 442, 8192^2 x 1024 967 / 743 / 674.
+// 1536^3 73 / 76 / 124, 1792^3 110 / 89 / 143, 2048^3 129 / 108 / 163, 2048^2 x 128 17.0 / 17.0 / 21.6, 2304^3 208 / 167 / 184, 3072^3 436 / 388 / 391,
+// 1700^2 x 8000 371 / 374 / 612, 4096^3 956 / 723 / 654, 4096^2 x 128 46.7 / 41.3 / 39.7, 6000 x 3000 x 2000 539 / 433 / 457, 8192^2 x 1024 980 / 766 / 689
+// (operands that change from call to call).
 // The 256-row tile's one set of accumulators is as precise as the fp32 kernels' where those do not split K, the
 // 128-row tile's two sets three times as precise (512 x 8192^2, split: 1.1e-6 / 5.5e-7 / 1.5e-6): the 256-row
 // tile only where they do not.
@@ -248,7 +249,7 @@ static bool pieces_run(const MmlikeCall &c)
 // us of BOOST with its plain sum on the matrix cores: a pair of workgroups on a compute unit takes 0.188 us per k, one alone
 // 0.11; with A transposed a quarter more, with a threshold per output a tenth.  It is ahead of the wide kernel at every size and
 // layout that both run (1.1 to 1.4 times), and of the tile kernels from some 768^3 on, us, tile kernel / here: 512^3 15.1 / 28.0,
-// 1024^3 82 / 62, 1003 x 1501 x 777 96 / 78, 256 x 4096^2 313 / 221, 1536^3 270 / 199, 4096 x 512 x 8192 1232 / 863, but not where tiles
+// 1024^3 77 / 61, 1003 x 1501 x 777 96 / 78, 256 x 4096^2 305 / 220, 1536^3 260 / 198, 4096 x 512 x 8192 1185 / 866, but not where tiles
 // just miss a round of a short K or columns one of 256: 900 x 2100 x 500 72 / 99, 2699 x 261 x 2999 191 / 320.  The estimate
 // is within a tenth for three calls in four of 260 drawn ones; a plan of the tile kernels has to be 6 % slower than it,
 // which loses 3.7 % at most there and gains 1.9 % on average where 2.2 % was there to gain.

@@ -16,10 +16,11 @@
 // before the vector loop, whose B values are not live then (in between them, 45 registers too many).  Both sums are
 // partial over 64 k: then the matrix cores' goes through LDS into the lanes that own the outputs, the sum of both is added
 // to the main accumulators, and what that rounds away starts the next partial sum.  Error against 64 bits, wide kernel / here:
-// K = 64 1.5e-7 / 1.0e-7, 512 1.3e-7 / 8.6e-8, 2048 1.2e-7 / 6.0e-8, 4096 1.4e-7 / 5.1e-8 (tile kernels, 4096 x 512 x 8192: 7.7e-8 / 4.9e-8).
+// K = 64 1.5e-7 / 9.5e-8, 512 1.2e-7 / 7.9e-8, 2048 1.2e-7 / 5.7e-8 (tile kernels, 4096 x 512 x 8192: 7.7e-8 / 4.9e-8); of a product
+// that stands alone in its sum, on average 2.2e-8 / 2.7e-8 and at most 6.0e-8 / 1.5e-7, with its triggered part 2.4e-8 / 3.1e-8 and 7.9e-8 / 1.5e-7.
 //
-// us, wide kernel / here: 2048^3 533 / 415 (41 TFLOP/s), 4096^3 4205 / 3240, 8192^2 x 512 2130 / 1680; A transposed 603 / 473, B
-// transposed 568 / 441, thres[i][j] 569 / 438.  What bounds it: issue; a matrix instruction
+// us, wide kernel / here, operands that change from call to call: 2048^3 545 / 422 (40.7 TFLOP/s), 4096^3 4350 / 3370, 8192^2 x 512 2190 /
+// 1745; A transposed 582 / 484, B transposed 552 / 434, thres[i][j] 549 / 434.  What bounds it: issue; a matrix instruction
 // takes the second issue port for its 32 clocks (0.6 clocks per 64 products), taking B apart once per 32 rows as much
 // again, staging and barriers the rest of 6.4 clocks at 2.2 GHz.  DISCOUNT in this manner -- f sum p + (1 - f) sum of the p
 // <= th, the predicate a clamp too -- has three vector instructions for its four and was slower, 4297 / 4050 us at 4096^3.
