@@ -272,31 +272,33 @@ mmlike_tile_kernel(const TileArgs<T> args)
     // one k of the lane's 4 x 4: the factors go on the operand that faces the thresholds; a threshold of zero's on both, where
     // an overflow is always as good as the value (count_rounding.h)
     auto fast_k = [&](const T (&a)[4], const T (&b)[4], auto fast) {
-        if constexpr (FAST && decltype(fast)::value == BY_ROUNDING_ZERO) {
-            T x[4], y[4], neg[4], s[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { x[i] = a[i] * COUNT_ZERO_A; y[i] = b[i] * COUNT_ZERO_B; neg[i] = COUNT_ZERO_NEG; s[i] = 1; }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                count_by_rounding4(x[r], y, neg, s, sum[r]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else if constexpr (FAST) {
+        if constexpr (FAST) {
             constexpr bool ROW = TF == THRES_ROW;
-            T x[4];
+            if constexpr (decltype(fast)::value == BY_ROUNDING_ZERO) {
+                T x[4], y[4], neg[4], s[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[i] = (ROW ? a[i] : b[i]) * gain[i % NS];
-            most = __builtin_fmaxf(most, __builtin_fmaxf(__builtin_fabsf(x[0]), __builtin_fabsf(x[1])));
-            most = __builtin_fmaxf(most, __builtin_fmaxf(__builtin_fabsf(x[2]), __builtin_fabsf(x[3])));
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                T neg[4], s[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) { neg[c] = thr(r, c); s[c] = sway[ROW ? r : c % NS]; }
-                count_by_rounding4(ROW ? x[r] : a[r], ROW ? b : x, neg, s, sum[r]);
+                for (int i = 0; i < 4; ++i) { x[i] = a[i] * COUNT_ZERO_A; y[i] = b[i] * COUNT_ZERO_B; neg[i] = COUNT_ZERO_NEG; s[i] = 1; }
                 __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    count_by_rounding4(x[r], y, neg, s, sum[r]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                T x[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] = (ROW ? a[i] : b[i]) * gain[i % NS];
+                most = __builtin_fmaxf(most, __builtin_fmaxf(__builtin_fabsf(x[0]), __builtin_fabsf(x[1])));
+                most = __builtin_fmaxf(most, __builtin_fmaxf(__builtin_fabsf(x[2]), __builtin_fabsf(x[3])));
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    T neg[4], s[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) { neg[c] = thr(r, c); s[c] = sway[ROW ? r : c % NS]; }
+                    count_by_rounding4(ROW ? x[r] : a[r], ROW ? b : x, neg, s, sum[r]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         }
     };
