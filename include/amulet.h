@@ -515,7 +515,10 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K);
  * the fp32 kernels over sums of many products of like size; a product that stands
  * alone in its sum, as with a diagonal A, is within 1.8e-7 of itself and 3e-8 on
  * average, where those kernels' one rounding is 6e-8 and 2.1e-8.  A named shape
- * runs its own fp32 kernel).  The adaptive
+ * runs its own fp32 kernel); " critical_rows <64 or 128>" for a tile kernel in
+ * whose stead the fp64 discount task ran by critical values, on tiles of so many
+ * rows and 128 columns (the rows past its own are a launch of their own, of the
+ * tile kernels).  The adaptive
  * calls make one launch per trial and one for the rest.  Static storage of the
  * calling thread, until its next call of this function.
  */

@@ -30,6 +30,8 @@ SOURCES = ["amulet_api.hip", "mmlike_valu_identity_col.hip"] + [
     for task in ("discount", "boost", "count_gt")
     for form in ("col", "row", "const", "elem")
 ] + ["mmlike_boost_%s.hip" % form for form in ("col", "row", "const", "elem")] + [
+    "mmlike_critical_f64_%s.hip" % form for form in ("col", "const")
+] + [
     "mmlike_tile_%s_%s.hip" % (elem, task)
     for elem in ("f64", "f32")
     for task in ("discount", "boost", "count_gt")

@@ -153,6 +153,7 @@ struct KernelNote {
     int ring, registers, bypass;   // (join count)
     int64_t rows;
     int pieces;                    // (rows of a tile of the kernel on the matrix cores that stood in for the shape)
+    int critical;                  // (rows of a tile of the kernel by critical values that stood in for the tile kernel)
 };
 constexpr unsigned KERNEL_NOTES = 16;
 static thread_local KernelNote g_notes[KERNEL_NOTES];
@@ -160,7 +161,7 @@ static thread_local unsigned g_notes_made = 0;
 static KernelNote &new_note(int task, int f64, int shape, int64_t rows)
 {
     KernelNote &n = g_notes[g_notes_made++ % KERNEL_NOTES];
-    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, rows, 0};
+    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, rows, 0, 0};
     return n;
 }
 
@@ -305,7 +306,7 @@ static bool tile_wanted(const MmlikeCall &c, TilePlan &plan)
 {
     // us per k of one of two resident workgroups (tile kernels), and of a 32 x 256 workgroup
     static const double tile_us[4] = {0.0, 0.125, 0.130, 0.0955}, large_us[4] = {0.0, 0.115, 0.121, 0.0895};
-    plan.pieces = 0;
+    plan.pieces = plan.critical = 0;
     if (c.task == TASK_IDENTITY) return identity_split_wanted(c, plan);
     double pieces_us = -1.0;
     if (c.task == TASK_BOOST && pieces_run(c)) {
@@ -812,6 +813,12 @@ static int lookup_shape_f64(int task, int64_t M, int64_t N, int64_t K)
     return default_shape_f64(task, M, N);
 }
 
+// fp64 DISCOUNT by critical values: a threshold per column or one for all, a pair of columns, and (with what the
+// tile kernels ask for) offsets that fit 32 bits
+static bool critical_f64_runs(const F64Call &c)
+{
+    return c.task == TASK_DISCOUNT && (c.thres_form == THRES_COL || c.thres_form == THRES_CONST) && c.N >= 2 && tile_runs<double>(c);
+}
 // fp64: the tile kernels in place of the built-in `shape` (see tile_wanted).  They are ahead of the shape grid's
 // kernels nearly everywhere: TFLOP/s, grid / tile, 4096^3 discount 16.9 / 17.6, boost 16.4 / 18.0, count 22.4 / 24.3; us, 512^3
 // discount 40.5 / 22.8, 256^3 16.3 / 7.5, 1024^3 boost 139 / 128; but not in two cases: thres[i][j] leaves the tile kernel
@@ -819,15 +826,16 @@ static int lookup_shape_f64(int task, int64_t M, int64_t N, int64_t K)
 // kernel's workgroups (512^3 47 / 25 us, 2048^3 1185 / 1314), and rows of A a multiple of 256 KiB apart, whose
 // lines a stage of 8 k fetches in halves and the caches do not keep in between (discount 512^2 x 65536 2158 /
 // 2355 us; the count has room for it).
+static const double kTileUsF64[4] = {0.0, 0.251, 0.246, 0.172};
 static bool tile_wanted_f64(const F64Call &c, int shape, TilePlan &plan)
 {
-    static const double tile_us[4] = {0.0, 0.251, 0.246, 0.172};
     const bool per_output = c.thres_form == THRES_ELEM && ((c.M + 15) / 16) * ((c.N + 127) / 128) > 1024;
     const bool halves = c.task != TASK_COUNT_GT && !c.trans_a && c.lda % 32768 == 0;
     if (c.task == TASK_IDENTITY || per_output || halves || !tile_runs<double>(c)) return false;
     const int waves = shape % F64_TILES == 1 ? 8 : 4;
     const int64_t range = wide_k_range_f64((c.M + 4 * waves - 1) / (4 * waves) * ((c.N + 127) / 128) * waves, c.K, 16);
-    plan = choose_tile_plan<double>(c.M, c.N, c.K, tile_us[c.task], (c.K + range - 1) / range, c.thres_form == THRES_ELEM);
+    plan = choose_tile_plan<double>(c.M, c.N, c.K, kTileUsF64[c.task], (c.K + range - 1) / range, c.thres_form == THRES_ELEM);
+    if (critical_f64_runs(c)) choose_critical_f64(c.M, c.N, c.K, kTileUsF64[c.task], compute_units(), plan);
     return true;
 }
 
@@ -840,7 +848,8 @@ static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, v
     if (c.thres_form == THRES_ROW && c.thres) sub.thres = c.thres + r0;
     if (c.thres_form == THRES_ELEM && c.thres) sub.thres = c.thres + r0 * c.ldt;
     sub.R = c.R + r0 * c.ldr;
-    if (tile && tile_runs<double>(sub)) {
+    const bool critical = tile && tile->critical && critical_f64_runs(sub);
+    if (tile && !critical && tile_runs<double>(sub)) {
         g_last_hip_error = launch_tile_call<double>(sub, *tile, (hipStream_t)stream);
         return g_last_hip_error == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
     }
@@ -856,8 +865,26 @@ static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, v
     a.vecA = (aligned16(a.A) && c.lda % 2 == 0) ? 1 : 0;
     a.kchunk = (int)c.K;
     a.tail_base = 0; a.tail_blocks = 0; a.tail_splits = 1; a.block_base = 0;
-    new_note(c.task, 1, shape, rows);
-    const hipError_t e = launch_mmlike_f64(c.task, c.thres_form, shape, a, (hipStream_t)stream);
+    KernelNote &note = new_note(c.task, 1, shape, rows);
+    hipError_t e;
+    if (critical) {
+        // (a slab of an adaptive call: all of it)
+        const int64_t first = rows == c.M ? tile->rest : rows;
+        // (told as the plan it stands in for)
+        note.shape = -1; note.rows = first; note.critical = tile->critical;
+        note.tile = tile->wide; note.parts = tile->parts; note.kpart = tile->kpart; note.kgroup = tile->kgroup;
+        a.M = (int)first;
+        e = c.thres_form == THRES_COL ? launch_mmlike_critical_f64<THRES_COL>(a, tile->critical, (hipStream_t)stream)
+                                      : launch_mmlike_critical_f64<THRES_CONST>(a, tile->critical, (hipStream_t)stream);
+        if (e == hipSuccess && first < rows) {
+            sub.M = rows - first;
+            sub.A = c.trans_a ? sub.A + first : sub.A + first * c.lda;
+            sub.R += first * c.ldr;
+            e = launch_tile_call<double>(sub, choose_tile_plan<double>(sub.M, c.N, c.K, kTileUsF64[c.task], tile->rest_parts), (hipStream_t)stream);
+        }
+    } else {
+        e = launch_mmlike_f64(c.task, c.thres_form, shape, a, (hipStream_t)stream);
+    }
     g_last_hip_error = e;
     return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
 }
@@ -1663,7 +1690,7 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K)
 
 const char *amulet_recent_kernel(int back)
 {
-    static thread_local char text[160];
+    static thread_local char text[192];
     text[0] = 0;
     if (back < 0 || back >= (int)KERNEL_NOTES || (unsigned)back >= g_notes_made) return text;
     const KernelNote &n = g_notes[(g_notes_made - 1 - (unsigned)back) % KERNEL_NOTES];
@@ -1679,8 +1706,9 @@ const char *amulet_recent_kernel(int back)
         snprintf(text, sizeof(text), "i8_tile_%s%s%s%s rows %lld parts %d kpart %d kgroup %d", tiles[n.tile], n.ring ? "_ring6" : "",
                  n.registers ? "_registers" : "", n.bypass ? "_bypass" : "", rows, n.parts, n.kpart, n.kgroup);
     } else {
-        snprintf(text, sizeof(text), "%s_tile_%s rows %lld parts %d kpart %d kgroup %d", n.f64 ? "f64" : "f32", n.tile ? "32x64" : "16x64",
-                 rows, n.parts, n.kpart, n.kgroup);
+        const int len = snprintf(text, sizeof(text), "%s_tile_%s rows %lld parts %d kpart %d kgroup %d", n.f64 ? "f64" : "f32", n.tile ? "32x64" : "16x64",
+                                 rows, n.parts, n.kpart, n.kgroup);
+        if (n.critical) snprintf(text + len, sizeof(text) - (size_t)len, " critical_rows %d", n.critical);
     }
     return text;
 }

@@ -397,6 +397,10 @@ struct TilePlan {
     // instead of a tile kernel, a kernel that shares its sums with the bf16 matrix cores: the identity task's
     // (identity_split.hip), rows of its tile; BOOST's (mmlike_boost_impl.h), 32; 0: neither
     int pieces;
+    // fp64 DISCOUNT by critical values (mmlike_critical_f64_impl.h): rows of its tile, 0: not so; the rows from `rest` on
+    // are the tile kernels', whose K has at most rest_parts parts
+    int critical;
+    int64_t rest, rest_parts;
 };
 
 // The plan with the lowest estimated time.  A compute unit holds two workgroups (16 waves) and is
@@ -420,7 +424,7 @@ inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_
 {
     constexpr int V = 16 / (int)sizeof(T);
     auto up = [](int64_t n, int64_t to) { return (n + to - 1) / to * to; };
-    TilePlan best = {0, 0, 0, 0, 0.0, 0};
+    TilePlan best = {0, 0, 0, 0, 0.0, 0, 0, 0, 0};
     for (int wide = 0; wide < 2; ++wide) {
         const int rows = wide ? 32 : 16, groups = wide ? 4 : 8;
         const int64_t grid = xcd_grid((M + rows - 1) / rows, (N + 63) / 64);
@@ -438,6 +442,39 @@ inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_
         }
     }
     return best;
+}
+
+// us of fp64 DISCOUNT by critical values (mmlike_critical_f64_impl.h) on tiles of 64 x 128, two workgroups to a compute unit, or of
+// 128 x 128, one: a pair takes 0.452 us per k, one alone 0.255, a large one 0.41, and 3.2 or 11.5 us per round for its first loads and
+// its write-back.  Within 3 % and 4 % (rms) of 130 drawn calls of 2^27 to 2^35 products, all layouts.
+inline double critical_f64_us(int64_t M, int64_t N, int64_t K, int rows, int64_t units)
+{
+    const int64_t W = xcd_grid((M + rows - 1) / rows, (N + 127) / 128), slots = rows == 64 ? 2 * units : units, rest = W % slots;
+    const double full = (double)(W / slots), all = full + (rest ? 1.0 : 0.0);
+    if (rows == 64) return 5.9 + 3.2 * all + (double)K * (0.4515 * full + (rest == 0 ? 0.0 : rest <= units ? 0.255 : 0.4515));
+    return 11.5 * all + 0.41 * (double)K * all;
+}
+// The plan `tile` of the tile kernels, or that kernel for all rows, or for as many as fill whole rounds (the small tile: and half a
+// round), and the tile kernels for the others: what is estimated lowest, by 3 % at least.  The other rows' K has no more parts than
+// the tile kernels' plan for all of them.
+inline void choose_critical_f64(int64_t M, int64_t N, int64_t K, double us_per_k, int64_t units, TilePlan &tile)
+{
+    const int64_t parts = tile.parts, tiles_n = (N + 127) / 128;
+    double best = 0.97 * tile.us;
+    for (int rows = 64; rows <= 128; rows += 64) {
+        auto take = [&](int64_t first) {
+            if (first < M && M - first < 16) return;      // (fewer than the tile kernels take in some layouts)
+            double us = critical_f64_us(first, N, K, rows, units);
+            if (first < M) us += choose_tile_plan<double>(M - first, N, K, us_per_k, parts).us;
+            if (us < best) { best = us; tile.critical = rows; tile.rest = first; tile.rest_parts = parts; }
+        };
+        take(M);
+        const int64_t half = units, W = xcd_grid((M + rows - 1) / rows, tiles_n), step = rows == 64 ? half : units;
+        for (int64_t full = W / step * step; full > 0 && full + 2 * step > W; full -= step) {
+            const int64_t first = full / tiles_n * rows;        // (xcd_grid pads to eights, and so do these)
+            if (first > 0 && first < M) take(first);
+        }
+    }
 }
 
 // From this estimate on the tile kernels count by rounding, in 0.88 of it (mmlike_tile_impl.h)
@@ -601,6 +638,9 @@ struct MmlikeArgsF64 {
     int tail_base, tail_blocks, tail_splits;   // as in MmlikeArgs
     int block_base;   // added to blockIdx.x (launch_row_of_blocks)
 };
+// DISCOUNT by critical values (mmlike_critical_f64_impl.h), tiles of `rows` (64 or 128) x 128
+template <int TF>
+hipError_t launch_mmlike_critical_f64(const MmlikeArgsF64 &a, int rows, hipStream_t s);
 // predicate tasks: vector-ALU kernel; identity task: fp64 matrix-core kernel
 // fp64 shapes of the predicate tasks: a small grid of the same two axes as the fp32 one
 // (k axis: K whole, in 2, in 4 parts per tile; tile: 16 x 128 with 4 waves, 32 x 128 with 8).
