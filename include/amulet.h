@@ -509,9 +509,9 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K);
  * through registers, _bypass: R around the caches); then " rows <rows of R>", and
  * for a tile kernel " parts <workgroups per tile, each over a range of K> kpart
  * <k of such a range> kgroup <k of it that a group of waves sums>"; and for the
- * identity and boost tasks " bf16_pieces 3 tile_rows <32, 128 or 256>" where a
+ * identity and boost tasks " bf16_pieces 3 tile_rows <32, 64, 128 or 256>" where a
  * kernel that forms plain sums on the bf16 matrix cores stood in for the shape
- * (larger problems; three bf16 pieces per value, fp32 sums: no less precise than
+ * (larger problems, and few tiles of a long K; three bf16 pieces per value, fp32 sums: no less precise than
  * the fp32 kernels over sums of many products of like size; a product that stands
  * alone in its sum, as with a diagonal A, is within 1.8e-7 of itself and 3e-8 on
  * average, where those kernels' one rounding is 6e-8 and 2.1e-8.  A named shape

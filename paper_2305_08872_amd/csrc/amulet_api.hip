@@ -272,6 +272,22 @@ static double count_wide_us(const MmlikeCall &c)
     const double more = (c.trans_a ? 1.32 : 1.03) * (c.thres_form == THRES_ROW ? 1.12 : 1.0);
     return wide_launch_us(c.M, c.N, c.K, more * 0.136, more * 0.08, more * 0.125) / 0.96;
 }
+// Identity of few tiles: the bf16-piece kernel whose waves share K (identity_split_waves.hip). us: 2, 4.6 per round of 256 tiles of 64 x 64, and per
+// 1000 k 8.6 or 0.0423 per tile of the round (they share the L2s and the power), 5.5 % more per operand stored along k and 13 % more
+// again if its lines are not a whole number of 64 bytes; the fp32 kernels 7 and 0.0656 per tile. Within 6 % and 7 % (rms) of 110 drawn calls of 63 to
+// 1056 tiles, K = 192 to 5900; a tenth lower, and from 480 k on, it is ahead in all of them (1.01 to 1.34), 1.2 of them on average, and
+// what it leaves loses 1 % more than the better of the two each time.
+static bool identity_waves_wanted(const MmlikeCall &c, TilePlan &plan)
+{
+    if (c.K < 480 || (c.trans_a && c.M < 4) || (!c.trans_b && c.N < 4)) return false;
+    const int64_t tiles = ((c.M + 63) / 64) * ((c.N + 63) / 64), units = compute_units(), places = (tiles + 7) / 8 * 8, full = places / units, rest = places % units;
+    auto more = [](bool along, int64_t ld) { return along ? 0.055 + (ld % 16 != 0 ? 0.13 : 0.0) : 0.0; };
+    const double per_k = (1.0 + more(!c.trans_a, c.lda) + more(c.trans_b, c.ldb)) * (double)c.K * 1e-3;
+    auto round = [&](int64_t n) { const double us = 0.0423 * (double)n; return 4.6 + per_k * (us < 8.6 ? 8.6 : us); };
+    const double here = 2.0 + (double)full * round(units) + (rest ? round(full && rest < 100 ? 100 : rest) : 0.0);
+    plan.pieces = 64;
+    return here < 0.9 * (7.0 + 0.0656e-3 * (double)c.K * (double)tiles);
+}
 static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
 {
     if (c.K < 96 || !pieces_run(c)) return false;
@@ -290,7 +306,8 @@ static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
     plan.pieces = t256 < t128 && !fp32_splits ? 256 : 128;
     // (420 drawn calls, all layouts: ahead by 7.8 % on average; without a margin calls with A alone transposed, short K or a
     // ragged last round lost up to 7 %)
-    return (plan.pieces == 256 ? t256 : t128) < (c.trans_a && !c.trans_b ? 0.91 : 0.97) * fp32;
+    if ((plan.pieces == 256 ? t256 : t128) < (c.trans_a && !c.trans_b ? 0.91 : 0.97) * fp32) return true;
+    return identity_waves_wanted(c, plan);
 }
 
 // fp32: the tile kernels, unless the 32 x 256 kernel's estimate is lower.  That kernel takes twice the
@@ -353,7 +370,7 @@ static int run_mmlike(const MmlikeCall &c, int shape, void *stream, const TilePl
     hipError_t e;
     if (tile && tile->pieces && pieces_run(c)) {
         note.pieces = tile->pieces;
-        if (c.task == TASK_IDENTITY) e = launch_identity_split(a, tile->pieces, s);
+        if (c.task == TASK_IDENTITY) e = tile->pieces == 64 ? launch_identity_split_waves(a, s) : launch_identity_split(a, tile->pieces, s);
         else if (c.thres_form == THRES_COL) e = launch_mmlike_boost<THRES_COL>(a, s);
         else if (c.thres_form == THRES_ROW) e = launch_mmlike_boost<THRES_ROW>(a, s);
         else if (c.thres_form == THRES_CONST) e = launch_mmlike_boost<THRES_CONST>(a, s);

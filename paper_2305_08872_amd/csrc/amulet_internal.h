@@ -610,6 +610,8 @@ hipError_t launch_identity_mfma(const MmlikeArgs &a, int variant, hipStream_t s)
 bool identity_dma_eligible(const MmlikeArgs &a);
 // the identity task from bf16 pieces (identity_split.hip): tiles of tile_rows (128 or 256) x 128
 hipError_t launch_identity_split(const MmlikeArgs &a, int tile_rows, hipStream_t s);
+// ... for problems of few tiles, of 64 x 64 (identity_split_waves.hip)
+hipError_t launch_identity_split_waves(const MmlikeArgs &a, hipStream_t s);
 bool identity_split_runs(bool trans_a, bool trans_b, int64_t K, int64_t lda, int64_t ldb);
 constexpr int ID_SMALL_STAGES = 4;   // ring depth of the streamed 64 x 64 tiles (fp32 and fp64)
 hipError_t enqueue_identity_dma(const MmlikeArgs &a, int tile, int nstage, unsigned grid_x, unsigned grid_y, hipStream_t s);
