@@ -30,7 +30,7 @@ SOURCES = ["amulet_api.hip", "mmlike_valu_identity_col.hip"] + [
     for task in ("discount", "boost", "count_gt")
     for form in ("col", "row", "const", "elem")
 ] + ["mmlike_boost_%s.hip" % form for form in ("col", "row", "const", "elem")] + [
-    "mmlike_critical_f64_%s.hip" % form for form in ("col", "const")
+    "mmlike_critical_f64_%s.hip" % name for name in ("discount_col", "discount_const", "boost", "count_gt")
 ] + [
     "mmlike_tile_%s_%s.hip" % (elem, task)
     for elem in ("f64", "f32")

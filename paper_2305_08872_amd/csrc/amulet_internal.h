@@ -397,7 +397,7 @@ struct TilePlan {
     // instead of a tile kernel, a kernel that shares its sums with the bf16 matrix cores: the identity task's
     // (identity_split.hip), rows of its tile; BOOST's (mmlike_boost_impl.h), 32; 0: neither
     int pieces;
-    // fp64 DISCOUNT by critical values (mmlike_critical_f64_impl.h): rows of its tile, 0: not so; the rows from `rest` on
+    // fp64 tasks by mmlike_critical_f64_impl.h: rows of its tile, 0: not so; the rows from `rest` on
     // are the tile kernels', whose K has at most rest_parts parts
     int critical;
     int64_t rest, rest_parts;
@@ -444,32 +444,39 @@ inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_
     return best;
 }
 
-// us of fp64 DISCOUNT by critical values (mmlike_critical_f64_impl.h) on tiles of 64 x 128, two workgroups to a compute unit, or of
-// 128 x 128, one: a pair takes 0.452 us per k, one alone 0.255, a large one 0.41, and 3.2 or 11.5 us per round for its first loads and
-// its write-back.  Within 3 % and 4 % (rms) of 130 drawn calls of 2^27 to 2^35 products, all layouts.
-inline double critical_f64_us(int64_t M, int64_t N, int64_t K, int rows, int64_t units)
+// us of mmlike_critical_f64_impl.h's kernels: tiles of 64 x 128 (DISCOUNT, BOOST) or 128 x 128 (COUNT), two workgroups to a compute
+// unit, a pair of which takes `pair` us per k and one alone `alone`, with `ends` per round for first loads and write-back; or DISCOUNT
+// on 128 x 128, one.  Within 3 to 4 % (rms) of 35 to 130 drawn calls per task of 2^26 to 2^35 products, all layouts.
+inline double critical_f64_us(int task, int64_t M, int64_t N, int64_t K, int rows, int64_t units)
 {
-    const int64_t W = xcd_grid((M + rows - 1) / rows, (N + 127) / 128), slots = rows == 64 ? 2 * units : units, rest = W % slots;
+    struct Cost { double pair, alone, ends; };
+    static const Cost cost[4] = {{}, {0.463, 0.262, 3.2}, {0.422, 0.233, 1.6}, {0.475, 0.286, 5.6}};
+    const bool pairs = task != TASK_DISCOUNT || rows == 64;
+    const int64_t W = xcd_grid((M + rows - 1) / rows, (N + 127) / 128), slots = pairs ? 2 * units : units, rest = W % slots;
     const double full = (double)(W / slots), all = full + (rest ? 1.0 : 0.0);
-    if (rows == 64) return 5.9 + 3.2 * all + (double)K * (0.4515 * full + (rest == 0 ? 0.0 : rest <= units ? 0.255 : 0.4515));
-    return 11.5 * all + 0.41 * (double)K * all;
+    if (!pairs) return 11.5 * all + 0.42 * (double)K * all;
+    const Cost &c = cost[task];
+    return 5.9 + c.ends * all + (double)K * (c.pair * full + (rest == 0 ? 0.0 : rest <= units ? c.alone : c.pair));
 }
+// K of a count: 15/8 per product over its threshold, exact in fp32
+constexpr int64_t C64_COUNT_K = (int64_t)1 << 20;
 // The plan `tile` of the tile kernels, or that kernel for all rows, or for as many as fill whole rounds (the small tile: and half a
 // round), and the tile kernels for the others: what is estimated lowest, by 3 % at least.  The other rows' K has no more parts than
 // the tile kernels' plan for all of them.
-inline void choose_critical_f64(int64_t M, int64_t N, int64_t K, double us_per_k, int64_t units, TilePlan &tile)
+inline void choose_critical_f64(int task, int64_t M, int64_t N, int64_t K, double us_per_k, int64_t units, TilePlan &tile)
 {
     const int64_t parts = tile.parts, tiles_n = (N + 127) / 128;
     double best = 0.97 * tile.us;
-    for (int rows = 64; rows <= 128; rows += 64) {
+    for (int rows = task == TASK_COUNT_GT ? 128 : 64; rows <= (task == TASK_BOOST ? 64 : 128); rows += 64) {
         auto take = [&](int64_t first) {
             if (first < M && M - first < 16) return;      // (fewer than the tile kernels take in some layouts)
-            double us = critical_f64_us(first, N, K, rows, units);
+            double us = critical_f64_us(task, first, N, K, rows, units);
             if (first < M) us += choose_tile_plan<double>(M - first, N, K, us_per_k, parts).us;
             if (us < best) { best = us; tile.critical = rows; tile.rest = first; tile.rest_parts = parts; }
         };
         take(M);
-        const int64_t half = units, W = xcd_grid((M + rows - 1) / rows, tiles_n), step = rows == 64 ? half : units;
+        // (a whole round, or with two workgroups to a unit half a one)
+        const int64_t W = xcd_grid((M + rows - 1) / rows, tiles_n), step = units;
         for (int64_t full = W / step * step; full > 0 && full + 2 * step > W; full -= step) {
             const int64_t first = full / tiles_n * rows;        // (xcd_grid pads to eights, and so do these)
             if (first > 0 && first < M) take(first);
@@ -640,8 +647,9 @@ struct MmlikeArgsF64 {
     int tail_base, tail_blocks, tail_splits;   // as in MmlikeArgs
     int block_base;   // added to blockIdx.x (launch_row_of_blocks)
 };
-// DISCOUNT by critical values (mmlike_critical_f64_impl.h), tiles of `rows` (64 or 128) x 128
-template <int TF>
+// DISCOUNT and COUNT by critical values, BOOST by a clamp (mmlike_critical_f64_impl.h), tiles of `rows` x 128: DISCOUNT 64 or 128,
+// COUNT 128, BOOST 64
+template <int TASK, int TF>
 hipError_t launch_mmlike_critical_f64(const MmlikeArgsF64 &a, int rows, hipStream_t s);
 // predicate tasks: vector-ALU kernel; identity task: fp64 matrix-core kernel
 // fp64 shapes of the predicate tasks: a small grid of the same two axes as the fp32 one

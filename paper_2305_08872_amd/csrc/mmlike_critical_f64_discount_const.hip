@@ -2,5 +2,5 @@
 #include "mmlike_critical_f64_impl.h"
 
 namespace amulet {
-template hipError_t launch_mmlike_critical_f64<2>(const MmlikeArgsF64 &, int, hipStream_t);
+template hipError_t launch_mmlike_critical_f64<1, 2>(const MmlikeArgsF64 &, int, hipStream_t);
 }
