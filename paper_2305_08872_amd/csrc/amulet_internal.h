@@ -260,10 +260,10 @@ inline int choose_full_split(int64_t part_tiles, int64_t units_per_xcd, int64_t 
 // adds its atomic adds, which the L2s retire at about 0.42 T per second for the whole chip:
 // `atom_per_tile` (16384 adds: 0.68 / 0.34) x tiles x s (measured: 256 tiles in 2 ranges + 20 us,
 // 64 tiles in 8 ranges + 23 us).  The s <= 1024 with at least 128 k per range and the lowest
-// estimate is returned (1: do not split).  Checked against sweeps of s = 1..8 at 64 ... 1536 tiles
+// estimate is returned (1: do not split), the estimate in `lowest`.  Checked against sweeps of s = 1..8 at 64 ... 1536 tiles
 // (K = 512 ... 4096): the chosen s is the best or within 3 % of the best one measured.
 inline int choose_stream_split(int64_t part_tiles, int64_t units, int64_t K, int cap, const double *rate,
-                               double ovh_alone = 50.0, double atom_per_tile = 0.68)
+                               double ovh_alone = 50.0, double atom_per_tile = 0.68, double *lowest = nullptr)
 {
     if (!k_split_allowed() || part_tiles <= 0 || units <= 0) return 1;
     const int max_s = K / 128 < 1024 ? (int)(K / 128) : 1024;
@@ -286,6 +286,7 @@ inline int choose_stream_split(int64_t part_tiles, int64_t units, int64_t K, int
         if (sp > 1) cost += atom_per_tile * (double)(part_tiles * 8) * sp;
         if (sp == 1 || cost < best * 0.99) { best = cost; best_s = sp; }
     }
+    if (lowest) *lowest = best;
     return best_s;
 }
 
@@ -659,7 +660,7 @@ hipError_t launch_mmlike_f64(int task, int form, int shape, const MmlikeArgsF64 
 hipError_t launch_identity_mfma_f64(const MmlikeArgsF64 &a, int tile, hipStream_t s);
 // the streamed fp64 identity kernel (identity_mfma_f64_dma.hip)
 bool identity_f64_dma_eligible(const MmlikeArgsF64 &a);
-hipError_t enqueue_identity_f64_dma(const MmlikeArgsF64 &a, int tile, unsigned grid_x, unsigned grid_y, hipStream_t s);
+hipError_t enqueue_identity_f64_dma(const MmlikeArgsF64 &a, int tile, int groups, unsigned grid_x, unsigned grid_y, hipStream_t s);
 
 // dst (cols x rows, pitch ld_dst) = transpose of src (rows x cols, pitch ld_src), bytes (pack.hip)
 hipError_t launch_pack_pad_i8(int64_t rows, int64_t cols, const int8_t *src, int64_t ld_src, int8_t *dst,

@@ -66,8 +66,12 @@ extern __shared__ __attribute__((aligned(16))) char dd_smem[];
 // 8-k slice of the tile keeps its global layout in LDS, "k-minor" (128 lines x 8 k, k contiguous:
 // row-major A, transposed B) or "k-major" (8 k x 128 lines: row-major B, transposed A), with the
 // swizzles given above for A and B respectively.
-template <int NSTAGE, bool TA, bool TB, int T>
-__global__ void __launch_bounds__(T * 4) __attribute__((amdgpu_waves_per_eu(4, 4)))
+// G groups of waves share the tile's K, each with a ring of its own, and their sums meet in LDS: where a compute unit has one tile
+// of 64 x 64, a SIMD would have one wave, and nothing to run between its reads, waits and barriers (1024^3, one tile to a unit: 41.0 us
+// with one group, 38.1 with two, 37.6 with four; 2048 x 1024 x 1024, two to
+// a unit: 70.5 and 67.9; 960 x 1024 x 2048 76 / 69.5 / 67.7).
+template <int NSTAGE, bool TA, bool TB, int T, int G>
+__global__ void __launch_bounds__(T * 4 * G) __attribute__((amdgpu_waves_per_eu(4, 4)))
 identity_mfma_f64_dma_kernel(const MmlikeArgsF64 args)
 {
     static_assert(NSTAGE >= 3 && NSTAGE <= 8, "the wait counts are written for rings of 3 to 8 stages");
@@ -79,7 +83,8 @@ identity_mfma_f64_dma_kernel(const MmlikeArgsF64 args)
     int K = args.K;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / TL::NT);
+    const int wave = __builtin_amdgcn_readfirstlane((G == 1 ? tid : tid % TL::NT) >> 6);     // of the group
     const int wr = wave >> 1, wc = wave & 1;
     const int li = lane & 15, lh = lane >> 4;
 
@@ -106,9 +111,12 @@ identity_mfma_f64_dma_kernel(const MmlikeArgsF64 args)
     }
     // whole stages stream through LDS; the k that remain (fewer than a stage, in the last k range
     // only: the others are whole stages) are multiplied from values each lane fetches itself
-    const int n_stages = K > 0 ? K / DD_BK : 0;
-    const int ktail = K > 0 ? K - n_stages * DD_BK : 0;
-    if (n_stages <= 0) return;   // (the host never makes a k range shorter than a stage)
+    const int all_stages = K > 0 ? K / DD_BK : 0;
+    const int ktail = group == G - 1 && K > 0 ? K - all_stages * DD_BK : 0;
+    if (all_stages <= 0) return;   // (the host never makes a k range shorter than a stage)
+    // a group's stages, one after the other; the first groups have those that are left over
+    const int most = (all_stages + G - 1) / G, n_stages = (all_stages + G - 1 - group) / G;
+    const int first_stage = group * (all_stages / G) + (group < all_stages % G ? group : all_stages % G);
 
     // ---- what each lane fetches: one A slot and one B slot per stage -----------------------
     // wave w owns the 1 KB slot group w of each operand's slice:
@@ -150,7 +158,8 @@ identity_mfma_f64_dma_kernel(const MmlikeArgsF64 args)
     // instruction writing LDS (it would drain all outstanding loads before every LDS read);
     // completion is tracked by hand: s_waitcnt vmcnt(n) before the stage's barrier.  M0 carries
     // the wave-uniform LDS destination; each lane's 16 bytes land at M0 + 16 * lane.
-    const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void_ptr)dd_smem;
+    char *const ring = dd_smem + group * NSTAGE * DD_STAGE_BYTES;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void_ptr)ring;
     auto dma16 = [&](const double *base, uint32_t voff, uint32_t lds_addr) {
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                      :
@@ -187,7 +196,7 @@ identity_mfma_f64_dma_kernel(const MmlikeArgsF64 args)
         b_off[x] = DD_A_BYTES + (B_KMINOR ? minor_off(wc * WC + li, x & 1) : major_off(wc * WC, x, cols_in));
     // fragment read i (0 .. READS-1) of matrix step g of the stage in slot `buf`: 0, 1 = A (mi), then B (ni)
     auto read_one = [&](int buf, int g, int i, double (&a)[2], double (&b)[NB]) {
-        const char *st = dd_smem + buf * DD_STAGE_BYTES;
+        const char *st = ring + buf * DD_STAGE_BYTES;
         if (i < 2) a[i] = *(const double *)(st + (A_KMINOR ? a_off[g] + i * 1024 : a_off[i] + g * 4 * ROWB));
         else b[i - 2] = *(const double *)(st + (B_KMINOR ? b_off[g] + (i - 2) * 1024 : b_off[i - 2] + g * 4 * ROWB));
     };
@@ -235,7 +244,7 @@ identity_mfma_f64_dma_kernel(const MmlikeArgsF64 args)
     // (its last fragments were consumed by matrix instructions before the barrier), so the slot of
     // stage s-1 is refilled after it with stage s+NSTAGE-1.
     int requested = 0;
-    const double *ap = a_base, *bp = b_base;        // operands of the next stage to request
+    const double *ap = a_base + first_stage * a_stage, *bp = b_base + first_stage * b_stage;   // operands of the next stage to request
 #pragma unroll
     for (int d = 0; d < NSTAGE - 1; ++d)
         if (d < n_stages) {
@@ -251,7 +260,7 @@ identity_mfma_f64_dma_kernel(const MmlikeArgsF64 args)
     // row and column clamped into the tile's existing ones, a k past the end read at the last k
     // and replaced by zero).
     if (ktail > 0) {
-        const int kt = kb + n_stages * DD_BK, kend = kb + K;
+        const int kt = kb + all_stages * DD_BK, kend = kb + K;
 #pragma unroll
         for (int step = 0; step < 2; ++step) {
             if (4 * step >= ktail) break;
@@ -339,43 +348,66 @@ identity_mfma_f64_dma_kernel(const MmlikeArgsF64 args)
     int s = 0;
     for (; s < steady_end; ++s) iteration(s, std::true_type());
     for (; s + 1 < n_stages; ++s) iteration(s, std::false_type());
-    mma_with(fa0, fb0, [&](int i) { side_reads(i, buf, 1, fa1, fb1); });
-    mma_with(fa1, fb1, [&](int) {});
+    if (G == 1 || n_stages > 0) {
+        mma_with(fa0, fb0, [&](int i) { side_reads(i, buf, 1, fa1, fb1); });
+        mma_with(fa1, fb1, [&](int) {});
+    }
+    // (as many barriers as a group with one stage more)
+    if (G > 1 && n_stages > 0 && n_stages < most) __builtin_amdgcn_s_barrier();
 
     // element v of lane l is R[4 v + l / 16][l % 16] of its 16 x 16 block.  R += acc: the 16 values
     // of a row of blocks are all read before the first is written back (as "*dst += acc" per
     // element the compiler must keep every store behind the load before it, a chain of 32 round
     // trips to memory).
     const bool edge = rows_in < DD_BM || cols_in < DD_BN;
+    // blocks of a row of blocks that are this wave's to add: with several groups a share of the wave's blocks each, their sums
+    // exchanged through LDS, where the rings were
+    constexpr int BLOCKS = 2 * NB, SHARE = BLOCKS / G, MINE = SHARE < NB ? SHARE : NB;
+    if constexpr (G > 1) {
+        d4 *const part = (d4 *)dd_smem + wave * BLOCKS * (G - 1) * 64 + lane;
+        __syncthreads();
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi) {
-        double *dst[4];
+        for (int b = 0; b < BLOCKS; ++b)
+            if (b / SHARE != group) part[(b * (G - 1) + group - (group > b / SHARE ? 1 : 0)) * 64] = acc[b / NB][b % NB];
+        __syncthreads();
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            dst[v] = args.R + (int64_t)(row0 + wr * 32 + mi * 16 + 4 * v + lh) * args.ldr + col0 + wc * WC + li;
-        if (ksplit || edge) {
-            // (an edge tile adds with atomics too, the elements that exist: R has one owner here, so
-            // the sum is the same single rounding, and an atomic needs no round trip to memory
-            // before the store, which under a per-element mask would be one after the other)
+        for (int b = 0; b < BLOCKS; ++b)
+            if (b / SHARE == group)
 #pragma unroll
-            for (int ni = 0; ni < NB; ++ni)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = wr * 32 + mi * 16 + 4 * v + lh, col = wc * WC + ni * 16 + li;
-                    if (row < rows_in && col < cols_in) unsafeAtomicAdd(dst[v] + ni * 16, acc[mi][ni][v]);
-                }
-        } else {
-            double old[NB][4];
-#pragma unroll
-            for (int ni = 0; ni < NB; ++ni)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) old[ni][v] = dst[v][ni * 16];
-#pragma unroll
-            for (int ni = 0; ni < NB; ++ni)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) dst[v][ni * 16] = old[ni][v] + acc[mi][ni][v];
-        }
+                for (int g = 0; g < G - 1; ++g) acc[b / NB][b % NB] += part[(b * (G - 1) + g) * 64];
     }
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int n0 = 0; n0 < NB; n0 += MINE) {
+            if (G > 1 && (mi * NB + n0) / SHARE != group) continue;
+            double *dst[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                dst[v] = args.R + (int64_t)(row0 + wr * 32 + mi * 16 + 4 * v + lh) * args.ldr + col0 + wc * WC + li;
+            if (ksplit || edge) {
+                // (an edge tile adds with atomics too, the elements that exist: R has one owner here, so
+                // the sum is the same single rounding, and an atomic needs no round trip to memory
+                // before the store, which under a per-element mask would be one after the other)
+#pragma unroll
+                for (int ni = n0; ni < n0 + MINE; ++ni)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int row = wr * 32 + mi * 16 + 4 * v + lh, col = wc * WC + ni * 16 + li;
+                        if (row < rows_in && col < cols_in) unsafeAtomicAdd(dst[v] + ni * 16, acc[mi][ni][v]);
+                    }
+            } else {
+                double old[MINE][4];
+#pragma unroll
+                for (int ni = 0; ni < MINE; ++ni)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) old[ni][v] = dst[v][(n0 + ni) * 16];
+#pragma unroll
+                for (int ni = 0; ni < MINE; ++ni)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) dst[v][(n0 + ni) * 16] = old[ni][v] + acc[mi][n0 + ni][v];
+            }
+        }
 }
 
 // At least one stage of K, at least two lines in an operand whose lines run across k (its 16-byte
@@ -392,34 +424,36 @@ bool identity_f64_dma_eligible(const MmlikeArgsF64 &a)
     return true;
 }
 
-template <int NSTAGE, bool TA, bool TB, int T>
+template <int NSTAGE, bool TA, bool TB, int T, int G>
 static hipError_t enqueue_f64_layout(const MmlikeArgsF64 &a, unsigned grid_x, unsigned grid_y, hipStream_t s)
 {
-    constexpr int LDS = NSTAGE * DdTile<T>::STAGE_BYTES;
-    static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(&identity_mfma_f64_dma_kernel<NSTAGE, TA, TB, T>),
+    constexpr int LDS = G * NSTAGE * DdTile<T>::STAGE_BYTES;
+    static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(&identity_mfma_f64_dma_kernel<NSTAGE, TA, TB, T, G>),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (granted != hipSuccess) return granted;
-    hipLaunchKernelGGL((identity_mfma_f64_dma_kernel<NSTAGE, TA, TB, T>), dim3(grid_x, grid_y), dim3(DdTile<T>::NT), LDS, s, a);
+    hipLaunchKernelGGL((identity_mfma_f64_dma_kernel<NSTAGE, TA, TB, T, G>), dim3(grid_x, grid_y), dim3(G * DdTile<T>::NT), LDS, s, a);
     return hipSuccess;
 }
 
-template <int NSTAGE, int T>
+template <int NSTAGE, int T, int G>
 static hipError_t enqueue_f64_tile(const MmlikeArgsF64 &a, unsigned grid_x, unsigned grid_y, hipStream_t s)
 {
-    if (a.transA && a.transB) return enqueue_f64_layout<NSTAGE, true, true, T>(a, grid_x, grid_y, s);
-    if (a.transA) return enqueue_f64_layout<NSTAGE, true, false, T>(a, grid_x, grid_y, s);
-    if (a.transB) return enqueue_f64_layout<NSTAGE, false, true, T>(a, grid_x, grid_y, s);
-    return enqueue_f64_layout<NSTAGE, false, false, T>(a, grid_x, grid_y, s);
+    if (a.transA && a.transB) return enqueue_f64_layout<NSTAGE, true, true, T, G>(a, grid_x, grid_y, s);
+    if (a.transA) return enqueue_f64_layout<NSTAGE, true, false, T, G>(a, grid_x, grid_y, s);
+    if (a.transB) return enqueue_f64_layout<NSTAGE, false, true, T, G>(a, grid_x, grid_y, s);
+    return enqueue_f64_layout<NSTAGE, false, false, T, G>(a, grid_x, grid_y, s);
 }
 
 // Enqueues grid.x x grid.y workgroups of the streamed kernel: tiles of 128 rows and columns (512
-// threads, ring of 4 stages) or of 64 (256 threads, ring of ID_SMALL_STAGES).  The caller has
+// threads, ring of 4 stages) or of 64 (256 threads, ring of ID_SMALL_STAGES, or `groups` such).  The caller has
 // checked identity_f64_dma_eligible and fills the split fields of `a` as for
 // identity_mfma_f64_kernel.
-hipError_t enqueue_identity_f64_dma(const MmlikeArgsF64 &a, int tile, unsigned grid_x, unsigned grid_y, hipStream_t s)
+hipError_t enqueue_identity_f64_dma(const MmlikeArgsF64 &a, int tile, int groups, unsigned grid_x, unsigned grid_y, hipStream_t s)
 {
-    if (tile == 128) return enqueue_f64_tile<4, 128>(a, grid_x, grid_y, s);
-    if (tile == 64) return enqueue_f64_tile<ID_SMALL_STAGES, 64>(a, grid_x, grid_y, s);
+    if (tile == 128) return enqueue_f64_tile<4, 128, 1>(a, grid_x, grid_y, s);
+    if (tile == 64 && groups == 4) return enqueue_f64_tile<ID_SMALL_STAGES, 64, 4>(a, grid_x, grid_y, s);
+    if (tile == 64 && groups == 2) return enqueue_f64_tile<ID_SMALL_STAGES, 64, 2>(a, grid_x, grid_y, s);
+    if (tile == 64) return enqueue_f64_tile<ID_SMALL_STAGES, 64, 1>(a, grid_x, grid_y, s);
     return hipErrorInvalidValue;
 }
 
