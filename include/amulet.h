@@ -511,14 +511,15 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K);
  * <k of such a range> kgroup <k of it that a group of waves sums>"; and for the
  * identity and boost tasks " bf16_pieces 3 tile_rows <32, 64, 128 or 256>" where a
  * kernel that forms plain sums on the bf16 matrix cores stood in for the shape
- * (larger problems, and few tiles of a long K; three bf16 pieces per value, fp32 sums: no less precise than
- * the fp32 kernels over sums of many products of like size; a product that stands
- * alone in its sum, as with a diagonal A, is within 1.8e-7 of itself and 3e-8 on
- * average, where those kernels' one rounding is 6e-8 and 2.1e-8.  A named shape
- * runs its own fp32 kernel); " critical_rows <64 or 128>" for a tile kernel in
- * whose stead the fp64 discount task ran by critical values, on tiles of so many
- * rows and 128 columns (the rows past its own are a launch of their own, of the
- * tile kernels).  The adaptive
+ * (larger problems, and few tiles of a long K; three bf16 pieces per value, fp32
+ * sums: no less precise than the fp32 kernels over sums of many products of like
+ * size; a product that stands alone in its sum, as with a diagonal A, is within
+ * 1.8e-7 of itself and 3e-8 on average, where those kernels' one rounding is 6e-8
+ * and 2.1e-8.  A named shape runs its own fp32 kernel); " critical_rows <64 or
+ * 128>" for a tile kernel in whose stead an fp64 predicate task ran in fewer
+ * operations (discount and count by critical values, boost by a clamp), on tiles of
+ * so many rows and 128 columns (the rows past its own are a launch of their own, of
+ * the tile kernels).  The adaptive
  * calls make one launch per trial and one for the rest.  Static storage of the
  * calling thread, until its next call of this function.
  */

@@ -838,8 +838,9 @@ static bool critical_f64_runs(const F64Call &c)
     if (c.task == TASK_IDENTITY || !(columns || (c.task == TASK_BOOST && c.thres_form == THRES_ROW))) return false;
     return c.N >= 2 && (c.task != TASK_COUNT_GT || c.K < C64_COUNT_K) && tile_runs<double>(c);
 }
-// fp64: the tile kernels in place of the built-in `shape` (see tile_wanted).  They are ahead of the shape grid's
-// kernels nearly everywhere: TFLOP/s, grid / tile, 4096^3 discount 16.9 / 17.6, boost 16.4 / 18.0, count 22.4 / 24.3; us, 512^3
+// fp64: the tile kernels in place of the built-in `shape` (see tile_wanted), or the kernel of
+// mmlike_critical_f64_impl.h where that is estimated faster (choose_critical_f64).  The tile kernels are ahead of
+// the shape grid's nearly everywhere: TFLOP/s, grid / tile, 4096^3 discount 16.9 / 17.6, boost 16.4 / 18.0, count 22.4 / 24.3; us, 512^3
 // discount 40.5 / 22.8, 256^3 16.3 / 7.5, 1024^3 boost 139 / 128; but not in two cases: thres[i][j] leaves the tile kernel
 // registers for one workgroup per unit, so it is taken where there are not more than one round of the grid
 // kernel's workgroups (512^3 47 / 25 us, 2048^3 1185 / 1314), and rows of A a multiple of 256 KiB apart, whose

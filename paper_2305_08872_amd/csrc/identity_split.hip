@@ -16,7 +16,7 @@
 // 1.75 GHz (the library's own bf16 product of that many operations runs at 1409 T/s, this kernel's six at 1140, with 256-row tiles
 // at 1260).  With operands that change from call to call, fp32 matrix instructions / here: 4096^3 956 / 723 us (144 / 190 TFLOP/s; 128-row
 // tiles: 256 rows take 654 there, see identity_split_wanted), 2048^3 129 / 108, 8192^2 x 1024 980 / 689 (256 rows).  Problems of fewer
-// tiles gain nothing: 1024^3 with 64 x 64 tiles, in two designs, 24 us against 21 for the fp32 kernel.
+// tiles gain nothing here (1024^3 with 64 x 64 tiles, in two designs, 24 us against 21 for the fp32 kernel): identity_split_waves.hip.
 //
 // Workgroup: 4 waves as 2 x 2, a wave WM x WN blocks of 32 x 32; two workgroups to a compute unit.  128 x 128 tiles with
 // two sets of accumulators, one for a0 b0 and one for the five smaller products, whose roundings then count less; or 256 x
