@@ -519,7 +519,7 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K);
  * 128>" for a tile kernel in whose stead an fp64 predicate task ran in fewer
  * operations (discount and count by critical values, boost by a clamp), on tiles of
  * so many rows and 128 columns (the rows past its own are a launch of their own, of
- * the tile kernels).  The adaptive
+ * the tile kernels; of a count with a threshold per row, the columns).  The adaptive
  * calls make one launch per trial and one for the rest.  Static storage of the
  * calling thread, until its next call of this function.
  */

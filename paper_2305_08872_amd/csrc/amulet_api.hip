@@ -830,13 +830,16 @@ static int lookup_shape_f64(int task, int64_t M, int64_t N, int64_t K)
     return default_shape_f64(task, M, N);
 }
 
-// fp64 tasks by mmlike_critical_f64_impl.h: a threshold per column or one for all, for BOOST also per row, a pair of columns, and
+// A count with thresholds that face rows is formed transposed there, B^T A^T, where they face columns.
+static bool critical_f64_swaps(const F64Call &c) { return c.task == TASK_COUNT_GT && c.thres_form == THRES_ROW; }
+// fp64 tasks by mmlike_critical_f64_impl.h: a threshold per column or one for all, for BOOST and COUNT also per row, a pair of columns, and
 // (with what the tile kernels ask for) offsets that fit 32 bits
 static bool critical_f64_runs(const F64Call &c)
 {
     const bool columns = c.thres_form == THRES_COL || c.thres_form == THRES_CONST;
-    if (c.task == TASK_IDENTITY || !(columns || (c.task == TASK_BOOST && c.thres_form == THRES_ROW))) return false;
-    return c.N >= 2 && (c.task != TASK_COUNT_GT || c.K < C64_COUNT_K) && tile_runs<double>(c);
+    if (c.task == TASK_IDENTITY || !(columns || (c.task != TASK_DISCOUNT && c.thres_form == THRES_ROW))) return false;
+    if (critical_f64_swaps(c) && (c.lda > 0x1000000 || c.ldb > 0x1000000)) return false;
+    return c.N >= 2 && c.M >= 2 && (c.task != TASK_COUNT_GT || c.K < C64_COUNT_K) && tile_runs<double>(c);
 }
 // fp64: the tile kernels in place of the built-in `shape` (see tile_wanted), or the kernel of
 // mmlike_critical_f64_impl.h where that is estimated faster (choose_critical_f64).  The tile kernels are ahead of
@@ -855,7 +858,8 @@ static bool tile_wanted_f64(const F64Call &c, int shape, TilePlan &plan)
     const int waves = shape % F64_TILES == 1 ? 8 : 4;
     const int64_t range = wide_k_range_f64((c.M + 4 * waves - 1) / (4 * waves) * ((c.N + 127) / 128) * waves, c.K, 16);
     plan = choose_tile_plan<double>(c.M, c.N, c.K, kTileUsF64[c.task], (c.K + range - 1) / range, c.thres_form == THRES_ELEM);
-    if (critical_f64_runs(c)) choose_critical_f64(c.task, c.M, c.N, c.K, kTileUsF64[c.task], compute_units(), plan);
+    const bool swaps = critical_f64_swaps(c);
+    if (critical_f64_runs(c)) choose_critical_f64(c.task, swaps ? c.N : c.M, swaps ? c.M : c.N, c.K, kTileUsF64[c.task], compute_units(), plan);
     return true;
 }
 
@@ -888,12 +892,18 @@ static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, v
     KernelNote &note = new_note(c.task, 1, shape, rows);
     hipError_t e;
     if (critical) {
+        const bool swaps = critical_f64_swaps(c);
         // (a slab of an adaptive call: all of it)
-        const int64_t first = rows == c.M ? tile->rest : rows;
+        const int64_t all = swaps ? c.N : rows, first = rows == c.M ? tile->rest : all;
         // (told as the plan it stands in for)
-        note.shape = -1; note.rows = first; note.critical = tile->critical;
+        note.shape = -1; note.rows = swaps ? rows : first; note.critical = tile->critical;
         note.tile = tile->wide; note.parts = tile->parts; note.kpart = tile->kpart; note.kgroup = tile->kgroup;
         a.M = (int)first;
+        if (swaps) {
+            a.A = sub.B; a.lda = c.ldb; a.transA = !c.trans_b;
+            a.B = sub.A; a.ldb = c.lda; a.transB = !c.trans_a;
+            a.N = (int)rows;
+        }
         switch (c.task * 4 + c.thres_form) {
         case TASK_DISCOUNT * 4 + THRES_COL: e = launch_mmlike_critical_f64<TASK_DISCOUNT, THRES_COL>(a, tile->critical, (hipStream_t)stream); break;
         case TASK_DISCOUNT * 4 + THRES_CONST: e = launch_mmlike_critical_f64<TASK_DISCOUNT, THRES_CONST>(a, tile->critical, (hipStream_t)stream); break;
@@ -901,14 +911,21 @@ static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, v
         case TASK_BOOST * 4 + THRES_ROW: e = launch_mmlike_critical_f64<TASK_BOOST, THRES_ROW>(a, tile->critical, (hipStream_t)stream); break;
         case TASK_BOOST * 4 + THRES_CONST: e = launch_mmlike_critical_f64<TASK_BOOST, THRES_CONST>(a, tile->critical, (hipStream_t)stream); break;
         case TASK_COUNT_GT * 4 + THRES_COL: e = launch_mmlike_critical_f64<TASK_COUNT_GT, THRES_COL>(a, tile->critical, (hipStream_t)stream); break;
+        case TASK_COUNT_GT * 4 + THRES_ROW: e = launch_mmlike_critical_f64<TASK_COUNT_GT, THRES_ROW>(a, tile->critical, (hipStream_t)stream); break;
         default: e = launch_mmlike_critical_f64<TASK_COUNT_GT, THRES_CONST>(a, tile->critical, (hipStream_t)stream); break;
         }
-        if (e == hipSuccess && first < rows) {
-            sub.M = rows - first;
-            sub.A = c.trans_a ? sub.A + first : sub.A + first * c.lda;
-            sub.R += first * c.ldr;
-            if (c.thres_form == THRES_ROW) sub.thres += first;
-            e = launch_tile_call<double>(sub, choose_tile_plan<double>(sub.M, c.N, c.K, kTileUsF64[c.task], tile->rest_parts), (hipStream_t)stream);
+        if (e == hipSuccess && first < all) {
+            if (swaps) {
+                sub.N = c.N - first;
+                sub.B = c.trans_b ? sub.B + first * c.ldb : sub.B + first;
+                sub.R += first;
+            } else {
+                sub.M = rows - first;
+                sub.A = c.trans_a ? sub.A + first : sub.A + first * c.lda;
+                sub.R += first * c.ldr;
+                if (c.thres_form == THRES_ROW) sub.thres += first;
+            }
+            e = launch_tile_call<double>(sub, choose_tile_plan<double>(sub.M, sub.N, c.K, kTileUsF64[c.task], tile->rest_parts), (hipStream_t)stream);
         }
     } else {
         e = launch_mmlike_f64(c.task, c.thres_form, shape, a, (hipStream_t)stream);

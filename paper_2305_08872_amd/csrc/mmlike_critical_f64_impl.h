@@ -12,6 +12,7 @@
 // rounded instead of itself: no more error than rounding it.  A count has t = clamp(+-a 2^300 - |c'|), 1 over the threshold whatever
 // b's sign, and adds t's high half as the fp32 number it also is, 15/8 or 0: fp32 additions issue from two waves at once, 32-bit ones
 // of whole numbers do not (register-only, nominal clocks per 64 products: 7.2 so, 9.0 with v_add_u32 or any other).
+// Thresholds of a count that face rows: the product of the transposed operands, transposed as it is added to R.
 // BOOST's p + max(p - th, 0) is acc = a b' + acc and acc + clamp(a b' - th'), b' and th' being 2^-202 of b and th.
 //
 // A sum is added up in parts of a quarter of K, 64 k at most: an error as small as the tile kernels', whose waves share K
@@ -24,7 +25,8 @@
 // 8.6, of which finding c is 1.1 (rows of a tile share it: 1.9 with 64 rows, 64 x 128 being the better tile for a K too short to hide a
 // large one's ends) and barrier, loads and LDS the rest.
 // us, tile kernels / here: discount 2048^3 1006 / 897, 4096^3 7800 / 7170, B transposed 7800 / 7280, 4096 x 2048 x 64 90 / 78;
-// boost 2048^3 963 / 850, 4096^3 7610 / 6640, per row 7720 / 6420; count 2048^3 727 / 586, 4096^3 5640 / 3760, 4096 x 2048 x 64 65 / 50.
+// boost 2048^3 963 / 850, 4096^3 7610 / 6640, per row 7720 / 6420; count 2048^3 727 / 586, 4096^3 5640 / 3760, 4096 x 2048 x 64 65 / 50,
+// per row 719 / 631, 5590 / 4070, 66 / 57.
 // Values that these do not take, for all of a call, 4096^3: discount 9200, boost 7800, count 5800.
 // A goes through LDS and is read back by broadcast: through the scalar cache, 8 bytes of 64 rows at a time, 4096^3 took
 // 12 200 us.  256 columns in 256 registers per wave, two waves to a SIMD: 8530.  Stages of 8 k instead of 16: 7440 (128 rows).
@@ -92,6 +94,7 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
     typedef Critical64Lds<TASK, NW> Lds;
     constexpr bool transA = (TRANS & 1) != 0, transB = (TRANS & 2) != 0;
     constexpr int PAIRS = c64_pairs(TASK), ROWS = c64_rows(TASK, NW), BK = NW;
+    constexpr bool ROW_SCALARS = TASK == TASK_BOOST && TF == THRES_ROW, SWAPPED = TASK == TASK_COUNT_GT && TF == THRES_ROW;
     constexpr int AE = PAIRS * BK / 8;  // values of A a thread stages (and two of B)
     const int M = args.M, N = args.N, K = args.K;
     const int lane = tid & 63;
@@ -113,7 +116,7 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
     const int at = lane % (64 / PAIRS), first_row = wave * (C64_TM * PAIRS) + lane / (64 / PAIRS) * C64_TM;
     auto own_col = [&](int c) { return at * 2 + (c & 1) + (c >> 1) * 64; };
     bool own;
-    constexpr int NT = TF == THRES_ROW ? C64_TM : 2 * PAIRS;
+    constexpr int NT = ROW_SCALARS ? C64_TM : 2 * PAIRS;
     double th[NT], od[2 * PAIRS];
     bool fit = true, zeros = false;
     auto fits = [&](double &t) {
@@ -137,7 +140,7 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
         }
         return false;
     };
-    if constexpr (TF == THRES_ROW) {
+    if constexpr (ROW_SCALARS) {
         // (the tile's 64 rows looked at by every wave, then its own)
         const int row = row0 + lane;
         double t = args.thres[row < M ? row : M - 1];
@@ -301,7 +304,7 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
         return o;
     };
     auto rows_of = [&](int buf, int k, int pair) { return *(const cd2 *)&L.a[buf][k][first_row + 2 * pair]; };
-    auto th_of = [&](int r, int c) { return th[TF == THRES_ROW ? r : c]; };
+    auto th_of = [&](int r, int c) { return th[ROW_SCALARS ? r : c]; };
     // 2 with the sign of the critical value of a column (A has the rest of 2^300): an operand that an instruction can hold
     cu2 sgn[2 * PAIRS];
 #pragma unroll
@@ -449,6 +452,28 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
         }
         else return TASK == TASK_BOOST && !PLAIN ? all[r][c] / C64_BOOST_SCALE : all[r][c];
     };
+    if constexpr (SWAPPED) {
+        // (a lane's eight rows lie next to each other in R)
+#pragma unroll
+        for (int j = 0; j < 2 * PAIRS; ++j) {
+            const int col = col_at(l % (64 / PAIRS) * 2 + (j & 1) + 64 * (j >> 1), own);
+            below[j & 1] = !PLAIN && args.thres[col] < 0.0;
+            double *const dst = args.R + (int64_t)col * args.ldr + wrow;
+            if (!own) continue;
+            if (wrow + C64_TM <= M) {
+                cd2 old[C64_TM / 2];
+#pragma unroll
+                for (int r = 0; r < C64_TM / 2; ++r) old[r] = *(const cd2_any *)(dst + 2 * r);
+#pragma unroll
+                for (int r = 0; r < C64_TM / 2; ++r) *(cd2_any *)(dst + 2 * r) = old[r] + cd2{sum(2 * r, j), sum(2 * r + 1, j)};
+            } else {
+#pragma unroll
+                for (int r = 0; r < C64_TM; ++r)
+                    if (wrow + r < M) dst[r] += sum(r, j);
+            }
+        }
+        return true;
+    }
 #pragma unroll
     for (int p = 0; p < PAIRS; ++p) {
         cd2 old[C64_TM];

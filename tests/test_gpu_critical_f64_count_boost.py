@@ -63,8 +63,9 @@ def make(seed, M, N, K, form, tA=False, tB=False, pad=0):
     return A, B, torch.empty(n, dtype=torch.float64, device="cuda").uniform_(0.05, 2, generator=g)
 
 
+@pytest.mark.parametrize("form", ["col", "row"])
 @pytest.mark.parametrize("sign", [1, -1])
-def test_products_at_the_threshold(am, sign):
+def test_products_at_the_threshold(am, sign, form):
     """One product per sum, thresholds one ulp below, at and above some of them: every decision shows."""
     M, N, K = 3072, 2048, 64
     g = torch.Generator(device="cuda").manual_seed(64)
@@ -75,12 +76,12 @@ def test_products_at_the_threshold(am, sign):
         a, b = sign * value(M), sign * value(N)
         A, B = torch.zeros(M, K, dtype=torch.float64, device="cuda"), torch.zeros(K, N, dtype=torch.float64, device="cuda")
         A[:, K - 3], B[K - 3] = a, b
-        th = a[torch.arange(N, device="cuda") % M] * b
-        step = torch.arange(N, device="cuda") % 3
+        th = a[torch.arange(N, device="cuda") % M] * b if form == "col" else a * b[torch.arange(M, device="cuda") % N]
+        step = torch.arange(len(th), device="cuda") % 3
         th = torch.where(step == 0, th, torch.nextafter(th, (step == 1).double() * 1e9))
         R = torch.zeros(M, N, dtype=torch.float64, device="cuda")
-        assert "critical_rows 128" in run(am, "count_gt", A, B, th, R, "col")[0]
-        assert torch.equal(R, (a[:, None] * b > th).double()), (bits, sign)
+        assert "critical_rows 128" in run(am, "count_gt", A, B, th, R, form)[0]
+        assert torch.equal(R, (a[:, None] * b > (th if form == "col" else th[:, None])).double()), (bits, sign)
 
 
 @pytest.mark.parametrize("task", ["count_gt", "discount"])
@@ -143,7 +144,7 @@ SIZES = [(4096, 2048, 64, 0), (4095, 2047, 67, 1), (4161, 2050, 271, 3), (8193, 
 
 
 @pytest.mark.parametrize("tA,tB", [(False, False), (True, False), (False, True), (True, True)])
-@pytest.mark.parametrize("task,form", [("count_gt", "col"), ("count_gt", "const"), ("boost", "col"), ("boost", "row"), ("boost", "const")])
+@pytest.mark.parametrize("task,form", [("count_gt", "col"), ("count_gt", "row"), ("count_gt", "const"), ("boost", "col"), ("boost", "row"), ("boost", "const")])
 def test_remainders_forms_and_layouts(am, task, form, tA, tB):
     ran = []
     for M, N, K, pad in SIZES:
@@ -158,10 +159,10 @@ def test_remainders_forms_and_layouts(am, task, form, tA, tB):
     assert sum("critical_rows" in r for r in ran) >= 3, ran
 
 
-@pytest.mark.parametrize("task,form", [("count_gt", "col"), ("boost", "row")])
+@pytest.mark.parametrize("task,form", [("count_gt", "col"), ("count_gt", "row"), ("boost", "row")])
 def test_rows_left_to_the_tile_kernels(am, task, form):
     left = 0
-    for M, N, K in [(2560, 1751, 1792), (5120, 1751, 1300), (9000, 1100, 900)]:
+    for M, N, K in [(2560, 1751, 1792), (5120, 1751, 1300), (1751, 5120, 1300), (9000, 1100, 900)]:
         A, B, th = make(M, M, N, K, form)
         R = torch.zeros(M, N, dtype=torch.float64, device="cuda")
         kernels = run(am, task, A, B, th, R, form)
@@ -173,7 +174,7 @@ def test_rows_left_to_the_tile_kernels(am, task, form):
 
 @pytest.mark.parametrize("tA,tB", [(False, False), (True, True)])
 @pytest.mark.parametrize("what", ["thresholds", "tiny", "large", "late", "not numbers"])
-@pytest.mark.parametrize("task,form", [("count_gt", "col"), ("boost", "col"), ("boost", "row")])
+@pytest.mark.parametrize("task,form", [("count_gt", "col"), ("count_gt", "row"), ("boost", "col"), ("boost", "row")])
 def test_values_of_the_plain_way(am, task, form, what, tA, tB):
     if (task, what) == ("count_gt", "not numbers"):
         pytest.skip("a count of products that are no numbers is not specified")
