@@ -9,7 +9,11 @@
 //   acc = a w + acc
 // with base = max(b, b (1 - dis)) and cut = b (1 - dis) - b: t is 1 where a product of a positive b is over its threshold, and where
 // one of a negative b is not.  A product that is not over its threshold is added unrounded, one that is has its factor
-// rounded instead of itself: no more error than rounding it.  A count has t = clamp(+-a 2^300 - |c'|), 1 over the threshold whatever
+// rounded instead of itself: no more error than rounding it.  That takes a cut that is exact, and so a 1 - dis of 0 or 1/2 to 1 (it would be off
+// by half a last place of b, 1 / (1 - dis) times as much of the factor).  With others, masks: acc = a x + acc in the lanes where
+// a > c' and acc = a y + acc in the others, x being b (1 - dis) for a positive b and y for a negative one; the other of them is
+// b.  Three operations too, each term as exact, and as fast as the tile kernels' four (4096^3 7130 us by the clamp, 7690 by masks, tile
+// kernels 7840).  A count has t = clamp(+-a 2^300 - |c'|), 1 over the threshold whatever
 // b's sign, and adds t's high half as the fp32 number it also is, 15/8 or 0: fp32 additions issue from two waves at once, 32-bit ones
 // of whole numbers do not (register-only, nominal clocks per 64 products: 7.2 so, 9.0 with v_add_u32 or any other).
 // Thresholds of a count that face rows: the product of the transposed operands, transposed as it is added to R.
@@ -27,7 +31,7 @@
 // us, tile kernels / here: discount 2048^3 1006 / 897, 4096^3 7800 / 7170, B transposed 7800 / 7280, 4096 x 2048 x 64 90 / 78;
 // boost 2048^3 963 / 850, 4096^3 7610 / 6640, per row 7720 / 6420; count 2048^3 727 / 586, 4096^3 5640 / 3760, 4096 x 2048 x 64 65 / 50,
 // per row 719 / 631, 5590 / 4070, 66 / 57.
-// Values that these do not take, for all of a call, 4096^3: discount 9200, boost 7800, count 5800.
+// Values that none of these takes, for all of a call, 4096^3: discount 9200, boost 7800, count 5800.
 // A goes through LDS and is read back by broadcast: through the scalar cache, 8 bytes of 64 rows at a time, 4096^3 took
 // 12 200 us.  256 columns in 256 registers per wave, two waves to a SIMD: 8530.  Stages of 8 k instead of 16: 7440 (128 rows).
 // BOOST's plain sum on the fp64 matrix cores: they and the vector unit take turns (17.2 clocks, 8.1 + 9.2).
@@ -60,18 +64,21 @@ constexpr double C64_LEAST_TH = 0x1p-100, C64_MOST_TH = 0x1p100;
 template <int TASK, int NW>
 struct Critical64Lds {
     static constexpr int BK = NW;
-    // what an element of B comes to: the discount's base, c and cut; c; or b
+    // what an element of B comes to: the discount's base, c and cut (or x, c and y); c; or b
     static constexpr int KINDS = TASK == TASK_DISCOUNT ? 3 : 1, C = TASK == TASK_DISCOUNT ? 1 : 0, CUT = 2 % KINDS;
     double b[KINDS][2][BK][C64_BP];
     double a[2][BK][c64_rows(TASK, NW) + 2];
     double th[C64_COLS], half[C64_COLS], od[C64_COLS];
 };
 
-// The critical value of b for th, times -2^300, as th and half, half the distance to the next double, come (or, for thresholds below 0,
-// times 2^300).  a b rounds to more than th from the middle th + half on, a tie if the next double is even.  n = (th + half) / b to within 2^-19 of its last place: rcp is good to 2^-24,
+// How a tile's terms are formed; CRITICAL_DONE: they have been.
+enum CriticalWay { CRITICAL_DONE, BY_CLAMP, BY_MASKS, BY_OWN_OPERATIONS };
+
+// The critical value of b for th, times what th and half, half the distance to the next double, come with: -2^300 (for thresholds
+// below 0 2^300), or 1 (MASKS).  a b rounds to more than th from the middle th + half on, a tie if the next double is even.  n = (th + half) / b to within 2^-19 of its last place: rcp is good to 2^-24,
 // one step to 2^-48, and the second step's remainder is exact but for its own rounding.  So the first a over the threshold is
 // n or the next one away from 0, which its own product tells; b > 0, or ANY: the one below it is wanted.
-template <bool ANY>
+template <bool ANY, bool MASKS>
 __device__ __forceinline__ double critical_value_f64(double b, double th, double half)
 {
     const double r = __builtin_amdgcn_rcp(b);
@@ -84,14 +91,15 @@ __device__ __forceinline__ double critical_value_f64(double b, double th, double
     const uint64_t nb = __builtin_bit_cast(uint64_t, n), bb = __builtin_bit_cast(uint64_t, b), tb = __builtin_bit_cast(uint64_t, th);
     const int away = __builtin_fabs(n * b) > __builtin_fabs(th) ? 1 : 0;
     if constexpr (ANY) return __builtin_bit_cast(double, ((nb - (uint64_t)away) & ~(1ull << 63)) | ((bb ^ tb) & (1ull << 63)));
-    return __builtin_bit_cast(double, nb + (int64_t)((int)((uint32_t)((bb ^ ~tb) >> 63)) - away));
+    return __builtin_bit_cast(double, nb + (int64_t)((int)((uint32_t)((bb ^ (MASKS ? tb : ~tb)) >> 63)) - away));
 }
 
-// PLAIN: the task's own four operations, for a tile that the first way gives back (false) with R as it was.
-template <int TASK, int TF, int TRANS, int NW, bool PLAIN, typename Args>
-__device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsigned tid, Critical64Lds<TASK, NW> &L)
+// The next way for a tile that this one does not take, with R as it was.
+template <int TASK, int TF, int TRANS, int NW, CriticalWay WAY, typename Args>
+__device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const unsigned tid, Critical64Lds<TASK, NW> &L)
 {
     typedef Critical64Lds<TASK, NW> Lds;
+    constexpr bool PLAIN = WAY == BY_OWN_OPERATIONS, MASKS = WAY == BY_MASKS;
     constexpr bool transA = (TRANS & 1) != 0, transB = (TRANS & 2) != 0;
     constexpr int PAIRS = c64_pairs(TASK), ROWS = c64_rows(TASK, NW), BK = NW;
     constexpr bool ROW_SCALARS = TASK == TASK_BOOST && TF == THRES_ROW, SWAPPED = TASK == TASK_COUNT_GT && TF == THRES_ROW;
@@ -101,7 +109,7 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tiles_m = (M + ROWS - 1) / ROWS, tiles_n = (N + C64_COLS - 1) / C64_COLS;
     int tm, tn;
-    if (!xcd_tile((int)blockIdx.x + args.block_base, tiles_m, tiles_n, tm, tn)) return true;
+    if (!xcd_tile((int)blockIdx.x + args.block_base, tiles_m, tiles_n, tm, tn)) return CRITICAL_DONE;
     const int row0 = tm * ROWS, col0 = tn * C64_COLS;
     const double *__restrict__ Ag = args.A;
     const double *__restrict__ Bg = args.B;
@@ -118,7 +126,7 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
     bool own;
     constexpr int NT = ROW_SCALARS ? C64_TM : 2 * PAIRS;
     double th[NT], od[2 * PAIRS];
-    bool fit = true, zeros = false;
+    bool fit = true, exact = true, zeros = false;
     auto fits = [&](double &t) {
         if constexpr (TASK == TASK_BOOST) {
             // (above +inf or no number, nothing: the clamp takes both.  A k past the last one is nothing times nothing: over a
@@ -162,18 +170,21 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
             if constexpr (TASK == TASK_DISCOUNT) {
                 od[j] = 1.0 - args.dis[col];
                 if (none) od[j] = 1.0;
-                if constexpr (!PLAIN) fit = fit && od[j] >= 0.0 && od[j] <= 1.0;
+                if constexpr (!PLAIN) fit = fit && __builtin_fabs(od[j]) <= C64_MOST_TH;
+                exact = exact && (od[j] == 0.0 || (od[j] >= 0.5 && od[j] <= 1.0));
             }
         }
     }
-    if (!PLAIN && __builtin_amdgcn_ballot_w64(!fit) != 0) return false;     // (all waves face the same columns)
+    // (all waves face the same columns)
+    if (!PLAIN && __builtin_amdgcn_ballot_w64(!fit) != 0) return BY_OWN_OPERATIONS;
+    if (TASK == TASK_DISCOUNT && WAY == BY_CLAMP && __builtin_amdgcn_ballot_w64(!exact) != 0) return BY_MASKS;
     zeros = __builtin_amdgcn_ballot_w64(zeros) != 0;
     if constexpr (!PLAIN && TASK != TASK_BOOST) {
         if (wave == 0)
 #pragma unroll
             for (int j = 0; j < 2 * PAIRS; ++j) {
-                L.th[own_col(j)] = th[j] * -C64_SCALE;
-                L.half[own_col(j)] = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, th[j]) & 0xfff0000000000000ull) * -0x1p247;
+                L.th[own_col(j)] = th[j] * (MASKS ? 1.0 : -C64_SCALE);
+                L.half[own_col(j)] = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, th[j]) & 0xfff0000000000000ull) * (MASKS ? 0x1p-53 : -0x1p247);
                 if constexpr (TASK == TASK_DISCOUNT) L.od[own_col(j)] = od[j];
             }
         __syncthreads();
@@ -267,11 +278,16 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
                 const uint32_t top = (uint32_t)(__builtin_bit_cast(uint64_t, b) >> 32) & 0x7fffffffu;
                 constexpr uint32_t LEAST = (1023u - 600u) << 20, MOST = (1023u + 100u) << 20;
                 in = in && (top - LEAST <= MOST - LEAST || b == 0.0);
-                c[i] = critical_value_f64<TASK == TASK_COUNT_GT>(b, L.th[col], L.half[col]);
+                c[i] = critical_value_f64<TASK == TASK_COUNT_GT, MASKS>(b, L.th[col], L.half[col]);
                 if constexpr (TASK == TASK_DISCOUNT) {
                     const double m = b * L.od[col];
-                    asm("v_max_f64 %0, %1, %2" : "=v"(base[i]) : "v"(b), "v"(m));
-                    cut[i] = m - b;
+                    if constexpr (MASKS) {
+                        base[i] = b > 0.0 ? m : b;
+                        cut[i] = b > 0.0 ? b : m;
+                    } else {
+                        asm("v_max_f64 %0, %1, %2" : "=v"(base[i]) : "v"(b), "v"(m));
+                        cut[i] = m - b;
+                    }
                 }
             }
         }
@@ -329,6 +345,16 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
                              "v_add_f64 %4, %4, %0\n\tv_add_f64 %5, %5, %1\n\tv_add_f64 %6, %6, %2\n\tv_add_f64 %7, %7, %3"
                              : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "+v"(acc[r][0]), "+v"(acc[r][1]), "+v"(acc[r + 1][0]), "+v"(acc[r + 1][1])
                              : "v"(a), "v"(e), "v"(o.b[0][0]), "v"(o.b[0][1]), "v"(th[0]), "v"(th[1]), "v"(od[0]), "v"(od[1]), "s"(active) : "vcc");
+            } else if constexpr (TASK == TASK_DISCOUNT && MASKS) {
+#define AMULET_EITHER(SUM, MASK, A, X, Y) "s_mov_b64 exec, " MASK "\n\tv_fma_f64 " SUM ", " A ", " X ", " SUM "\n\ts_xor_b64 exec, exec, %[active]\n\tv_fma_f64 " SUM ", " A ", " Y ", " SUM "\n\t"
+                uint64_t over[4];
+                asm volatile("v_cmp_gt_f64_e64 %4, %[a], %[c0]\n\tv_cmp_gt_f64_e64 %5, %[a], %[c1]\n\tv_cmp_gt_f64_e64 %6, %[e], %[c0]\n\tv_cmp_gt_f64_e64 %7, %[e], %[c1]\n\t"
+                             AMULET_EITHER("%0", "%4", "%[a]", "%[x0]", "%[y0]") AMULET_EITHER("%1", "%5", "%[a]", "%[x1]", "%[y1]")
+                             AMULET_EITHER("%2", "%6", "%[e]", "%[x0]", "%[y0]") AMULET_EITHER("%3", "%7", "%[e]", "%[x1]", "%[y1]") "s_mov_b64 exec, %[active]"
+                             : "+v"(acc[r][0]), "+v"(acc[r][1]), "+v"(acc[r + 1][0]), "+v"(acc[r + 1][1]), "=&s"(over[0]), "=&s"(over[1]), "=&s"(over[2]), "=&s"(over[3])
+                             : [a] "v"(a), [e] "v"(e), [c0] "v"(o.c[0]), [c1] "v"(o.c[1]), [x0] "v"(o.b[0][0]), [x1] "v"(o.b[0][1]), [y0] "v"(o.cut[0]), [y1] "v"(o.cut[1]), [active] "s"(active)
+                             : "scc");
+#undef AMULET_EITHER
             } else if constexpr (TASK == TASK_DISCOUNT) {
                 asm volatile("v_fma_f64 %0, %8, %10, %11 clamp\n\tv_fma_f64 %1, %8, %10, %12 clamp\n\tv_fma_f64 %2, %9, %10, %11 clamp\n\tv_fma_f64 %3, %9, %10, %12 clamp\n\t"
                              "v_fma_f64 %0, %0, -|%13|, %15\n\tv_fma_f64 %1, %1, -|%14|, %16\n\tv_fma_f64 %2, %2, -|%13|, %15\n\tv_fma_f64 %3, %3, -|%14|, %16\n\t"
@@ -401,7 +427,7 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
     load(K);
     store(0);
     if (PLAIN) __syncthreads();
-    else if (refused()) return false;
+    else if (refused()) return BY_OWN_OPERATIONS;
     for (int t = 0; t < stages; ++t) {
         const int buf = t & 1, k0 = t * BK;
         if (t + 1 < stages) load(K - (t + 1) * BK);
@@ -434,10 +460,10 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
         if (t + 1 < stages) store(buf ^ 1);
         // (looked at after the first stage, some 64 or 128 k, and twice as many each time, and at the end)
         if (!PLAIN && (t & (t + 1)) == 0 && t >= 7) {
-            if (refused()) return false;
+            if (refused()) return BY_OWN_OPERATIONS;
         } else __syncthreads();
     }
-    if (!PLAIN && refused()) return false;
+    if (!PLAIN && refused()) return BY_OWN_OPERATIONS;
     if constexpr (TASK != TASK_COUNT_GT) gather();
 
     int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
@@ -472,7 +498,7 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
                     if (wrow + r < M) dst[r] += sum(r, j);
             }
         }
-        return true;
+        return CRITICAL_DONE;
     }
 #pragma unroll
     for (int p = 0; p < PAIRS; ++p) {
@@ -501,7 +527,7 @@ __device__ __forceinline__ bool critical_tile_f64(const Args &args, const unsign
                 }
         }
     }
-    return true;
+    return CRITICAL_DONE;
 }
 
 // A tile by critical values, or, if it holds what they do not take, by the task's own operations.
@@ -512,10 +538,16 @@ mmlike_critical_f64_kernel(const MmlikeArgsF64 args)
     extern __shared__ __attribute__((aligned(16))) char critical64_smem[];
     Critical64Lds<TASK, NW> &L = *(Critical64Lds<TASK, NW> *)critical64_smem;
     const unsigned wave = own_wave();
-    if (critical_tile_f64<TASK, TF, TRANS, NW, false>(args, threadIdx.x, L)) return;
+    const CriticalWay way = critical_tile_f64<TASK, TF, TRANS, NW, BY_CLAMP>(args, threadIdx.x, L);
+    if (way == CRITICAL_DONE) return;
     unsigned tid;
+    if constexpr (TASK == TASK_DISCOUNT)
+        if (way == BY_MASKS) {
+            const auto &again = opaque_args<MmlikeArgsF64>(wave, tid);
+            if (critical_tile_f64<TASK, TF, TRANS, NW, BY_MASKS>(again, tid, L) == CRITICAL_DONE) return;
+        }
     const auto &again = opaque_args<MmlikeArgsF64>(wave, tid);
-    critical_tile_f64<TASK, TF, TRANS, NW, true>(again, tid, L);
+    critical_tile_f64<TASK, TF, TRANS, NW, BY_OWN_OPERATIONS>(again, tid, L);
 }
 
 template <int TASK, int TF, int TRANS, int NW>

@@ -71,6 +71,44 @@ def test_products_at_the_threshold(am, rows, M, N, K, sign):
         assert torch.equal(R, torch.where(p > th, 0.0, p)), (bits, sign)
 
 
+@pytest.mark.parametrize("rows,M,N,K", [(64, 3072, 2048, 64), (128, 2048, 2048, 256)])
+@pytest.mark.parametrize("rest", [(1.0, 0.7, 0.5, 0.0), (0.3,), (0.3, 0.1, 1e-2, 1e-4), (1e-6, 1e-9, 1e-12, 2.0 ** -52), (1.5, 3.0, -0.25, -5.0)])
+def test_error_of_a_term(am, rest, rows, M, N, K):
+    """One product per sum, discounts that leave `rest` of what is over: two roundings if it is, one if it is not, whatever is left."""
+    import numpy as np
+    g = torch.Generator(device="cuda").manual_seed(K)
+
+    def value(n):
+        v = torch.empty(n, dtype=torch.float64, device="cuda").uniform_(1, 8, generator=g)
+        return v * (torch.randint(0, 2, (n,), generator=g, device="cuda") * 2 - 1)
+    a, b = value(M), value(N)
+    A, B = torch.zeros(M, K, dtype=torch.float64, device="cuda"), torch.zeros(K, N, dtype=torch.float64, device="cuda")
+    A[:, K - 3], B[K - 3] = a, b
+    th = torch.empty(N, dtype=torch.float64, device="cuda").uniform_(0.5, 20, generator=g)
+    dis = 1.0 - torch.tensor(rest, dtype=torch.float64, device="cuda").repeat(N)[:N]
+    R = torch.zeros(M, N, dtype=torch.float64, device="cuda")
+    assert "critical_rows %d" % rows in run(am, A, B, th, dis, R)[0]
+    if np.finfo(np.longdouble).nmant <= 52:
+        pytest.skip("no wider type to compare with")
+    long = [x.cpu().numpy().astype(np.longdouble) for x in (a, b, 1.0 - dis)]
+    over = (a[:, None] * b > th).cpu().numpy()
+    want = long[0][:, None] * long[1] * np.where(over, long[2], 1.0)
+    error = np.abs(R.cpu().numpy() - want)
+    assert (error <= 2.0 ** -53 * np.where(over, 2, 1) * np.abs(want) * (1 + 2.0 ** -9)).all(), rest
+
+
+@pytest.mark.parametrize("M,N,K", [(3072, 2048, 64), (2048, 2048, 2048)])
+@pytest.mark.parametrize("left", [1e-3, 1e-6, 2.0 ** -52])
+def test_error_where_everything_is_over(am, left, M, N, K):
+    A, B, th, dis = make(K, M, N, K)
+    A, B, th, dis = A.abs() + 0.5, B.abs() + 0.5, th * 0.1, torch.full_like(dis, 1.0 - left)
+    R = torch.zeros(M, N, dtype=torch.float64, device="cuda")
+    assert "critical_rows" in run(am, A, B, th, dis, R)[0]
+    want, mag = reference(A, B, th, dis, 0.0)
+    # K sums, and a product's two roundings, here and in the reference
+    assert bool(((R - want).abs() <= 2.0 ** -53 * (2 * K + 4) * mag).all())
+
+
 SIZES = [(3072, 2048, 64, 0), (2048, 2048, 256, 0), (3071, 2047, 67, 1), (2049, 2045, 263, 3), (4481, 1025, 79, 0), (1985, 2050, 271, 1)]
 
 
