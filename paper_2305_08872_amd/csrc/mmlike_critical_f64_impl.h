@@ -259,7 +259,15 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
         if constexpr (!PLAIN && TASK == TASK_BOOST) {
 #pragma unroll
             for (int i = 0; i < AE; ++i) in = in && boost_takes(sa[i]);
-        } else if (!PLAIN && zeros) {
+        } else if constexpr (!PLAIN && TASK == TASK_DISCOUNT) {
+            // (|a| below 2^900: with |b| of 2^100 at most no product is past the largest double, which would be infinite before the discount
+            // is taken off.  High halves as fp32 numbers come in the same order, and then no numbers, which a maximum keeps)
+            auto high = [](double v) { return __builtin_bit_cast(float, (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32)); };
+            float most = high(sa[0]);
+            if constexpr (AE == 2) asm("v_maximum3_f32 %0, |%1|, |%2|, |%2|" : "=v"(most) : "v"(high(sa[0])), "v"(high(sa[1])));
+            in = in && __builtin_fabsf(most) < __builtin_bit_cast(float, (1023u + 900u) << 20);
+        }
+        if (!PLAIN && TASK != TASK_BOOST && zeros) {
             // (a threshold of 0 has 0 for its critical value, as no product is rounded to 0: |a| of 2^-299 or more, or 0)
 #pragma unroll
             for (int i = 0; i < AE; ++i) in = in && (__builtin_fabs(sa[i]) >= 0x1p-299 || sa[i] == 0.0);

@@ -109,6 +109,20 @@ def test_error_where_everything_is_over(am, left, M, N, K):
     assert bool(((R - want).abs() <= 2.0 ** -53 * (2 * K + 4) * mag).all())
 
 
+def test_products_past_the_largest_number(am):
+    """Infinite before the discount is taken off."""
+    for M, N, K in [(3072, 2048, 64), (2048, 2048, 256)]:
+        A, B, th, dis = make(K, M, N, K)
+        A[7, 9], A[2040, K - 1], A[5, 5] = 1.5e308, -1.7e308, 2.0 ** 900
+        B[9], B[K - 1], B[5] = B[9] * 3 + torch.sign(B[9]), B[K - 1] * 5 + torch.sign(B[K - 1]), 2.0 ** 99
+        R = torch.zeros(M, N, dtype=torch.float64, device="cuda")
+        assert "critical_rows" in run(am, A, B, th, dis, R)[0]
+        want, mag = reference(A, B, th, dis, 0.0)
+        big = ~torch.isfinite(want)
+        assert int(big.sum()) > N and bool((R == want)[big].all())
+        assert bool(((R - want).abs() <= 2.0 ** -53 * (2 * K + 4) * mag)[~big].all())
+
+
 SIZES = [(3072, 2048, 64, 0), (2048, 2048, 256, 0), (3071, 2047, 67, 1), (2049, 2045, 263, 3), (4481, 1025, 79, 0), (1985, 2050, 271, 1)]
 
 
