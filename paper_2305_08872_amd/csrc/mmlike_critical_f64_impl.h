@@ -66,7 +66,7 @@ struct Critical64Lds {
     static constexpr int BK = NW;
     // what an element of B comes to: the discount's base, c and cut (or x, c and y); c; or b
     static constexpr int KINDS = TASK == TASK_DISCOUNT ? 3 : 1, C = TASK == TASK_DISCOUNT ? 1 : 0, CUT = 2 % KINDS;
-    double b[KINDS][2][BK][C64_BP];
+    double b[2][KINDS][BK][C64_BP];
     double a[2][BK][c64_rows(TASK, NW) + 2];
     double th[C64_COLS], half[C64_COLS], od[C64_COLS];
 };
@@ -203,6 +203,12 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
     const int arow_in = row0 + arow < M ? row0 + arow : M - 1;
     const double *asrc = transA ? Ag + (int64_t)ak * args.lda + arow_in : Ag + (int64_t)arow_in * args.lda + ak;
     constexpr int ASTEP = transA ? BK / AE : 1;
+    // (the places computed again where they are used: held through the K loop they are registers too many)
+    auto thread_again = [&] {
+        int x = wave * 64 + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(x));
+        return x;
+    };
     uint64_t bad = 0;      // lanes that staged a value out of range
     double sb[2], sa[AE];
     auto load = [&](int left) {      // `left` k of the range from this stage on
@@ -223,8 +229,11 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
             }
         } else {
             // a k past the last one: nothing times nothing (the plain way stops before it)
-            int last = left - 1;
+            int last = left - 1, ak, arow, bk, bc;
             asm volatile("" : "+s"(last));
+            const int x = thread_again();
+            place_a(x, ak, arow);
+            place_b(x, bk, bc);
             auto at = [&](int k) { return k < last ? k : last; };
             const double *from = bsrc + (int64_t)(at(bk) - bk) * (transB ? 1 : args.ldb);
             const double b0 = from[0], b1 = from[bnext];
@@ -241,9 +250,8 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
         asrc += transA ? (int64_t)BK * args.lda : (int64_t)BK;
     };
     auto store = [&](int buf) {
-        // (the places in LDS computed again: held through the K loop they are registers too many)
-        int x = wave * 64 + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), ak, arow, bk, bc;
-        asm volatile("" : "+v"(x));
+        int ak, arow, bk, bc;
+        const int x = thread_again();
         place_a(x, ak, arow);
         place_b(x, bk, bc);
 #pragma unroll
@@ -304,9 +312,9 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
             if constexpr (transB) { to[bk][bc] = v[0]; to[bk][bc + 64] = v[1]; }
             else *(cd2 *)&to[bk][bc] = cd2{v[0], v[1]};
         };
-        if constexpr (PLAIN || TASK != TASK_COUNT_GT) put(L.b[0][buf], base);
-        if constexpr (!PLAIN && TASK != TASK_BOOST) put(L.b[Lds::C][buf], c);
-        if constexpr (!PLAIN && TASK == TASK_DISCOUNT) put(L.b[Lds::CUT][buf], cut);
+        if constexpr (PLAIN || TASK != TASK_COUNT_GT) put(L.b[buf][0], base);
+        if constexpr (!PLAIN && TASK != TASK_BOOST) put(L.b[buf][Lds::C], c);
+        if constexpr (!PLAIN && TASK == TASK_DISCOUNT) put(L.b[buf][Lds::CUT], cut);
     };
     auto refused = [&] { return __syncthreads_or(bad != 0) != 0; };
 
@@ -323,8 +331,8 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
     auto columns_of = [&](int buf, int k) {
         Columns o;
 #pragma unroll
-        for (int p = 0; p < PAIRS; ++p) o.b[p] = *(const cd2 *)&L.b[0][buf][k][at * 2 + 64 * p];
-        if constexpr (!PLAIN && TASK == TASK_DISCOUNT) { o.c = *(const cd2 *)&L.b[Lds::C][buf][k][at * 2]; o.cut = *(const cd2 *)&L.b[Lds::CUT][buf][k][at * 2]; }
+        for (int p = 0; p < PAIRS; ++p) o.b[p] = *(const cd2 *)&L.b[buf][0][k][at * 2 + 64 * p];
+        if constexpr (!PLAIN && TASK == TASK_DISCOUNT) { o.c = *(const cd2 *)&L.b[buf][Lds::C][k][at * 2]; o.cut = *(const cd2 *)&L.b[buf][Lds::CUT][k][at * 2]; }
         return o;
     };
     auto rows_of = [&](int buf, int k, int pair) { return *(const cd2 *)&L.a[buf][k][first_row + 2 * pair]; };

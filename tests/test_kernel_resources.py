@@ -34,11 +34,11 @@ def _kernels(obj, tmp):
 
 
 @pytest.mark.parametrize("source", [s for s in hip_build.SOURCES
-                                    if re.match(r"mmlike_(tile_|valu_(discount|boost|count_gt)_)", s)])
+                                    if re.match(r"mmlike_(tile_|critical_f64_|valu_(discount|boost|count_gt)_)|identity_split_waves", s)])
 def test_predicate_task_kernels_keep_everything_in_registers(source, tmp_path):
     obj = os.path.join(hip_build.OBJ_DIR, os.path.splitext(source)[0] + ".o")
     if not os.path.exists(obj):
         hip_build.build()
     kernels = list(_kernels(obj, str(tmp_path)))
-    assert len(kernels) >= 16
+    assert len(kernels) >= (16 if re.match("mmlike_(tile|valu)_", source) else 4)
     assert [k for k in kernels if k[1] != 0] == []
