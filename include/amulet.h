@@ -504,7 +504,9 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K);
  * of a compute kernel -- 0 the last, up to 15; "" where there is none -- whichever
  * entry point made it.  A shape's name as amulet_shape_name or
  * amulet_f64_shape_name gives it, or a tile kernel's: f32_tile_16x64,
- * f32_tile_32x64, f64_tile_... (predicate tasks), i8_tile_64x64 to i8_tile_256x256
+ * f32_tile_32x64, f64_tile_... (predicate tasks), f64_critical_64x128 or
+ * f64_critical_128x128 (predicate tasks in fewer fp64 operations: discount and
+ * count by critical values, boost by a clamp), i8_tile_64x64 to i8_tile_256x256
  * (join count; _ring6: the deeper operand ring, _registers: operands staged
  * through registers, _bypass: R around the caches); then " rows <rows of R>", and
  * for a tile kernel " parts <workgroups per tile, each over a range of K> kpart
@@ -515,11 +517,9 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K);
  * sums: no less precise than the fp32 kernels over sums of many products of like
  * size; a product that stands alone in its sum, as with a diagonal A, is within
  * 1.8e-7 of itself and 3e-8 on average, where those kernels' one rounding is 6e-8
- * and 2.1e-8.  A named shape runs its own fp32 kernel); " critical_rows <64 or
- * 128>" for a tile kernel in whose stead an fp64 predicate task ran in fewer
- * operations (discount and count by critical values, boost by a clamp), on tiles of
- * so many rows and 128 columns (the rows past its own are a launch of their own, of
- * the tile kernels; of a count with a threshold per row, the columns).  The adaptive
+ * and 2.1e-8.  A named shape runs its own fp32 kernel); and for f64_critical_...
+ * " critical_rows <rows of its tile>" (the rows past its own are a launch of their
+ * own, of the tile kernels; of a count with a threshold per row, the columns).  The adaptive
  * calls make one launch per trial and one for the rest.  Static storage of the
  * calling thread, until its next call of this function.
  */

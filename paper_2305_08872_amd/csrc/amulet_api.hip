@@ -153,7 +153,7 @@ struct KernelNote {
     int ring, registers, bypass;   // (join count)
     int64_t rows;
     int pieces;                    // (rows of a tile of the kernel on the matrix cores that stood in for the shape)
-    int critical;                  // (rows of a tile of the kernel by critical values that stood in for the tile kernel)
+    int critical;                  // (rows of a tile of the kernel by critical values, which has no shape id either)
 };
 constexpr unsigned KERNEL_NOTES = 16;
 static thread_local KernelNote g_notes[KERNEL_NOTES];
@@ -895,9 +895,7 @@ static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, v
         const bool swaps = critical_f64_swaps(c);
         // (a slab of an adaptive call: all of it)
         const int64_t all = swaps ? c.N : rows, first = rows == c.M ? tile->rest : all;
-        // (told as the plan it stands in for)
         note.shape = -1; note.rows = swaps ? rows : first; note.critical = tile->critical;
-        note.tile = tile->wide; note.parts = tile->parts; note.kpart = tile->kpart; note.kgroup = tile->kgroup;
         a.M = (int)first;
         if (swaps) {
             a.A = sub.B; a.lda = c.ldb; a.transA = !c.trans_b;
@@ -1735,7 +1733,7 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K)
 
 const char *amulet_recent_kernel(int back)
 {
-    static thread_local char text[192];
+    static thread_local char text[160];
     text[0] = 0;
     if (back < 0 || back >= (int)KERNEL_NOTES || (unsigned)back >= g_notes_made) return text;
     const KernelNote &n = g_notes[(g_notes_made - 1 - (unsigned)back) % KERNEL_NOTES];
@@ -1750,10 +1748,11 @@ const char *amulet_recent_kernel(int back)
         static const char *const tiles[5] = {"256x256", "128x256", "128x128", "64x64", "192x256"};
         snprintf(text, sizeof(text), "i8_tile_%s%s%s%s rows %lld parts %d kpart %d kgroup %d", tiles[n.tile], n.ring ? "_ring6" : "",
                  n.registers ? "_registers" : "", n.bypass ? "_bypass" : "", rows, n.parts, n.kpart, n.kgroup);
+    } else if (n.critical) {
+        snprintf(text, sizeof(text), "f64_critical_%dx128 rows %lld critical_rows %d", n.critical, rows, n.critical);
     } else {
-        const int len = snprintf(text, sizeof(text), "%s_tile_%s rows %lld parts %d kpart %d kgroup %d", n.f64 ? "f64" : "f32", n.tile ? "32x64" : "16x64",
-                                 rows, n.parts, n.kpart, n.kgroup);
-        if (n.critical) snprintf(text + len, sizeof(text) - (size_t)len, " critical_rows %d", n.critical);
+        snprintf(text, sizeof(text), "%s_tile_%s rows %lld parts %d kpart %d kgroup %d", n.f64 ? "f64" : "f32", n.tile ? "32x64" : "16x64",
+                 rows, n.parts, n.kpart, n.kgroup);
     }
     return text;
 }

@@ -54,8 +54,10 @@ def test_a_call_that_names_no_shape_tells_which_kernel_it_ran(lib):
     for task in (1, 2, 3):
         name, got = f32(lib, task, 256, 256, 256)
         assert name in ("f32_tile_16x64", "f32_tile_32x64") and got["rows"] == 256 and got["kpart"] * got["parts"] >= 256
-        name, got = f64(lib, task, 4096, 4096, 4096)
-        assert name in ("f64_tile_16x64", "f64_tile_32x64") and got["rows"] == 4096 and got["parts"] == 1
+        name, got = f64(lib, task, 1024, 1024, 1024)
+        assert name in ("f64_tile_16x64", "f64_tile_32x64") and got["rows"] == 1024 and got["parts"] == 1
+        rows = 64 if task == 2 else 128
+        assert f64(lib, task, 4096, 4096, 4096) == ("f64_critical_%dx128" % rows, {"rows": 4096, "critical_rows": rows})
     name, got = i8(lib, 1000, 1000, 1000)
     assert name.startswith("i8_tile_") and got["rows"] == 1000
     # where no tile kernel runs: the selected shape
