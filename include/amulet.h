@@ -519,7 +519,9 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K);
  * 1.8e-7 of itself and 3e-8 on average, where those kernels' one rounding is 6e-8
  * and 2.1e-8.  A named shape runs its own fp32 kernel); and for f64_critical_...
  * " critical_rows <rows of its tile>" (the rows past its own are a launch of their
- * own, of the tile kernels; of a count with a threshold per row, the columns).  The adaptive
+ * own, of the tile kernels; of a count with a threshold per row, the columns); and
+ * for the fp64 identity task " k_groups <2 or 4>" where so many groups of waves
+ * share a tile's K.  The adaptive
  * calls make one launch per trial and one for the rest.  Static storage of the
  * calling thread, until its next call of this function.
  */

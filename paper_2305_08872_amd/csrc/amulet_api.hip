@@ -154,6 +154,7 @@ struct KernelNote {
     int64_t rows;
     int pieces;                    // (rows of a tile of the kernel on the matrix cores that stood in for the shape)
     int critical;                  // (rows of a tile of the kernel by critical values, which has no shape id either)
+    int groups;                    // (fp64 identity: groups of waves that share a tile's K)
 };
 constexpr unsigned KERNEL_NOTES = 16;
 static thread_local KernelNote g_notes[KERNEL_NOTES];
@@ -161,7 +162,7 @@ static thread_local unsigned g_notes_made = 0;
 static KernelNote &new_note(int task, int f64, int shape, int64_t rows)
 {
     KernelNote &n = g_notes[g_notes_made++ % KERNEL_NOTES];
-    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, rows, 0, 0};
+    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, rows, 0, 0, 1};
     return n;
 }
 
@@ -926,7 +927,7 @@ static int run_f64_rows(const F64Call &c, int shape, int64_t r0, int64_t rows, v
             e = launch_tile_call<double>(sub, choose_tile_plan<double>(sub.M, sub.N, c.K, kTileUsF64[c.task], tile->rest_parts), (hipStream_t)stream);
         }
     } else {
-        e = launch_mmlike_f64(c.task, c.thres_form, shape, a, (hipStream_t)stream);
+        e = launch_mmlike_f64(c.task, c.thres_form, shape, a, note.groups, (hipStream_t)stream);
     }
     g_last_hip_error = e;
     return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
@@ -1743,6 +1744,7 @@ const char *amulet_recent_kernel(int back)
                            : n.task != TASK_IDENTITY ? amulet_f64_shape_name(n.shape)
                            : n.shape % F64_TILES == 0 ? "mfma_f64_64x64_dma4" : "mfma_f64_128x128_dma4";
         if (n.pieces) snprintf(text, sizeof(text), "%s rows %lld bf16_pieces 3 tile_rows %d", name, rows, n.pieces);
+        else if (n.groups > 1) snprintf(text, sizeof(text), "%s rows %lld k_groups %d", name, rows, n.groups);
         else snprintf(text, sizeof(text), "%s rows %lld", name, rows);
     } else if (n.task == AMULET_TASK_COUNT_I8) {
         static const char *const tiles[5] = {"256x256", "128x256", "128x128", "64x64", "192x256"};

@@ -656,8 +656,8 @@ hipError_t launch_mmlike_critical_f64(const MmlikeArgsF64 &a, int rows, hipStrea
 // fp64 shapes of the predicate tasks: a small grid of the same two axes as the fp32 one
 // (k axis: K whole, in 2, in 4 parts per tile; tile: 16 x 128 with 4 waves, 32 x 128 with 8).
 enum { F64_KAXIS = 3, F64_TILES = 2, F64_SHAPE_COUNT = F64_KAXIS * F64_TILES };
-hipError_t launch_mmlike_f64(int task, int form, int shape, const MmlikeArgsF64 &a, hipStream_t s);
-hipError_t launch_identity_mfma_f64(const MmlikeArgsF64 &a, int tile, hipStream_t s);
+hipError_t launch_mmlike_f64(int task, int form, int shape, const MmlikeArgsF64 &a, int &groups, hipStream_t s);
+hipError_t launch_identity_mfma_f64(const MmlikeArgsF64 &a, int tile, int &groups, hipStream_t s);
 // the streamed fp64 identity kernel (identity_mfma_f64_dma.hip)
 bool identity_f64_dma_eligible(const MmlikeArgsF64 &a);
 hipError_t enqueue_identity_f64_dma(const MmlikeArgsF64 &a, int tile, int groups, unsigned grid_x, unsigned grid_y, hipStream_t s);

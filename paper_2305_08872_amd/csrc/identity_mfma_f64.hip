@@ -331,7 +331,7 @@ static hipError_t launch_di_layout(const MmlikeArgsF64 &a, unsigned grid, int64_
 // The streamed 64 x 64 tile, for problems with fewer 128 x 128 tiles than compute units (the fp64
 // counterpart of the fp32 kernel's small tile, identity_mfma.hip, where the reasons are given):
 // K split by the streamed kernels' model with four workgroups (rings of 32 KB) to a unit.
-static hipError_t launch_di_small(const MmlikeArgsF64 &a, hipStream_t s)
+static hipError_t launch_di_small(const MmlikeArgsF64 &a, int &groups, hipStream_t s)
 {
     MmlikeArgsF64 b = a;
     b.kchunk = a.K;
@@ -360,19 +360,19 @@ static hipError_t launch_di_small(const MmlikeArgsF64 &a, hipStream_t s)
         }
     }
     const int64_t workgroups = resident(splits);
-    const int groups = workgroups > 2 || b.kchunk < 256 || (workgroups == 2 && (splits > 1 || a.K < 512)) ? 1 : workgroups == 1 && b.kchunk >= 1024 ? 4 : 2;
+    groups = workgroups > 2 || b.kchunk < 256 || (workgroups == 2 && (splits > 1 || a.K < 512)) ? 1 : workgroups == 1 && b.kchunk >= 1024 ? 4 : 2;
     return launch_row_of_blocks(b, grid, 256, [&](unsigned n) {
         (void)enqueue_identity_f64_dma(b, 64, groups, n, (unsigned)splits, s);
     });
 }
 
-// tile: 64 = the streamed 64 x 64 tile where the streamed kernel takes the problem; else 128 x 128
-hipError_t launch_identity_mfma_f64(const MmlikeArgsF64 &a, int tile, hipStream_t s)
+// tile: 64 = the streamed 64 x 64 tile where the streamed kernel takes the problem; else 128 x 128.  groups: of waves that share a tile's K
+hipError_t launch_identity_mfma_f64(const MmlikeArgsF64 &a, int tile, int &groups, hipStream_t s)
 {
     if (tile == 64) {
         MmlikeArgsF64 b = a;
         b.kchunk = a.K;
-        if (identity_f64_dma_eligible(b)) return launch_di_small(a, s);
+        if (identity_f64_dma_eligible(b)) return launch_di_small(a, groups, s);
     }
     const int64_t tiles_m = (a.M + DI_BM - 1) / DI_BM;
     const int64_t tiles_n = (a.N + DI_BN - 1) / DI_BN;
