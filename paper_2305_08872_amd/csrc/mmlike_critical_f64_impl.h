@@ -258,7 +258,7 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
         for (int i = 0; i < AE; ++i) L.a[buf][ak + ASTEP * i][arow] = !PLAIN && TASK == TASK_COUNT_GT ? sa[i] * (C64_SCALE / 2) : sa[i];
         double c[2], base[2], cut[2];
         bool in = true;
-        // |a| and |b| of 2^-400 to 2^100, or 0
+        // |a| and |b| from 2^-400 to below 2^100, or 0
         auto boost_takes = [](double v) {
             const uint32_t top = (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32) & 0x7fffffffu;
             constexpr uint32_t LEAST = (1023u - 400u) << 20, MOST = (1023u + 100u) << 20;
@@ -268,7 +268,7 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
 #pragma unroll
             for (int i = 0; i < AE; ++i) in = in && boost_takes(sa[i]);
         } else if constexpr (!PLAIN && TASK == TASK_DISCOUNT) {
-            // (|a| below 2^900: with |b| of 2^100 at most no product is past the largest double, which would be infinite before the discount
+            // (|a| below 2^900: with |b| below 2^100 no product is past the largest double, which would be infinite before the discount
             // is taken off.  High halves as fp32 numbers come in the same order, and then no numbers, which a maximum keeps)
             auto high = [](double v) { return __builtin_bit_cast(float, (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32)); };
             float most = high(sa[0]);
@@ -289,11 +289,11 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
                 base[i] = b * C64_BOOST_SCALE;
                 in = in && boost_takes(b);
             } else if constexpr (!PLAIN) {
-                // |b| of 2^-600 to 2^101, or 0 (whose base and cut are 0 whatever its c, which is not a number): with th of
-                // 2^-100 to 2^100 c is 2^-201 to 2^700, and a distance of one last place of it times 2^300 more than 1
+                // |b| from 2^-600 to below 2^100, or 0 (whose base and cut are 0 whatever its c, which is not a number): with th of
+                // 2^-100 to 2^100 c is 2^-200 to 2^700, and a distance of one last place of it times 2^300 more than 1
                 const uint32_t top = (uint32_t)(__builtin_bit_cast(uint64_t, b) >> 32) & 0x7fffffffu;
                 constexpr uint32_t LEAST = (1023u - 600u) << 20, MOST = (1023u + 100u) << 20;
-                in = in && (top - LEAST <= MOST - LEAST || b == 0.0);
+                in = in && (top - LEAST < MOST - LEAST || b == 0.0);
                 c[i] = critical_value_f64<TASK == TASK_COUNT_GT, MASKS>(b, L.th[col], L.half[col]);
                 if constexpr (TASK == TASK_DISCOUNT) {
                     const double m = b * L.od[col];

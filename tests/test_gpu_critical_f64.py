@@ -157,7 +157,7 @@ def test_rows_left_to_the_tile_kernels(am, M, N, K):
 
 
 @pytest.mark.parametrize("tA,tB", [(False, False), (True, True)])
-@pytest.mark.parametrize("what", ["thresholds", "tiny b", "large", "discounts", "late", "not numbers"])
+@pytest.mark.parametrize("what", ["thresholds", "tiny b", "large", "discounts", "late", "not numbers", "limits"])
 def test_values_of_the_plain_way(am, what, tA, tB):
     for M, N, K in [(3071, 2046, 75), (2047, 2048, 259)]:
         A, B, th, dis = make(K, M, N, K, tA, tB)
@@ -179,6 +179,11 @@ def test_values_of_the_plain_way(am, what, tA, tB):
         elif what == "late":
             b[K - 1, ::2] = 1e-300
             b[min(K - 1, 200), 1000] = 1e50
+        elif what == "limits":
+            lo, hi = -600, 100
+            for i, v in enumerate([2.0 ** hi, 2.0 ** hi * (1 - 2.0 ** -53), 2.0 ** hi * 1.5, 2.0 ** lo, 2.0 ** lo * (1 - 2.0 ** -53)]):
+                b[i, 130 * i + 2], b[K - 1 - i, 130 * i + 40] = v, -v
+            th[:6] = torch.tensor([2.0 ** 100, 2.0 ** 100 * (1 + 2.0 ** -52), 2.0 ** -100, 2.0 ** -101, -(2.0 ** 100), -(2.0 ** -100)], dtype=torch.float64, device="cuda")
         else:
             a[3, 4], a[5, 6], b[7, 8], b[9, 10] = float("inf"), float("nan"), float("nan"), float("-inf")
         R = torch.zeros(M, N, dtype=torch.float64, device="cuda")

@@ -173,7 +173,7 @@ def test_rows_left_to_the_tile_kernels(am, task, form):
 
 
 @pytest.mark.parametrize("tA,tB", [(False, False), (True, True)])
-@pytest.mark.parametrize("what", ["thresholds", "tiny", "large", "late", "not numbers"])
+@pytest.mark.parametrize("what", ["thresholds", "tiny", "large", "late", "not numbers", "limits"])
 @pytest.mark.parametrize("task,form", [("count_gt", "col"), ("count_gt", "row"), ("boost", "col"), ("boost", "row")])
 def test_values_of_the_plain_way(am, task, form, what, tA, tB):
     if (task, what) == ("count_gt", "not numbers"):
@@ -197,6 +197,11 @@ def test_values_of_the_plain_way(am, task, form, what, tA, tB):
         elif what == "late":
             b[K - 1, ::2] = 1e-300
             b[min(K - 1, 200), 1000] = 1e50
+        elif what == "limits":
+            lo, hi = (-400, 100) if task == "boost" else (-600, 100)
+            for i, v in enumerate([2.0 ** hi, 2.0 ** hi * (1 - 2.0 ** -53), 2.0 ** hi * 1.5, 2.0 ** lo, 2.0 ** lo * (1 - 2.0 ** -53)]):
+                b[i, 130 * i + 2], b[K - 1 - i, 130 * i + 40] = v, -v
+            th[:6] = torch.tensor([2.0 ** 100, 2.0 ** 100 * (1 + 2.0 ** -52), 2.0 ** -100, 2.0 ** -101, -(2.0 ** 100), -(2.0 ** -100)], dtype=torch.float64, device="cuda")
         else:
             a[3, 4], a[5, 6], b[7, 8], b[9, 10] = inf, float("nan"), float("nan"), -inf
         R = torch.zeros(M, N, dtype=torch.float64, device="cuda")
