@@ -72,7 +72,10 @@ struct Critical64Lds {
 };
 
 // How a tile's terms are formed; CRITICAL_DONE: they have been.
-enum CriticalWay { CRITICAL_DONE, BY_CLAMP, BY_MASKS, BY_OWN_OPERATIONS };
+enum CriticalWay { CRITICAL_DONE, BY_CLAMP, BY_MASKS, BY_CLAMP_TO_LAST, BY_OWN_OPERATIONS };
+// DISCOUNT's masks, and BOOST's clamp with a test for K's end at each k, for thresholds below 0 and a K that is not whole stages (4096^2 x
+// 4093 6750 us, 6630 without the test, tile kernels 7600)
+constexpr CriticalWay c64_second_way(int task) { return task == TASK_DISCOUNT ? BY_MASKS : task == TASK_BOOST ? BY_CLAMP_TO_LAST : BY_OWN_OPERATIONS; }
 
 // The critical value of b for th, times what th and half, half the distance to the next double, come with: -2^300 (for thresholds
 // below 0 2^300), or 1 (MASKS).  a b rounds to more than th from the middle th + half on, a tie if the next double is even.  n = (th + half) / b to within 2^-19 of its last place: rcp is good to 2^-24,
@@ -99,7 +102,7 @@ template <int TASK, int TF, int TRANS, int NW, CriticalWay WAY, typename Args>
 __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const unsigned tid, Critical64Lds<TASK, NW> &L)
 {
     typedef Critical64Lds<TASK, NW> Lds;
-    constexpr bool PLAIN = WAY == BY_OWN_OPERATIONS, MASKS = WAY == BY_MASKS;
+    constexpr bool PLAIN = WAY == BY_OWN_OPERATIONS, MASKS = WAY == BY_MASKS, TO_LAST = PLAIN || WAY == BY_CLAMP_TO_LAST;
     constexpr bool transA = (TRANS & 1) != 0, transB = (TRANS & 2) != 0;
     constexpr int PAIRS = c64_pairs(TASK), ROWS = c64_rows(TASK, NW), BK = NW;
     constexpr bool ROW_SCALARS = TASK == TASK_BOOST && TF == THRES_ROW, SWAPPED = TASK == TASK_COUNT_GT && TF == THRES_ROW;
@@ -126,13 +129,14 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
     bool own;
     constexpr int NT = ROW_SCALARS ? C64_TM : 2 * PAIRS;
     double th[NT], od[2 * PAIRS];
-    bool fit = true, exact = true, zeros = false;
+    bool fit = true, first = true, zeros = false;     // (what all but the last way, or the first, take)
     auto fits = [&](double &t) {
         if constexpr (TASK == TASK_BOOST) {
             // (above +inf or no number, nothing: the clamp takes both.  A k past the last one is nothing times nothing: over a
             // threshold below 0)
+            first = first && !(t < 0.0 && K % BK != 0);
             const double m = __builtin_fabs(t);
-            fit = fit && (t == 0.0 || (m >= C64_LEAST_BOOST_TH && m <= C64_MOST_TH) || !(t < __builtin_inf())) && !(t < 0.0 && K % BK != 0);
+            fit = fit && (t == 0.0 || (m >= C64_LEAST_BOOST_TH && m <= C64_MOST_TH) || !(t < __builtin_inf()));
             t *= -C64_BOOST_SCALE;
         } else {
             // (no product is above +inf or above no number: no critical value, or, discounting, nothing taken off whatever it is)
@@ -171,13 +175,13 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
                 od[j] = 1.0 - args.dis[col];
                 if (none) od[j] = 1.0;
                 if constexpr (!PLAIN) fit = fit && __builtin_fabs(od[j]) <= C64_MOST_TH;
-                exact = exact && (od[j] == 0.0 || (od[j] >= 0.5 && od[j] <= 1.0));
+                first = first && (od[j] == 0.0 || (od[j] >= 0.5 && od[j] <= 1.0));
             }
         }
     }
     // (all waves face the same columns)
     if (!PLAIN && __builtin_amdgcn_ballot_w64(!fit) != 0) return BY_OWN_OPERATIONS;
-    if (TASK == TASK_DISCOUNT && WAY == BY_CLAMP && __builtin_amdgcn_ballot_w64(!exact) != 0) return BY_MASKS;
+    if (TASK != TASK_COUNT_GT && WAY == BY_CLAMP && __builtin_amdgcn_ballot_w64(!first) != 0) return c64_second_way(TASK);
     zeros = __builtin_amdgcn_ballot_w64(zeros) != 0;
     if constexpr (!PLAIN && TASK != TASK_BOOST) {
         if (wave == 0)
@@ -450,7 +454,7 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
         // (the plain way in eights, so that its loop is unrolled, and to the last k)
 #pragma unroll
         for (int h = 0; h < BK; h += 8) {
-            if (PLAIN && k0 + h >= K) break;
+            if (TO_LAST && k0 + h >= K) break;
             if (PLAIN || h == 0) {
                 o[0] = columns_of(buf, h);
 #pragma unroll
@@ -458,7 +462,7 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
             }
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                if (PLAIN && k0 + h + k >= K) break;
+                if (TO_LAST && k0 + h + k >= K) break;
                 const bool more = k < 7 || (!PLAIN && h + 8 < BK);
 #pragma unroll
                 for (int i = 0; i < HALF; ++i) {
@@ -557,10 +561,10 @@ mmlike_critical_f64_kernel(const MmlikeArgsF64 args)
     const CriticalWay way = critical_tile_f64<TASK, TF, TRANS, NW, BY_CLAMP>(args, threadIdx.x, L);
     if (way == CRITICAL_DONE) return;
     unsigned tid;
-    if constexpr (TASK == TASK_DISCOUNT)
-        if (way == BY_MASKS) {
+    if constexpr (TASK != TASK_COUNT_GT)
+        if (way != BY_OWN_OPERATIONS) {
             const auto &again = opaque_args<MmlikeArgsF64>(wave, tid);
-            if (critical_tile_f64<TASK, TF, TRANS, NW, BY_MASKS>(again, tid, L) == CRITICAL_DONE) return;
+            if (critical_tile_f64<TASK, TF, TRANS, NW, c64_second_way(TASK)>(again, tid, L) == CRITICAL_DONE) return;
         }
     const auto &again = opaque_args<MmlikeArgsF64>(wave, tid);
     critical_tile_f64<TASK, TF, TRANS, NW, BY_OWN_OPERATIONS>(again, tid, L);

@@ -159,6 +159,19 @@ def test_remainders_forms_and_layouts(am, task, form, tA, tB):
     assert sum("critical_rows" in r for r in ran) >= 3, ran
 
 
+@pytest.mark.parametrize("form,tA,tB", [("col", False, False), ("row", True, False), ("const", False, True), ("col", True, True)])
+@pytest.mark.parametrize("K", [65, 71, 72, 263])
+def test_boost_below_zero_stops_at_the_last_k(am, form, K, tA, tB):
+    """Thresholds of both signs: a k past the last one, nothing times nothing, would be over those below 0."""
+    M, N = 4093, 2047
+    A, B, th = make(K, M, N, K, form, tA, tB)
+    th[::2] *= -1.0
+    R = torch.full((M, N), 0.25, dtype=torch.float64, device="cuda")
+    assert "critical_rows 64" in run(am, "boost", A, B, th, R, form, tA, tB)[0]
+    want, mag = reference("boost", A, B, th, form, 0.25, tA, tB)
+    assert bool(close("boost", R, want, mag, K).all())
+
+
 @pytest.mark.parametrize("task,form", [("count_gt", "col"), ("count_gt", "row"), ("boost", "row")])
 def test_rows_left_to_the_tile_kernels(am, task, form):
     left = 0
