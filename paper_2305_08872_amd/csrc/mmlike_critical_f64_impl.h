@@ -59,6 +59,8 @@ constexpr double C64_SCALE = 0x1p300;
 // (2^-202: p - th is then below 1 wherever BOOST takes the operands)
 constexpr double C64_BOOST_SCALE = 0x1p-202, C64_LEAST_BOOST_TH = 0x1p-400;
 constexpr double C64_LEAST_TH = 0x1p-100, C64_MOST_TH = 0x1p100;
+// more than a product of a discount's operands: |a| below 2^900, |b| below 2^100
+constexpr double C64_PRODUCTS = 0x1p1000;
 
 // NW waves: 8 (stages of 8 k, two workgroups to a compute unit) or, for the discount, 16 (16 k, one)
 template <int TASK, int NW>
@@ -139,14 +141,19 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
             fit = fit && (t == 0.0 || (m >= C64_LEAST_BOOST_TH && m <= C64_MOST_TH) || !(t < __builtin_inf()));
             t *= -C64_BOOST_SCALE;
         } else {
-            // (no product is above +inf or above no number: no critical value, or, discounting, nothing taken off whatever it is)
-            const bool none = !(t < __builtin_inf());
+            // (no product is above +inf or above no number: no critical value, or, discounting, nothing taken off whatever it is.  A
+            // discount's products are below 2^1000: none is over a threshold from there on, and all are over one from -2^1000 down,
+            // whose critical value, infinite, masks take)
+            const bool none = !(t < (TASK == TASK_DISCOUNT ? C64_PRODUCTS : __builtin_inf()));
+            const bool always = TASK == TASK_DISCOUNT && t <= -C64_PRODUCTS;
             const double m = __builtin_fabs(t);
             zeros = zeros || t == 0.0;
-            fit = fit && (none || t == 0.0 || (m >= C64_LEAST_TH && m <= C64_MOST_TH));
+            fit = fit && (none || always || t == 0.0 || (m >= C64_LEAST_TH && m <= C64_MOST_TH));
             if (none) t = TASK == TASK_DISCOUNT ? 1.0 : __builtin_nan("");
             // (a b > -m unless a -b > the number below m)
             if (t < 0.0) t = -__builtin_bit_cast(double, __builtin_bit_cast(uint64_t, m) - 1);
+            if (always) t = -__builtin_inf();
+            first = first && !always;
             t += 0.0;
             return none;
         }
@@ -299,6 +306,7 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
                 constexpr uint32_t LEAST = (1023u - 600u) << 20, MOST = (1023u + 100u) << 20;
                 in = in && (top - LEAST < MOST - LEAST || b == 0.0);
                 c[i] = critical_value_f64<TASK == TASK_COUNT_GT, MASKS>(b, L.th[col], L.half[col]);
+                if constexpr (MASKS) c[i] = L.th[col] < -C64_PRODUCTS ? __builtin_copysign(__builtin_inf(), -b) : c[i];
                 if constexpr (TASK == TASK_DISCOUNT) {
                     const double m = b * L.od[col];
                     if constexpr (MASKS) {
@@ -358,13 +366,16 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
             const double a = rows[0], e = rows[1];
             double t[4];
             if constexpr (TASK == TASK_DISCOUNT && PLAIN) {
-                // (the discount under the execution mask: mmlike_valu_f64.hip)
-                asm volatile("v_mul_f64 %0, %8, %10\n\tv_mul_f64 %1, %8, %11\n\tv_mul_f64 %2, %9, %10\n\tv_mul_f64 %3, %9, %11\n\t"
-                             "v_cmpx_gt_f64_e32 vcc, %0, %12\n\tv_mul_f64 %0, %0, %14\n\ts_mov_b64 exec, %16\n\tv_cmpx_gt_f64_e32 vcc, %1, %13\n\tv_mul_f64 %1, %1, %15\n\ts_mov_b64 exec, %16\n\t"
-                             "v_cmpx_gt_f64_e32 vcc, %2, %12\n\tv_mul_f64 %2, %2, %14\n\ts_mov_b64 exec, %16\n\tv_cmpx_gt_f64_e32 vcc, %3, %13\n\tv_mul_f64 %3, %3, %15\n\ts_mov_b64 exec, %16\n\t"
+                // (four comparisons first: each followed by its own masked product, as in mmlike_valu_f64.hip, 4096^3 9220 us, so 8865)
+                uint64_t over[4];
+                asm volatile("v_mul_f64 %0, %[a], %[b0]\n\tv_mul_f64 %1, %[a], %[b1]\n\tv_mul_f64 %2, %[e], %[b0]\n\tv_mul_f64 %3, %[e], %[b1]\n\t"
+                             "v_cmp_gt_f64_e64 %8, %0, %[th0]\n\tv_cmp_gt_f64_e64 %9, %1, %[th1]\n\tv_cmp_gt_f64_e64 %10, %2, %[th0]\n\tv_cmp_gt_f64_e64 %11, %3, %[th1]\n\t"
+                             "s_mov_b64 exec, %8\n\tv_mul_f64 %0, %0, %[od0]\n\ts_mov_b64 exec, %9\n\tv_mul_f64 %1, %1, %[od1]\n\t"
+                             "s_mov_b64 exec, %10\n\tv_mul_f64 %2, %2, %[od0]\n\ts_mov_b64 exec, %11\n\tv_mul_f64 %3, %3, %[od1]\n\ts_mov_b64 exec, %[active]\n\t"
                              "v_add_f64 %4, %4, %0\n\tv_add_f64 %5, %5, %1\n\tv_add_f64 %6, %6, %2\n\tv_add_f64 %7, %7, %3"
-                             : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "+v"(acc[r][0]), "+v"(acc[r][1]), "+v"(acc[r + 1][0]), "+v"(acc[r + 1][1])
-                             : "v"(a), "v"(e), "v"(o.b[0][0]), "v"(o.b[0][1]), "v"(th[0]), "v"(th[1]), "v"(od[0]), "v"(od[1]), "s"(active) : "vcc");
+                             : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "+v"(acc[r][0]), "+v"(acc[r][1]), "+v"(acc[r + 1][0]), "+v"(acc[r + 1][1]),
+                               "=&s"(over[0]), "=&s"(over[1]), "=&s"(over[2]), "=&s"(over[3])
+                             : [a] "v"(a), [e] "v"(e), [b0] "v"(o.b[0][0]), [b1] "v"(o.b[0][1]), [th0] "v"(th[0]), [th1] "v"(th[1]), [od0] "v"(od[0]), [od1] "v"(od[1]), [active] "s"(active));
             } else if constexpr (TASK == TASK_DISCOUNT && MASKS) {
 #define AMULET_EITHER(SUM, MASK, A, X, Y) "s_mov_b64 exec, " MASK "\n\tv_fma_f64 " SUM ", " A ", " X ", " SUM "\n\ts_xor_b64 exec, exec, %[active]\n\tv_fma_f64 " SUM ", " A ", " Y ", " SUM "\n\t"
                 uint64_t over[4];

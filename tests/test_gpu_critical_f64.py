@@ -157,7 +157,7 @@ def test_rows_left_to_the_tile_kernels(am, M, N, K):
 
 
 @pytest.mark.parametrize("tA,tB", [(False, False), (True, True)])
-@pytest.mark.parametrize("what", ["thresholds", "tiny b", "large", "discounts", "late", "not numbers", "limits"])
+@pytest.mark.parametrize("what", ["thresholds", "tiny b", "large", "discounts", "late", "not numbers", "limits", "always and never"])
 def test_values_of_the_plain_way(am, what, tA, tB):
     for M, N, K in [(3071, 2046, 75), (2047, 2048, 259)]:
         A, B, th, dis = make(K, M, N, K, tA, tB)
@@ -165,6 +165,11 @@ def test_values_of_the_plain_way(am, what, tA, tB):
         if what == "thresholds":
             th[:8] = torch.tensor([0.0, -0.0, -1.5, 1e-200, 1e200, float("inf"), float("-inf"), 5e-324], dtype=torch.float64, device="cuda")
             th[300], th[1000] = float("nan"), float("inf")
+        elif what == "always and never":
+            top = 1.7976931348623157e308
+            th[:10] = torch.tensor([float("inf"), float("-inf"), top, -top, 2.0 ** 1000, -(2.0 ** 1000), 0.0, -1.0, 1.0, -0.0], dtype=torch.float64, device="cuda")
+            th[200:205], th[1000:], b[4, ::3], b[7] = -top, float("-inf"), 0.0, 2.0 ** 99
+            a[40, 7], a[41, 7] = 2.0 ** 899, -(2.0 ** 899)
         elif what == "tiny b":
             b[K // 2, 5::7] = 2.0 ** -1000
             b[K // 2, 6::7] = -5e-324
