@@ -134,11 +134,11 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
     bool fit = true, first = true, zeros = false;     // (what all but the last way, or the first, take)
     auto fits = [&](double &t) {
         if constexpr (TASK == TASK_BOOST) {
-            // (above +inf or no number, nothing: the clamp takes both.  A k past the last one is nothing times nothing: over a
+            // (above +inf or no number, nothing: the clamp takes both, and all from 2^-400 up.  A k past the last one is nothing times nothing: over a
             // threshold below 0)
             first = first && !(t < 0.0 && K % BK != 0);
             const double m = __builtin_fabs(t);
-            fit = fit && (t == 0.0 || (m >= C64_LEAST_BOOST_TH && m <= C64_MOST_TH) || !(t < __builtin_inf()));
+            fit = fit && (t == 0.0 || (m >= C64_LEAST_BOOST_TH && t >= -C64_MOST_TH) || !(t < __builtin_inf()));
             t *= -C64_BOOST_SCALE;
         } else {
             // (no product is above +inf or above no number: no critical value, or, discounting, nothing taken off whatever it is.  A

@@ -166,6 +166,8 @@ def test_boost_below_zero_stops_at_the_last_k(am, form, K, tA, tB):
     M, N = 4093, 2047
     A, B, th = make(K, M, N, K, form, tA, tB)
     th[::2] *= -1.0
+    if form != "const":
+        th[1], th[3], th[5], th[150], th[151] = 2.0 ** 100, 2.0 ** 101, 1e200, 1.7976931348623157e308, float("inf")
     R = torch.full((M, N), 0.25, dtype=torch.float64, device="cuda")
     assert "critical_rows 64" in run(am, "boost", A, B, th, R, form, tA, tB)[0]
     want, mag = reference("boost", A, B, th, form, 0.25, tA, tB)
