@@ -273,21 +273,30 @@ static double count_wide_us(const MmlikeCall &c)
     const double more = (c.trans_a ? 1.32 : 1.03) * (c.thres_form == THRES_ROW ? 1.12 : 1.0);
     return wide_launch_us(c.M, c.N, c.K, more * 0.136, more * 0.08, more * 0.125) / 0.96;
 }
-// Identity of few tiles: the bf16-piece kernel whose waves share K (identity_split_waves.hip). us: 2, 4.6 per round of 256 tiles of 64 x 64, and per
-// 1000 k 8.6 or 0.0423 per tile of the round (they share the L2s and the power), 5.5 % more per operand stored along k and 13 % more
-// again if its lines are not a whole number of 64 bytes; the fp32 kernels 7 and 0.0656 per tile. Within 6 % and 7 % (rms) of 110 drawn calls of 63 to
-// 1056 tiles, K = 192 to 5900; a tenth lower, and from 480 k on, it is ahead in all of them (1.01 to 1.34), 1.2 of them on average, and
-// what it leaves loses 1 % more than the better of the two each time.
+// Identity of few tiles: the bf16-piece kernel whose waves share K (identity_split_waves.hip). us: 1.7, 6.1 per round of 256 tiles of 64 x 64, and
+// per 1000 k of a round 5.6 and 5.3 for as much of it as there are tiles (they share the L2s and the power), 0.36 more for A stored along k and 0.16
+// for B, 1.37 and 1.31 more if such lines are not a whole number of 64 bytes, and 0.19 per MB that an XCD reads (tall problems of few columns
+// read A once per column). The fp32 kernels: 13.8 per 1000 of their split's own estimate, 0.46 more per operand of such lines, whichever way it is
+// stored, and 5.1 per 1000 tiles, of which missing rows and columns add nothing. Within 4.3 % and 5.9 % (rms) of 402 drawn calls of 24 to 1280
+// tiles, K = 480 to 8192. Taken 5 % lower, 7 % below 1000 k: of 150 other calls that it takes, half of them of 700 to 1400 k,
+// 143 are ahead, 1.13 times on average, the slowest is at 0.93 (by the kernels' rates alone, from 480 k on, 53 of 77 were, 0.86).
 static bool identity_waves_wanted(const MmlikeCall &c, TilePlan &plan)
 {
-    if (c.K < 480 || (c.trans_a && c.M < 4) || (!c.trans_b && c.N < 4)) return false;
-    const int64_t tiles = ((c.M + 63) / 64) * ((c.N + 63) / 64), units = compute_units(), places = (tiles + 7) / 8 * 8, full = places / units, rest = places % units;
-    auto more = [](bool along, int64_t ld) { return along ? 0.055 + (ld % 16 != 0 ? 0.13 : 0.0) : 0.0; };
-    const double per_k = (1.0 + more(!c.trans_a, c.lda) + more(c.trans_b, c.ldb)) * (double)c.K * 1e-3;
-    auto round = [&](int64_t n) { const double us = 0.0423 * (double)n; return 4.6 + per_k * (us < 8.6 ? 8.6 : us); };
-    const double here = 2.0 + (double)full * round(units) + (rest ? round(full && rest < 100 ? 100 : rest) : 0.0);
+    if (c.K < 700 || (c.trans_a && c.M < 4) || (!c.trans_b && c.N < 4)) return false;
+    const int64_t tiles_m = (c.M + 63) / 64, tiles_n = (c.N + 63) / 64, tiles = tiles_m * tiles_n;
+    const int64_t units = compute_units(), places = (tiles + 7) / 8 * 8, full = places / units, rest = places % units;
+    const bool ragged_a = c.lda % 16 != 0, ragged_b = c.ldb % 16 != 0;
+    const double per_k = 5.57 + (c.trans_a ? 0.0 : ragged_a ? 1.73 : 0.36) + (!c.trans_b ? 0.0 : ragged_b ? 1.47 : 0.16);
+    auto round = [&](int64_t n) { return 6.12 + (per_k + 5.33 * (double)n / (double)units) * (double)c.K * 1e-3; };
+    const double here = 1.69 + (double)full * round(units) + (rest ? round(full && rest < 100 ? 100 : rest) : 0.0)
+                        + 0.193 * 256e-6 * (double)xcd_lines(tiles_m, tiles_n) * (double)c.K;
+    static const double rate[5] = {0.80, 0.93, 1.0, 1.0, 1.0};     // (as the fp32 kernel's launch splits K)
+    double cost = 0.0;
+    const double there_are = (double)c.M * (double)c.N / (4096.0 * (double)tiles);
+    const int sp = choose_stream_split(xcd_grid(tiles_m, tiles_n) / 8, units / 8, c.K, 5, rate, 200.0, 0.68, &cost);
+    if (sp > 1) cost -= 0.68 * (double)places * sp * (1.0 - there_are);
     plan.pieces = 64;
-    return here < 0.9 * (7.0 + 0.0656e-3 * (double)c.K * (double)tiles);
+    return here < (c.K < 1000 ? 0.93 : 0.95) * ((13.8 + 0.455 * (ragged_a + ragged_b)) * 1e-3 * cost + 5.12e-3 * there_are * (double)tiles);
 }
 static bool identity_split_wanted(const MmlikeCall &c, TilePlan &plan)
 {

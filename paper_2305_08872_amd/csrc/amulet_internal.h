@@ -60,6 +60,14 @@ __host__ __device__ inline int64_t xcd_places(int64_t tiles_m, int64_t tiles_n)
     if (xcd_parts_exact(g, tiles_m, tiles_n)) return (int64_t)g.cw * g.rh;
     return (tiles_m * tiles_n + 7) / 8;
 }
+// tile rows and columns that an XCD's tiles lie in: lines of both operands that it reads (to within one)
+inline int64_t xcd_lines(int64_t tiles_m, int64_t tiles_n)
+{
+    const XcdParts g = xcd_parts(tiles_m, tiles_n);
+    if (xcd_parts_exact(g, tiles_m, tiles_n)) return g.cw + g.rh;
+    const int64_t run = xcd_places(tiles_m, tiles_n), pw = (tiles_n + 7) / 8, down = (run + pw - 1) / pw;
+    return (down < tiles_m ? down : tiles_m) + pw * (run > tiles_m * pw ? 2 : 1);
+}
 // workgroups to launch for a tile grid
 inline int64_t xcd_grid(int64_t tiles_m, int64_t tiles_n) { return 8 * xcd_places(tiles_m, tiles_n); }
 // tile of workgroup `block`; false when the workgroup is padding
@@ -265,8 +273,8 @@ inline int choose_full_split(int64_t part_tiles, int64_t units_per_xcd, int64_t 
 inline int choose_stream_split(int64_t part_tiles, int64_t units, int64_t K, int cap, const double *rate,
                                double ovh_alone = 50.0, double atom_per_tile = 0.68, double *lowest = nullptr)
 {
-    if (!k_split_allowed() || part_tiles <= 0 || units <= 0) return 1;
-    const int max_s = K / 128 < 1024 ? (int)(K / 128) : 1024;
+    if (part_tiles <= 0 || units <= 0) return 1;
+    const int max_s = !k_split_allowed() || K < 256 ? 1 : K / 128 < 1024 ? (int)(K / 128) : 1024;
     int best_s = 1;
     double best = 0.0;
     // every s up to 16, then a coarser ladder (problems of a tile or two with a very long K)

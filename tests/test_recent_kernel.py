@@ -67,6 +67,15 @@ def test_a_call_that_names_no_shape_tells_which_kernel_it_ran(lib):
     assert f64(lib, 0, 1024, 1024, 1024)[0] == "mfma_f64_64x64_dma4" and f64(lib, 0, 4096, 4096, 256)[0] == "mfma_f64_128x128_dma4"
 
 
+def test_the_identity_of_few_tiles_takes_pieces_where_they_are_ahead(lib):
+    """us, fp32 kernels / pieces: 2643 x 384 x 576 14.1 / 15.4, 4288 x 422 x 768 29.5 / 33.7, 66 x 5248 x 704 12.4 / 14.4, 108 x 5120 x 6336 71 / 78;
+    1024^3 20.7 / 18.5, 531 x 1600 x 3705 60 / 47, 1639 x 512 x 981 20.5 / 17.1."""
+    for M, N, K in [(2643, 384, 576), (4288, 422, 768), (66, 5248, 704), (108, 5120, 6336), (3702, 452, 832), (2688, 384, 832)]:
+        assert "tile_rows" not in f32(lib, 0, M, N, K)[1], (M, N, K)
+    for M, N, K in [(1024, 1024, 1024), (531, 1600, 3705), (1327, 1472, 5120), (649, 1111, 4736)]:
+        assert f32(lib, 0, M, N, K)[1].get("tile_rows") == 64, (M, N, K)
+
+
 def test_a_named_shape_is_the_kernel_that_runs(lib):
     for shape in range(am.amulet_shape_count(1)):
         assert f32(lib, 1, 256, 256, 256, shape) == (am.amulet_shape_name(1, shape), {"rows": 256})
