@@ -346,13 +346,16 @@ static hipError_t launch_di_small(const MmlikeArgsF64 &a, int &groups, hipStream
     // Groups of waves that share a tile's K (identity_mfma_f64_dma.hip): with one workgroup to a unit, whose SIMDs have one wave
     // otherwise, two from 256 k on and four from 1024; with two, two from 512 k on of tiles that are not split (where what they save
     // is more than the exchange of their sums, 0.7 us; split ones 1 to 3 % slower).  The unit's rate is then 0.88, 0.91 or
-    // 0.96, so that not splitting K may be the faster: 960 x 1024 x 2048 71.5 us in 2 ranges, 67.7 whole.
+    // 0.96, so that not splitting K may be the faster: 960 x 1024 x 2048 71.5 us in 2 ranges, 67.7 whole.  With both operands
+    // stored along k two are no faster than one (26 drawn calls 1.2 % slower, 7187 x 256 x 794 56.8 / 58.6) and four no reason not to split:
+    // four or one there.
+    const bool along_k = !a.transA && a.transB;
     const double shared[2] = {a.K >= 1024 ? 0.91 : 0.88, 0.96};
     if (tiles_m * tiles_n <= 2 * cap * (int64_t)compute_units()) {
         static const double rate[4] = {0.80, 0.93, 1.0, 1.0};
         double us = 0.0;
         int sp = choose_stream_split(part_tiles, units, a.K, cap, rate, 100.0, 0.34, &us);
-        if (sp > 1 && a.K >= 256 && resident(1) <= 2 && (double)resident(1) / shared[resident(1) - 1] * (double)a.K + 100.0 < 0.99 * us) sp = 1;
+        if (sp > 1 && !along_k && a.K >= 256 && resident(1) <= 2 && (double)resident(1) / shared[resident(1) - 1] * (double)a.K + 100.0 < 0.99 * us) sp = 1;
         if (sp > 1) {
             const int64_t chunk = chunk_with_a_whole_last_stage(a.K, ((a.K + sp - 1) / sp + DI_BK - 1) / DI_BK * DI_BK, DI_BK);
             b.kchunk = (int)chunk;
@@ -360,7 +363,7 @@ static hipError_t launch_di_small(const MmlikeArgsF64 &a, int &groups, hipStream
         }
     }
     const int64_t workgroups = resident(splits);
-    groups = workgroups > 2 || b.kchunk < 256 || (workgroups == 2 && (splits > 1 || a.K < 512)) ? 1 : workgroups == 1 && b.kchunk >= 1024 ? 4 : 2;
+    groups = workgroups == 1 && b.kchunk >= 1024 ? 4 : along_k || workgroups > 2 || b.kchunk < 256 || (workgroups == 2 && (splits > 1 || a.K < 512)) ? 1 : 2;
     return launch_row_of_blocks(b, grid, 256, [&](unsigned n) {
         (void)enqueue_identity_f64_dma(b, 64, groups, n, (unsigned)splits, s);
     });
