@@ -869,7 +869,7 @@ static bool tile_wanted_f64(const F64Call &c, int shape, TilePlan &plan)
     const int64_t range = wide_k_range_f64((c.M + 4 * waves - 1) / (4 * waves) * ((c.N + 127) / 128) * waves, c.K, 16);
     plan = choose_tile_plan<double>(c.M, c.N, c.K, kTileUsF64[c.task], (c.K + range - 1) / range, c.thres_form == THRES_ELEM);
     const bool swaps = critical_f64_swaps(c);
-    if (critical_f64_runs(c)) choose_critical_f64(c.task, swaps ? c.N : c.M, swaps ? c.M : c.N, c.K, kTileUsF64[c.task], compute_units(), plan);
+    if (critical_f64_runs(c)) choose_critical_f64(c.task, swaps ? c.N : c.M, swaps ? c.M : c.N, c.K, kTileUsF64[c.task], compute_units(), swaps, plan);
     return true;
 }
 

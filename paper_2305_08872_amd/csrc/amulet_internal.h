@@ -455,8 +455,9 @@ inline TilePlan choose_tile_plan(int64_t M, int64_t N, int64_t K, double us_per_
 
 // us of mmlike_critical_f64_impl.h's kernels: tiles of 64 x 128 (DISCOUNT, BOOST) or 128 x 128 (COUNT), two workgroups to a compute
 // unit, a pair of which takes `pair` us per k and one alone `alone`, with `ends` per round for first loads and write-back; or DISCOUNT
-// on 128 x 128, one.  Within 3 to 4 % (rms) of 35 to 130 drawn calls per task of 2^26 to 2^35 products, all layouts.
-inline double critical_f64_us(int task, int64_t M, int64_t N, int64_t K, int rows, int64_t units)
+// on 128 x 128, one.  A count transposed as it is added to R takes 0.036 more per tile: a lane's eight outputs, not the wave's, lie next
+// to each other.  Within 3 to 4 % (rms) of 35 to 130 drawn calls per task of 2^26 to 2^35 products, all layouts.
+inline double critical_f64_us(int task, int64_t M, int64_t N, int64_t K, int rows, int64_t units, bool transposed)
 {
     struct Cost { double pair, alone, ends; };
     static const Cost cost[4] = {{}, {0.463, 0.262, 3.2}, {0.422, 0.233, 1.6}, {0.475, 0.286, 5.6}};
@@ -465,22 +466,24 @@ inline double critical_f64_us(int task, int64_t M, int64_t N, int64_t K, int row
     const double full = (double)(W / slots), all = full + (rest ? 1.0 : 0.0);
     if (!pairs) return 11.5 * all + 0.42 * (double)K * all;
     const Cost &c = cost[task];
-    return 5.9 + c.ends * all + (double)K * (c.pair * full + (rest == 0 ? 0.0 : rest <= units ? c.alone : c.pair));
+    return 5.9 + c.ends * all + (transposed ? 0.036 * (double)W : 0.0) + (double)K * (c.pair * full + (rest == 0 ? 0.0 : rest <= units ? c.alone : c.pair));
 }
 // K of a count: 15/8 per product over its threshold, exact in fp32
 constexpr int64_t C64_COUNT_K = (int64_t)1 << 20;
 // The plan `tile` of the tile kernels, or that kernel for all rows, or for as many as fill whole rounds (the small tile: and half a
-// round), and the tile kernels for the others: what is estimated lowest, by 3 % at least.  The other rows' K has no more parts than
+// round), and the tile kernels for the others: what is estimated lowest, by 3 % at least, by 8 % for DISCOUNT
+// (whose estimate is up to a fifth low at a K of 64), with 1 us against it and 2 for a second launch: of 330 drawn calls two are then slower than by
+// the tile kernels by more than 1.5 % (2 and 4.1); by 3 % alone 21 of 330 others were, the slowest by a sixth.  The other rows' K has no more parts than
 // the tile kernels' plan for all of them.
-inline void choose_critical_f64(int task, int64_t M, int64_t N, int64_t K, double us_per_k, int64_t units, TilePlan &tile)
+inline void choose_critical_f64(int task, int64_t M, int64_t N, int64_t K, double us_per_k, int64_t units, bool transposed, TilePlan &tile)
 {
     const int64_t parts = tile.parts, tiles_n = (N + 127) / 128;
-    double best = 0.97 * tile.us;
+    double best = (task == TASK_DISCOUNT ? 0.92 : 0.97) * tile.us;
     for (int rows = task == TASK_COUNT_GT ? 128 : 64; rows <= (task == TASK_BOOST ? 64 : 128); rows += 64) {
         auto take = [&](int64_t first) {
             if (first < M && M - first < 16) return;      // (fewer than the tile kernels take in some layouts)
-            double us = critical_f64_us(task, first, N, K, rows, units);
-            if (first < M) us += choose_tile_plan<double>(M - first, N, K, us_per_k, parts).us;
+            double us = critical_f64_us(task, first, N, K, rows, units, transposed) + 1.0;
+            if (first < M) us += 2.0 + choose_tile_plan<double>(M - first, N, K, us_per_k, parts).us;
             if (us < best) { best = us; tile.critical = rows; tile.rest = first; tile.rest_parts = parts; }
         };
         take(M);
