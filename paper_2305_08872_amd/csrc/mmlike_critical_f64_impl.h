@@ -221,6 +221,8 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
         return x;
     };
     uint64_t bad = 0;      // lanes that staged a value out of range
+    float most = 0.0f;     // the largest high half of A's values
+    constexpr float MOST_A = __builtin_bit_cast(float, (1023u + 900u) << 20);
     double sb[2], sa[AE];
     auto load = [&](int left) {      // `left` k of the range from this stage on
         if (left >= BK) {
@@ -282,9 +284,10 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
             // (|a| below 2^900: with |b| below 2^100 no product is past the largest double, which would be infinite before the discount
             // is taken off.  High halves as fp32 numbers come in the same order, and then no numbers, which a maximum keeps)
             auto high = [](double v) { return __builtin_bit_cast(float, (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32)); };
-            float most = high(sa[0]);
-            if constexpr (AE == 2) asm("v_maximum3_f32 %0, |%1|, |%2|, |%2|" : "=v"(most) : "v"(high(sa[0])), "v"(high(sa[1])));
-            in = in && __builtin_fabsf(most) < __builtin_bit_cast(float, (1023u + 900u) << 20);
+            // (B transposed, there is no register for the largest: looked at each time)
+            if constexpr (transB) most = 0.0f;
+            asm("v_maximum3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(high(sa[0])), "v"(high(sa[AE - 1])));
+            if constexpr (transB) in = in && most < MOST_A;
         }
         if (!PLAIN && TASK != TASK_BOOST && zeros) {
             // (a threshold of 0 has 0 for its critical value, as no product is rounded to 0: |a| of 2^-299 or more, or 0)
@@ -328,7 +331,7 @@ __device__ __forceinline__ CriticalWay critical_tile_f64(const Args &args, const
         if constexpr (!PLAIN && TASK != TASK_BOOST) put(L.b[buf][Lds::C], c);
         if constexpr (!PLAIN && TASK == TASK_DISCOUNT) put(L.b[buf][Lds::CUT], cut);
     };
-    auto refused = [&] { return __syncthreads_or(bad != 0) != 0; };
+    auto refused = [&] { return __syncthreads_or(bad != 0 || (!transB && !(most < MOST_A))) != 0; };
 
     typedef typename std::conditional<TASK == TASK_COUNT_GT, uint32_t, double>::type sum_t;
     sum_t acc[C64_TM][2 * PAIRS];
