@@ -28,10 +28,12 @@
 // of the four operations with their execution mask 18.8, of BOOST's three 14.0 (four: 18.2); the kernels 15.8, 14.8 and, for the count,
 // 8.6, of which finding c is 1.1 (rows of a tile share it: 1.9 with 64 rows, 64 x 128 being the better tile for a K too short to hide a
 // large one's ends) and barrier, loads and LDS the rest.
-// us, tile kernels / here: discount 2048^3 1006 / 897, 4096^3 7800 / 7170, B transposed 7800 / 7280, 4096 x 2048 x 64 90 / 78;
+// us, tile kernels / here: discount 2048^3 1006 / 897, 4096^3 7800 / 7140, B transposed 7790 / 7250, 4096 x 2048 x 64 92 / 82;
 // boost 2048^3 963 / 850, 4096^3 7610 / 6640, per row 7720 / 6420; count 2048^3 727 / 586, 4096^3 5640 / 3760, 4096 x 2048 x 64 65 / 50,
 // per row 719 / 631, 5590 / 4070, 66 / 57.
-// Values that none of these takes, for all of a call, 4096^3: discount 9200, boost 7800, count 5800.
+// Values that none of these takes, in every tile, 4096^3 (tile kernels 7850, 7890, 5670): discount 8900, boost 8400 and count 5900 where the first stage
+// has them, 10 700, 10 200 and 6900 at a quarter of K, and 16 300, 15 300 and 9800 where only the last half has: a tile is looked at after its
+// first stage, after 8, and after twice as many each time, and what is refused at the end has run twice.
 // A goes through LDS and is read back by broadcast: through the scalar cache, 8 bytes of 64 rows at a time, 4096^3 took
 // 12 200 us.  256 columns in 256 registers per wave, two waves to a SIMD: 8530.  Stages of 8 k instead of 16: 7440 (128 rows).
 // BOOST's plain sum on the fp64 matrix cores: they and the vector unit take turns (17.2 clocks, 8.1 + 9.2).
