@@ -35,7 +35,7 @@ SOURCES = ["amulet_api.hip", "mmlike_valu_identity_col.hip"] + [
     "mmlike_tile_%s_%s.hip" % (elem, task)
     for elem in ("f64", "f32")
     for task in ("discount", "boost", "count_gt")
-] + ["identity_mfma.hip", "identity_mfma_dma.hip", "identity_split.hip", "identity_split_waves.hip", "count_i8.hip", "count_i8_dma.hip", "count_i8_tile.hip", "valu_probe.hip", "mmlike_valu_f64.hip", "identity_mfma_f64.hip", "identity_mfma_f64_dma.hip", "pack.hip"]
+] + ["identity_mfma.hip", "identity_mfma_dma.hip", "identity_split.hip", "identity_split_waves.hip", "count_i8.hip", "count_i8_dma.hip", "count_i8_stream.hip", "count_i8_tile.hip", "valu_probe.hip", "mmlike_valu_f64.hip", "identity_mfma_f64.hip", "identity_mfma_f64_dma.hip", "pack.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",

@@ -83,6 +83,15 @@ static bool identity_small_tile_wanted(int64_t M, int64_t N, bool f64 = false)
     return unused(small) + 0.05 < unused(large);
 }
 
+// R += of whole tiles by count_i8_stream.hip rather than the tile kernels: more than one 256 x 256 tile to a unit, or just one and
+// a K that makes up for the longer start.  us, tile kernels / there, calls whose operands change: 5120 x 4096 x 1856 77 / 62, 4096^2 x
+// 1856 39.7 / 42.2, x 2560 54 / 49, x 4096 76 / 57, 6144 x 4096 x 4096 137 / 99, 8192 x 4096 x 3392 139 / 101, 5888^2 x 4096 179 / 147,
+// 6144 x 8192 x 2560 164 / 128, 7680^2 x 3072 214 / 172; the persistent kernel that took 832 tiles and more: 8192^2 x 2048 156 / 147.
+static bool join_stream_wanted(int64_t tiles256, int64_t K)
+{
+    return tiles256 > 256 ? K >= COUNT_STREAM_LEAST_K : tiles256 == 256 && K >= 2432;
+}
+
 static int default_shape(int task, int64_t M, int64_t N, int64_t K)
 {
     // Matrix cores.  Fewer 128 x 256 tiles than compute units: the register-staged 128 x 128 tile
@@ -100,7 +109,8 @@ static int default_shape(int task, int64_t M, int64_t N, int64_t K)
         // workgroup, ms: 768 tiles x K = 8192 0.265 / 0.280, 896 x 4096 0.204 / 0.213, 1024 0.2125 /
         // 0.230, 1152 0.249 / 0.267, 1408 0.296 / 0.320, 1536 0.312 / 0.337; below that the one-tile
         // kernel is ahead: 512 tiles 0.125 / 0.121, 576 0.156 / 0.154, 640 x K = 2048 0.114 / 0.106)
-        return tiles256 >= 768 ? 8 : 6;
+        // (K long enough for R to be read on the way, count_i8_stream.hip: from one round on)
+        return tiles256 >= 768 || join_stream_wanted(tiles256, K) ? 8 : 6;
     }
     // a dense contraction: matrix cores, 128 x 128 tile, operands streamed HBM -> LDS where the
     // problem allows it (operands with 16-byte aligned rows in any layout, at least a stage of K;
@@ -429,10 +439,9 @@ struct CountRoute {
 // Join count, built-in choice: true, and how, if the tile kernels are to run the call.  They are, unless they cannot
 // run the problem -- 64 k, a 16-byte unit in an operand whose lines run across k, byte offsets that fit 31
 // bits -- or it is one of many whole tiles that the streamed kernels (count_i8_dma.hip) can take, where those
-// are ahead: their persistent form starts a tile while the last one's R is still on its way, and their
-// write-back of an R that is not read is shorter.  us, theirs / here:
-//   R += : 8192^2 x 4096 218 / 243, 7168 x 8192 x 4096 210 / 229, 8192^2 x 2048 156 / 165; but 8192^2 x 1024
-//     128 / 122, 6144 x 8192 x 4096 171 / 170, and 30 x 30 tiles, which do not divide over the XCDs, 164 / 141;
+// are ahead: their persistent form reads R during its K loop and starts a tile while the last one's counts are
+// on their way, and their write-back of an R that is not read is shorter.  us, theirs / here:
+//   R += : join_stream_wanted; but 8192^2 x 1024, too short for that, 128 / 122;
 //     with an operand to transpose first (at 8192^2 x 4096: A 233 / 244, B 235 / 265, both 250 / 252) from
 //     twice that K on;
 //   R = : 6144^2 x 4096 128 / 140, 3072^2 x 2048 26 / 30, 12288 x 8192 x 512 94 / 112; up to one 128 x 256
@@ -448,7 +457,7 @@ static bool count_tile_wanted(int trans_a, int trans_b, int64_t M, int64_t N, in
     const bool whole = aligned16(R) && ldr % 4 == 0 && K % 64 == 0 && N % 256 == 0 && M % (tiles256 >= 1024 ? 256 : 128) == 0 &&
                        (trans_a || (aligned16(A) && lda % 16 == 0)) && (trans_b || (aligned16(B) && ldb % 16 == 0));
     if (whole && (assign ? M / 128 * (N / 256) > 256
-                         : M % 256 == 0 && tiles256 >= 832 && tiles256 % 8 == 0 && K >= (trans_a || trans_b ? 4096 : 2048)))
+                  : M % 256 == 0 && (trans_a || trans_b ? tiles256 >= 832 && tiles256 % 8 == 0 && K >= 4096 : join_stream_wanted(tiles256, K))))
         return false;
     // (streamed straight to LDS, a piece of a row may start at any 4-byte address)
     auto dwords = [](const void *p, int64_t ld, int64_t line) { return ((uintptr_t)p & 3u) == 0 && ld % 4 == 0 && line % 4 == 0; };

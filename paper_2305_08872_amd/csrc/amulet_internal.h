@@ -615,6 +615,10 @@ hipError_t launch_zero_r_i32(const CountArgs &a, hipStream_t s);
 // direct HBM -> LDS kernels: tile (64 * wr) x 256, wr = 2 or 4
 bool count_i8_dma_eligible(const CountArgs &a, int wr);
 hipError_t launch_count_i8_dma(const CountArgs &a, int wr, hipStream_t s, bool persistent = false);
+// ... persistent, a stream of stages across tiles whose R is read on the way (count_i8_stream.hip)
+constexpr int COUNT_STREAM_LEAST_K = 1856;
+bool count_i8_stream_eligible(const CountArgs &a);
+hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s);
 
 // Identity task on the fp32 matrix cores; its five shape ids follow its eight VALU shapes: a
 // 128 x 128 tile (4 waves, register staged), a 256 x 256 tile (16 waves), the 128 x 128 tile

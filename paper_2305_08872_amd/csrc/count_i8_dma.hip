@@ -537,6 +537,8 @@ template <int WR, int NSTAGE>
 static hipError_t launch_dma_persistent(const CountArgs &a, hipStream_t s)
 {
     typedef DmaTile<WR, NSTAGE> T;
+    // (R += of a long K, below which count_i8_stream.hip's groups of R's values do not fit between a tile's first and last stages)
+    if (WR == 4 && count_i8_stream_eligible(a)) return launch_count_i8_stream(a, s);
     const int64_t grid = persistent_grid<WR>(a);
     if (grid == 0) return launch_dma<WR, NSTAGE>(a, s);
     static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(&count_i8_dma_persistent_kernel<WR, NSTAGE>),

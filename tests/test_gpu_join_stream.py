@@ -1,0 +1,35 @@
+"""R += of the join count by the kernel that reads R during its K loop (count_i8_stream.hip): every count of R, from an R that
+holds other values and has a pitch of its own, at the least K it takes and at K whose groups of stages are uneven, with tiles that
+do and do not divide over the workgroups."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K,pad", [
+    (4096, 8192, 3392, 0),       # two tiles to a workgroup, three stages to each group of four of R's values
+    (4096, 8192, 3328, 0),       # a stage too few: groups of eight
+    (4096, 4096, 1856, 4),       # one tile to a workgroup, three stages to each group of eight
+    (4096, 8192, 1792, 0),       # a stage too few: the kernel with its own write-back of R
+    (4352, 8192, 3456, 8),       # places without a tile, a last round of few tiles
+    (8192, 4864, 4160, 4),       # groups of 3 and 4 stages
+])
+def test_count_i8_r_read_during_the_k_loop(M, N, K, pad):
+    import paper_2305_08872_amd as am
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    A = torch.randint(-128, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    B = torch.randint(-128, 128, (K, N), generator=g, device="cuda", dtype=torch.int8)
+    held = torch.randint(-2 ** 31, 2 ** 31 - 1, (M, N + pad), generator=g, device="cuda", dtype=torch.int32)
+    # (whole numbers below 2^53 throughout: exact in 64 bits)
+    product = A.double() @ B.double()
+    for _ in range(2):           # (the second call finds the first one's counts)
+        want = held.long()
+        want[:, :N] += product.long()
+        want = ((want + 2 ** 31) % 2 ** 32 - 2 ** 31).int()
+        print("join stream", M, N, K, pad, flush=True)
+        am.amulet_count_i8_shape(8, A, B, held[:, :N])
+        torch.cuda.synchronize()
+        assert "persistent" in am.amulet_recent_kernel()
+        assert torch.equal(held, want)
