@@ -83,13 +83,17 @@ static bool identity_small_tile_wanted(int64_t M, int64_t N, bool f64 = false)
     return unused(small) + 0.05 < unused(large);
 }
 
-// R += of whole tiles by count_i8_stream.hip rather than the tile kernels: more than one 256 x 256 tile to a unit, or just one and
-// a K that makes up for the longer start.  us, tile kernels / there, calls whose operands change: 5120 x 4096 x 1856 77 / 62, 4096^2 x
-// 1856 39.7 / 42.2, x 2560 54 / 49, x 4096 76 / 57, 6144 x 4096 x 4096 137 / 99, 8192 x 4096 x 3392 139 / 101, 5888^2 x 4096 179 / 147,
-// 6144 x 8192 x 2560 164 / 128, 7680^2 x 3072 214 / 172; the persistent kernel that took 832 tiles and more: 8192^2 x 2048 156 / 147.
+// R += of whole tiles by count_i8_stream.hip rather than the tile kernels, whose smaller tiles are ahead where they fill the last
+// round better and K is short.  us, tile kernels / there, one call over and over; calls on three sets of matrices in turn: 4096^2 x
+// 1856 40 / 42; 40 / 42, x 2432 50 / 45; 53 / 48, x 4096 63 / 57; 77 / 57, 5120 x 4096 x 1856 58 / 59; 78 / 76, 8192 x 4096 x 1856
+// 74 / 73; 99 / 89, 6144 x 4096 x 4096 107 / 98; 136 / 99, 6144 x 8192 x 2560 129 / 127; 164 / 128; 272 tiles (4352 x 4096) x 2560
+// 70 / 77; 73 / 77, x 3392 83 / 86; 103 / 86, 784 (12544 x 4096) x 2560 150 / 166; 187 / 162, 528 (8448 x 4096) x 4096 144 / 149; 188 / 147.
+// The persistent kernel that took 832 tiles and more: 7168 x 8192 x 2048 149 / 136, 8192^2 x 2048 156 / 147.
 static bool join_stream_wanted(int64_t tiles256, int64_t K)
 {
-    return tiles256 > 256 ? K >= COUNT_STREAM_LEAST_K : tiles256 == 256 && K >= 2432;
+    const int64_t last = tiles256 % 256;
+    if (tiles256 < 256 || (tiles256 == 256 && K < 2432)) return false;
+    return K >= (tiles256 >= 832 || last == 0 || last >= 64 ? COUNT_STREAM_LEAST_K : 3392);
 }
 
 static int default_shape(int task, int64_t M, int64_t N, int64_t K)

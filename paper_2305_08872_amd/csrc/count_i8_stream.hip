@@ -49,8 +49,8 @@ static_assert(cs_least_stages(8) * CS_BK == COUNT_STREAM_LEAST_K, "");
 
 extern __shared__ __attribute__((aligned(16))) int8_t cs_smem[];
 
-// GROUP: values of R that a lane reads at a time
-template <int GROUP>
+// GROUP: values of R that a lane reads at a time.  NT: R is read and written around the caches.
+template <int GROUP, bool NT>
 __global__ void __launch_bounds__(64 * CS_WAVES) __attribute__((amdgpu_waves_per_eu(4, 4)))
 count_i8_stream_kernel(const CountArgs args)
 {
@@ -202,7 +202,8 @@ count_i8_stream_kernel(const CountArgs args)
                   [&]() {
 #pragma unroll
                       for (int j = 0; j < GROUP; ++j) {
-                          asm volatile("global_load_dword %0, %1, %2 nt" : "=v"(rv[j]) : "v"(r_voff), "s"(r_rows) : "memory");
+                          if (NT) asm volatile("global_load_dword %0, %1, %2 nt" : "=v"(rv[j]) : "v"(r_voff), "s"(r_rows) : "memory");
+                          else asm volatile("global_load_dword %0, %1, %2" : "=v"(rv[j]) : "v"(r_voff), "s"(r_rows) : "memory");
                           // the accumulators' order: rows 0 .. 3, 8 .. 11, ... of a block, then the block beside or below
                           const int e = q * GROUP + j;
                           r_rows += (e & 3) < 3 ? args.ldr : (e & 15) < 15 ? 5 * args.ldr : (e & 16) == 0 ? 32 - 27 * args.ldr : 5 * args.ldr - 32;
@@ -247,7 +248,9 @@ count_i8_stream_kernel(const CountArgs args)
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
                         const v4i c = *(const v4i *)(img + r_at + i * 256);
-                        __builtin_nontemporal_store(c, (v4i *)(r_wave + ((int64_t)(x * 32 + h * 16 + i * 8) * args.ldr + y * 32) * 4 + r_off));
+                        v4i *const at = (v4i *)(r_wave + ((int64_t)(x * 32 + h * 16 + i * 8) * args.ldr + y * 32) * 4 + r_off);
+                        if (NT) __builtin_nontemporal_store(c, at);
+                        else *at = c;
                     }
                     __builtin_amdgcn_wave_barrier();
                     asm volatile("" ::: "memory");
@@ -265,19 +268,26 @@ bool count_i8_stream_eligible(const CountArgs &a)
     return !a.assign && xcd_places(a.M / CS_TILE, a.N / CS_TILE) >= compute_units() / 8 && count_i8_dma_eligible(a, 4) && a.K / CS_BK >= cs_least_stages(8) && a.ldr <= 0x7fffffffLL / (4 * 64);
 }
 
-template <int GROUP>
+template <int GROUP, bool NT>
 static hipError_t launch_stream(const CountArgs &a, hipStream_t s)
 {
-    static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(&count_i8_stream_kernel<GROUP>), hipFuncAttributeMaxDynamicSharedMemorySize, CS_LDS_BYTES);
+    static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(&count_i8_stream_kernel<GROUP, NT>), hipFuncAttributeMaxDynamicSharedMemorySize, CS_LDS_BYTES);
     if (granted != hipSuccess) return granted;
     if (forced_launch_failure()) return hipErrorLaunchFailure;
-    hipLaunchKernelGGL(count_i8_stream_kernel<GROUP>, dim3((unsigned)(compute_units() / 8 * 8)), dim3(64 * CS_WAVES), CS_LDS_BYTES, s, a);
+    hipLaunchKernelGGL((count_i8_stream_kernel<GROUP, NT>), dim3((unsigned)(compute_units() / 8 * 8)), dim3(64 * CS_WAVES), CS_LDS_BYTES, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s)
 {
-    return a.K / CS_BK >= cs_least_stages(4) ? launch_stream<4>(a, s) : launch_stream<8>(a, s);
+    // R around the caches, so that it does not displace operands, where a call's matrices do not fit the last-level cache (256 MiB)
+    // or its K is long enough: an R that a call finds there is worth less than the operands of the calls around it.  us, R through
+    // the caches / around them, one call over and over; calls on three sets of matrices in turn: 8192 x 4096 x 1856 73 / 80; 89 / 76,
+    // 6144 x 4096 x 2560 76 / 81; 97 / 80, 6144^2 x 3072 113 / 120; 153 / 120, 8192 x 4096 x 4096 99 / 108; 144 / 109 (tile
+    // kernels 74, 80, 120, 121; 99, 97, 159, 148), 7168 x 8192 x 3072 195 / 167; 206 / 167.
+    const double bytes = 4.0 * (double)a.M * (double)a.N + (double)a.K * ((double)a.M + (double)a.N);
+    if (a.K / CS_BK >= cs_least_stages(4)) return launch_stream<4, true>(a, s);
+    return a.K >= 2560 || bytes > 285e6 ? launch_stream<8, true>(a, s) : launch_stream<8, false>(a, s);
 }
 
 }  // namespace amulet
