@@ -164,7 +164,7 @@ struct KernelNote {
     int f64;
     int shape;                     // shape id, or -1: a tile kernel, and then
     int tile, parts, kpart, kgroup;
-    int ring, registers, bypass;   // (join count)
+    int ring, registers, bypass, deep;   // (join count)
     int64_t rows;
     int pieces;                    // (rows of a tile of the kernel on the matrix cores that stood in for the shape)
     int critical;                  // (rows of a tile of the kernel by critical values, which has no shape id either)
@@ -176,7 +176,7 @@ static thread_local unsigned g_notes_made = 0;
 static KernelNote &new_note(int task, int f64, int shape, int64_t rows)
 {
     KernelNote &n = g_notes[g_notes_made++ % KERNEL_NOTES];
-    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, rows, 0, 0, 1};
+    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, 0, rows, 0, 0, 1};
     return n;
 }
 
@@ -486,7 +486,7 @@ static int run_count_tile(const CountRoute &route, int trans_a, int trans_b, int
     a.bypass = route.bypass;
     KernelNote &n = new_note(AMULET_TASK_COUNT_I8, 0, -1, M);
     n.tile = plan.tile; n.parts = plan.parts; n.kpart = plan.kpart; n.kgroup = plan.kgroup;
-    n.ring = plan.alone; n.registers = plan.through_registers; n.bypass = a.bypass && plan.tile <= CT_128x256;
+    n.ring = plan.alone; n.deep = plan.deep; n.registers = plan.through_registers; n.bypass = a.bypass && plan.tile <= CT_128x256;
     hipError_t e = hipSuccess;
     if (assign && plan.parts > 1) {     // several workgroups add into a tile: from zero
         CountArgs z;
@@ -1770,8 +1770,8 @@ const char *amulet_recent_kernel(int back)
         else snprintf(text, sizeof(text), "%s rows %lld", name, rows);
     } else if (n.task == AMULET_TASK_COUNT_I8) {
         static const char *const tiles[5] = {"256x256", "128x256", "128x128", "64x64", "192x256"};
-        snprintf(text, sizeof(text), "i8_tile_%s%s%s%s rows %lld parts %d kpart %d kgroup %d", tiles[n.tile], n.ring ? "_ring6" : "",
-                 n.registers ? "_registers" : "", n.bypass ? "_bypass" : "", rows, n.parts, n.kpart, n.kgroup);
+        snprintf(text, sizeof(text), "i8_tile_%s%s%s%s rows %lld parts %d kpart %d kgroup %d%s", tiles[n.tile], n.ring ? "_ring6" : "",
+                 n.registers ? "_registers" : "", n.bypass ? "_bypass" : "", rows, n.parts, n.kpart, n.kgroup, n.deep ? " stage_k 128" : "");
     } else if (n.critical) {
         snprintf(text, sizeof(text), "f64_critical_%dx128 rows %lld critical_rows %d", n.critical, rows, n.critical);
     } else {

@@ -563,6 +563,7 @@ struct CountTilePlan {
     int parts;              // workgroups per tile, each over kpart k (more than one: atomic adds into R)
     int kpart, kgroup;
     int alone;              // 128 x 256: at most one workgroup to a unit, and K for a ring of all of its LDS
+    int deep;               // 128 x 128 and 64 x 64, streamed, at most one workgroup to a unit: stages of 128 k
     double us;              // the estimate it was chosen by
 };
 
@@ -575,6 +576,9 @@ struct CountTilePlan {
 // K over several workgroups (the two smaller tiles): 0.3 us and 1 T atomic adds per second beside other workgroups' arithmetic, 4 us
 // more to clear an R that is to be written.  Fitted to and checked against every tile and split at 210 drawn
 // sizes (64 ... 8192 each way, all layouts and alignments): 1.4 % behind the fastest on average, 28 % at most.
+// The two smaller tiles, streamed, with at most one workgroup to a unit: stages of 128 k (count_i8_tile.hip), where whole stages make a range no
+// more than 2.5 % longer and a short last one, whose k are not pipelined, is one of at least eight: 320 x 1024 x 1152 5.2 us by 64 k, 6.0 by 128,
+// 576 x 872 x 704 6.1 / 6.5.
 // (`rows192`: the 192 x 256 tile, 12 waves, may be taken: rows at any byte address, A not transposed, R through the caches.)
 inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool through_registers, bool assign, bool rows192)
 {
@@ -583,7 +587,8 @@ inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool thr
         {128, 128, 1, 2, 0.206, 0.48, 4.8, 9.2, 1.52}, {64, 64, 2, 2, 0.19, 0.46, 2.8, 4.1, 1.67},
         {192, 256, 1, 1, 0.56, 0.0, 12.8, 0.0, 1.42}};
     auto up64 = [](int64_t n) { return (n + 63) / 64 * 64; };
-    CountTilePlan best = {0, through_registers ? 1 : 0, 0, 0, 0, 0, 0.0};
+    auto up128 = [](int64_t n) { return (n + 127) / 128 * 128; };
+    CountTilePlan best = {0, through_registers ? 1 : 0, 0, 0, 0, 0, 0, 0.0};
     for (int i = 0; i < 5; ++i) {
         const auto &t = tiles[i];
         if ((through_registers && t.registers == 0.0) || (i == CT_192x256 && !rows192)) continue;
@@ -600,8 +605,15 @@ inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool thr
             if (best.parts == 0 || us < best.us) {
                 best.tile = i; best.parts = (int)parts; best.kpart = (int)kpart; best.kgroup = (int)kgroup; best.us = us;
                 best.alone = i == CT_128x256 && W <= 256 && kgroup > 4 * 64 ? 1 : 0;
+                best.deep = (i == CT_128 || i == CT_64) && !through_registers && W <= 256 && kgroup >= 256 && up128(kgroup) - kgroup <= kgroup / 40 && (K % 128 == 0 || kgroup >= 1024) ? 1 : 0;
             }
         }
+    }
+    if (best.deep) {                 // ranges of whole stages
+        const int64_t kpart = up128(best.kpart);
+        best.kpart = (int)kpart;
+        best.parts = (int)((K + kpart - 1) / kpart);
+        best.kgroup = (int)up128((kpart + tiles[best.tile].groups - 1) / tiles[best.tile].groups);
     }
     return best;
 }

@@ -20,6 +20,12 @@
 // call one byte off: 3000 x 4004 x 2504 (written) 38 / 49, 5000 x 7000 x 3000 145 / 175, 8000^2 x 4000 235 / 314,
 // 2048^2 x 8192 40 / 67.
 //
+// With at most one workgroup to a unit the smaller tiles take stages of 128 k (a ring of 4, 128 KiB): half the barriers, twice the bytes in
+// flight and, of lines along k, whole lines of the caches at a time. us, stages of 64 k / of 128, calls on three sets of matrices in turn:
+// 512^3 4.1 / 4.0, 1024^2 x 4096 14.6 / 13.3, 2048^3 15.9 / 14.8, 1536^2 x 8192 36.8 / 32.3, 2412 x 896 x 4184 27.0 / 23.6, 320 x 2688 x
+// 7808 22.4 / 19.6, 288 x 7744 x 3968 23.2 / 19.6, 448 x 5012 x 5040 with B transposed 33.9 / 29.2.  Two workgroups to a unit have no room for it.
+// (Through registers the same, with one set of registers: 4 us more at the start and 4 % less per k, 2999 x 4001 x 2503 39.6 / 43.6.)
+//
 // Through registers a stage takes 0.8 us in a tile of 256 rows and in one of 192 (not its loads' round trip: with 4 stages on their
 // way in registers instead of 2 the same), and what a unit does not overlap is the write-back of its tile, 24 us and 19: so rows at any
 // address have a tile of 192 x 256, us, 256 / 192: 2999 x 4001 x 2503 57.7 / 53.3 (written 52 / 47), 6000 x 6001 x 1501 113 / 100,
@@ -60,18 +66,21 @@ constexpr int ct_waves(int waves) { return waves == 12 ? 3 : 4; }
 // Waves: WK groups of WR x WC, a group sums its own kgroup of the workgroup's k; a wave MB x NB blocks of 32 x 32.
 // NST: stages of the ring.  TA / TB: A stored K x M / B stored N x K.  REG: through registers.  KS: K over several workgroups.
 // NT: R is read and written around the caches.
-template <int MB, int NB, int WR, int WC, int WK, int NST, bool TA, bool TB, bool REG, bool KS, bool NT>
+// BK: k of a stage, 64 or (streamed only) 128.
+template <int MB, int NB, int WR, int WC, int WK, int NST, bool TA, bool TB, bool REG, bool KS, bool NT, int BK>
 __global__ void __launch_bounds__(64 * WR * WC * WK) __attribute__((amdgpu_waves_per_eu(ct_waves(WR * WC * WK), ct_waves(WR * WC * WK))))
 count_i8_tile_kernel(const CountTileArgs args)
 {
     constexpr int BM = 32 * MB * WR, BN = 32 * NB * WC;
-    constexpr int A_BYTES = BM * CT_BK, B_BYTES = BN * CT_BK, G_BYTES = A_BYTES + B_BYTES, STAGE_BYTES = WK * G_BYTES;
+    constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK, G_BYTES = A_BYTES + B_BYTES, STAGE_BYTES = WK * G_BYTES;
     constexpr int NW = WR * WC;                          // waves of a group
     constexpr int LINES = G_BYTES / 1024, A_LINES = A_BYTES / 1024, LOADS = (LINES + NW - 1) / NW;
     constexpr int A_LOADS = A_LINES / NW;                // of a wave's loads the first ones are A's
     constexpr bool RAGGED = LINES % NW != 0;             // the last load is the first waves' only
     static_assert((REG || !RAGGED) && A_LINES % NW == 0, "the stage's kilobytes divide over the group's waves");
     static_assert(!(TA && (BM & (BM - 1)) != 0), "the units of a k-row are exchanged within powers of two");
+    static_assert(BK == 64 || (BK == 128 && !REG), "stages of 64 k, streamed ones also of 128");
+    constexpr int UK = BK / 16;                          // 16-byte units of a line along k
     constexpr int UA = BM / 16, UB = BN / 16;            // 16-byte units in a k-row of an operand kept k-major
 
     const int M = args.M, N = args.N, K = args.K;
@@ -88,10 +97,11 @@ count_i8_tile_kernel(const CountTileArgs args)
     const int kb = part0 + g * args.kgroup;
     int klen = part_len - g * args.kgroup;
     klen = klen < 0 ? 0 : klen < args.kgroup ? klen : args.kgroup;
-    const int n_full = klen / CT_BK, tail = klen - n_full * CT_BK;
-    const int n_st = ((args.kgroup < part_len ? args.kgroup : part_len) + CT_BK - 1) / CT_BK;
+    const int n_full = klen / BK, tail = klen - n_full * BK;
+    const int n_st = ((args.kgroup < part_len ? args.kgroup : part_len) + BK - 1) / BK;
 
-    // unit u of k-row k of an operand kept k-major stands at u ^ swz(k)
+    // unit u of line r of an operand kept k-minor stands at u ^ along(r), unit u of k-row k of one kept k-major at u ^ swz(k)
+    auto along = [](int r) { return UK == 4 ? (r >> 2) & 3 : (r >> 1) & 7; };
     auto swz = [](int units, int k) { return 2 * (((k & 7) / (16 / units)) & (units / 2 - 1)); };
 
     const int rbase = TA && row0 > M - 16 ? M - 16 : row0, cbase = !TB && col0 > N - 16 ? N - 16 : col0;
@@ -104,8 +114,8 @@ count_i8_tile_kernel(const CountTileArgs args)
         const int s = (is_a ? line : line - A_LINES) * 64 + lane;
         const int edge = is_a ? M : N, org = is_a ? row0 : col0, base = is_a ? rbase : cbase;
         const uint32_t ld = (uint32_t)(is_a ? args.lda : args.ldb);
-        if (is_a ? !TA : TB) {       // lines along k: 64 bytes each
-            const int r = s >> 2, u = (s & 3) ^ ((r >> 2) & 3);
+        if (is_a ? !TA : TB) {       // lines along k: BK bytes each
+            const int r = s / UK, u = (s % UK) ^ along(r);
             const int rc = org + r < edge ? r : edge - 1 - org;
             voff[q] = (uint32_t)rc * ld + (uint32_t)(u * 16);
         } else {
@@ -118,8 +128,8 @@ count_i8_tile_kernel(const CountTileArgs args)
     const int8_t *const a_base = TA ? args.A + rbase : args.A + (int64_t)row0 * args.lda;
     const int8_t *const b_base = TB ? args.B + (int64_t)col0 * args.ldb : args.B + cbase;
     auto window = [&](int t) {
-        const int w = kb + (t < n_full ? t : n_full) * CT_BK;
-        return w < K - CT_BK ? w : K - CT_BK;
+        const int w = kb + (t < n_full ? t : n_full) * BK;
+        return w < K - BK ? w : K - BK;
     };
     // operands of the next stage to request; a short last stage steps to the window that ends at K
     int w_next = window(0);
@@ -127,7 +137,7 @@ count_i8_tile_kernel(const CountTileArgs args)
     const int8_t *pb = b_base + (TB ? (int64_t)w_next : (int64_t)w_next * args.ldb);
     const int w_last = window(n_full);
     auto advance = [&]() {
-        const int step = w_last - w_next < CT_BK ? w_last - w_next : CT_BK;
+        const int step = w_last - w_next < BK ? w_last - w_next : BK;
         w_next += step;
         pa += TA ? (int64_t)step * args.lda : (int64_t)step;
         pb += TB ? (int64_t)step : (int64_t)step * args.ldb;
@@ -165,7 +175,7 @@ count_i8_tile_kernel(const CountTileArgs args)
     // (A's bytes outside the k of the range are zeroed on the way -- a zero adds nothing -- in the last,
     // short stage and in the stages a shorter group only waits through)
     uint32_t minor_mask[4];
-    const int tail_off = kb + n_full * CT_BK - window(n_full), tail_end = tail_off + tail;
+    const int tail_off = kb + n_full * BK - window(n_full), tail_end = tail_off + tail;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         minor_mask[d] = 0;
@@ -198,19 +208,20 @@ count_i8_tile_kernel(const CountTileArgs args)
     // ---- fragments: four bytes offsets per operand suffice, the rest are immediates ----
     const int tb = lane >> 4, ts = lane & 15;
     const int t_k = 16 * (tb >> 1) + (ts >> 1), t_c = 16 * (tb & 1) + 8 * (ts & 1);
-    auto minor_off = [&](int line, int ks) { return line * 64 + (((2 * ks + lh) ^ ((line >> 2) & 3)) * 16); };
+    auto minor_off = [&](int line, int ks) { return line * BK + (((2 * ks + lh) ^ along(line)) * 16); };
     auto major_off = [&](int units, int line0) {     // + k-rows
         const int c = line0 + t_c;
         return t_k * units * 16 + ((c >> 4) ^ swz(units, t_k)) * 16 + (c & 15);
     };
-    int a_off[TA ? MB : 2], b_off[TB ? 2 : NB];
+    constexpr int STEPS = BK / 32;                       // k-steps of 32
+    int a_off[TA ? MB : STEPS], b_off[TB ? STEPS : NB];
 #pragma unroll
-    for (int x = 0; x < (TA ? MB : 2); ++x)
+    for (int x = 0; x < (TA ? MB : STEPS); ++x)
         a_off[x] = g * G_BYTES + (TA ? major_off(UA, (wr * MB + x) * 32) : minor_off(wr * MB * 32 + li, x));
 #pragma unroll
-    for (int x = 0; x < (TB ? 2 : NB); ++x)
+    for (int x = 0; x < (TB ? STEPS : NB); ++x)
         b_off[x] = g * G_BYTES + A_BYTES + (TB ? minor_off(wc * NB * 32 + li, x) : major_off(UB, (wc * NB + x) * 32));
-    auto frag_minor = [&](const int8_t *st, int off, int blk) { return *(const v4i *)(st + off + blk * 2048); };
+    auto frag_minor = [&](const int8_t *st, int off, int blk) { return *(const v4i *)(st + off + blk * 32 * BK); };
     auto frag_major = [&](const int8_t *st, int units, int off, int ks) {
         const int8_t *p = st + off + ks * 32 * units * 16;
         const v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)p);
@@ -240,7 +251,7 @@ count_i8_tile_kernel(const CountTileArgs args)
     };
     // the last, short stage: A's bytes outside the k not yet summed are zeroed (a zero adds nothing)
     auto mask_tail = [&](v4i (&a)[MB], int ks) {
-        const int off = kb + n_full * CT_BK - window(n_full), end = off + tail;
+        const int off = kb + n_full * BK - window(n_full), end = off + tail;
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
             const int k0 = 32 * ks + 16 * lh + 4 * d;
@@ -281,6 +292,14 @@ count_i8_tile_kernel(const CountTileArgs args)
                 read_frags(slot, 1, fa1, fb1);
                 mma(fa0, fb0);
                 __builtin_amdgcn_sched_barrier(0);
+                if constexpr (STEPS > 2) {
+                    read_frags(slot, 2, fa0, fb0);
+                    mma(fa1, fb1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_frags(slot, 3, fa1, fb1);
+                    mma(fa0, fb0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 between(t, slot);
                 read_frags(ns, 0, fa0, fb0);
                 __builtin_amdgcn_sched_barrier(0);
@@ -290,12 +309,16 @@ count_i8_tile_kernel(const CountTileArgs args)
         }
         for (; t < n_st; ++t) {
             if (t == n_full && tail > 0) {
-                read_frags(slot, 0, fa0, fb0);
-                read_frags(slot, 1, fa1, fb1);
-                mask_tail(fa0, 0);
-                mask_tail(fa1, 1);
-                mma(fa0, fb0);
-                mma(fa1, fb1);
+#pragma unroll
+                for (int ks = 0; ks < STEPS; ks += 2) {
+                    if (STEPS > 2 && 32 * (ks + 2) <= tail_off) continue;      // (summed already)
+                    read_frags(slot, ks, fa0, fb0);
+                    read_frags(slot, ks + 1, fa1, fb1);
+                    mask_tail(fa0, ks);
+                    mask_tail(fa1, ks + 1);
+                    mma(fa0, fb0);
+                    mma(fa1, fb1);
+                }
             }
             between(t, slot);
             slot = slot == NST - 1 ? 0 : slot + 1;
@@ -464,12 +487,12 @@ count_i8_tile_kernel(const CountTileArgs args)
     }
 }
 
-template <int MB, int NB, int WR, int WC, int WK, int NST, bool TA, bool TB, bool REG, bool KS, bool NT = false>
+template <int MB, int NB, int WR, int WC, int WK, int NST, bool TA, bool TB, bool REG, bool KS, bool NT = false, int BK = CT_BK>
 static hipError_t launch_tile(int parts, const CountTileArgs &args, hipStream_t s)
 {
-    constexpr int BM = 32 * MB * WR, BN = 32 * NB * WC, RING = (REG ? 2 : NST) * WK * CT_BK * (BM + BN), IMAGE = 64 * BN * 4;
+    constexpr int BM = 32 * MB * WR, BN = 32 * NB * WC, RING = (REG ? 2 : NST) * WK * BK * (BM + BN), IMAGE = 64 * BN * 4;
     constexpr int LDS = RING > IMAGE ? RING : IMAGE;
-    auto *const kernel = &count_i8_tile_kernel<MB, NB, WR, WC, WK, NST, TA, TB, REG, KS, NT>;
+    auto *const kernel = &count_i8_tile_kernel<MB, NB, WR, WC, WK, NST, TA, TB, REG, KS, NT, BK>;
     static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (granted != hipSuccess) return granted;
     const int64_t grid = xcd_grid((args.M + BM - 1) / BM, (args.N + BN - 1) / BN);
@@ -498,9 +521,17 @@ static hipError_t launch_tile_plan(const CountTilePlan &plan, const CountTileArg
         if constexpr (REG && !TA) return launch_tile<2, 2, 3, 4, 1, 4, TA, TB, REG, false>(1, a, s);
         return hipErrorInvalidValue;
     case CT_128:
+        if constexpr (!REG) {
+            if (plan.deep && plan.parts > 1) return launch_tile<2, 1, 2, 4, 1, 4, TA, TB, REG, true, false, 128>(plan.parts, a, s);
+            if (plan.deep) return launch_tile<2, 1, 2, 4, 1, 4, TA, TB, REG, false, false, 128>(1, a, s);
+        }
         if (plan.parts > 1) return launch_tile<2, 1, 2, 4, 1, 4, TA, TB, REG, true>(plan.parts, a, s);
         return launch_tile<2, 1, 2, 4, 1, 4, TA, TB, REG, false>(1, a, s);
     default:
+        if constexpr (!REG) {
+            if (plan.deep && plan.parts > 1) return launch_tile<1, 1, 2, 2, 2, 4, TA, TB, REG, true, false, 128>(plan.parts, a, s);
+            if (plan.deep) return launch_tile<1, 1, 2, 2, 2, 4, TA, TB, REG, false, false, 128>(1, a, s);
+        }
         if (plan.parts > 1) return launch_tile<1, 1, 2, 2, 2, 4, TA, TB, REG, true>(plan.parts, a, s);
         return launch_tile<1, 1, 2, 2, 2, 4, TA, TB, REG, false>(1, a, s);
     }

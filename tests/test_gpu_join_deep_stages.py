@@ -1,0 +1,37 @@
+"""The join count's smaller tiles with stages of 128 k: one stage and less than a ring of them, ranges with a short last stage of
+one to four k-steps, K over several workgroups, ragged rows and columns, every layout; exact."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kernel,split,M,N,K", [
+    ("i8_tile_64x64", False, 256, 256, 512),          # two stages to a group of waves
+    ("i8_tile_64x64", False, 1020, 1024, 3328),       # whole stages, ragged rows
+    ("i8_tile_64x64", False, 640, 1156, 4228),        # the second group's last stage has 4 k
+    ("i8_tile_64x64", True, 132, 1000, 8068),         # parts; the last one's groups end in 128 and 4 k
+    ("i8_tile_128x128", False, 2412, 896, 4184),      # a last stage of 88 k
+    ("i8_tile_128x128", False, 448, 5012, 5040),      # ... of 48
+    ("i8_tile_128x128", True, 260, 2052, 8068),
+])
+def test_stages_of_128_k(kernel, split, M, N, K):
+    import paper_2305_08872_amd as am
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randint(-3, 4, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    B = torch.randint(-3, 4, (K, N), generator=g, device="cuda", dtype=torch.int8)
+    want = (A.float() @ B.float()).to(torch.int32)    # |sum| < 2^24: exact
+    am.amulet_clear_selections()
+    for tA, tB in [(False, False), (True, False), (False, True), (True, True)]:
+        print(kernel, split, tA, tB, M, N, K, flush=True)
+        sA, sB = A.t().contiguous() if tA else A, B.t().contiguous() if tB else B
+        R = torch.full((M, N), 11, dtype=torch.int32, device="cuda")
+        ws = torch.empty(am.amulet_count_i8_workspace_bytes(tA, tB, M, N, K) + 16, dtype=torch.int8, device="cuda")
+        am.amulet_count_i8_general(sA, sB, R, ws, trans_a=tA, trans_b=tB)
+        torch.cuda.synchronize()
+        ran = am.amulet_recent_kernel().split()
+        assert ran[0] == kernel and ran[-2:] == ["stage_k", "128"] and (int(ran[4]) > 1) == split, ran
+        assert torch.equal(R, want + 11), (tA, tB)
+    am.amulet_count_i8_assign(A, B, R)
+    torch.cuda.synchronize()
+    assert torch.equal(R, want)
