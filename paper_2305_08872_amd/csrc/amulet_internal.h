@@ -573,8 +573,9 @@ struct CountTilePlan {
 // itself and `shared` per pair of workgroups on a unit, 1.4 to 1.7 times that through registers; the rest of a
 // tile -- first loads, sums, write-back -- `rest_...`, a fifth less when R is not read.  W workgroups (with the
 // tile order's padding) are whole rounds and a last one in which at most one workgroup per unit is alone.
-// K over several workgroups (the two smaller tiles): 0.3 us and 1 T atomic adds per second beside other workgroups' arithmetic, 4 us
-// more to clear an R that is to be written.  Fitted to and checked against every tile and split at 210 drawn
+// K over several workgroups (the two smaller tiles): 0.3 us and 1 T atomic adds per second beside other workgroups' arithmetic; 2 us
+// and 1 per 4e5 counts more to clear an R that is to be written (us, K whole / in the parts that this gives: 470 x 512 x 3520 12.3 / 9.3,
+// 64 x 1710 x 2368 10.7 / 8.7, 489 x 384 x 3244 11.0 / 8.8; 6942 x 131 x 2368 would be 16.8 / 20.5).  Fitted to and checked against every tile and split at 210 drawn
 // sizes (64 ... 8192 each way, all layouts and alignments): 1.4 % behind the fastest on average, 28 % at most.
 // The two smaller tiles, streamed, with at most one workgroup to a unit: stages of 128 k (count_i8_tile.hip), where whole stages make a range no
 // more than 2.5 % longer and a short last one, whose k are not pipelined, is one of at least eight: 320 x 1024 x 1152 5.2 us by 64 k, 6.0 by 128,
@@ -601,7 +602,7 @@ inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool thr
             const double alone = stages * t.alone + r * t.rest_alone, shared = t.resident > 1 ? stages * t.shared + r * t.rest_shared : alone;
             const int64_t W = grid * parts, rem = W % round;
             double us = 1.2 + (double)(W / round) * shared + (rem == 0 ? 0.0 : rem <= 256 ? alone : shared);
-            if (parts > 1) us += 0.3 + (double)M * (double)N * (double)parts / 1.0e6 + (assign ? 4.0 : 0.0);
+            if (parts > 1) us += 0.3 + (double)M * (double)N * (double)parts / 1.0e6 + (assign ? 2.0 + (double)M * (double)N / 4.0e5 : 0.0);
             if (best.parts == 0 || us < best.us) {
                 best.tile = i; best.parts = (int)parts; best.kpart = (int)kpart; best.kgroup = (int)kgroup; best.us = us;
                 best.alone = i == CT_128x256 && W <= 256 && kgroup > 4 * 64 ? 1 : 0;
