@@ -580,8 +580,14 @@ struct CountTilePlan {
 // The two smaller tiles, streamed, with at most one workgroup to a unit: stages of 128 k (count_i8_tile.hip), where whole stages make a range no
 // more than 2.5 % longer and a short last one, whose k are not pipelined, is one of at least eight: 320 x 1024 x 1152 5.2 us by 64 k, 6.0 by 128,
 // 576 x 872 x 704 6.1 / 6.5.
-// (`rows192`: the 192 x 256 tile, 12 waves, may be taken: rows at any byte address, A not transposed, R through the caches.)
-inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool through_registers, bool assign, bool rows192)
+// Of 64 x 64 tiles, not where both operands lie across k, whose loads gain nothing of a longer stage (A transposed, 1024 x 960 x 5100 18.4 by 64 k, 19.2
+// by 128; 3000 x 300 x 1024 level), and from 384 k to a group of waves (1024 x 960, K = 512 4.0 % slower to 1 % faster by layout, 768 1 % slower to 5 % faster).
+// Rows of an odd number of 64 bytes along k start in the middle of a cache line: 64 k of one are half a line, 128 k
+// parts of two.  There the 64 x 64 tile gains only where both operands lie along k (of 1024 x 960 x 3520 A B 13.1 / 12.9, A B^T 12.7 / 11.7,
+// A^T B^T level), with not many more rows than columns (3840 x 256 x 2240 10.3 / 10.6), and the 128 x 128 tile with A along k
+// (300 x 7000 x 3520 A B 1 % faster, A B^T 10 %, A^T B 6 % slower).
+// (`trans`: 1 A transposed, 2 B.  `rows192`: the 192 x 256 tile, 12 waves, may be taken: rows at any byte address, A not transposed, R through the caches.)
+inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool through_registers, bool assign, bool rows192, int trans)
 {
     static const struct { int bm, bn, groups, resident; double alone, shared, rest_alone, rest_shared, registers; } tiles[5] = {
         {256, 256, 1, 1, 0.57, 0.0, 17.0, 0.0, 1.42}, {128, 256, 1, 2, 0.42, 0.60, 10.5, 16.0, 0.0},
@@ -589,6 +595,12 @@ inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool thr
         {192, 256, 1, 1, 0.56, 0.0, 12.8, 0.0, 1.42}};
     auto up64 = [](int64_t n) { return (n + 63) / 64 * 64; };
     auto up128 = [](int64_t n) { return (n + 127) / 128 * 128; };
+    auto deep_pays = [&](int tile, int64_t kgroup) {
+        if (up128(kgroup) - kgroup > kgroup / 40 || (K % 128 != 0 && kgroup < 1024)) return false;
+        if (tile == CT_64 && (trans == 1 || kgroup < 384)) return false;
+        if (K % 128 == 64) return tile == CT_64 ? trans == 2 && M <= 8 * N : (trans & 1) == 0;
+        return kgroup >= 256;
+    };
     CountTilePlan best = {0, through_registers ? 1 : 0, 0, 0, 0, 0, 0, 0.0};
     for (int i = 0; i < 5; ++i) {
         const auto &t = tiles[i];
@@ -606,7 +618,7 @@ inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool thr
             if (best.parts == 0 || us < best.us) {
                 best.tile = i; best.parts = (int)parts; best.kpart = (int)kpart; best.kgroup = (int)kgroup; best.us = us;
                 best.alone = i == CT_128x256 && W <= 256 && kgroup > 4 * 64 ? 1 : 0;
-                best.deep = (i == CT_128 || i == CT_64) && !through_registers && W <= 256 && kgroup >= 256 && up128(kgroup) - kgroup <= kgroup / 40 && (K % 128 == 0 || kgroup >= 1024) ? 1 : 0;
+                best.deep = (i == CT_128 || i == CT_64) && !through_registers && W <= 256 && deep_pays(i, kgroup) ? 1 : 0;
             }
         }
     }

@@ -22,7 +22,7 @@
 //
 // With at most one workgroup to a unit the smaller tiles take stages of 128 k (a ring of 4, 128 KiB): half the barriers, twice the bytes in
 // flight and, of lines along k, whole lines of the caches at a time. us, stages of 64 k / of 128, calls on three sets of matrices in turn:
-// 512^3 4.1 / 4.0, 1024^2 x 4096 14.6 / 13.3, 2048^3 15.9 / 14.8, 1536^2 x 8192 36.8 / 32.3, 2412 x 896 x 4184 27.0 / 23.6, 320 x 2688 x
+// 1024^2 x 4096 14.6 / 13.3, 2048^3 15.9 / 14.8, 1536^2 x 8192 36.8 / 32.3, 2412 x 896 x 4184 27.0 / 23.6, 320 x 2688 x
 // 7808 22.4 / 19.6, 288 x 7744 x 3968 23.2 / 19.6, 448 x 5012 x 5040 with B transposed 33.9 / 29.2.  Two workgroups to a unit have no room for it.
 // (Through registers the same, with one set of registers: 4 us more at the start and 4 % less per k, 2999 x 4001 x 2503 39.6 / 43.6.)
 //
@@ -528,7 +528,7 @@ static hipError_t launch_tile_plan(const CountTilePlan &plan, const CountTileArg
         if (plan.parts > 1) return launch_tile<2, 1, 2, 4, 1, 4, TA, TB, REG, true>(plan.parts, a, s);
         return launch_tile<2, 1, 2, 4, 1, 4, TA, TB, REG, false>(1, a, s);
     default:
-        if constexpr (!REG) {
+        if constexpr (!REG && !(TA && !TB)) {
             if (plan.deep && plan.parts > 1) return launch_tile<1, 1, 2, 2, 2, 4, TA, TB, REG, true, false, 128>(plan.parts, a, s);
             if (plan.deep) return launch_tile<1, 1, 2, 2, 2, 4, TA, TB, REG, false, false, 128>(1, a, s);
         }

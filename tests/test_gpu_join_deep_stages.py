@@ -1,4 +1,4 @@
-"""The join count's smaller tiles with stages of 128 k: one stage and less than a ring of them, ranges with a short last stage of
+"""The join count's smaller tiles with stages of 128 k: less than a ring of them, ranges with a short last stage of
 one to four k-steps, K over several workgroups, ragged rows and columns, every layout; exact."""
 import pytest
 import torch
@@ -7,10 +7,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kernel,split,M,N,K", [
-    ("i8_tile_64x64", False, 256, 256, 512),          # two stages to a group of waves
+    ("i8_tile_64x64", False, 1020, 960, 768),         # three stages to a group of waves
     ("i8_tile_64x64", False, 1020, 1024, 3328),       # whole stages, ragged rows
     ("i8_tile_64x64", False, 640, 1156, 4228),        # the second group's last stage has 4 k
     ("i8_tile_64x64", True, 132, 1000, 8068),         # parts; the last one's groups end in 128 and 4 k
+    ("i8_tile_64x64", False, 1024, 960, 3520),        # rows of an odd number of 64 bytes
     ("i8_tile_128x128", False, 2412, 896, 4184),      # a last stage of 88 k
     ("i8_tile_128x128", False, 448, 5012, 5040),      # ... of 48
     ("i8_tile_128x128", True, 260, 2052, 8068),
@@ -30,7 +31,9 @@ def test_stages_of_128_k(kernel, split, M, N, K):
         am.amulet_count_i8_general(sA, sB, R, ws, trans_a=tA, trans_b=tB)
         torch.cuda.synchronize()
         ran = am.amulet_recent_kernel().split()
-        assert ran[0] == kernel and ran[-2:] == ["stage_k", "128"] and (int(ran[4]) > 1) == split, ran
+        # (the 64 x 64 tile keeps stages of 64 k for operands across k, and of such rows where either lies so)
+        deep = kernel == "i8_tile_128x128" or ((not tA and tB) if K % 128 == 64 else (not tA or tB))
+        assert ran[0] == kernel and (ran[-2:] == ["stage_k", "128"]) == deep and (int(ran[4]) > 1) == split, ran
         assert torch.equal(R, want + 11), (tA, tB)
     am.amulet_count_i8_assign(A, B, R)
     torch.cuda.synchronize()
