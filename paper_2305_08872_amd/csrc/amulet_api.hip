@@ -169,6 +169,7 @@ struct KernelNote {
     int pieces;                    // (rows of a tile of the kernel on the matrix cores that stood in for the shape)
     int critical;                  // (rows of a tile of the kernel by critical values, which has no shape id either)
     int groups;                    // (fp64 identity: groups of waves that share a tile's K)
+    CountRan ran;                  // (join count by a shape id)
 };
 constexpr unsigned KERNEL_NOTES = 16;
 static thread_local KernelNote g_notes[KERNEL_NOTES];
@@ -176,7 +177,7 @@ static thread_local unsigned g_notes_made = 0;
 static KernelNote &new_note(int task, int f64, int shape, int64_t rows)
 {
     KernelNote &n = g_notes[g_notes_made++ % KERNEL_NOTES];
-    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, 0, rows, 0, 0, 1};
+    n = KernelNote{task, f64, shape, 0, 1, 0, 0, 0, 0, 0, 0, rows, 0, 0, 1, CountRan()};
     return n;
 }
 
@@ -533,8 +534,7 @@ static int run_count(int shape, int64_t M, int64_t N, int64_t K, const int8_t *A
             a.pers_groups = g; a.pers_group_stages = st; a.pers_xcds = x; a.pers_xcd_span = sp;
         }
     }
-    new_note(AMULET_TASK_COUNT_I8, 0, shape, M);
-    hipError_t e = launch_count_i8(shape, a, (hipStream_t)stream);
+    hipError_t e = launch_count_i8(shape, a, (hipStream_t)stream, new_note(AMULET_TASK_COUNT_I8, 0, shape, M).ran);
     g_last_hip_error = e;
     return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
 }
@@ -1767,6 +1767,8 @@ const char *amulet_recent_kernel(int back)
                            : n.shape % F64_TILES == 0 ? "mfma_f64_64x64_dma4" : "mfma_f64_128x128_dma4";
         if (n.pieces) snprintf(text, sizeof(text), "%s rows %lld bf16_pieces 3 tile_rows %d", name, rows, n.pieces);
         else if (n.groups > 1) snprintf(text, sizeof(text), "%s rows %lld k_groups %d", name, rows, n.groups);
+        else if (n.ran.r_group) snprintf(text, sizeof(text), "%s rows %lld workgroups %d r_in_k_loop %d r_bypass %d", name, rows, n.ran.workgroups, n.ran.r_group, n.ran.r_bypass);
+        else if (n.ran.workgroups) snprintf(text, sizeof(text), "%s rows %lld workgroups %d", name, rows, n.ran.workgroups);
         else snprintf(text, sizeof(text), "%s rows %lld", name, rows);
     } else if (n.task == AMULET_TASK_COUNT_I8) {
         static const char *const tiles[5] = {"256x256", "128x256", "128x128", "64x64", "192x256"};

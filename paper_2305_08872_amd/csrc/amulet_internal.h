@@ -634,16 +634,22 @@ hipError_t launch_count_i8_tile(int trans, const CountTilePlan &plan, const Coun
 // shape 0: plain per-output loop; MFMA tiles 1: 128 x 128 (4 waves), 2: 256 x 256 (8 waves),
 // 3: 128 x 256 (8 waves)
 enum { COUNT_SHAPE_COUNT = 9 };
-hipError_t launch_count_i8(int shape, const CountArgs &a, hipStream_t s);
+// Of what a shape id's launch came to, what the id does not say (amulet_recent_kernel).
+struct CountRan {
+    int workgroups = 0;     // of a persistent kernel, whose workgroups walk several tiles; 0: one tile to a workgroup
+    int r_group = 0;        // count_i8_stream_kernel: values of R that a lane reads at a time during the K loop
+    int r_bypass = 0;       // ... R around the caches
+};
+hipError_t launch_count_i8(int shape, const CountArgs &a, hipStream_t s, CountRan &ran);
 // R[0..M) x [0..N) = 0 (a fill kernel: usable under graph capture)
 hipError_t launch_zero_r_i32(const CountArgs &a, hipStream_t s);
 // direct HBM -> LDS kernels: tile (64 * wr) x 256, wr = 2 or 4
 bool count_i8_dma_eligible(const CountArgs &a, int wr);
-hipError_t launch_count_i8_dma(const CountArgs &a, int wr, hipStream_t s, bool persistent = false);
+hipError_t launch_count_i8_dma(const CountArgs &a, int wr, hipStream_t s, bool persistent, CountRan &ran);
 // ... persistent, a stream of stages across tiles whose R is read on the way (count_i8_stream.hip)
 constexpr int COUNT_STREAM_LEAST_K = 1856;
 bool count_i8_stream_eligible(const CountArgs &a);
-hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s);
+hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s, CountRan &ran);
 
 // Identity task on the fp32 matrix cores; its five shape ids follow its eight VALU shapes: a
 // 128 x 128 tile (4 waves, register staged), a 256 x 256 tile (16 waves), the 128 x 128 tile

@@ -373,7 +373,7 @@ static hipError_t launch_mfma(const CountArgs &a, hipStream_t s)
     });
 }
 
-hipError_t launch_count_i8(int shape, const CountArgs &a, hipStream_t s)
+hipError_t launch_count_i8(int shape, const CountArgs &a, hipStream_t s, CountRan &ran)
 {
     switch (shape) {
     case 0: {
@@ -418,7 +418,7 @@ hipError_t launch_count_i8(int shape, const CountArgs &a, hipStream_t s)
         if (Mi == 0 || Ni == 0) return launch_mfma<2, 2, 2, 4, 4, 64>(a, s);
         CountArgs in = a;
         in.M = Mi; in.N = Ni;
-        hipError_t e = launch_count_i8_dma(in, wr, s, persistent && wr == 4);
+        hipError_t e = launch_count_i8_dma(in, wr, s, persistent && wr == 4, ran);
         if (e == hipSuccess && a.M > Mi) {          // bottom strip: rows Mi.., all columns
             CountArgs bot = a;
             bot.A = a.A + (int64_t)Mi * a.lda; bot.R = a.R + (int64_t)Mi * a.ldr; bot.M = a.M - Mi;

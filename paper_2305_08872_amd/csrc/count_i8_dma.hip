@@ -534,13 +534,14 @@ static int64_t persistent_grid(const CountArgs &a)
 }
 
 template <int WR, int NSTAGE>
-static hipError_t launch_dma_persistent(const CountArgs &a, hipStream_t s)
+static hipError_t launch_dma_persistent(const CountArgs &a, hipStream_t s, CountRan &ran)
 {
     typedef DmaTile<WR, NSTAGE> T;
     // (R += of a long K, below which count_i8_stream.hip's groups of R's values do not fit between a tile's first and last stages)
-    if (WR == 4 && count_i8_stream_eligible(a)) return launch_count_i8_stream(a, s);
+    if (WR == 4 && count_i8_stream_eligible(a)) return launch_count_i8_stream(a, s, ran);
     const int64_t grid = persistent_grid<WR>(a);
     if (grid == 0) return launch_dma<WR, NSTAGE>(a, s);
+    ran.workgroups = (int)grid;
     static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(&count_i8_dma_persistent_kernel<WR, NSTAGE>),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
     if (granted != hipSuccess) return granted;
@@ -552,9 +553,9 @@ static hipError_t launch_dma_persistent(const CountArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_count_i8_dma(const CountArgs &a, int wr, hipStream_t s, bool persistent)
+hipError_t launch_count_i8_dma(const CountArgs &a, int wr, hipStream_t s, bool persistent, CountRan &ran)
 {
-    if (wr == 4) return persistent ? launch_dma_persistent<4, 4>(a, s) : launch_dma<4, 4>(a, s);
+    if (wr == 4) return persistent ? launch_dma_persistent<4, 4>(a, s, ran) : launch_dma<4, 4>(a, s);
     return launch_dma<2, 3>(a, s);
 }
 

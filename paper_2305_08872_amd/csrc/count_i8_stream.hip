@@ -269,16 +269,20 @@ bool count_i8_stream_eligible(const CountArgs &a)
 }
 
 template <int GROUP, bool NT>
-static hipError_t launch_stream(const CountArgs &a, hipStream_t s)
+static hipError_t launch_stream(const CountArgs &a, hipStream_t s, CountRan &ran)
 {
+    const int grid = compute_units() / 8 * 8;
+    ran.workgroups = grid;
+    ran.r_group = GROUP;
+    ran.r_bypass = NT ? 1 : 0;
     static hipError_t granted = hipFuncSetAttribute(reinterpret_cast<const void *>(&count_i8_stream_kernel<GROUP, NT>), hipFuncAttributeMaxDynamicSharedMemorySize, CS_LDS_BYTES);
     if (granted != hipSuccess) return granted;
     if (forced_launch_failure()) return hipErrorLaunchFailure;
-    hipLaunchKernelGGL((count_i8_stream_kernel<GROUP, NT>), dim3((unsigned)(compute_units() / 8 * 8)), dim3(64 * CS_WAVES), CS_LDS_BYTES, s, a);
+    hipLaunchKernelGGL((count_i8_stream_kernel<GROUP, NT>), dim3((unsigned)grid), dim3(64 * CS_WAVES), CS_LDS_BYTES, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s)
+hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s, CountRan &ran)
 {
     // R around the caches, so that it does not displace operands, where a call's matrices do not fit the last-level cache (256 MiB)
     // or its K is long enough: an R that a call finds there is worth less than the operands of the calls around it.  us, R through
@@ -286,8 +290,8 @@ hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s)
     // 6144 x 4096 x 2560 76 / 81; 97 / 80, 6144^2 x 3072 113 / 120; 153 / 120, 8192 x 4096 x 4096 99 / 108; 144 / 109 (tile
     // kernels 74, 80, 120, 121; 99, 97, 159, 148), 7168 x 8192 x 3072 195 / 167; 206 / 167.
     const double bytes = 4.0 * (double)a.M * (double)a.N + (double)a.K * ((double)a.M + (double)a.N);
-    if (a.K / CS_BK >= cs_least_stages(4)) return launch_stream<4, true>(a, s);
-    return a.K >= 2560 || bytes > 285e6 ? launch_stream<8, true>(a, s) : launch_stream<8, false>(a, s);
+    if (a.K / CS_BK >= cs_least_stages(4)) return launch_stream<4, true>(a, s, ran);
+    return a.K >= 2560 || bytes > 285e6 ? launch_stream<8, true>(a, s, ran) : launch_stream<8, false>(a, s, ran);
 }
 
 }  // namespace amulet

@@ -85,6 +85,18 @@ def test_a_named_shape_is_the_kernel_that_runs(lib):
         assert i8(lib, 256, 256, 256, shape) == (am.amulet_shape_name(100, shape), {"rows": 256})
 
 
+def test_a_join_count_by_a_persistent_shape_names_the_kernel_that_ran(lib):
+    """Four kernels share that shape id: the one that reads R during its K loop (by four or by eight values a lane), the
+    one that reads it in its write-back, and, with too few whole tiles to walk, one workgroup to a tile."""
+    for call, group in [((8192, 8192, 4096), 4), ((8192, 8192, 3392, 8), 4), ((8192, 8192, 3328, 8), 8), ((4096, 4096, 1856, 8), 8)]:
+        got = i8(lib, *call)[1]
+        assert got["workgroups"] == 256 and got["r_in_k_loop"] == group and got["r_bypass"] in (0, 1), (call, got)
+    assert i8(lib, 8192, 8192, 1792, 8)[1] == {"rows": 8192, "workgroups": 256}
+    assert i8(lib, 4096, 4096, 1792, 8)[1] == {"rows": 4096}
+    # R written: nothing of it is read
+    assert kernel(lib, lambda: lib.amulet_count_i8_assign(8, 8192, 8192, 4096, ptr(), 4096, ptr(), 8192, ptr(), 8192, None))[1] == {"rows": 8192, "workgroups": 256}
+
+
 def test_earlier_launches_stay_readable_and_are_the_threads_own(lib):
     import threading
     f32(lib, 1, 300, 256, 256)
