@@ -499,10 +499,10 @@ static int run_count_tile(const CountRoute &route, int trans_a, int trans_b, int
     return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;
 }
 
-// m_load / n_load: rows of A / columns of B that exist in memory (0: just M, N)
+// m_load / n_load: rows of A / columns of B that exist in memory (0: just M, N); m_whole: rows of the count that these are part of (0: M)
 static int run_count(int shape, int64_t M, int64_t N, int64_t K, const int8_t *A, int64_t lda,
                      const int8_t *B, int64_t ldb, int32_t *R, int64_t ldr, void *stream,
-                     int64_t m_load = 0, int64_t n_load = 0, bool assign = false)
+                     int64_t m_load = 0, int64_t n_load = 0, bool assign = false, int64_t m_whole = 0)
 {
     CountArgs a;
     a.assign = assign ? 1 : 0;
@@ -511,6 +511,7 @@ static int run_count(int shape, int64_t M, int64_t N, int64_t K, const int8_t *A
     a.M = (int)M; a.N = (int)N; a.K = (int)K;
     a.Mload = (int)(m_load > M ? m_load : M);
     a.Nload = (int)(n_load > N ? n_load : N);
+    a.Mwhole = m_whole > M ? m_whole : M;
     a.vecA = (aligned16(A) && lda % 16 == 0) ? 1 : 0;
     a.vecB = (aligned16(B) && ldb % 16 == 0) ? 1 : 0;
     a.vecR = (aligned16(R) && ldr % 4 == 0) ? 1 : 0;
@@ -564,6 +565,7 @@ __global__ void fill_i8_kernel(int8_t *p, size_t n, uint32_t salt)
 struct TrialCtx {
     int task;
     int64_t M, N, K;   // of a trial: as many of the task's rows as the time allows
+    int64_t rows;      // of the whole task
     int built_in;      // the whole task's built-in shape,
     bool tile;         // whether tile kernels stand in for it,
     TilePlan plan;     // and how
@@ -581,7 +583,7 @@ static int trial_launch(TrialCtx *c, int shape)
     if (c->task == AMULET_TASK_COUNT_I8)
         return tile ? run_count_tile(c->route, 0, 0, c->M, c->N, c->K, (const int8_t *)c->A, c->K, (const int8_t *)c->B, c->N,
                                      (int32_t *)c->R, c->N, false, c->stream)
-                    : run_count(shape, c->M, c->N, c->K, (const int8_t *)c->A, c->K, (const int8_t *)c->B, c->N, (int32_t *)c->R, c->N, c->stream);
+                    : run_count(shape, c->M, c->N, c->K, (const int8_t *)c->A, c->K, (const int8_t *)c->B, c->N, (int32_t *)c->R, c->N, c->stream, 0, 0, false, c->rows);
     MmlikeCall call = {c->task, THRES_COL, 0, 0, c->M, c->N, c->K, (const float *)c->A, c->K,
                        (const float *)c->B, c->N, (const float *)c->params, 0,
                        (const float *)c->params + c->N, (float *)c->R, c->N};
@@ -1265,7 +1267,7 @@ int amulet_count_i8_adaptive(int64_t M, int64_t N, int64_t K, const int8_t *A, i
     auto run_slab = [&](int shape, int64_t r0, int64_t rows) {
         if (tile && shape == built_in)
             return run_count_tile(route, 0, 0, rows, N, K, A + r0 * lda, lda, B, ldb, R + r0 * ldr, ldr, false, stream);
-        return run_count(shape, rows, N, K, A + r0 * lda, lda, B, ldb, R + r0 * ldr, ldr, stream);
+        return run_count(shape, rows, N, K, A + r0 * lda, lda, B, ldb, R + r0 * ldr, ldr, stream, 0, 0, false, M);
     };
     const int64_t budget = M / 2;
     int64_t next_row = 0;
@@ -1626,7 +1628,7 @@ int amulet_tune(int task, int64_t M, int64_t N, int64_t K, void *stream)
     const size_t es = i8 ? 1 : 4;
     TrialCtx c;
     memset(&c, 0, sizeof(c));
-    c.task = task; c.M = Mt; c.N = N; c.K = K; c.stream = (hipStream_t)stream;
+    c.task = task; c.M = Mt; c.N = N; c.K = K; c.rows = M; c.stream = (hipStream_t)stream;
     int result = AMULET_ERR_LAUNCH;
     bool ok = hipMalloc(&c.A, (size_t)Mt * K * es) == hipSuccess &&
               hipMalloc(&c.B, (size_t)K * N * es) == hipSuccess &&

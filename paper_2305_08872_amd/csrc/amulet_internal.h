@@ -531,6 +531,7 @@ struct CountArgs {
     int64_t lda, ldb, ldr;
     int M, N, K;
     int Mload, Nload;  // rows of A / columns of B that exist in memory (>= M, N): a tile inside them loads without guards
+    int64_t Mwhole;    // rows of the whole count, of which M may be a trial's: what a shape's kernels are chosen by
     int vecA, vecB;  // 1 when the operand and its row pitch allow 16-byte loads
     int vecR;        // 1 when R and its row pitch allow 16-byte accesses
     int kchunk;      // k range of one workgroup when a launch splits K (set by the launcher)

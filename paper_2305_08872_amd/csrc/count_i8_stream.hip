@@ -289,7 +289,7 @@ hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s, CountRan &r
     // the caches / around them, one call over and over; calls on three sets of matrices in turn: 8192 x 4096 x 1856 73 / 80; 89 / 76,
     // 6144 x 4096 x 2560 76 / 81; 97 / 80, 6144^2 x 3072 113 / 120; 153 / 120, 8192 x 4096 x 4096 99 / 108; 144 / 109 (tile
     // kernels 74, 80, 120, 121; 99, 97, 159, 148), 7168 x 8192 x 3072 195 / 167; 206 / 167.
-    const double bytes = 4.0 * (double)a.M * (double)a.N + (double)a.K * ((double)a.M + (double)a.N);
+    const double bytes = 4.0 * (double)a.Mwhole * (double)a.N + (double)a.K * ((double)a.Mwhole + (double)a.N);
     if (a.K / CS_BK >= cs_least_stages(4)) return launch_stream<4, true>(a, s, ran);
     return a.K >= 2560 || bytes > 285e6 ? launch_stream<8, true>(a, s, ran) : launch_stream<8, false>(a, s, ran);
 }
