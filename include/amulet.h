@@ -313,7 +313,8 @@ int amulet_mmlike_f64_autopack(int task, int thres_form, int trans_a, int trans_
  * groups per XCD, s 64-k stages between them, XCD modulus x in 1..8, XCD span h
  * in sixteenths of K -- overrides how the persistent kernel of large problems
  * spreads its workgroups' write-backs in time; it changes timing only, never
- * results.)
+ * results.  With it set that kernel runs also where the one that reads R during
+ * its K loop, and has nothing to spread, would be taken.)
  */
 int amulet_count_i8(int64_t M, int64_t N, int64_t K,
                     const int8_t *A, int64_t lda,

@@ -435,6 +435,13 @@ static int check_mmlike(const MmlikeCall &c)
 
 // phases of the persistent join-count kernels (see count_i8_dma_persistent_kernel)
 static const int kPersPhases[4] = {8, 2, 2, 16};   // groups, stages between groups, XCD modulus, XCD span (sixteenths)
+// ... as the diagnostic override AMULET_I8_PHASES="groups,stages,xcds,span" names them; false: it does not
+static bool named_phases(int (&p)[4])
+{
+    const char *e = getenv("AMULET_I8_PHASES");
+    return e && sscanf(e, "%d,%d,%d,%d", &p[0], &p[1], &p[2], &p[3]) == 4 && p[0] >= 1 && p[0] <= 64 && p[1] >= 0 && p[1] <= 64 &&
+           p[2] >= 1 && p[2] <= 8 && p[3] >= 0 && p[3] <= 16;
+}
 
 // How the tile kernels of the join count (count_i8_tile.hip) run a call.
 struct CountRoute {
@@ -461,8 +468,11 @@ static bool count_tile_wanted(int trans_a, int trans_b, int64_t M, int64_t N, in
     const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
     const bool whole = aligned16(R) && ldr % 4 == 0 && K % 64 == 0 && N % 256 == 0 && M % (tiles256 >= 1024 ? 256 : 128) == 0 &&
                        (trans_a || (aligned16(A) && lda % 16 == 0)) && (trans_b || (aligned16(B) && ldb % 16 == 0));
+    // (the persistent kernel with phases, where it was ahead of the tile kernels; it still runs where phases are named)
+    const bool phased = tiles256 >= 832 && tiles256 % 8 == 0 && K >= (trans_a || trans_b ? 4096 : 2048);
+    int named[4];
     if (whole && (assign ? M / 128 * (N / 256) > 256
-                  : M % 256 == 0 && (trans_a || trans_b ? tiles256 >= 832 && tiles256 % 8 == 0 && K >= 4096 : join_stream_wanted(tiles256, K))))
+                  : M % 256 == 0 && (phased || (!trans_a && !trans_b && join_stream_wanted(tiles256, K) && !named_phases(named)))))
         return false;
     // (streamed straight to LDS, a piece of a row may start at any 4-byte address)
     auto dwords = [](const void *p, int64_t ld, int64_t line) { return ((uintptr_t)p & 3u) == 0 && ld % 4 == 0 && line % 4 == 0; };
@@ -517,24 +527,17 @@ static int run_count(int shape, int64_t M, int64_t N, int64_t K, const int8_t *A
     a.vecR = (aligned16(R) && ldr % 4 == 0) ? 1 : 0;
     a.kchunk = (int)K;
     a.block_base = 0;
-    a.pers_groups = kPersPhases[0];
-    a.pers_group_stages = kPersPhases[1];
-    a.pers_xcds = kPersPhases[2];
-    a.pers_xcd_span = kPersPhases[3];
-    if (assign) {
+    int phases[4];
+    a.pers_named = named_phases(phases);
+    if (!a.pers_named) {
         // R = form: all workgroups in step.  A phase makes a workgroup sum its first tile in two passes,
         // the second of which has to read R, and the write-back the phases spread out is stores only
         // here (cfg3 0.1875 ms in step against 0.192-0.1945 over twelve phase arrangements; 8192^2 x 1024
         // 0.085 / 0.093).
-        a.pers_groups = 1; a.pers_group_stages = 0; a.pers_xcds = 1; a.pers_xcd_span = 0;
+        static const int in_step[4] = {1, 0, 1, 0};
+        memcpy(phases, assign ? in_step : kPersPhases, sizeof(phases));
     }
-    if (const char *e = getenv("AMULET_I8_PHASES")) {   // diagnostic override, "groups,stages,xcds,span"
-        int g = 1, st = 0, x = 1, sp = 0;
-        if (sscanf(e, "%d,%d,%d,%d", &g, &st, &x, &sp) == 4 && g >= 1 && g <= 64 && st >= 0 && st <= 64 && x >= 1 && x <= 8 &&
-            sp >= 0 && sp <= 16) {
-            a.pers_groups = g; a.pers_group_stages = st; a.pers_xcds = x; a.pers_xcd_span = sp;
-        }
-    }
+    a.pers_groups = phases[0]; a.pers_group_stages = phases[1]; a.pers_xcds = phases[2]; a.pers_xcd_span = phases[3];
     hipError_t e = launch_count_i8(shape, a, (hipStream_t)stream, new_note(AMULET_TASK_COUNT_I8, 0, shape, M).ran);
     g_last_hip_error = e;
     return e == hipSuccess ? AMULET_OK : AMULET_ERR_LAUNCH;

@@ -540,6 +540,7 @@ struct CountArgs {
     // of an XCD in pers_groups groups, pers_group_stages stages (of 64 k) apart, and XCD x another
     // (x % pers_xcds) * pers_xcd_span / pers_xcds sixteenths of the range
     int pers_groups, pers_group_stages, pers_xcds, pers_xcd_span;
+    bool pers_named = false;   // by AMULET_I8_PHASES: the kernel that has phases runs, not the one that reads R during its K loop
     // 1: R = the counts instead of R += (amulet_count_i8_assign): a workgroup that owns its tile
     // alone stores its sums without reading R; a launch that splits K clears R first and adds
     int assign = 0;

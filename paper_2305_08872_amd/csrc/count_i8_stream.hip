@@ -265,7 +265,7 @@ count_i8_stream_kernel(const CountArgs args)
 // (a place for every workgroup; whole aligned tiles whose byte offsets fit 31 bits, as for the other streamed kernels, R's too)
 bool count_i8_stream_eligible(const CountArgs &a)
 {
-    return !a.assign && compute_units() >= 8 && xcd_places(a.M / CS_TILE, a.N / CS_TILE) >= compute_units() / 8 && count_i8_dma_eligible(a, 4) && a.K / CS_BK >= cs_least_stages(8) && a.ldr <= 0x7fffffffLL / (4 * 64);
+    return !a.assign && !a.pers_named && compute_units() >= 8 && xcd_places(a.M / CS_TILE, a.N / CS_TILE) >= compute_units() / 8 && count_i8_dma_eligible(a, 4) && a.K / CS_BK >= cs_least_stages(8) && a.ldr <= 0x7fffffffLL / (4 * 64);
 }
 
 template <int GROUP, bool NT>

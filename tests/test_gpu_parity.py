@@ -255,7 +255,7 @@ def test_count_i8_few_tiles_long_k_split_over_workgroups(am, shape):
 def test_count_i8_persistent_workgroups(am, shape, phases, monkeypatch):
     """Sizes large enough for the persistent streamed kernels (every workgroup walks at least two
     tiles of its XCD's part), with ragged edges around the whole-tile interior and a K of five
-    stages (None, the built-in choice: whole tiles and 32 stages, from which on it is taken), so that a workgroup's first tile is summed in two passes (2 + 3 stages, or 1 + 4 ...
+    stages (None, the built-in choice with phases named: whole tiles and 32 stages, from which on it is taken), so that a workgroup's first tile is summed in two passes (2 + 3 stages, or 1 + 4 ...
     by phase).  Phase arrangements "slot groups, stages between them, XCD modulus, XCD span in
     sixteenths of K" (none, coarse, the default, fine, odd), full int8 value range, non-zero R_in,
     bit-exact; the row and column checksums cover the whole matrix, sampled rows and columns go
@@ -276,7 +276,8 @@ def test_count_i8_persistent_workgroups(am, shape, phases, monkeypatch):
     if shape is None:
         assert am.amulet_selected_shape(am.AMULET_TASK_COUNT_I8, M, N, K) == 8   # the default at this size
         am.amulet_count_i8(dev(A), dev(B), dR)
-        assert am.amulet_recent_kernel().split()[0] == am.amulet_shape_name(am.AMULET_TASK_COUNT_I8, 8)   # and it runs
+        ran = am.amulet_recent_kernel().split()
+        assert ran[0] == am.amulet_shape_name(am.AMULET_TASK_COUNT_I8, 8) and ran[-2] == "workgroups"   # and it runs, with phases
     else:
         am.amulet_count_i8_shape(shape, dev(A), dev(B), dR)
     torch.cuda.synchronize()

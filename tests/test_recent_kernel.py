@@ -97,6 +97,17 @@ def test_a_join_count_by_a_persistent_shape_names_the_kernel_that_ran(lib):
     assert kernel(lib, lambda: lib.amulet_count_i8_assign(8, 8192, 8192, 4096, ptr(), 4096, ptr(), 8192, ptr(), 8192, None))[1] == {"rows": 8192, "workgroups": 256}
 
 
+def test_named_phases_run_the_kernel_that_has_them(lib, monkeypatch):
+    """AMULET_I8_PHASES is about the persistent kernel's write-backs: set, that kernel runs where the one without phases
+    would, and where tile kernels were taken before that one they are; a value that is out of range is as if it were not set."""
+    for phases, named in [("8,2,2,16", True), ("1,0,1,0", True), ("0,2,2,16", False), ("8,2", False)]:
+        monkeypatch.setenv("AMULET_I8_PHASES", phases)
+        for call in [(8192, 8192, 4096), (8192, 8192, 2048), (8192, 8192, 4096, 8)]:
+            got = i8(lib, *call)[1]
+            assert got["workgroups"] == 256 and ("r_in_k_loop" in got) == (not named), (phases, call, got)
+        assert i8(lib, 4096, 4096, 4096)[0].startswith("i8_tile_") == named
+
+
 def test_earlier_launches_stay_readable_and_are_the_threads_own(lib):
     import threading
     f32(lib, 1, 300, 256, 256)
