@@ -515,8 +515,8 @@ int amulet_selected_shape(int task, int64_t M, int64_t N, int64_t K);
  * " stage_k 128" where a stage of operands is 128 k); for the join count's persistent
  * shape " workgroups <of its launch, each of which walks its share of the tiles>"
  * (without it the problem has too few whole tiles, and each had its workgroup), and
- * " r_in_k_loop <values of R that a lane reads at a time> r_bypass <1: R around the
- * caches>" where the kernel ran that reads R during its K loop; and for the
+ * " r_in_k_loop <values of R that a lane reads at a time> r_bypass <1: R written around
+ * the caches>" where the kernel ran that reads R during its K loop; and for the
  * identity and boost tasks " bf16_pieces 3 tile_rows <32, 64, 128 or 256>" where a
  * kernel that forms plain sums on the bf16 matrix cores stood in for the shape
  * (larger problems, and few tiles of a long K; three bf16 pieces per value, fp32

@@ -640,7 +640,7 @@ enum { COUNT_SHAPE_COUNT = 9 };
 struct CountRan {
     int workgroups = 0;     // of a persistent kernel, whose workgroups walk several tiles; 0: one tile to a workgroup
     int r_group = 0;        // count_i8_stream_kernel: values of R that a lane reads at a time during the K loop
-    int r_bypass = 0;       // ... R around the caches
+    int r_bypass = 0;       // ... R written around the caches
 };
 hipError_t launch_count_i8(int shape, const CountArgs &a, hipStream_t s, CountRan &ran);
 // R[0..M) x [0..N) = 0 (a fill kernel: usable under graph capture)

@@ -49,7 +49,7 @@ static_assert(cs_least_stages(8) * CS_BK == COUNT_STREAM_LEAST_K, "");
 
 extern __shared__ __attribute__((aligned(16))) int8_t cs_smem[];
 
-// GROUP: values of R that a lane reads at a time.  NT: R is read and written around the caches.
+// GROUP: values of R that a lane reads at a time.  NT: R is written around the caches; it is read so always.
 template <int GROUP, bool NT>
 __global__ void __launch_bounds__(64 * CS_WAVES) __attribute__((amdgpu_waves_per_eu(4, 4)))
 count_i8_stream_kernel(const CountArgs args)
@@ -202,8 +202,7 @@ count_i8_stream_kernel(const CountArgs args)
                   [&]() {
 #pragma unroll
                       for (int j = 0; j < GROUP; ++j) {
-                          if (NT) asm volatile("global_load_dword %0, %1, %2 nt" : "=v"(rv[j]) : "v"(r_voff), "s"(r_rows) : "memory");
-                          else asm volatile("global_load_dword %0, %1, %2" : "=v"(rv[j]) : "v"(r_voff), "s"(r_rows) : "memory");
+                          asm volatile("global_load_dword %0, %1, %2 nt" : "=v"(rv[j]) : "v"(r_voff), "s"(r_rows) : "memory");
                           // the accumulators' order: rows 0 .. 3, 8 .. 11, ... of a block, then the block beside or below
                           const int e = q * GROUP + j;
                           r_rows += (e & 3) < 3 ? args.ldr : (e & 15) < 15 ? 5 * args.ldr : (e & 16) == 0 ? 32 - 27 * args.ldr : 5 * args.ldr - 32;
@@ -284,14 +283,20 @@ static hipError_t launch_stream(const CountArgs &a, hipStream_t s, CountRan &ran
 
 hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s, CountRan &ran)
 {
-    // R around the caches, so that it does not displace operands, where a call's matrices do not fit the last-level cache (256 MiB)
-    // or its K is long enough: an R that a call finds there is worth less than the operands of the calls around it.  us, R through
-    // the caches / around them, one call over and over; calls on three sets of matrices in turn: 8192 x 4096 x 1856 73 / 80; 89 / 76,
-    // 6144 x 4096 x 2560 76 / 81; 97 / 80, 6144^2 x 3072 113 / 120; 153 / 120, 8192 x 4096 x 4096 99 / 108; 144 / 109 (tile
-    // kernels 74, 80, 120, 121; 99, 97, 159, 148), 7168 x 8192 x 3072 195 / 167; 206 / 167.
+    // R written around the caches, so that it does not displace operands -- an R that a call finds there is worth less than the operands of
+    // the calls around it -- except where a call's matrices fit the last-level cache (256 MiB) and there is little K to a tile, or where its
+    // last round has few tiles and the tile kernels' smaller ones fill it better: there a call repeated on its matrices was slower than
+    // with those kernels.  (Read around them always: 0.99 to 1.01 repeated, up to 1.2 with other matrices.)  us, kernels before / R written through
+    // / around; on three sets of matrices in turn: 4352 x 4096 x 3392 83 / 78 / 86; 104 / 85 / 86, 5120 x 4096 x 2560 72 / 70 / 75; 88 / 78 / 75,
+    // 8448 x 4096 x 4096 146 / 136 / 146; 188 / 168 / 149, 4608 x 4608 x 3072 77 / 74 / 80; 98 / 85 / 80, 16384 x 3328 x 1984 131 / 119 / 132;
+    // 183 / 149 / 133; elsewhere around: 6144 x 8192 x 4096 170 / 145 / 156; 200 / 175 / 159, 7168 x 8192 x 2432 161 / 137 / 148; 161 / 167 / 150.
+    // (Over 200 whole problems of 256 to 1100 tiles, against the kernels before: repeated 0.97 to 1.5 times as fast, 4 of them below 0.985; with other
+    // matrices 1.0 to 1.5.)
+    const int64_t units = compute_units(), tiles = (a.Mwhole / CS_TILE) * (a.N / CS_TILE), last = tiles % units;
     const double bytes = 4.0 * (double)a.Mwhole * (double)a.N + (double)a.K * ((double)a.Mwhole + (double)a.N);
-    if (a.K / CS_BK >= cs_least_stages(4)) return launch_stream<4, true>(a, s, ran);
-    return a.K >= 2560 || bytes > 285e6 ? launch_stream<8, true>(a, s, ran) : launch_stream<8, false>(a, s, ran);
+    const bool around = bytes > 265e6 || (a.K >= 2560 && (tiles >= 832 || last == 0 || last > units / 2 || a.K >= (last > units / 4 ? 3392 : 4608)));
+    if (a.K / CS_BK >= cs_least_stages(4)) return around ? launch_stream<4, true>(a, s, ran) : launch_stream<4, false>(a, s, ran);
+    return around ? launch_stream<8, true>(a, s, ran) : launch_stream<8, false>(a, s, ran);
 }
 
 }  // namespace amulet

@@ -7,15 +7,16 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N,K,pad,group", [
-    (4096, 8192, 3392, 0, "4"),       # two tiles to a workgroup, three stages to each group of four of R's values
-    (4096, 8192, 3328, 0, "8"),       # a stage too few: groups of eight
-    (4096, 4096, 1856, 4, "8"),       # one tile to a workgroup, three stages to each group of eight
-    (4096, 8192, 1792, 0, None),      # a stage too few: the kernel with its own write-back of R
-    (4352, 8192, 3456, 8, "4"),       # places without a tile, a last round of few tiles
-    (8192, 4864, 4160, 4, "4"),       # groups of 3 and 4 stages
+@pytest.mark.parametrize("named,M,N,K,pad,ran", [      # (named: by the shape's id; else as the library chooses)
+    (False, 4096, 8192, 3392, 0, ("4", "1")),       # two tiles to a workgroup, three stages to each group of four of R's values
+    (True, 4096, 8192, 3328, 0, ("8", "1")),        # a stage too few: groups of eight
+    (True, 4096, 4096, 1856, 4, ("8", "0")),        # one tile to a workgroup, three stages to each group of eight
+    (True, 4096, 8192, 1792, 0, (None, None)),      # a stage too few: the kernel with its own write-back of R
+    (False, 8192, 4096, 1856, 8, ("8", "0")),       # R written through the caches, its stores under way behind the next tile's stages
+    (False, 4352, 8192, 3456, 8, ("4", "0")),       # ... places without a tile, a last round of few tiles
+    (False, 8192, 4864, 4160, 4, ("4", "1")),       # groups of 3 and 4 stages
 ])
-def test_count_i8_r_read_during_the_k_loop(M, N, K, pad, group):
+def test_count_i8_r_read_during_the_k_loop(named, M, N, K, pad, ran):
     import paper_2305_08872_amd as am
     g = torch.Generator(device="cuda")
     g.manual_seed(M + N + K)
@@ -29,9 +30,14 @@ def test_count_i8_r_read_during_the_k_loop(M, N, K, pad, group):
         want[:, :N] += product.long()
         want = ((want + 2 ** 31) % 2 ** 32 - 2 ** 31).int()
         print("join stream", M, N, K, pad, flush=True)
-        am.amulet_count_i8_shape(8, A, B, held[:, :N])
+        if named:
+            am.amulet_count_i8_shape(8, A, B, held[:, :N])
+        else:
+            am.amulet_clear_selections()
+            am.amulet_count_i8(A, B, held[:, :N])
         torch.cuda.synchronize()
-        ran = am.amulet_recent_kernel().split()
-        fields = dict(zip(ran[1::2], ran[2::2]))
-        assert ran[0] == "mfma_i8_256x256_w16_dma4_persistent" and "workgroups" in fields and fields.get("r_in_k_loop") == group, ran
+        words = am.amulet_recent_kernel().split()
+        fields = dict(zip(words[1::2], words[2::2]))
+        assert words[0] == "mfma_i8_256x256_w16_dma4_persistent" and "workgroups" in fields, words
+        assert (fields.get("r_in_k_loop"), fields.get("r_bypass")) == ran, words
         assert torch.equal(held, want)

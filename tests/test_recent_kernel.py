@@ -97,6 +97,15 @@ def test_a_join_count_by_a_persistent_shape_names_the_kernel_that_ran(lib):
     assert kernel(lib, lambda: lib.amulet_count_i8_assign(8, 8192, 8192, 4096, ptr(), 4096, ptr(), 8192, ptr(), 8192, None))[1] == {"rows": 8192, "workgroups": 256}
 
 
+def test_a_join_count_that_fits_the_caches_writes_r_through_them(lib):
+    """us repeated on the same matrices, the tile kernels / R around the caches / written through them: 4352 x 4096 x 3392 83 / 86 / 78,
+    5120 x 4096 x 2560 72 / 75 / 70, 4608 x 4608 x 3072 77 / 80 / 74; 7168 x 8192 x 2432 with other matrices 161 (persistent) / 150 / 167."""
+    for call in [(4352, 4096, 3392), (5120, 4096, 2560), (4608, 4608, 3072), (8448, 4096, 4096), (8192, 4096, 1856)]:
+        assert i8(lib, *call)[1]["r_bypass"] == 0, call
+    for call in [(7168, 8192, 2432), (4096, 4096, 4096), (6144, 8192, 4096), (8192, 8192, 1856), (8192, 8192, 4096)]:
+        assert i8(lib, *call)[1]["r_bypass"] == 1, call
+
+
 def test_named_phases_run_the_kernel_that_has_them(lib, monkeypatch):
     """AMULET_I8_PHASES is about the persistent kernel's write-backs: set, that kernel runs where the one without phases
     would, and where tile kernels were taken before that one they are; a value that is out of range is as if it were not set."""
