@@ -85,10 +85,11 @@ static bool identity_small_tile_wanted(int64_t M, int64_t N, bool f64 = false)
 
 // R += of whole tiles by count_i8_stream.hip rather than the tile kernels, whose smaller tiles are ahead where they fill the last
 // round better and K is short.  us, tile kernels / there, one call over and over; calls on three sets of matrices in turn: 4096^2 x
-// 1856 40 / 42; 40 / 42, x 2432 50 / 45; 53 / 48, x 4096 63 / 57; 77 / 57, 5120 x 4096 x 1856 58 / 59; 78 / 76, 8192 x 4096 x 1856
-// 74 / 73; 99 / 89, 6144 x 4096 x 4096 107 / 98; 136 / 99, 6144 x 8192 x 2560 129 / 127; 164 / 128; 272 tiles (4352 x 4096) x 2560
-// 70 / 77; 73 / 77, x 3392 83 / 86; 103 / 86, 784 (12544 x 4096) x 2560 150 / 166; 187 / 162, 528 (8448 x 4096) x 4096 144 / 149; 188 / 147.
-// The persistent kernel that took 832 tiles and more: 7168 x 8192 x 2048 149 / 136, 8192^2 x 2048 156 / 147.
+// 1856 39 / 38; 39 / 37, x 2432 49 / 42; 49 / 42, x 4096 63 / 57; 75 / 57, 5120 x 4096 x 1856 58 / 59; 77 / 64, 8192 x 4096 x 1856
+// 74 / 68; 98 / 83, 6144 x 4096 x 4096 108 / 99; 136 / 99, 6144 x 8192 x 2560 129 / 129; 162 / 129; 272 tiles (4352 x 4096) x 3392
+// 83 / 78; 104 / 86, 528 (8448 x 4096) x 4096 146 / 135; 188 / 168.  (The line of few tiles past a round lies where it does for R written around
+// the caches -- 272 tiles x 2560 70 / 77; 74 / 77, 784 (12544 x 4096) x 2560 150 / 161; 188 / 162; through them, 264 tiles x 2240 are 1.05 times as fast there.)
+// The persistent kernel that took 832 tiles and more: 7168 x 8192 x 2048 149 / 136, 8192^2 x 2048 156 / 148.
 static bool join_stream_wanted(int64_t tiles256, int64_t K)
 {
     const int64_t last = tiles256 % 256;

@@ -651,6 +651,7 @@ hipError_t launch_count_i8_dma(const CountArgs &a, int wr, hipStream_t s, bool p
 // ... persistent, a stream of stages across tiles whose R is read on the way (count_i8_stream.hip)
 constexpr int COUNT_STREAM_LEAST_K = 1856;
 bool count_i8_stream_eligible(const CountArgs &a);
+bool count_i8_stream_in_step_loses(const CountArgs &a);
 hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s, CountRan &ran);
 
 // Identity task on the fp32 matrix cores; its five shape ids follow its eight VALU shapes: a

@@ -538,7 +538,7 @@ static hipError_t launch_dma_persistent(const CountArgs &a, hipStream_t s, Count
 {
     typedef DmaTile<WR, NSTAGE> T;
     // (R += of a long K, below which count_i8_stream.hip's groups of R's values do not fit between a tile's first and last stages)
-    if (WR == 4 && count_i8_stream_eligible(a)) return launch_count_i8_stream(a, s, ran);
+    if (WR == 4 && count_i8_stream_eligible(a) && !count_i8_stream_in_step_loses(a)) return launch_count_i8_stream(a, s, ran);
     const int64_t grid = persistent_grid<WR>(a);
     if (grid == 0) return launch_dma<WR, NSTAGE>(a, s);
     ran.workgroups = (int)grid;

@@ -267,6 +267,19 @@ bool count_i8_stream_eligible(const CountArgs &a)
     return !a.assign && !a.pers_named && compute_units() >= 8 && xcd_places(a.M / CS_TILE, a.N / CS_TILE) >= compute_units() / 8 && count_i8_dma_eligible(a, 4) && a.K / CS_BK >= cs_least_stages(8) && a.ldr <= 0x7fffffffLL / (4 * 64);
 }
 
+// Rows of R 16, 32 or 64 KB apart lie in the same channels of the memory system, and here all workgroups write theirs at the same time.
+// Where there are many rows and K is short, count_i8_dma_persistent_kernel, whose phases spread the writes over time, is ahead: us, there / here,
+// 16384 x 8192 x 2432 305 / 318 (rows 256 bytes longer 309 / 300), x 2560 317 / 340 (319 / 315), 24576 x 8192 x 2176 423 / 462 (430 / 436),
+// 12288 x 8192 x 2560 245 / 256, 16384^2 x 2176 570 / 599 (615 / 598), 28672 x 4096 x 2560 300 / 328, 32768 x 4096 x 2432 323 / 358 (312 / 310).
+// Not with fewer rows or a longer K -- 10240 x 8192 x 3072 227 / 222, 16384 x 8192 x 3392 365 / 366, x 4096 406 / 411 (three sets of matrices in turn
+// 488 / 433), 16384^2 x 2560 654 / 644, 20480 x 4096 x 2560 1.03 times -- nor 128 KB apart: 12288 x 32768 x 2432 1002 / 961.
+bool count_i8_stream_in_step_loses(const CountArgs &a)
+{
+    const int64_t pitch = 4 * a.ldr, tiles_m = a.Mwhole / CS_TILE, tiles = tiles_m * (a.N / CS_TILE);
+    if ((pitch != 16384 && pitch != 32768 && pitch != 65536) || tiles < 832 || tiles % 8 != 0 || a.K < 2048) return false;
+    return tiles_m >= (pitch == 16384 ? 96 : pitch == 32768 ? 48 : 40) && a.K < (pitch == 65536 ? 2560 : 3392);
+}
+
 template <int GROUP, bool NT>
 static hipError_t launch_stream(const CountArgs &a, hipStream_t s, CountRan &ran)
 {
@@ -286,7 +299,7 @@ hipError_t launch_count_i8_stream(const CountArgs &a, hipStream_t s, CountRan &r
     // R written around the caches, so that it does not displace operands -- an R that a call finds there is worth less than the operands of
     // the calls around it -- except where a call's matrices fit the last-level cache (256 MiB) and there is little K to a tile, or where its
     // last round has few tiles and the tile kernels' smaller ones fill it better: there a call repeated on its matrices was slower than
-    // with those kernels.  (Read around them always: 0.99 to 1.01 repeated, up to 1.2 with other matrices.)  us, kernels before / R written through
+    // with those kernels.  (Read around them always: 0.99 to 1.01 repeated, up to 1.25 with other matrices.)  us, kernels before / R written through
     // / around; on three sets of matrices in turn: 4352 x 4096 x 3392 83 / 78 / 86; 104 / 85 / 86, 5120 x 4096 x 2560 72 / 70 / 75; 88 / 78 / 75,
     // 8448 x 4096 x 4096 146 / 136 / 146; 188 / 168 / 149, 4608 x 4608 x 3072 77 / 74 / 80; 98 / 85 / 80, 16384 x 3328 x 1984 131 / 119 / 132;
     // 183 / 149 / 133; elsewhere around: 6144 x 8192 x 4096 170 / 145 / 156; 200 / 175 / 159, 7168 x 8192 x 2432 161 / 137 / 148; 161 / 167 / 150.

@@ -106,6 +106,18 @@ def test_a_join_count_that_fits_the_caches_writes_r_through_them(lib):
         assert i8(lib, *call)[1]["r_bypass"] == 1, call
 
 
+def test_a_tall_join_count_whose_rows_of_r_share_channels_keeps_the_phases(lib):
+    """us, the persistent kernel / R read during the K loop: 16384 x 8192 x 2560 317 / 340, 24576 x 8192 x 2176 423 / 462, 16384^2 x 2176 570 / 599,
+    28672 x 4096 x 2560 300 / 328; by a few rows or k less or more, or with rows of R at another pitch, the second is level or ahead."""
+    def fields(M, N, K, ldr=None):
+        return kernel(lib, lambda: lib.amulet_count_i8(M, N, K, ptr(), K, ptr(), N, ptr(), ldr or N, None))[1]
+    for call in [(16384, 8192, 2560), (24576, 8192, 2176), (12288, 8192, 3328), (16384, 16384, 2176), (28672, 4096, 2560), (16384, 7936, 2560, 8192)]:
+        assert fields(*call) == {"rows": call[0], "workgroups": 256}, call
+    for call in [(16384, 8192, 2560, 8192 + 64), (12032, 8192, 2560), (16384, 8192, 3392), (16384, 16384, 2560), (24320, 4096, 2560), (12288, 12288, 2176),
+                 (12288, 32768, 2176), (16384, 8192, 1984)]:
+        assert "r_in_k_loop" in fields(*call), call
+
+
 def test_named_phases_run_the_kernel_that_has_them(lib, monkeypatch):
     """AMULET_I8_PHASES is about the persistent kernel's write-backs: set, that kernel runs where the one without phases
     would, and where tile kernels were taken before that one they are; a value that is out of range is as if it were not set."""
