@@ -191,7 +191,9 @@ count_i8_stream_kernel(const CountArgs args)
             }
         };
         // The loads are asm like the operands', awaited by the stages' own counts: three stages on, R's values stand ahead of what may
-        // still be under way.  Nothing touches their registers in between.
+        // still be under way.  Nothing may touch their registers in between, which the language does not promise: tests/test_stream_registers.py
+        // walks the assembly for it.  (121 vector registers by fours, 125 by eights, of 128; 35 and 27 scalars stand in lanes of one, none of
+        // them in the loop of stages without loads of R.)
         const uint32_t r_voff = (uint32_t)(4 * lh) * (uint32_t)args.ldr * 4u + (uint32_t)li * 4u;
         const int32_t *r_rows = args.R + (int64_t)(row0 + wr * 64) * args.ldr + col0 + wc * 64;
         const int span = last - s;

@@ -1,5 +1,5 @@
-"""Register use of the built kernels, read from the metadata of this repository's own objects: a predicate-task
-kernel that keeps registers in scratch memory pays for it with memory traffic that no timing at one
+"""Register use of the built kernels, read from the metadata of this repository's own objects: a kernel of the predicate
+tasks or of the join count's usual paths that keeps registers in scratch memory pays for it with memory traffic that no timing at one
 size shows (CPU only)."""
 import os
 import re
@@ -34,7 +34,7 @@ def _kernels(obj, tmp):
 
 
 @pytest.mark.parametrize("source", [s for s in hip_build.SOURCES
-                                    if re.match(r"mmlike_(tile_|critical_f64_|valu_(discount|boost|count_gt)_)|identity_split_waves", s)])
+                                    if re.match(r"mmlike_(tile_|critical_f64_|valu_(discount|boost|count_gt)_)|identity_split_waves|count_i8_(stream|tile)", s)])
 def test_predicate_task_kernels_keep_everything_in_registers(source, tmp_path):
     obj = os.path.join(hip_build.OBJ_DIR, os.path.splitext(source)[0] + ".o")
     if not os.path.exists(obj):
