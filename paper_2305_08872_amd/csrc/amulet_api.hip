@@ -483,7 +483,8 @@ static bool count_tile_wanted(int trans_a, int trans_b, int64_t M, int64_t N, in
     // they do, R is still there at the next call: 7900^2 x 2000 178 / 194, 5000 x 7000 x 3000 144 / 166
     const double bytes = 4.0 * (double)M * (double)N + (double)K * ((double)M + (double)N);
     route.bypass = !assign && bytes > 285e6 ? 1 : 0;
-    route.plan = choose_count_tile(M, N, K, !stream_to_lds, assign, !stream_to_lds && !trans_a && !route.bypass, (trans_a ? 1 : 0) | (trans_b ? 2 : 0));
+    route.plan = choose_count_tile(M, N, K, !stream_to_lds, assign, !stream_to_lds && !trans_a && !route.bypass, (trans_a ? 1 : 0) | (trans_b ? 2 : 0),
+                                   (trans_a && lda % 64 == 0) || (!trans_b && ldb % 64 == 0));
     return true;
 }
 

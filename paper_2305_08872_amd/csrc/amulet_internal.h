@@ -587,9 +587,13 @@ struct CountTilePlan {
 // Rows of an odd number of 64 bytes along k start in the middle of a cache line: 64 k of one are half a line, 128 k
 // parts of two.  There the 64 x 64 tile gains only where both operands lie along k (of 1024 x 960 x 3520 A B 13.1 / 12.9, A B^T 12.7 / 11.7,
 // A^T B^T level), with not many more rows than columns (3840 x 256 x 2240 10.3 / 10.6), and the 128 x 128 tile with A along k
-// (300 x 7000 x 3520 A B 1 % faster, A B^T 10 %, A^T B 6 % slower).
-// (`trans`: 1 A transposed, 2 B.  `rows192`: the 192 x 256 tile, 12 waves, may be taken: rows at any byte address, A not transposed, R through the caches.)
-inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool through_registers, bool assign, bool rows192, int trans)
+// (300 x 7000 x 3520 A B 1 % faster, A B^T 10 %, A^T B 6 % slower).  So for tight rows; where K is whole stages 128 k are ahead at any pitch (by 3 to 11 % on
+// average at 64 bytes past a line), and of such K a pitch of whole lines gains 2 to 15 % that this rule leaves.
+// With both operands across k and a short last stage, not where the rows of neither are multiples of 64 bytes apart, so that the pieces of every k-row share
+// lines with their neighbours' (128 x 128 tile, by 64 k / by 128: 7000 x 300 x 5040 0.96 times, 300 x 7000 x 2500 0.98, 1500^2 x 5040 0.97; rows of A 64 bytes
+// on 0.97, 1.01 and 1.03, of both 1.06, 1.06 and 1.09; 448 x 5012 x 5040 1.06, 2048^2 x 5040 1.11).
+// (`trans`: 1 A transposed, 2 B.  `lines`: rows of an operand that lies across k are multiples of 64 bytes apart.  `rows192`: the 192 x 256 tile, 12 waves, may be taken: rows at any byte address, A not transposed, R through the caches.)
+inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool through_registers, bool assign, bool rows192, int trans, bool lines)
 {
     static const struct { int bm, bn, groups, resident; double alone, shared, rest_alone, rest_shared, registers; } tiles[5] = {
         {256, 256, 1, 1, 0.57, 0.0, 17.0, 0.0, 1.42}, {128, 256, 1, 2, 0.42, 0.60, 10.5, 16.0, 0.0},
@@ -600,6 +604,7 @@ inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool thr
     auto deep_pays = [&](int tile, int64_t kgroup) {
         if (up128(kgroup) - kgroup > kgroup / 40 || (K % 128 != 0 && kgroup < 1024)) return false;
         if (tile == CT_64 && (trans == 1 || kgroup < 384)) return false;
+        if (trans == 1 && K % 128 != 0 && !lines) return false;
         if (K % 128 == 64) return tile == CT_64 ? trans == 2 && M <= 8 * N : (trans & 1) == 0;
         return kgroup >= 256;
     };

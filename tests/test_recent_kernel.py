@@ -118,6 +118,21 @@ def test_a_tall_join_count_whose_rows_of_r_share_channels_keeps_the_phases(lib):
         assert "r_in_k_loop" in fields(*call), call
 
 
+def test_stages_of_128_k_of_operands_across_k_want_rows_of_whole_lines(lib):
+    """A transposed, B not, a short last stage: 128 k a stage where rows of A or B are multiples of 64 bytes apart, else 64
+    (7000 x 300 x 5040 31.8 us by 64 k, 33.3 by 128).  K in whole stages, or an operand along k: 128 at any pitch."""
+    def stage(tA, tB, M, N, K, lda, ldb):
+        name, got = kernel(lib, lambda: lib.amulet_count_i8_general(tA, tB, M, N, K, ptr(), lda, ptr(), ldb, ptr(), N, ptr(), 1 << 30, None))
+        assert name == "i8_tile_128x128" and got["parts"] == 1
+        return got.get("stage_k", 64)
+    for M, N, K in [(7000, 300, 5040), (300, 7000, 2500), (1500, 1500, 5040), (1200, 2600, 3564)]:
+        assert stage(1, 0, M, N, K, M, N) == 64
+        assert stage(1, 0, M, N, K, (M + 63) // 64 * 64, N) == 128 and stage(1, 0, M, N, K, M, (N + 63) // 64 * 64) == 128
+        assert stage(1, 0, M, N, 4096, M, N) == 128
+        assert stage(0, 0, M, N, K, K, N) == 128 and stage(1, 1, M, N, K, M, K) == 128
+    assert stage(1, 0, 448, 5012, 5040, 448, 5012) == 128
+
+
 def test_named_phases_run_the_kernel_that_has_them(lib, monkeypatch):
     """AMULET_I8_PHASES is about the persistent kernel's write-backs: set, that kernel runs where the one without phases
     would, and where tile kernels were taken before that one they are; a value that is out of range is as if it were not set."""
