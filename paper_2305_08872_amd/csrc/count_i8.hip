@@ -329,6 +329,7 @@ hipError_t launch_zero_r_i32(const CountArgs &a, hipStream_t s)
     const unsigned gx = (unsigned)((a.N + 255) / 256 < 1024 ? (a.N + 255) / 256 : 1024);
     for (int64_t r0 = 0; r0 < a.M; r0 += 65535) {
         const int64_t rows = a.M - r0 < 65535 ? a.M - r0 : 65535;
+        if (forced_launch_failure()) return hipErrorLaunchFailure;
         hipLaunchKernelGGL(zero_r_i32_kernel, dim3(gx, (unsigned)rows), dim3(256), 0, s, a.R + r0 * a.ldr, a.ldr, (int)rows, a.N);
     }
     return hipGetLastError();
@@ -389,6 +390,7 @@ hipError_t launch_count_i8(int shape, const CountArgs &a, hipStream_t s, CountRa
                 sub.R = a.R + r0 * a.ldr + c0;
                 sub.M = (int)rows;
                 sub.N = (int)cols;
+                if (forced_launch_failure()) return hipErrorLaunchFailure;
                 hipLaunchKernelGGL(count_i8_simple_kernel, dim3((unsigned)((cols + 63) / 64), (unsigned)((rows + 3) / 4)),
                                    dim3(256), 0, s, sub);
             }

@@ -129,6 +129,7 @@ hipError_t launch_pack_pad_i8(int64_t rows, int64_t cols, const int8_t *src, int
     int64_t gx = (units + 255) / 256;
     if (gx > 64) gx = 64;
     const int64_t gy = rows_p < 65535 ? rows_p : 65535;
+    if (forced_launch_failure()) return hipErrorLaunchFailure;
     hipLaunchKernelGGL(pack_pad_i8_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, s, src, ld_src, rows, cols,
                        dst, ld_dst, rows_p, units);
     return hipGetLastError();
@@ -141,6 +142,7 @@ hipError_t launch_zero_block_i8(int8_t *dst, int64_t ld, int64_t row0, int64_t n
     int64_t gx = (ncols + 255) / 256;
     if (gx > 64) gx = 64;
     const int64_t gy = nrows < 65535 ? nrows : 65535;
+    if (forced_launch_failure()) return hipErrorLaunchFailure;
     hipLaunchKernelGGL(zero_block_i8_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, s, dst, ld, row0, nrows,
                        col0, ncols);
     return hipGetLastError();
@@ -152,6 +154,7 @@ hipError_t launch_transpose_i8(int64_t rows, int64_t cols, const int8_t *src, in
     const int64_t tiles = ((rows + 63) / 64) * ((cols + 63) / 64);
     const int64_t grid = tiles < 65536 ? tiles : 65536;
     const int vec = ((((uintptr_t)src | (uintptr_t)dst) & 15u) == 0 && ld_src % 16 == 0 && ld_dst % 16 == 0) ? 1 : 0;
+    if (forced_launch_failure()) return hipErrorLaunchFailure;
     hipLaunchKernelGGL(transpose_i8_kernel, dim3((unsigned)grid), dim3(256), 0, s, src, ld_src, dst, ld_dst, rows,
                        cols, vec);
     return hipGetLastError();
@@ -168,6 +171,7 @@ hipError_t launch_pack(int elem_bytes, int64_t rows, int64_t cols, const void *s
     if (gx > 64) gx = 64;                       // a row of up to 256 KiB in one pass, longer rows in several
     const int64_t gy = rows < 65535 ? rows : 65535;
     const dim3 grid((unsigned)gx, (unsigned)gy), block(256);
+    if (forced_launch_failure()) return hipErrorLaunchFailure;
     if (vec) {
         hipLaunchKernelGGL(pack_rows16_kernel, grid, block, 0, s, (const uint8_t *)src, ld_src * elem_bytes,
                            (uint8_t *)dst, ld_dst * elem_bytes, rows, units);

@@ -251,6 +251,30 @@ def test_refused_launch_is_reported_by_the_vector_alu_path(lib):
         am.amulet_debug_fail_launches(0)
 
 
+def test_refused_launches_take_in_copies_and_fills(lib):
+    """Nothing reaches the device for a refused launch, whichever it is: the fill that clears an R to be written in several parts
+    of K (or of an empty sum), the plain loop, copies into a workspace.  The seam's own error tells it from a launch without a GPU."""
+    one, ws = ctypes.c_void_p(1 << 20), ctypes.c_void_p(1 << 21)
+    odd = ctypes.c_void_p((1 << 20) + 1)
+    calls = {
+        "parts of K": lambda: lib.amulet_count_i8_assign(-1, 470, 512, 3520, one, 3520, one, 512, one, 512, None),
+        "parts of K, by shape": lambda: lib.amulet_count_i8_assign(3, 256, 256, 4096, one, 4096, one, 256, one, 256, None),
+        "empty sum": lambda: lib.amulet_count_i8_assign(-1, 64, 64, 0, one, 64, one, 64, one, 64, None),
+        "plain loop": lambda: lib.amulet_count_i8_shape(0, 70, 90, 33, one, 33, one, 90, one, 90, None),
+        "transpose": lambda: lib.amulet_count_i8_general(1, 0, 8192, 8192, 4096, one, 8192, one, 8192, one, 8192, ws, 1 << 30, None),
+        "pad": lambda: lib.amulet_count_i8_general(0, 0, 64, 64, 33, odd, 33, odd, 64, one, 64, ws, 1 << 30, None),
+        "pack": lambda: lib.amulet_pack(4, 64, 64, one, 64, ws, 80, None),
+    }
+    try:
+        for name, call in calls.items():
+            am.amulet_debug_fail_launches(1)
+            assert call() == -5, name
+            assert am.amulet_last_launch_error() == "unspecified launch failure", (name, am.amulet_last_launch_error())
+            am.amulet_debug_fail_launches(0)
+    finally:
+        am.amulet_debug_fail_launches(0)
+
+
 def test_selection_cache_is_keyed_by_size_bucket(lib):
     """Without a tuned entry every size gets the built-in default; the default of a bucket's
     sizes is the same function of the sizes as before (the cache key alone changed)."""
