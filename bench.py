@@ -96,8 +96,10 @@ class ShaderClock:
 
 
 def kernel_name(am):
-    """Name of the kernel that the last call ran (of a shape id, or a tile kernel, which has none)."""
-    return am.amulet_recent_kernel().split()[0]
+    """Name of the kernel that the last call ran (of a shape id, or a tile kernel, which has none); of the kernels that share the
+    join count's persistent shape, the one that reads R during its K loop is told apart."""
+    words = am.amulet_recent_kernel().split()
+    return words[0] + (" r_in_k_loop" if "r_in_k_loop" in words else "")
 
 
 INT8_MFMA_PEAK_TOPS = 5000.0   # MI355X dense int8 matrix peak, 5.0 POP/s

@@ -215,6 +215,7 @@ def test_every_count_kernel_at_a_size_of_its_own(am, kernel, split, assign, M, N
         torch.cuda.synchronize()
         ran = _kernel(am)
         assert ran[0] == kernel and ("parts" in ran and int(ran[2]) > 1) == split, ran
+        assert ("r_in_k_loop" in ran) == (kernel.endswith("persistent") and not assign), ran
         assert torch.equal(R, want if assign else want + 11), (tA, tB)
 
 
