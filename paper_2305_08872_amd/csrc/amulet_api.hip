@@ -89,7 +89,7 @@ static bool identity_small_tile_wanted(int64_t M, int64_t N, bool f64 = false)
 // 74 / 68; 98 / 83, 6144 x 4096 x 4096 108 / 99; 136 / 99, 6144 x 8192 x 2560 129 / 129; 162 / 129; 272 tiles (4352 x 4096) x 3392
 // 83 / 78; 104 / 86, 528 (8448 x 4096) x 4096 146 / 135; 188 / 168.  (The line of few tiles past a round lies where it does for R written around
 // the caches -- 272 tiles x 2560 70 / 77; 74 / 77, 784 (12544 x 4096) x 2560 150 / 161; 188 / 162; through them, 264 tiles x 2240 are 1.05 times as fast there.)
-// The persistent kernel that took 832 tiles and more: 7168 x 8192 x 2048 149 / 136, 8192^2 x 2048 156 / 148.
+// The persistent kernel that took 832 tiles and more: 7168 x 8192 x 2048 149 / 136, 8192^2 x 2048 156 / 148.  (256: the compute units that all this was timed on.)
 static bool join_stream_wanted(int64_t tiles256, int64_t K)
 {
     const int64_t last = tiles256 % 256;

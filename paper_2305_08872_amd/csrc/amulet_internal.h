@@ -579,7 +579,7 @@ struct CountTilePlan {
 // to be written 2 us and 1 per 4e5 counts, 4 at most up to 2.5e6 counts; above, whose adds find less of R in the L2s, no such bound (us, K whole / in parts: 470 x 512 x 3520
 // 12.3 / 9.3, 64 x 1710 x 2368 10.7 / 8.7, 489 x 384 x 3244 11.0 / 8.8, 282 x 5756 x 13692 101 / 81, 408 x 4604 x 12703 78 / 66, 192 x 6592 x 3072 28 / 24; but 4677 x 960 x
 // 15908 111 / 155, 3917 x 1468 x 6903 90 / 110, 6428 x 728 x 6272 100 / 115.  100 calls of 3e5 to 6e6 counts: 1.2 % behind the better of the two, 2.6 % without
-// the bound, 5.7 % with it throughout, 11 % at 4 always.  300 of fewer: 1.13 times as fast as at 4 always, one in eight slower, by up to 17 %, where K is below 2300.)  Fitted to and checked against every tile and split at 210 drawn
+// the bound, 5.7 % with it throughout, 11 % at 4 always.  300 of fewer: 1.13 times as fast as at 4 always, one in eight slower, by up to 17 %, nearly all of K below 2300.)  Fitted to and checked against every tile and split at 210 drawn
 // sizes (64 ... 8192 each way, all layouts and alignments): 1.4 % behind the fastest on average, 28 % at most.
 // The two smaller tiles, streamed, with at most one workgroup to a unit: stages of 128 k (count_i8_tile.hip), where whole stages make a range no
 // more than 2.5 % longer and a short last one, whose k are not pipelined, is one of at least eight: 320 x 1024 x 1152 5.2 us by 64 k, 6.0 by 128,
@@ -588,7 +588,7 @@ struct CountTilePlan {
 // by 128; 3000 x 300 x 1024 level), and from 384 k to a group of waves (1024 x 960, K = 512 4.0 % slower to 1 % faster by layout, 768 1 % slower to 5 % faster).
 // Rows of an odd number of 64 bytes along k start in the middle of a cache line: 64 k of one are half a line, 128 k
 // parts of two.  There the 64 x 64 tile gains only where both operands lie along k (of 1024 x 960 x 3520 A B 13.1 / 12.9, A B^T 12.7 / 11.7,
-// A^T B^T level), with not many more rows than columns (3840 x 256 x 2240 10.3 / 10.6), and the 128 x 128 tile with A along k
+// A^T B^T level), with not many more rows than columns (3840 x 256 x 2240 10.3 / 10.6, x 3520 1 % slower, x 5056 3 % faster: this one size drew the line at 8 times), and the 128 x 128 tile with A along k
 // (300 x 7000 x 3520 A B 1 % faster, A B^T 10 %, A^T B 6 % slower).  So for tight rows; where K is whole stages 128 k are ahead at any pitch (by 3 to 11 % on
 // average at 64 bytes past a line), and of such K a pitch of whole lines gains 2 to 15 % that this rule leaves.
 // With both operands across k and a short last stage, not where the rows of neither are multiples of 64 bytes apart, so that the pieces of every k-row share

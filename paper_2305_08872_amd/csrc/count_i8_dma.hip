@@ -422,6 +422,9 @@ count_i8_dma_kernel(const CountArgs args)
 // halves of an XCD's slots half a tile apart and XCD pairs a quarter / this arrangement):
 // 8192 x 8192 x 4096 0.236 / 0.2215 / 0.2125, x 1024 0.132 / 0.135 / 0.124, x 8192 0.373 / 0.356 / 0.343,
 // 16384 x 8192 x 4096 0.447 / 0.430 / 0.395, 16384 x 16384 x 4096 0.834 / 0.820 / 0.832.
+// (Of these R += is now count_i8_stream.hip's, which reads R during the K loop and has no phases.  R += still runs here for a K too short for that --
+// the shape named, tuned or tried: the built-in choice has tile kernels there -- for tall problems whose rows of R share channels
+// (count_i8_stream_in_step_loses), with AMULET_I8_PHASES set, and from 2^23 counts between rows on.  R = runs here, in step, from 1024 tiles on.)
 template <int WR, int NSTAGE>
 __global__ void __launch_bounds__(256 * WR) __attribute__((amdgpu_waves_per_eu(4, 4)))
 count_i8_dma_persistent_kernel(const CountArgs args)

@@ -14,9 +14,10 @@
 // All workgroups run in step: with half of the XCDs half a tile behind (the first tile in two passes, R read in both) 224 us.
 //
 // us, count_i8_dma_persistent_kernel / here: 8192^2 x 4096 218 / 205, x 3392 197 / 182, x 2048 156 / 147, 7168 x 8192 x 4096 210 / 196,
-// 9216 x 8192 x 4096 258 / 247, 16384^2 x 4096 939 / 855, 16384 x 8192 x 4096 406 / 405.
-// Bound: 160 us of K loop (matrix cores, LDS and stream each busy for 80 to 85 % of it) and 512 MB of R that compete with
-// the operands' 570 MB from beyond the L2s; written without being read, 184 us.
+// 9216 x 8192 x 4096 258 / 247, 16384^2 x 4096 841 / 806 (three sets of matrices in turn 947 / 861), 16384 x 8192 x 4096 406 / 411 (488 / 433).
+// Bound: 160 us of K loop (its matrix instructions alone are 131, its stream alone 123) and R, 537 MB read and written, beside the operands' 403 MB
+// from beyond the L2s: 4.6 TB/s, where a large copy reaches 4.8.  By counters data return is busy for 88 % of the launch, the matrix cores
+// for 53, LDS for 29; written without being read, 184 us.
 //
 // The tile, the layout of a stage in LDS, the fragments' reads and the place of the barrier are count_i8_dma.hip's.
 #include <hip/hip_runtime.h>
