@@ -455,7 +455,7 @@ struct CountRoute {
 // are ahead: their persistent form reads R during its K loop and starts a tile while the last one's counts are
 // on their way, and their write-back of an R that is not read is shorter.  us, theirs / here:
 //   R += : join_stream_wanted; but 8192^2 x 1024, too short for that, 128 / 122;
-//     with an operand to transpose first (at 8192^2 x 4096: A 233 / 244, B 235 / 265, both 250 / 252) from
+//     with an operand to transpose first (at 8192^2 x 4096: A 222 / 244, B 227 / 265, both 239 / 252) from
 //     twice that K on;
 //   R = : 6144^2 x 4096 128 / 140, 3072^2 x 2048 26 / 30, 12288 x 8192 x 512 94 / 112; up to one 128 x 256
 //     tile per unit, where theirs is another kernel, 2048 x 4096 x 4096 42 / 35.

@@ -576,11 +576,12 @@ struct CountTilePlan {
 // tile -- first loads, sums, write-back -- `rest_...`, a fifth less when R is not read.  W workgroups (with the
 // tile order's padding) are whole rounds and a last one in which at most one workgroup per unit is alone.
 // K over several workgroups (the two smaller tiles): 0.3 us and 1 T atomic adds per second beside other workgroups' arithmetic; to clear an R that is
-// to be written 2 us and 1 per 4e5 counts, 4 at most up to 2.5e6 counts; above, whose adds find less of R in the L2s, no such bound (us, K whole / in parts: 470 x 512 x 3520
+// to be written 2 us and 1 per 4e5 counts, 4 at most up to 2.5e6 counts; above, whose adds find less of R in the L2s, no such bound,
+// nor where operands stream and K is whole stages of 128 k, which make a whole K faster than the model has it (us, K whole / in parts: 470 x 512 x 3520
 // 12.3 / 9.3, 64 x 1710 x 2368 10.7 / 8.7, 489 x 384 x 3244 11.0 / 8.8, 282 x 5756 x 13692 101 / 81, 408 x 4604 x 12703 78 / 66, 192 x 6592 x 3072 28 / 24; but 4677 x 960 x
-// 15908 111 / 155, 3917 x 1468 x 6903 90 / 110, 6428 x 728 x 6272 100 / 115.  100 calls of 3e5 to 6e6 counts: 1.2 % behind the better of the two, 2.6 % without
-// the bound, 5.7 % with it throughout, 11 % at 4 always.  300 of fewer: 1.13 times as fast as at 4 always, one in eight slower, by up to 17 %, nearly all of K below 2300.)  Fitted to and checked against every tile and split at 210 drawn
-// sizes (64 ... 8192 each way, all layouts and alignments): 1.4 % behind the fastest on average, 28 % at most.
+// 15908 111 / 155, 3917 x 1468 x 6903 90 / 110, 6428 x 728 x 6272 100 / 115, 1024 x 1856 x 5120 23 / 29.  102 calls of 3e5 to 6e6 counts: 0.8 % behind the better of the two, 2.8 % without
+// the bound, 5.7 % with it throughout, 11 % at 4 always; 120 of the last kind 1.14 times as fast as at 4 always, one of them 2 % slower.  300 of fewer: 1.13 times as fast as at 4 always, one in eight slower, by up to 17 %, nearly all of K below 2300.)
+// Fitted to and checked against every tile and split at 210 drawn sizes (64 ... 8192 each way, all layouts and alignments): 1.4 % behind the fastest on average, 28 % at most.
 // The two smaller tiles, streamed, with at most one workgroup to a unit: stages of 128 k (count_i8_tile.hip), where whole stages make a range no
 // more than 2.5 % longer and a short last one, whose k are not pipelined, is one of at least eight: 320 x 1024 x 1152 5.2 us by 64 k, 6.0 by 128,
 // 576 x 872 x 704 6.1 / 6.5.
@@ -601,7 +602,7 @@ inline CountTilePlan choose_count_tile(int64_t M, int64_t N, int64_t K, bool thr
         {256, 256, 1, 1, 0.57, 0.0, 17.0, 0.0, 1.42}, {128, 256, 1, 2, 0.42, 0.60, 10.5, 16.0, 0.0},
         {128, 128, 1, 2, 0.206, 0.48, 4.8, 9.2, 1.52}, {64, 64, 2, 2, 0.19, 0.46, 2.8, 4.1, 1.67},
         {192, 256, 1, 1, 0.56, 0.0, 12.8, 0.0, 1.42}};
-    const double counts = (double)M * (double)N, clear = counts > 2.5e6 || counts < 8.0e5 ? 2.0 + counts / 4.0e5 : 4.0;
+    const double counts = (double)M * (double)N, clear = counts > 2.5e6 || counts < 8.0e5 || (!through_registers && K % 128 == 0) ? 2.0 + counts / 4.0e5 : 4.0;
     auto up64 = [](int64_t n) { return (n + 63) / 64 * 64; };
     auto up128 = [](int64_t n) { return (n + 127) / 128 * 128; };
     auto deep_pays = [&](int tile, int64_t kgroup) {

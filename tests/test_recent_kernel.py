@@ -135,13 +135,13 @@ def test_stages_of_128_k_of_operands_across_k_want_rows_of_whole_lines(lib):
 
 def test_written_counts_have_k_in_parts_where_that_is_ahead(lib):
     """us, K in parts / whole: 470 x 512 x 3520 9.3 / 12.3, 282 x 5756 x 13692 81 / 101, 408 x 4604 x 12703 66 / 78, 192 x 6592 x 3072 24 / 28, 256 x 8644 x 14957 81 / 97;
-    4677 x 960 x 15908 155 / 111, 6428 x 728 x 6272 115 / 100, 2048 x 2289 x 6528 84 / 67."""
+    4677 x 960 x 15908 155 / 111, 6428 x 728 x 6272 115 / 100, 2048 x 2289 x 6528 84 / 67, 1024 x 1856 x 5120 29 / 23, 512 x 2368 x 3968 21 / 18."""
     def parts(M, N, K, at):
         return kernel(lib, lambda: lib.amulet_count_i8_assign(-1, M, N, K, ptr(at), K, ptr(at), N, ptr(), N, None))[1]["parts"]
     odd, even = (1 << 20) + 1, 1 << 20
     for M, N, K, at in [(470, 512, 3520, even), (282, 5756, 13692, odd), (408, 4604, 12703, even), (192, 6592, 3072, odd), (256, 8644, 14957, even), (2124, 1000, 19900, even)]:
         assert parts(M, N, K, at) > 1, (M, N, K)
-    for M, N, K, at in [(4677, 960, 15908, even), (6428, 728, 6272, odd), (2048, 2289, 6528, even), (64, 64, 256, even)]:
+    for M, N, K, at in [(4677, 960, 15908, even), (6428, 728, 6272, odd), (2048, 2289, 6528, even), (1024, 1856, 5120, even), (512, 2368, 3968, even), (64, 64, 256, even)]:
         assert parts(M, N, K, at) == 1, (M, N, K)
 
 
